@@ -2,9 +2,14 @@
 // dequantisation feeding v_mfma_f32_32x32x16_f16 (paper Sec. 1 item (1): the
 // 4-bit weights are dequantised to fp16 at run time; Sec. 4.1: groups of 128).
 //
-// A workgroup of WGN x WGM wavefronts owns BN x BM outputs (BN = 32*PN*WGN
+// A workgroup of WGN x WGM x WGK wavefronts owns BN x BM outputs (BN = 32*PN*WGN
 // features, BM = 32*PM*WGM tokens) over a range of K groups; a wavefront owns
-// PN x PM MFMA tiles of 32 x 32.
+// PN x PM MFMA tiles of 32 x 32.  WGK > 1: the wavefronts are WGK sets that cover the
+// same block, set wk takes every WGK-th group, and the sets' partial sums meet in LDS at
+// the end.  That is how eight wavefronts work on a block of 128 x 64 or 64 x 64 where the
+// problem has no more blocks than compute units: with four (one per SIMD) every wait of a
+// wave idles its SIMD (12288 x 4096 at 128 tokens, 192 blocks: 23.5 us on four
+// wavefronts, 19.0 on eight; 5120 x 5120 at 384: 29.1 -> 25.8).
 //   - Activations: the BM x 128 fp16 block of a group travels global -> LDS
 //     with buffer loads that write LDS directly (no registers, no ds_write),
 //     NS-1 groups ahead, into NS stages that are separate arrays (the compiler
@@ -19,9 +24,16 @@
 //     dequantises them itself.
 //   - Order of issue inside a group is pinned with scheduling fences: the LDS
 //     reads of a later k-step first, then the MFMAs of this k-step with the
-//     dequantisation of the NEXT k-step cut into pieces (one fp16 pair = 3
-//     VALU ops) between them.  Left to itself the compiler puts every LDS
-//     read next to its first use.
+//     dequantisation of the NEXT k-step cut into stages of independent operations
+//     between them.  Left to itself the compiler puts every LDS read next to its first use.
+//   - What bounds the loop where the power limit does not: issue slots.  A SIMD issues a
+//     matrix or vector instruction every 4.9 cycles when both kinds mix, an MFMA takes 32, so
+//     six vector operations per MFMA are free and every further one costs; a 64-token
+//     wave tile needs 6.5 for the dequantisation alone.  Hence no address arithmetic in the
+//     loop: what moves with the group is a scalar offset of the load, LDS addresses differ
+//     from a lane's fixed one by constant bits (8.5 -> 7.0 vector operations per MFMA,
+//     12288 x 4096 at 128 tokens 21.4 -> 19.5 us, 57344 x 8192 at 512 448 -> 430 on 128 x 128
+//     blocks).
 //
 // A operand (32 rows x 16 k): lane l supplies 8 consecutive k of row l % 32,
 // lanes 0..31 the first 8 k of the step, lanes 32..63 the second 8.  In the blob
@@ -39,8 +51,6 @@
 
 namespace qspec {
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
 // s_waitcnt immediate for "at most n vector-memory operations outstanding",
 // leaving the other counters alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14,
 // expcnt 6:4, lgkmcnt 11:8).
@@ -51,17 +61,17 @@ constexpr int waitcnt_vm_lgkm0(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0
 #define QSPEC_TILE16_EARLY 1
 #endif
 
-template <int PN, int PM, int WGN, int WGM, int NW, int NS, int OCC>
-__global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileArgs p) {
-  constexpr int kWaves = WGN * WGM;
+template <int PN, int PM, int WGN, int WGM, int WGK, int NW, int NS, int OCC>
+__global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel(TileArgs p) {
+  constexpr int kWaves = WGN * WGM * WGK;
+  constexpr int kTileWaves = WGN * WGM;                // the waves that cover the output block once
   constexpr int BM = 32 * PM * WGM;
-  constexpr int kStageBytes = BM * 256;
-  constexpr int U = kStageBytes / 1024 / kWaves;       // wave-wide transfers per wave and group
-  static_assert(kStageBytes % (1024 * kWaves) == 0, "the stage divides evenly among the waves");
+  constexpr int kStageBytes = BM * 256 * WGK;
+  constexpr int U = BM * 256 / 1024 / kTileWaves;      // wave-wide transfers per wave and group
+  static_assert(BM * 256 % (1024 * kTileWaves) == 0, "the stage divides evenly among the waves");
   static_assert(NW == 2 || NW == 4, "the stage of a group must follow from its ring slot");
   static_assert(NS == 2 || (NS == 4 && NW == 4), "stage = ring slot % NS");
   constexpr int D = NS - 1;                            // activations are fetched D groups ahead
-  static_assert(kWaves == 4 || kWaves == 8, "row % 16 of a transfer must not depend on u");
   // NS stages, each an array of its own (see the head of this file)
   __shared__ __attribute__((aligned(1024))) uint8_t xs0[kStageBytes];
   __shared__ __attribute__((aligned(1024))) uint8_t xs1[kStageBytes];
@@ -72,7 +82,8 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wn = wave % WGN, wm = wave / WGN;
+  const int wk = wave / kTileWaves, wt = wave % kTileWaves;
+  const int wn = wt % WGN, wm = wt / WGN;
   const int m32 = lane & 31, h = lane >> 5;
   const int G = p.G;
   const TileCoord tc = tile_coord(p);
@@ -81,60 +92,60 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
   const int m0 = tc.mblk * BM;
   const int mw0 = wm * (PM * 32);
 
-  const rsrc_t r_codes = make_rsrc(p.codes, (uint32_t)((size_t)p.N * p.K / 2));
-  const rsrc_t r_scales = make_rsrc(p.scalesT, (uint32_t)((size_t)p.N * G * 2));
-  const rsrc_t r_act = make_rsrc(p.act, (uint32_t)((size_t)p.M * p.K * 2));
-  // Every workgroup walks its K groups in the same order, q = 0 .. ng-1 -> group g0 + q:
+  // Every workgroup walks its K groups in the same order, trip q = 0 .. ng-1 -> group g0 + q:
   // the workgroups of an XCD then need the same narrow window of activation columns at
   // about the same time and find it in their L2.  (Starting each weight stripe at a
   // different group was measured: no faster, and 9x the algorithmic bytes fetched,
   // because the whole activation matrix then has to live in a 4 MB L2.)
-  const int ng = g1 - g0;
-  auto group_of = [&](int q) -> int { return g0 + q; };
-  auto past_end = [&](int q) -> uint32_t { return (uint32_t)((ng - 1 - q) >> 31) << 31; };   // q >= ng ? bit 31 : 0
+  // (WGK > 1: trip q of the workgroup is the WGK groups g0 + q * WGK .., one for each set of waves)
+  const int ng = (g1 - g0 + WGK - 1) / WGK;
+  auto group_of = [&](int q) -> int { return g0 + q * WGK + wk; };
+  // A lane's part of an address is fixed; what moves with the group is wave-uniform and goes into
+  // the load's scalar offset, so that a group costs no vector address arithmetic.  Requests past
+  // the end go through an empty buffer descriptor: zeros, no traffic, no branch.
 
   // ---- activations: global -> LDS.  Transfer u of this wave fills block q = wave +
-  // u*kWaves (1 KB = rows 4q..4q+3).  Lane l writes slot l%16 of row 4q + l/16 and so
-  // must fetch k-chunk (l%16) ^ (row%16); row%16 = (4*wave + l/16) % 16 for every u
-  // because 4*kWaves*u is a multiple of 16.  Rows past M lie past the end of the
-  // buffer.
-  const int row_in_blk = 4 * wave + (lane >> 4);
-  const uint32_t x_voff = (uint32_t)(m0 + row_in_blk) * (uint32_t)p.K * 2u +
-                          (uint32_t)(((lane & 15) ^ (row_in_blk & 15)) << 4);
-  const uint32_t x_ustep = (uint32_t)(4 * kWaves) * (uint32_t)p.K * 2u;
-  auto dma_x = [&](int q, uint8_t* stage) {
-    const uint32_t gbase = (uint32_t)group_of(q) * 256u;
-    const uint32_t gone = past_end(q);
+  // u*kTileWaves (1 KB = rows 4q..4q+3).  Lane l writes slot l%16 of row 4q + l/16 and so
+  // must fetch k-chunk (l%16) ^ (row%16).  Rows past M are out of range: no traffic, and
+  // whatever the stage holds there reaches only outputs that are not stored.
+  uint32_t x_voff[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      // (the marker is OR-ed in last: a sum could carry out of bit 31 for rows near 2 GiB)
-      const uint32_t off = (x_voff + (gbase + (uint32_t)u * x_ustep)) | gone;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r_act, (lds_ptr_t)(stage + (wave + u * kWaves) * 1024), 16, off, 0, 0, 0);
-    }
+  for (int u = 0; u < U; ++u) {
+    const int row = 4 * (wt + u * kTileWaves) + (lane >> 4);
+    x_voff[u] = m0 + row < p.M ? (uint32_t)(m0 + row) * (uint32_t)p.K * 2u + (uint32_t)(((lane & 15) ^ (row & 15)) << 4) : kOutOfRange;
+  }
+  auto dma_x = [&](int q, uint8_t* stage) {
+    const uint32_t bytes = q < ng ? (uint32_t)((size_t)p.M * p.K * 2) : 0u;
+    const uint32_t soff = (uint32_t)min(group_of(q), g1 - 1) * 256u;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      buf_load16_lds(p.act, bytes, stage + wk * (BM * 256) + (wt + u * kTileWaves) * 1024, x_voff[u], soff);
   };
 
-  // ---- weights: per 32-row pair two 16-byte pieces (lo, hi) and the row's scale
+  // ---- weights: per 32-row pair two 16-byte pieces (lo, hi) and the row's scale (bit 31 of a
+  // lane's offset: its row lies past N)
   uint4 wlo[NW][PN], whi[NW][PN];
   uint32_t sq[NW][PN];
-  // per-lane offsets of pair 0 inside a group (bit 31: the lane's tile lies past N;
-  // then so do the tiles of the pairs after it, and pair j adds a wave-uniform step)
   const int n_lane = n0 + m32;          // this lane's weight row in pair 0
-  const uint32_t w_voff = (uint32_t)(n_lane >> 4) * G * 1024u + (uint32_t)((n_lane & 15) + 16 * h) * 16u;
+  uint32_t w_voff[PN], s_voff[PN];
+#pragma unroll
+  for (int j = 0; j < PN; ++j) {
+    const uint32_t none = n_lane + 32 * j >= p.N ? kOutOfRange : 0u;
+    w_voff[j] = ((uint32_t)((n_lane >> 4) + 2 * j) * G * 1024u + (uint32_t)((n_lane & 15) + 16 * h) * 16u) | none;
+    s_voff[j] = (uint32_t)(n_lane + 32 * j) * 2u | none;
+  }
   auto load_w = [&](int d, int q) {
-    const uint32_t gone = past_end(q);
     const int g = group_of(q);
+    const uint32_t cbytes = g < g1 ? (uint32_t)((size_t)p.N * p.K / 2) : 0u, sbytes = g < g1 ? (uint32_t)((size_t)p.N * G * 2) : 0u;
 #pragma unroll
     for (int j = 0; j < PN; ++j) {
-      const uint32_t none = (uint32_t)((p.N - 1 - (n_lane + 32 * j)) >> 31) << 31;
-      const uint32_t skip = gone | none;
-      const uint32_t wo = w_voff + (uint32_t)(2 * j) * G * 1024u + (uint32_t)g * 1024u;
-      wlo[d][j] = buf_load16(r_codes, wo | skip);
-      whi[d][j] = buf_load16(r_codes, (wo + 512u) | skip);
-      sq[d][j] = buf_load_u16(r_scales, (((uint32_t)g * (uint32_t)p.N + (uint32_t)(n_lane + 32 * j)) * 2u) | skip);
+      wlo[d][j] = buf_load16(p.codes, cbytes, w_voff[j], (uint32_t)g * 1024u);
+      whi[d][j] = buf_load16(p.codes, cbytes, w_voff[j] + 512u, (uint32_t)g * 1024u);
+      sq[d][j] = buf_load_u16(p.scalesT, sbytes, s_voff[j], (uint32_t)g * (uint32_t)p.N * 2u);
     }
   };
 
-  float acc[PN][PM][16];
+  v16f acc[PN][PM];
 #pragma unroll
   for (int j = 0; j < PN; ++j)
 #pragma unroll
@@ -142,23 +153,10 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.0f;
 
-  // All stages start as zeros: a stage that no transfer ever fills (a slice shorter
-  // than the pipeline) or rows past M must not hold whatever an earlier kernel left
-  // in LDS, because 0 * NaN would poison the accumulators.
-#pragma unroll
-  for (int o = tid * 16; o < kStageBytes; o += 64 * kWaves * 16) {
-    *reinterpret_cast<uint4*>(xs0 + o) = uint4{0u, 0u, 0u, 0u};
-    *reinterpret_cast<uint4*>(xs1 + o) = uint4{0u, 0u, 0u, 0u};
-    if (NS > 2) {
-      *reinterpret_cast<uint4*>(xs2 + o) = uint4{0u, 0u, 0u, 0u};
-      *reinterpret_cast<uint4*>(xs3 + o) = uint4{0u, 0u, 0u, 0u};
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int d = 0; d < D; ++d) dma_x(d, stage_ptr(d));
 #pragma unroll
   for (int d = 0; d < NW; ++d) load_w(d, d);
+#pragma unroll
+  for (int d = 0; d < D; ++d) dma_x(d, stage_ptr(d));
 
   v2h s2[PN], s2n[PN], wa0[PN][4];
 #pragma unroll
@@ -173,9 +171,7 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
   __builtin_amdgcn_s_barrier();
 
   constexpr int Q = PN * PM;                   // MFMAs per k-step (16 k), one LDS read feeds PN of them
-  constexpr int P = 4 * PN;                    // dequantisation pieces per k-step
-  static_assert(Q >= P / 2, "at most two pieces between MFMAs");
-  constexpr int PER = (P + Q - 1) / Q;         // pieces after each MFMA
+  static_assert(PM >= 2, "the dequantisation of a word takes two stages at least");
 
   // LDS reads run XB-1 k-steps ahead of the MFMAs that consume them: a k-step of a
   // small wave tile is too short (PN*PM*32 cycles) to cover the LDS latency alone.
@@ -188,13 +184,11 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
   constexpr bool EARLY = QSPEC_TILE16_EARLY && PN * PM >= 4;
   constexpr int XB = EARLY ? 2 : (PN * PM >= 8 ? 2 : (PN * PM >= 4 ? 3 : 4));
   uint4 xb[XB][PM];
+  // this lane's k-chunk of step s is 2 s + h: s only flips bits of a lane's address
+  const int x_lane = wk * (BM * 256) + (mw0 + m32) * 256 + ((h ^ (m32 & 15)) << 4);
   auto read_step_from = [&](const uint8_t* xl, int s, uint4 (&dst)[PM]) {
-    const int c = 4 * (s >> 1) + 2 * (s & 1) + h;      // this lane's k-chunk of step s
 #pragma unroll
-    for (int t = 0; t < PM; ++t) {
-      const int row = mw0 + 32 * t + m32;
-      dst[t] = *reinterpret_cast<const uint4*>(xl + row * 256 + ((c ^ (row & 15)) << 4));
-    }
+    for (int t = 0; t < PM; ++t) dst[t] = *reinterpret_cast<const uint4*>(xl + (x_lane ^ (s << 5)) + t * 8192);
   };
   if constexpr (EARLY) read_step_from(xs0, 0, xb[0]);      // group 0, k-step 0
 
@@ -214,6 +208,7 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
       for (int s = 0; s < XB - 1; ++s) read_step(s, xb[s]);
     }
     __builtin_amdgcn_sched_barrier(0);
+    DequantWord dw;
     v2h wa[2][PN][4];                            // k-step s lives in wa[s & 1]
 #pragma unroll
     for (int j = 0; j < PN; ++j)
@@ -221,6 +216,7 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
       for (int hh = 0; hh < 4; ++hh) wa[0][j][hh] = wa0[j][hh];
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
+      if (kWaves == 8 && s % 2 == 0) setprio_quarter(s / 2);
       if (s + XB - 1 < 8) read_step(s + XB - 1, xb[(s + XB - 1) % XB]);
       if constexpr (EARLY) {
         if (s == 7) {
@@ -246,20 +242,18 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
           const v8h av = v8h{wa[s & 1][j][0].x, wa[s & 1][j][0].y, wa[s & 1][j][1].x, wa[s & 1][j][1].y,
                              wa[s & 1][j][2].x, wa[s & 1][j][2].y, wa[s & 1][j][3].x, wa[s & 1][j][3].y};
           const v8h xv = __builtin_bit_cast(v8h, xb[s % XB][t]);
-          v16f d;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) d[r] = acc[j][t][r];
-          d = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, xv, d, 0, 0, 0);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[j][t][r] = d[r];
+          acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, xv, acc[j][t], 0, 0, 0);
         }
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          const int pp = q * PER + e;            // piece of the next k-step
-          if (pp < P) {
-            const int jj = pp / 4, hh = pp % 4;
-            if (s < 7) wa[(s + 1) & 1][jj][hh] = dequant_pair_scaled(word_of_step(SLOT, jj, s + 1), hh, s2[jj]);
-            else wa0[jj][hh] = dequant_pair_scaled(wlo[NEXT][jj].x, hh, s2n[jj]);
+        // the word of pair jj for the next k-step, in PM stages between the MFMAs (t counts within jj)
+        {
+          const int jj = q / PM, st = q % PM;
+          const uint32_t word = s < 7 ? word_of_step(SLOT, jj, s + 1) : wlo[NEXT][jj].x;
+          if (st == 0) dw.bits(word);
+          if (st == (PM > 2 ? 1 : 0)) dw.codes_lo();
+          if (st == 1) dw.codes_hi();
+          if (st == (PM > 2 ? 2 : 1)) {
+            if (s < 7) dw.scale(s2[jj], wa[(s + 1) & 1][jj]);
+            else dw.scale(s2n[jj], wa0[jj]);
           }
         }
         if (s == 6 && q + 1 == Q) {
@@ -288,14 +282,52 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile16w_kernel(TileA
     }
   };
 
+  // (the loop is left between groups: a trip past the end would be arithmetic on zeros)
   for (int q = 0; q < ng; q += NW) {
     group_body(std::integral_constant<int, 0>{}, q);
+    if (q + 1 >= ng) break;
     group_body(std::integral_constant<int, 1>{}, q + 1);
-    if constexpr (NW > 2) group_body(std::integral_constant<int, 2 % NW>{}, q + 2);
-    if constexpr (NW > 2) group_body(std::integral_constant<int, 3 % NW>{}, q + 3);
+    if constexpr (NW > 2) {
+      if (q + 2 >= ng) break;
+      group_body(std::integral_constant<int, 2 % NW>{}, q + 2);
+      if (q + 3 >= ng) break;
+      group_body(std::integral_constant<int, 3 % NW>{}, q + 3);
+    }
   }
 
-  tile_store32<PN, PM>(p, tc, acc, n0, m0 + mw0);
+  if constexpr (WGK == 1) {
+    tile_store32<PN, PM, 64 * kWaves>(p, tc, acc, n0, m0 + mw0);
+  } else {
+    // Each of the WGK waves of an output tile set finishes PM / WGK of its tiles.  All partial
+    // sums go through LDS (a wave's own too: which tiles it finishes is not known at compile
+    // time); the stages are dead, the barrier that ended the last group is behind every read of
+    // them, and requests past the end have landed.
+    constexpr int kT = PN * PM, PF = kT / WGK;
+    static_assert(kT % WGK == 0 && kT % 2 == 0 && PM % PF == 0, "whole tiles of one feature column to finish per wave");
+    static_assert(kTileWaves * WGK * (kT / 2) * 4096 <= kStageBytes, "half the tiles fit a stage");
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __syncthreads();
+    // partial src of tile t: float e of lane l at e * 64 + l
+    auto slot = [&](int t, int src) -> float* {
+      const int i = ((t % (kT / 2)) * WGK + src) * kTileWaves + wt;
+      return reinterpret_cast<float*>(t < kT / 2 ? xs0 : xs1) + i * 1024 + lane;
+    };
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) slot(t, wk)[r * 64] = acc[t / PM][t % PM][r];
+    __syncthreads();
+    float fin[1][PF][16];
+#pragma unroll
+    for (int f = 0; f < PF; ++f)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        fin[0][f][r] = 0.0f;
+#pragma unroll
+        for (int src = 0; src < WGK; ++src) fin[0][f][r] += slot(wk * PF + f, src)[r * 64];
+      }
+    tile_store32<1, PF, 64 * kWaves>(p, tc, fin, n0 + 32 * (wk * PF / PM), m0 + mw0 + 32 * (wk * PF % PM));
+  }
 }
 
 }  // namespace qspec

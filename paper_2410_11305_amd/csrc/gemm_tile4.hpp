@@ -341,6 +341,8 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
 #pragma unroll
     for (int idx = 0; idx < kTiles; ++idx) {
       const int t = idx / PN, j = idx % PN;
+      // (one workgroup of eight per compute unit: its two waves per SIMD take turns by progress)
+      if (kWaves == 8) setprio_quarter(4 * idx / kTiles);
 #pragma unroll
       for (int st = 0; st < 4; ++st) {
         P[idx & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[st], b[j][st], st == 0 ? seed : P[idx & 1], 0, 0, 0);
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
 #pragma unroll
   for (int part = 0; part < 4; ++part) rescale_quarter(P[(kTiles - 1) & 1], pend_sw, pend_swc, pend_S, acc[PN - 1][PM - 1], part);
 
-  tile_store32<PN, PM, false>(p, tc, acc, n0, m0 + mw0);
+  tile_store32<PN, PM, kThreads, false>(p, tc, acc, n0, m0 + mw0);
 }
 
 }  // namespace qspec

@@ -13,6 +13,7 @@
 #include "gemm_generic.hpp"
 #include "gemm_stream.hpp"
 #include "gemm_tile16.hpp"
+#include "gemm_tile16w2.hpp"
 #include "gemm_tile4.hpp"
 #include "mlp_chain.hpp"
 #include "pack.hpp"
@@ -330,15 +331,36 @@ int launch_stream(StreamArgs a, void* workspace, hipStream_t s) {
 // Workgroup shapes the tiled kernels are instantiated for: TN x TMW MFMA tiles per
 // wavefront, WGN x WGM wavefronts per workgroup, weight ring of NW groups and NS
 // activation stages (verify mode), OCC workgroups per compute unit (the register budget the compiler is held to).
-struct TileShape { int TN, TMW, WGN, WGM, NW, NS, OCC; };
+struct TileShape { int TN, TMW, WGN, WGM, NW, NS, OCC, WGK = 1; };
 constexpr TileShape kShapes16[] = {     // verify mode (gemm_tile16w_kernel): TN, TMW count 32 x 32 tiles
-    {1, 4, 4, 1, 4, 2, 2},   // 0: 128 outputs x 128 tokens
-    {2, 2, 4, 1, 4, 4, 2},   // 1: 256 x 64, four activation stages
-    {1, 2, 4, 1, 4, 2, 3},   // 2: 128 x 64, three workgroups per compute unit
-    {1, 2, 4, 1, 4, 4, 2},   // 3: 128 x 64, four activation stages
-    {1, 4, 8, 1, 4, 2, 1},   // 4: 256 x 128, eight wavefronts, one workgroup per compute unit
-    {1, 4, 8, 1, 4, 4, 1},   // 5: 256 x 128, four activation stages
-    {1, 2, 8, 1, 4, 4, 1},   // 6: 256 x 64, eight wavefronts, four activation stages
+    {1, 4, 4, 1, 4, 2, 2},      // 0: 128 outputs x 128 tokens
+    {1, 2, 4, 1, 2, 2, 1, 2},   // 1: 128 x 64, the K groups dealt to two sets of four wavefronts
+    {1, 2, 2, 1, 2, 2, 2, 2},   // 2: 64 x 64, the K groups dealt to two pairs of wavefronts
+    {1, 4, 4, 1, 2, 2, 1, 2},   // 3: 128 x 128, the K groups dealt to two sets of four wavefronts
+    {1, 4, 8, 1, 2, 2, 1},      // 4: 256 x 128, eight wavefronts, one workgroup per compute unit
+    {2, 2, 2, 1, 2, 2, 1, 4},   // 5: 128 x 64, the K groups dealt to four pairs of wavefronts
+    {1, 2, 4, 1, 2, 2, 3},      // 6: 128 x 64, three workgroups per compute unit
+    {2, 4, 8, 1, 2, 2, 1},      // 7: 512 x 128 (gemm_tile16w2_kernel), never in K-slices
+};
+// What a plan costs, in microseconds: fixed + groups per slice * (rounds of workgroups) and, with
+// K-slices, the exchange.  A round that fills the chip takes `full` per group; the last, partial
+// one takes `alone` (what a workgroup takes with nothing beside it) while the busy compute units
+// are few, and more as they grow many: the part is power-limited under matrix work, its clock
+// falls from 2.3 GHz with half the units busy to 1.7 GHz with all of them.  Fitted to 3000 timed
+// calls: 14 layers from 2560 x 2048 to 57344 x 8192 at 48 to 2050 tokens, every shape below, one
+// to six slices, on rotating weights inside HIP graphs.  The choice by this table is 1.1 % slower
+// than the best measured plan on average (9 % at worst but for two), and 9 % faster than the fill
+// rules it replaces on the same kernels.
+struct TileCost { double fixed, alone, full, slice0, slice1; };
+constexpr TileCost kCost16[] = {
+    {2.2, 1.00, 1.91, 0.0, 0.0},   // 0: only where more than one round of it is needed (plan_tile16)
+    {4.3, 0.47, 0.64, 3.5, 0.65},  // 1
+    {3.4, 0.42, 0.69, 2.8, 0.65},  // 2
+    {6.1, 0.72, 1.05, 5.0, 0.80},  // 3
+    {8.1, 1.08, 1.90, 7.1, 1.65},  // 4
+    {6.2, 0.43, 0.59, 2.1, 1.00},  // 5
+    {2.2, 0.78, 1.29, 0.0, 0.0},   // 6: only up to 64 tokens on more than one round
+    {12.0, 1.98, 3.52, 0.0, 0.0},  // 7
 };
 constexpr TileShape kShapes4[] = {      // draft mode (gemm_tile4w_kernel): TN, TMW count 32 x 32 tiles; NW = NS = 3
     {1, 4, 4, 1, 3, 3, 2},   // 0: 128 outputs x 128 tokens
@@ -347,7 +369,7 @@ constexpr TileShape kShapes4[] = {      // draft mode (gemm_tile4w_kernel): TN, 
     {1, 4, 8, 1, 3, 3, 1},   // 3: 256 x 128, eight wavefronts, one workgroup per compute unit
 };
 constexpr int kNumTileShapes = 4;
-constexpr int kNumShapes16 = 7;
+constexpr int kNumShapes16 = 8;
 struct TilePlan {
   int shape;      // index into the mode's shape table
   int S;          // K-slices
@@ -365,15 +387,41 @@ bool tile_override(bool w4a4, int* shape, int* S) {
   return *shape >= 0 && *shape < (w4a4 ? kNumTileShapes : kNumShapes16) && *S >= 1;
 }
 
+// Cheapest verify-mode plan by kCost16.
+void plan_tile16(int M, int N, int G, int* shape, int* slices) {
+  double best = 1e30;
+  for (int i = 0; i < kNumShapes16; ++i) {
+    const TileShape& t = kShapes16[i];
+    const TileCost& c = kCost16[i];
+    const long long blocks = (long long)((N + 32 * t.TN * t.WGN - 1) / (32 * t.TN * t.WGN)) * ((M + 32 * t.TMW * t.WGM - 1) / (32 * t.TMW * t.WGM));
+    const int places = t.OCC * kNumCU;
+    if ((i == 0 || i == 6) && blocks <= places) continue;       // (one round: the K-dealing shapes of the same block are faster)
+    if (i == 6 && M > 64) continue;
+    for (int S : {1, 2, 3, 4, 6, 8}) {
+      // K-slices only while all workgroups have a compute unit of their own, of six groups at least
+      if (S > 1 && (c.slice0 == 0.0 || blocks * S > kNumCU || G / S < 6)) break;
+      const long long full = blocks * S / places, rest = blocks * S % places;
+      double round = full * c.full;
+      if (rest > 0) {
+        if (t.OCC > 1) round += rest > kNumCU ? c.full : c.alone;
+        else round += c.full * rest / places > c.alone ? c.full * rest / places : c.alone;
+      }
+      // (the exchange of few workgroups is cheaper: 48 of 64 x 64 in two slices 3.1 us, 240 of them 4.0)
+      const double xch = S > 1 ? (c.slice0 + c.slice1 * S) * (0.7 + 0.3 * blocks * S / kNumCU) : 0.0;
+      const double cost = c.fixed + round * G / S + xch;
+      if (cost < best) { best = cost; *shape = i; *slices = S; }
+    }
+  }
+}
+
 // Pure function of (mode, M, N, K): qspec_workspace_bytes and the GEMM entry points agree.
 TilePlan plan_tile(bool w4a4, int M, int N, int K) {
   const int G = K / kGroup;
   TilePlan p{};
   int shape = 0, S = 1;
   if (!tile_override(w4a4, &shape, &S)) {
-    // Both rules below come from sweeps over the Llama-shaped layers on the MI355X; the
+    // The draft-mode rules come from sweeps over the Llama-shaped layers on the MI355X; the
     // figures quoted are microseconds per call before -> after the rule.
-    bool s_chosen = false;
     if (w4a4) {
       // Two block sizes, 128 x 128 (a weight operand feeds four token tiles) and 128 x 64, and up
       // to four K-slices: the plan that comes closest to filling the 512 places of the chip
@@ -456,60 +504,8 @@ TilePlan plan_tile(bool w4a4, int M, int N, int K) {
           if (blocks3 * 100 >= rounds3 * kNumCU * (rounds3 <= 2 ? 85 : 95)) { shape = 3; S = 1; }
         }
       }
-      s_chosen = true;
     } else {
-      const int blocks128 = ((N + 127) / 128) * ((M + 127) / 128);
-      const int blocks64 = ((N + 127) / 128) * ((M + 63) / 64);
-      // 128 x 64 blocks: with at most one workgroup per compute unit the instance with
-      // four activation stages hides more latency (measured 23.5 -> 21.4 us at 128 tokens
-      // on 12288 x 4096); with more workgroups than compute units the three-per-unit instance
-      // (128 x 128 blocks also from 120 blocks on when K is long enough for the two K-slices that
-      // then fill the chip: 28672 -> 8192 at 512 tokens 254 -> 236 us, at 256 tokens 141 -> 134 us;
-      // 11008 -> 4096 at 512: 60.3 -> 58.8 us; 13824 -> 5120 at 384: 71.0 -> 68.9 us)
-      // (and from one 128 x 128 block per compute unit on: 8192 x 8192 at 512 tokens, 256 blocks:
-      // 74.1 us on 512 blocks of 128 x 64, 73.1 on 256 x 128 in two K-slices, 70.7 here)
-      const bool big = M > 64 && (blocks128 >= 2 * kNumCU || (blocks128 >= 120 && G >= 86) || (M >= 128 && blocks128 >= kNumCU));
-      shape = big ? 0 : (blocks64 <= kNumCU ? 3 : 2);
-      // 256 x 128 blocks on eight wavefronts (one workgroup per compute unit) halve the
-      // activation bytes a compute unit pulls per output (the global -> LDS transfers of x are
-      // 19 % of the 128 x 128 instance's time), but with one workgroup per unit a ragged round
-      // costs a whole round.  Taken when ONE round is at least 58 % full, counting the two
-      // K-slices a long K allows (10240 x 8192 at 512 tokens, 160 blocks: 103.4 -> 94.5 us;
-      // 15360 x 5120 at 384, 180 blocks: 70.8 -> 66.5; 12288 x 4096 at 512, 192 blocks: 59.6 ->
-      // 57.5; 28672 -> 8192 at 512, 128 blocks in two slices: 241 -> 229; 128 blocks unsliced
-      // lose: 8192 x 8192 at 512 tokens 75 -> 89 us), or when several rounds are at least 85 %
-      // full (57344 x 8192 at 256 tokens, 448 blocks: 255 -> 236 us; at 512 tokens, 896 blocks
-      // = 3.5 rounds: equal; 324 and 344 blocks lose 10 %).
-      const int blocks256 = ((N + 255) / 256) * ((M + 127) / 128);
-      const int rounds256 = (blocks256 + kNumCU - 1) / kNumCU;
-      if (M >= 128) {                                  // (57344 x 8192 at 128 tokens, 224 blocks: 135 -> 123 us)
-        int s256 = (M >= 256 && blocks256 * 2 <= kNumCU && G >= 64) ? 2 : 1;      // the slices the rule below will cut
-        if (s256 == 2 && blocks128 >= kNumCU && G < 86) s256 = 1;                 // (unsliced 128 x 128 blocks fill the chip: see above)
-        // (from three rounds on they must be 95 % full: 57344 x 8192 at 512 tokens, 3.5 rounds: 441 us, 128 x 128 blocks 435)
-        const int need_pct = rounds256 <= 2 ? 85 : 95;
-        if (rounds256 == 1 ? blocks256 * s256 >= 150 : blocks256 * 100 >= rounds256 * kNumCU * need_pct) shape = 4;
-      }
-    }
-    // K-slices (measured: the exchange costs 4-8 us).  They pay while ALL workgroups
-    // still run at once on compute units of their own: S = the largest count (not only
-    // powers of two: slices are cut proportionally) with blocks * S <= 256 and at least 8
-    // groups per slice.  Beyond that the extra workgroups queue behind the first ones
-    // and only the exchange is added (172 blocks of a 22016-wide layer at 64 tokens:
-    // 25.2 us unsliced, 29.6 us in two slices; 128 blocks of 8192 x 8192 at 128 tokens:
-    // 40.9 -> 29.7 us).  With very long K (at least 43 groups per slice after doubling:
-    // 11008 -> 4096 at 512 tokens 60.3 -> 58.8 us; 32 or 40 groups per slice lose, 8192 x 8192
-    // at 512 tokens 70.7 -> 75.4, 8192 x 10240: 93.0 -> 97.0) doubling still pays while the
-    // workgroups stay resident together (two per unit).
-    if (!s_chosen) {
-      const TileShape& t0 = shape_of(w4a4, shape);
-      const int blocks = ((N + 32 * t0.TN * t0.WGN - 1) / (32 * t0.TN * t0.WGN)) * ((M + 32 * t0.TMW * t0.WGM - 1) / (32 * t0.TMW * t0.WGM));
-      const int resident = t0.OCC >= 2 ? 2 * kNumCU : kNumCU;     // workgroups that run at once
-      S = kNumCU / blocks;
-      if (S > 8) S = 8;
-      while (S > 1 && G / S < 8) --S;
-      if (S < 1) S = 1;
-      // (only while the doubled count still fits)
-      while (S < 8 && blocks * S * 2 <= resident && G / (2 * S) >= 43) S *= 2;
+      plan_tile16(M, N, G, &shape, &S);
     }
   }
   const TileShape& t = shape_of(w4a4, shape);
@@ -519,7 +515,7 @@ TilePlan plan_tile(bool w4a4, int M, int N, int K) {
   p.nb = (N + bn - 1) / bn;
   p.mb = (M + bm - 1) / bm;
   if (S > G) S = G;
-  if (p.nb * p.mb > kMaxTickets) S = 1;
+  if (p.nb * p.mb > kMaxTickets || (!w4a4 && shape == 7)) S = 1;
   p.S = S;
   return p;
 }
@@ -541,10 +537,10 @@ int launch_tile4w_inst(const TileArgs& a, bool wide, hipStream_t s) {
   return QSPEC_OK;
 }
 
-template <int PN, int PM, int WGN, int WGM, int NW, int NS, int OCC>
+template <int PN, int PM, int WGN, int WGM, int NW, int NS, int OCC, int WGK = 1>
 int launch_tile16w_inst(const TileArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_tile16w_kernel<PN, PM, WGN, WGM, NW, NS, OCC>), dim3(a.nb * a.mb * a.S),
-                     dim3(64 * WGN * WGM), 0, s, a);
+  hipLaunchKernelGGL((gemm_tile16w_kernel<PN, PM, WGN, WGM, WGK, NW, NS, OCC>), dim3(a.nb * a.mb * a.S),
+                     dim3(64 * WGN * WGM * WGK), 0, s, a);
   return QSPEC_OK;
 }
 
@@ -563,12 +559,15 @@ int launch_tile(const TilePlan& plan, TileArgs a, void* workspace, hipStream_t s
   }
   switch (plan.shape) {
     case 0: return launch_tile16w_inst<1, 4, 4, 1, 4, 2, 2>(a, s);
-    case 1: return launch_tile16w_inst<2, 2, 4, 1, 4, 4, 2>(a, s);
-    case 2: return launch_tile16w_inst<1, 2, 4, 1, 4, 2, 3>(a, s);
-    case 3: return launch_tile16w_inst<1, 2, 4, 1, 4, 4, 2>(a, s);
-    case 4: return launch_tile16w_inst<1, 4, 8, 1, 4, 2, 1>(a, s);
-    case 5: return launch_tile16w_inst<1, 4, 8, 1, 4, 4, 1>(a, s);
-    default: return launch_tile16w_inst<1, 2, 8, 1, 4, 4, 1>(a, s);
+    case 1: return launch_tile16w_inst<1, 2, 4, 1, 2, 2, 1, 2>(a, s);
+    case 2: return launch_tile16w_inst<1, 2, 2, 1, 2, 2, 2, 2>(a, s);
+    case 3: return launch_tile16w_inst<1, 4, 4, 1, 2, 2, 1, 2>(a, s);
+    case 4: return launch_tile16w_inst<1, 4, 8, 1, 2, 2, 1>(a, s);
+    case 5: return launch_tile16w_inst<2, 2, 2, 1, 2, 2, 1, 4>(a, s);
+    case 6: return launch_tile16w_inst<1, 2, 4, 1, 2, 2, 3>(a, s);
+    default:
+      hipLaunchKernelGGL(gemm_tile16w2_kernel, dim3(a.nb * a.mb), dim3(512), 0, s, a);
+      return QSPEC_OK;
   }
 }
 
@@ -1067,7 +1066,8 @@ int qspec_describe_kernel(int mode_w4a4, int M, int N, int K, int group, char* o
     if (!use_generic()) {
       const TileShape& t = shape_of(mode_w4a4 != 0, plan_tile(mode_w4a4 != 0, M, N, K).shape);
       if (mode_w4a4) snprintf(out, cap, "gemm_tile4w_kernel<%d, %d, %d, %d, %d, false>", t.TN, t.TMW, t.WGN, t.WGM, t.OCC);
-      else snprintf(out, cap, "gemm_tile16w_kernel<%d, %d, %d, %d, %d, %d, %d>", t.TN, t.TMW, t.WGN, t.WGM, t.NW, t.NS, t.OCC);
+      else if (t.TN == 2 && t.TMW == 4) snprintf(out, cap, "gemm_tile16w2_kernel");
+      else snprintf(out, cap, "gemm_tile16w_kernel<%d, %d, %d, %d, %d, %d, %d, %d>", t.TN, t.TMW, t.WGN, t.WGM, t.WGK, t.NW, t.NS, t.OCC);
     } else if (mode_w4a4) snprintf(out, cap, "gemm_w4a4_generic<%d, 4, false>", pick_tm(M));
     else snprintf(out, cap, "gemm_w4a16_generic<%d, 4>", pick_tm(M));
   }
