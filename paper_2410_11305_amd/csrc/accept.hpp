@@ -8,12 +8,12 @@
 // extra token) is the verify pass's own top-1.  Ties go to the lowest token id.
 //
 // Two launches, no atomics, no state: argmax_partial_kernel scans one chunk of
-// one row per workgroup (HBM-bound: every logit is read once, 16 bytes per
-// lane) and leaves a 64-bit key per chunk in the workspace; accept_kernel (one
-// wavefront per sequence) reduces the keys of each row and walks the drafts in
-// order.  A key is (order-preserving image of the fp16 value) << 32 | ~index,
-// so that the unsigned maximum is the largest value and, among equals, the
-// lowest index.
+// one row per workgroup (every logit is read once, 16 bytes per lane) and leaves
+// a 64-bit key per chunk in the workspace; accept_kernel (one workgroup per
+// sequence, one wavefront per row) reduces the keys of its rows and finds the
+// first rejected draft.  A key is (order-preserving image of the fp16 value) << 32
+// | ~index, so that the unsigned maximum is the largest value and, among equals,
+// the lowest index.
 #pragma once
 #include "buffer.hpp"
 #include "common.hpp"
@@ -21,6 +21,7 @@
 namespace qspec {
 
 constexpr int kArgmaxThreads = 256;
+constexpr int kArgmaxLoads = 2;             // 16-byte loads in flight per lane: 4096 logits per trip of a workgroup
 constexpr int kArgmaxMaxChunks = 64;        // one lane of the second kernel per chunk
 
 // fp16 bits -> 16-bit unsigned whose order is the order of the values
@@ -31,15 +32,35 @@ __device__ inline uint32_t half_order_key(uint32_t bits) {
   return (bits & 0x8000u) ? (bits ^ 0xFFFFu) : (bits | 0x8000u);
 }
 
+// The same order as a signed 16-bit value, for both halves of a word at once (three
+// operations for two logits): negative values count down from 0, -0 and +0 are 0.
+typedef short v2s __attribute__((ext_vector_type(2)));
+__device__ inline v2s half_order_pair(uint32_t w) {
+  const v2s x = __builtin_bit_cast(v2s, w);
+  const v2s neg = x >> (short)15;
+  const uint32_t mag = (w & 0x7FFF7FFFu) ^ __builtin_bit_cast(uint32_t, neg);
+  return __builtin_bit_cast(v2s, mag) - neg;
+}
+__device__ inline uint32_t half_order_of(int k) { return (uint32_t)(k + 0x8000); }   // as half_order_key counts
+
+// Maximum over the 64 lanes (all active), wave-uniform.  DPP moves inside rows of 16 and
+// across them: six vector operations where six ds_bpermute are six trips through LDS.
+__device__ inline uint32_t wave_max_u32(uint32_t v) {
+#define QSPEC_DPP_MAX(ctrl, rows) \
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, rows, 0xf, false))
+  QSPEC_DPP_MAX(0x111, 0xf);      // row_shr 1, 2, 4, 8: lane 15 of a row holds the row's maximum
+  QSPEC_DPP_MAX(0x112, 0xf);
+  QSPEC_DPP_MAX(0x114, 0xf);
+  QSPEC_DPP_MAX(0x118, 0xf);
+  QSPEC_DPP_MAX(0x142, 0xa);      // row_bcast 15 into rows 1 and 3
+  QSPEC_DPP_MAX(0x143, 0xc);      // row_bcast 31 into rows 2 and 3: lane 63 holds the maximum
+#undef QSPEC_DPP_MAX
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
 __device__ inline uint64_t wave_max_u64(uint64_t k) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)k, off, 64);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(k >> 32), off, 64);
-    const uint64_t o = ((uint64_t)hi << 32) | lo;
-    k = o > k ? o : k;
-  }
-  return k;
+  const uint32_t hi = wave_max_u32((uint32_t)(k >> 32));
+  const uint32_t lo = wave_max_u32((uint32_t)(k >> 32) == hi ? (uint32_t)k : 0u);
+  return ((uint64_t)hi << 32) | lo;
 }
 
 struct ArgmaxArgs {
@@ -49,33 +70,62 @@ struct ArgmaxArgs {
 };
 
 // grid (C, R).  VEC: V % 8 == 0, rows are 16-byte aligned, 8 logits per load.
+// The scan costs two vector operations per logit (packed order, packed maximum); only the
+// lanes that hold the wave's maximum then look for its lowest index.  (One comparison and
+// two selects per logit, ten operations in all, took as long as the memory reads: 512 rows of
+// 32000 logits 10.2 -> 8.2 us.)
 template <bool VEC>
 __global__ __launch_bounds__(kArgmaxThreads) void argmax_partial_kernel(ArgmaxArgs p) {
+  constexpr int U = kArgmaxLoads;
   const int c = blockIdx.x, r = blockIdx.y;
   const int begin = c * p.chunk;
   const int end = min(p.V, begin + p.chunk);
   const uint16_t* row = p.logits + (size_t)r * p.V;
-  uint32_t best = 0u, best_i = 0xFFFFFFFFu;          // key 0 is below every real key (the lowest is 0x0000 only for NaN patterns)
-  bool have = false;
+  uint64_t key = 0ull;                               // below every real key
   if (VEC) {
-    for (int i = begin + (int)threadIdx.x * 8; i < end; i += kArgmaxThreads * 8) {
-      const uint4 q = *reinterpret_cast<const uint4*>(row + i);
-      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+    for (int base = begin; base < end; base += U * kArgmaxThreads * 8) {
+      // pieces past the end re-read the last one, under its own index
+      uint4 q[U];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t k = half_order_key(w[e >> 1] >> ((e & 1) * 16));
-        // indices rise inside a thread: a strict comparison keeps the lowest index of equal values
-        if (!have || k > best) { best = k; best_i = (uint32_t)(i + e); have = true; }
+      for (int u = 0; u < U; ++u) q[u] = *reinterpret_cast<const uint4*>(row + min(base + (u * kArgmaxThreads + (int)threadIdx.x) * 8, end - 8));
+      v2s k[U][4];
+      v2s m2 = {(short)-0x8000, (short)-0x8000};
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t w[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          k[u][e] = half_order_pair(w[e]);
+          m2 = __builtin_elementwise_max(m2, k[u][e]);
+        }
       }
+      const int m = max((int)m2.x, (int)m2.y);
+      const uint32_t top = wave_max_u32(half_order_of(m));
+      if (top <= (uint32_t)(key >> 32)) continue;    // (wave-uniform) equal values further on do not count
+      uint32_t first = 0xFFFFFFFFu;
+      if (half_order_of(m) == top) {
+#pragma unroll
+        for (int u = U - 1; u >= 0; --u) {
+          const uint32_t i = (uint32_t)min(base + (u * kArgmaxThreads + (int)threadIdx.x) * 8, end - 8);
+#pragma unroll
+          for (int e = 3; e >= 0; --e) {
+            if ((int)k[u][e].y == m) first = i + 2 * e + 1;
+            if ((int)k[u][e].x == m) first = i + 2 * e;
+          }
+        }
+      }
+      key = ((uint64_t)top << 32) | wave_max_u32(~first);
     }
   } else {
+    uint32_t best = 0u, best_i = 0xFFFFFFFFu;
+    bool have = false;
     for (int i = begin + (int)threadIdx.x; i < end; i += kArgmaxThreads) {
       const uint32_t k = half_order_key(row[i]);
+      // indices rise inside a thread: a strict comparison keeps the lowest index of equal values
       if (!have || k > best) { best = k; best_i = (uint32_t)i; have = true; }
     }
+    key = wave_max_u64(have ? (((uint64_t)best << 32) | (uint64_t)(~best_i)) : 0ull);
   }
-  uint64_t key = have ? (((uint64_t)best << 32) | (uint64_t)(~best_i)) : 0ull;
-  key = wave_max_u64(key);
   __shared__ uint64_t part[kArgmaxThreads / 64];
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = key;
   __syncthreads();
@@ -95,29 +145,39 @@ struct AcceptArgs {
   int gamma, C;
 };
 
-// One wavefront per sequence (grid B, 64 threads).
-__global__ __launch_bounds__(64) void accept_kernel(AcceptArgs p) {
-  const int b = blockIdx.x, lane = threadIdx.x;
+// One workgroup per sequence, one wavefront per row, kAcceptRows rows at a time (the loop of
+// further rows is for longer drafts): the rows' keys arrive together.  (One wavefront walking the
+// rows paid a trip to memory for each: the stores of the tokens keep the loads behind them;
+// 128 sequences of 4 rows 4.1 -> 3.3 us.)
+constexpr int kAcceptRows = 16;
+__global__ __launch_bounds__(64 * kAcceptRows) void accept_kernel(AcceptArgs p) {
+  __shared__ int32_t tops[kAcceptRows];
+  __shared__ int32_t same[kAcceptRows];
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = blockDim.x >> 6;
   const int rows = p.gamma + 1;
-  int n = 0;
   bool open = true;                       // no draft rejected so far
-  for (int j = 0; j < rows; ++j) {
-    uint64_t k = lane < p.C ? p.keys[((size_t)b * rows + j) * p.C + lane] : 0ull;
-    k = wave_max_u64(k);
-    const int32_t top = (int32_t)(~(uint32_t)k);
-    int32_t emit = -1;
-    if (open) {
-      if (j < p.gamma && p.draft[(size_t)b * p.gamma + j] == top) {
-        emit = top;                       // accepted draft
-        n = j + 1;
-      } else {
-        emit = top;                       // the verify pass's own token: correction, or the extra one
-        open = false;
-      }
+  for (int base = 0; base < rows; base += waves) {
+    const int here = min(waves, rows - base);
+    if (wave < here) {
+      const int j = base + wave;
+      const int32_t draft = p.draft[(size_t)b * p.gamma + min(j, p.gamma - 1)];
+      const uint64_t k = wave_max_u64(lane < p.C ? p.keys[((size_t)b * rows + j) * p.C + lane] : 0ull);
+      const int32_t top = (int32_t)(~(uint32_t)k);
+      if (lane == 0) { tops[wave] = top; same[wave] = j < p.gamma && draft == top; }
     }
-    if (lane == 0) p.out_tokens[(size_t)b * rows + j] = emit;
+    __syncthreads();
+    // the row where the drafts of this part end: the verify pass's own token (the correction, or the
+    // extra one at row gamma) is the last that is emitted
+    const uint64_t miss = __ballot(lane < here && same[lane < here ? lane : 0] == 0);
+    const int stop = miss ? __builtin_ctzll(miss) : here;
+    if (wave == 0) {
+      if (lane < here) p.out_tokens[(size_t)b * rows + base + lane] = open && lane <= stop ? tops[lane] : -1;
+      if (lane == 0 && open && miss) p.n_accept[b] = base + stop;
+    }
+    if (miss) open = false;
+    __syncthreads();                      // tops and same are free for the next part
   }
-  if (lane == 0) p.n_accept[b] = n;
 }
 
 struct KvArgs {

@@ -1033,7 +1033,7 @@ int qspec_greedy_accept(const void* logits_f16, const int32_t* draft_tokens, int
   if (V % 8 == 0) hipLaunchKernelGGL((argmax_partial_kernel<true>), dim3(plan.C, R), dim3(kArgmaxThreads), 0, s, a);
   else hipLaunchKernelGGL((argmax_partial_kernel<false>), dim3(plan.C, R), dim3(kArgmaxThreads), 0, s, a);
   AcceptArgs f{static_cast<const uint64_t*>(workspace), draft_tokens, n_accept, out_tokens, gamma, plan.C};
-  hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64), 0, s, f);
+  hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64 * (gamma + 1 < kAcceptRows ? gamma + 1 : kAcceptRows)), 0, s, f);
   return launch_status();
 }
 

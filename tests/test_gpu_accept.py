@@ -66,6 +66,56 @@ def test_accept_ties_signed_zeros_and_infinities(env, V):
     assert a_ref[:6].tolist() == [3] * 6 and a_ref[6:9].tolist() == [1] * 3 and a_ref[9:].tolist() == [0] * 3
 
 
+def test_accept_orders_every_pair_of_neighbouring_values(env):
+    """Each row holds two fp16 values that follow one another (from -inf to inf, the zeros
+    equal), the larger one anywhere among eight: the packed order of the scan, value by value."""
+    bits = np.arange(0x7C01, dtype=np.uint16)
+    up = np.concatenate([(bits[::-1] | 0x8000), bits]).view(np.float16)       # -inf .. -0, +0 .. inf
+    Bn = (up.size - 1) // 2
+    rng = np.random.default_rng(5)
+    at = rng.integers(0, 8, 2 * Bn)
+    logits = np.repeat(up[:2 * Bn, None], 8, axis=1)
+    logits[np.arange(2 * Bn), at] = up[1:2 * Bn + 1]
+    top = np.argmax(logits, axis=1).reshape(Bn, 2)
+    draft = top[:, :1].astype(np.int32)
+    a, out = run_accept(env, logits.reshape(Bn, 2, 8), draft)
+    assert (a == 1).all()
+    assert (out == top).all()
+
+
+@pytest.mark.parametrize("V", [2040, 2048, 2056, 4096, 4104, 64 * 4096, 64 * 4096 + 8, 64 * 6144 - 8])
+def test_accept_finds_maxima_at_the_edges_of_pieces_and_trips(env, V):
+    """The maximum, and an equal one further on, at the ends of a lane's load, of a trip of the
+    scan and of a chunk; the longest rows take a workgroup more than one trip."""
+    edges = sorted({i for e in (0, 8, 512, 2048, 4096, 4104, 6144, V) for i in (e - 1, e, e + 1) if 0 <= i < V})
+    rng = np.random.default_rng(V)
+    logits = rng.integers(-3, 3, (len(edges), 2, V)).astype(np.float16)
+    for b, i in enumerate(edges):
+        logits[b, :, i] = 7.0
+        logits[b, 1, edges[-1]] = 7.0
+    top = np.argmax(logits, axis=2)
+    a, out = run_accept(env, logits, top[:, :1].astype(np.int32))
+    assert (a == 1).all()
+    assert (out == top).all()
+
+
+@pytest.mark.parametrize("gamma", [14, 15, 16, 31, 32, 40])
+def test_accept_of_long_drafts_stops_at_every_row(env, gamma):
+    """One sequence per place of the first rejection: the rows are walked sixteen at a time."""
+    Bn, V = gamma + 2, 40
+    rng = np.random.default_rng(gamma)
+    logits = rng.standard_normal((Bn, gamma + 1, V)).astype(np.float16)
+    draft = np.argmax(logits, axis=2)[:, :gamma].astype(np.int32)
+    for b in range(gamma):
+        draft[b, b] = (draft[b, b] + 1) % V           # first rejection at b; the last two accept everything
+        draft[b, b + 1:] = rng.integers(0, V, gamma - b - 1)
+    a_ref, out_ref = acc.greedy_accept(logits, draft)
+    a, out = run_accept(env, logits, draft)
+    assert a_ref.tolist() == list(range(gamma)) + [gamma, gamma]
+    assert a.tolist() == a_ref.tolist()
+    assert out.tolist() == out_ref.tolist()
+
+
 @pytest.mark.parametrize("config", [1, 2, 3, 4, 5])
 def test_accept_benchmark_configuration(env, config):
     """Full size (the launch the benchmark times).  The pure-Python oracle walks a
@@ -105,7 +155,8 @@ def test_accept_is_deterministic_and_reuses_its_workspace(env):
         assert n.cpu().numpy().tolist() == a_ref.tolist() and o.cpu().numpy().tolist() == out_ref.tolist()
 
 
-@pytest.mark.parametrize("Bn,gamma,S,D", [(1, 1, 4, 8), (4, 3, 12, 128), (8, 3, 2048, 4096), (5, 5, 64, 1032), (3, 2, 3, 16)])
+@pytest.mark.parametrize("Bn,gamma,S,D", [(1, 1, 4, 8), (4, 3, 12, 128), (8, 3, 2048, 4096), (5, 5, 64, 1032), (3, 2, 3, 16),
+                                         (2, 2, 5, 2040), (2, 2, 5, 2048), (2, 2, 5, 2056), (2, 2, 5, 4104)])
 def test_kv_overwrite_matches_oracle(env, Bn, gamma, S, D):
     torch, B = env
     rng = np.random.default_rng(Bn * 1000 + S)
