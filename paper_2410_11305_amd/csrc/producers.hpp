@@ -210,6 +210,40 @@ __global__ __launch_bounds__(kRowMaxThreads) void rmsnorm_quant_kernel(const uin
   }
 }
 
+// g / (1 + exp(-g)) in binary64, rounded to binary32, for an fp16 value g.  The vector unit
+// bounds the SiLU kernel at large M, so: Taylor polynomial of degree 11 after one reduction by
+// n ln 2 (relative error 2^-46 with |r| <= ln 2 / 2), the power of two added to the exponent
+// field, and a reciprocal estimate with two Newton steps instead of a division.  That is the
+// correctly rounded result for every fp16 g (there are 63488: the tests walk all of them).
+// g outside +-700 is held there for the exponential, which changes nothing: the result is g
+// or underflows to zero.  -inf gives NaN (-inf / inf).
+// (128 x 28672 outputs, with the quantiser's divisions by reciprocal: 11.4 -> 10.2 us.)
+__device__ inline float silu_f32(float g) {
+  const float x = fminf(fmaxf(-g, -700.0f), 700.0f);
+  const float nf = rintf(x * 1.44269504f);
+  const int n = (int)nf;
+  const double r = fma((double)nf, -0.69314718055994530942, (double)x);
+  double e = 1.0 / 39916800.0;
+  e = fma(e, r, 1.0 / 3628800.0);
+  e = fma(e, r, 1.0 / 362880.0);
+  e = fma(e, r, 1.0 / 40320.0);
+  e = fma(e, r, 1.0 / 5040.0);
+  e = fma(e, r, 1.0 / 720.0);
+  e = fma(e, r, 1.0 / 120.0);
+  e = fma(e, r, 1.0 / 24.0);
+  e = fma(e, r, 1.0 / 6.0);
+  e = fma(e, r, 0.5);
+  e = fma(e, r, 1.0);
+  e = fma(e, r, 1.0);                                       // in [0.70, 1.42]
+  e = __builtin_bit_cast(double, __builtin_bit_cast(long long, e) + ((long long)n << 52));
+  const double d = 1.0 + e;
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(fma(-d, y, 1.0), y, y);
+  y = fma(fma(-d, y, 1.0), y, y);
+  const float s = (float)((double)g * y);
+  return g == -__builtin_inff() ? __builtin_nanf("") : s;
+}
+
 // gate_up: fp16 [M][2I], the gate in the first I columns.  One thread per 8 outputs,
 // n_words = M * I / 8.  h_out may be null.
 __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint4* __restrict__ gate_up, int I8,
@@ -229,9 +263,7 @@ __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint4* __rest
   float v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const double g = (double)(float)gh[e];
-    const float s = (float)(g / (1.0 + exp(-g)));
-    v[e] = (float)(_Float16)rounded_f32(s * (float)uh[e]);
+    v[e] = (float)(_Float16)rounded_f32(silu_f32((float)gh[e]) * (float)uh[e]);
   }
   finish_unit(v, (rotate & 1) != 0, live, idx, qa_words, sa, h_out, (rotate & 2) != 0);
 }

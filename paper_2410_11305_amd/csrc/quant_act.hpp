@@ -29,6 +29,17 @@ __device__ inline float row16_max(float a) {
 // code word); 16 adjacent lanes (one row) own one group, so the absmax is a
 // 4-step fold inside the row and no LDS is needed.
 //
+// The correctly rounded v / s from y, the correctly rounded 1 / s, for v / s below 2^4 and
+// operands whose quotient and remainder are normal (fp16 values over a seventh of one are):
+// v y is within 1.5 units in the last place, one remainder step brings it below one unit,
+// and from there a second one rounds correctly (Markstein 1990: the remainder is exact).
+// Five operations where the compiler's division takes a dozen.
+__device__ inline float div_by_reciprocal(float v, float s, float y) {
+  float q = v * y;
+  q = __builtin_fmaf(__builtin_fmaf(-q, s, v), y, q);
+  return __builtin_fmaf(__builtin_fmaf(-q, s, v), y, q);
+}
+
 // quantise_word: the arithmetic alone.  v = this thread's 8 activations (fp16 values
 // widened to binary32); returns its code word (8 nibbles in the device nibble order)
 // and the group's scale.  Every lane of the wavefront must call it (the shuffles).
@@ -40,9 +51,12 @@ __device__ inline uint32_t quantise_word(const float (&v)[8], float* s_out) {
   const float s = a / 7.0f;
   uint32_t w = 0;
   if (a > 0.0f) {
+    const bool finite = a < __builtin_inff();    // (an infinite scale: x / inf, which has no remainder)
+    const float y = 1.0f / s;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      float t = rintf(v[e] / s);                 // v_rndne: ties to even
+      const float q = div_by_reciprocal(v[e], s, y);
+      float t = rintf(finite ? q : v[e] * 0.0f); // v_rndne: ties to even; v / inf is 0, or NaN for an infinite v
       t = fminf(fmaxf(t, -8.0f), 7.0f);
       w |= ((uint32_t)(int)t & 0xFu) << (4 * nibble_pos(e));
     }

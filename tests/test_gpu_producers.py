@@ -117,6 +117,39 @@ def test_silu_mul_quant_whole_gate_range(env):
     run_silu(env, gu[finite])
 
 
+def test_quotients_next_to_rounding_points_of_every_scale(env):
+    """One group per positive finite fp16 maximum (every scale there is), filled with the fp16
+    values nearest (k + 1/2) s and their neighbours: the codes of the correctly rounded quotient."""
+    torch, B = env
+    a = np.arange(1, 0x7C00, dtype=np.uint16).view(np.float16)
+    s = a.astype(np.float32) / np.float32(7)
+    rng = np.random.default_rng(9)
+    x = (s[:, None].astype(np.float64) * (rng.integers(-7, 7, (a.size, 128)) + 0.5)).astype(np.float16)
+    x = (x.view(np.uint16).astype(np.int32) + rng.integers(-1, 2, x.shape)).clip(0, 0xFFFF).astype(np.uint16).view(np.float16)
+    x = np.where(np.abs(x) <= a[:, None], x, a[:, None])         # (NaN patterns and larger neighbours go too)
+    x[np.arange(a.size), rng.integers(0, 128, a.size)] = a
+    qa, sa = B.quant_act(dev(torch, x))
+    check_against(torch, qa, sa, None, x)
+    qa8, sa8 = B.quant_act_wide(dev(torch, x))
+    check_wide_against(torch, qa8, sa8, x)
+
+
+def test_infinite_group_maximum_leaves_the_finite_codes_zero(env):
+    torch, B = env
+    x = np.random.default_rng(10).standard_normal((4, 256)).astype(np.float16)
+    x[1, 5], x[2, 200] = np.inf, -np.inf
+    qa, sa = B.quant_act(dev(torch, x))
+    codes, scales = lay.decode_act_bytes(qa.cpu().numpy()), sa.cpu().numpy()
+    clean = np.where(np.isfinite(x), x, np.float16(0))
+    q_ref, s_ref = orc.quant_act(clean)
+    hit = np.zeros((4, 2), bool)
+    hit[1, 0] = hit[2, 1] = True
+    assert np.isinf(scales[hit]).all() and np.array_equal(scales[~hit], s_ref[~hit])
+    wide = np.repeat(hit, 128, axis=1)
+    assert np.array_equal(codes[~wide], q_ref[~wide])
+    assert (codes[wide & np.isfinite(x)] == 0).all()
+
+
 @pytest.mark.parametrize("config", [1, 2, 3, 4, 5])
 def test_producers_on_benchmark_shapes_feed_the_draft_gemm(env, config):
     """Draft-pass shapes of every configuration; the codes of the fused RMSNorm go
