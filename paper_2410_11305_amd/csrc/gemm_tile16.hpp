@@ -97,8 +97,10 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   // about the same time and find it in their L2.  (Starting each weight stripe at a
   // different group was measured: no faster, and 9x the algorithmic bytes fetched,
   // because the whole activation matrix then has to live in a 4 MB L2.)
-  // (WGK > 1: trip q of the workgroup is the WGK groups g0 + q * WGK .., one for each set of waves)
+  // (WGK > 1: trip q of the workgroup is the WGK groups g0 + q * WGK .., one for each set of waves;
+  // a set that has no group in the last trip, nmine = ng - 1, sits that trip out)
   const int ng = (g1 - g0 + WGK - 1) / WGK;
+  const int nmine = (g1 - g0 - wk + WGK - 1) / WGK;
   auto group_of = [&](int q) -> int { return g0 + q * WGK + wk; };
   // A lane's part of an address is fixed; what moves with the group is wave-uniform and goes into
   // the load's scalar offset, so that a group costs no vector address arithmetic.  Requests past
@@ -115,11 +117,11 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
     x_voff[u] = m0 + row < p.M ? (uint32_t)(m0 + row) * (uint32_t)p.K * 2u + (uint32_t)(((lane & 15) ^ (row & 15)) << 4) : kOutOfRange;
   }
   auto dma_x = [&](int q, uint8_t* stage) {
-    const uint32_t bytes = q < ng ? (uint32_t)((size_t)p.M * p.K * 2) : 0u;
-    const uint32_t soff = (uint32_t)min(group_of(q), g1 - 1) * 256u;
+    const int g = group_of(q);
+    const uint32_t bytes = g < g1 ? (uint32_t)((size_t)p.M * p.K * 2) : 0u;
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      buf_load16_lds(p.act, bytes, stage + wk * (BM * 256) + (wt + u * kTileWaves) * 1024, x_voff[u], soff);
+      buf_load16_lds(p.act, bytes, stage + wk * (BM * 256) + (wt + u * kTileWaves) * 1024, x_voff[u], (uint32_t)g * 256u);
   };
 
   // ---- weights: per 32-row pair two 16-byte pieces (lo, hi) and the row's scale (bit 31 of a
@@ -282,18 +284,21 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
     }
   };
 
-  // (the loop is left between groups: a trip past the end would be arithmetic on zeros)
-  for (int q = 0; q < ng; q += NW) {
+  // (the loop is left between groups: a trip past the end is no arithmetic on zeros, which an
+  // infinite activation would turn into NaN)
+  for (int q = 0; q < nmine; q += NW) {
     group_body(std::integral_constant<int, 0>{}, q);
-    if (q + 1 >= ng) break;
+    if (q + 1 >= nmine) break;
     group_body(std::integral_constant<int, 1>{}, q + 1);
     if constexpr (NW > 2) {
-      if (q + 2 >= ng) break;
+      if (q + 2 >= nmine) break;
       group_body(std::integral_constant<int, 2 % NW>{}, q + 2);
-      if (q + 3 >= ng) break;
+      if (q + 3 >= nmine) break;
       group_body(std::integral_constant<int, 3 % NW>{}, q + 3);
     }
   }
+  // the barrier of the trip that this set sat out (a set reads only activations it fetched itself)
+  if (WGK > 1 && nmine < ng) __builtin_amdgcn_s_barrier();
 
   if constexpr (WGK == 1) {
     tile_store32<PN, PM, 64 * kWaves>(p, tc, acc, n0, m0 + mw0);

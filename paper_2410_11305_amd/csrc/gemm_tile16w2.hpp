@@ -49,11 +49,10 @@ __global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
     x_voff[u] = m0 + row < p.M ? (uint32_t)(m0 + row) * (uint32_t)p.K * 2u + (uint32_t)(((lane & 15) ^ (row & 15)) << 4) : kOutOfRange;
   }
   auto dma_x = [&](int q, uint8_t* stage) {
-    // (an odd number of groups: the second of the last pair is the last one again, against zero weights)
-    const uint32_t bytes = q < G + (G & 1) ? (uint32_t)((size_t)p.M * p.K * 2) : 0u;
+    const uint32_t bytes = q < G ? (uint32_t)((size_t)p.M * p.K * 2) : 0u;
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      buf_load16_lds(p.act, bytes, stage + (wave + u * kWaves) * 1024, x_voff[u], (uint32_t)min(q, G - 1) * 256u);
+      buf_load16_lds(p.act, bytes, stage + (wave + u * kWaves) * 1024, x_voff[u], (uint32_t)q * 256u);
   };
 
   uint4 wlo[2][PN], whi[2][PN];
@@ -168,10 +167,11 @@ __global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
 #pragma unroll
     for (int j = 0; j < PN; ++j) s2[j] = s2n[j];
   };
-  for (int q = 0; q < G; q += 2) {
+  for (int q = 0; q + 1 < G; q += 2) {
     group_body(std::integral_constant<int, 0>{}, q);
     group_body(std::integral_constant<int, 1>{}, q + 1);
   }
+  if (G & 1) group_body(std::integral_constant<int, 0>{}, G - 1);
   tile_write_fp16<PN, PM, true>(p, acc, n0, m0);
 }
 

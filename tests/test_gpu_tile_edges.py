@@ -41,3 +41,27 @@ def test_512_by_128_blocks(plan, M, N, G):
 @pytest.mark.parametrize("shape", [1, 2, 3, 5])
 def test_k_groups_dealt_to_sets_of_wavefronts(plan, shape, S, G):
     _case(plan, shape, S, 129, 208, G)
+
+
+@pytest.mark.parametrize("shape,S,G", [(1, 1, 3), (1, 2, 5), (2, 1, 1), (2, 1, 5), (2, 4, 13), (3, 1, 3), (3, 2, 9), (5, 1, 2), (5, 1, 5),
+                                       (5, 1, 7), (5, 2, 9), (7, 1, 1), (7, 1, 3), (7, 1, 8), (0, 1, 3), (4, 1, 5), (4, 2, 5), (6, 1, 7)])
+def test_infinite_activations_meet_their_own_weights_only(plan, shape, S, G):
+    """An infinite activation gives its token +-inf by the sign of the weight (NaN where the code is
+    0) and leaves the other tokens alone, whichever group it sits in: where the groups of a slice do not
+    divide by the sets of wavefronts or by the loop's stride, no group is multiplied by stand-in weights."""
+    import torch
+    from paper_2410_11305_amd import binding as B
+    plan("QSPEC_TILE_W4A16", f"{shape},{S}")
+    M, N, K = 129, 208, 128 * G
+    codes, scales, x = synth.generic_case(77 + G, M, N, K)
+    rows = np.linspace(0, M - 1, G).astype(int)            # one token per group, a sign each
+    for g, m in enumerate(rows):
+        x[m, 128 * g + 37] = np.inf if g % 2 else -np.inf
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    y = B.gemm_w4a16(B.pack_weights(to(codes), to(scales)), to(x), N).cpu().numpy()
+    for g, m in enumerate(rows):
+        c = codes[:, 128 * g + 37].astype(np.float32) * (1.0 if g % 2 else -1.0)
+        with np.errstate(invalid="ignore"):
+            want = c * np.float32(np.inf)
+        assert np.array_equal(y[m].astype(np.float32), want, equal_nan=True), (g, m)
+    assert np.isfinite(np.delete(y, rows, axis=0)).all()
