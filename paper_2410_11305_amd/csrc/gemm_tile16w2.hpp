@@ -171,7 +171,7 @@ __global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
     group_body(std::integral_constant<int, 0>{}, q);
     group_body(std::integral_constant<int, 1>{}, q + 1);
   }
-  if (G & 1) group_body(std::integral_constant<int, 0>{}, G - 1);
+  if (G & 1) group_body(std::integral_constant<int, 0>{}, G - 1);      // (no stage is read behind it: its counted wait guards nothing)
   tile_write_fp16<PN, PM, true>(p, acc, n0, m0);
 }
 

@@ -43,6 +43,12 @@ def test_k_groups_dealt_to_sets_of_wavefronts(plan, shape, S, G):
     _case(plan, shape, S, 129, 208, G)
 
 
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 9])
+@pytest.mark.parametrize("shape", [0, 4, 6])
+def test_groups_left_over_behind_the_loop(plan, shape, G):
+    _case(plan, shape, 1, 300, 528, G)
+
+
 @pytest.mark.parametrize("shape,S,G", [(1, 1, 3), (1, 2, 5), (2, 1, 1), (2, 1, 5), (2, 4, 13), (3, 1, 3), (3, 2, 9), (5, 1, 2), (5, 1, 5),
                                        (5, 1, 7), (5, 2, 9), (7, 1, 1), (7, 1, 3), (7, 1, 8), (0, 1, 3), (4, 1, 5), (4, 2, 5), (6, 1, 7)])
 def test_infinite_activations_meet_their_own_weights_only(plan, shape, S, G):
