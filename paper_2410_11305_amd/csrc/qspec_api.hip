@@ -342,25 +342,31 @@ constexpr TileShape kShapes16[] = {     // verify mode (gemm_tile16w_kernel): TN
     {1, 2, 4, 1, 2, 2, 3},      // 6: 128 x 64, three workgroups per compute unit
     {2, 4, 8, 1, 2, 2, 1},      // 7: 512 x 128 (gemm_tile16w2_kernel), never in K-slices
 };
-// What a plan costs, in microseconds: fixed + groups per slice * (rounds of workgroups) and, with
-// K-slices, the exchange.  A round that fills the chip takes `full` per group; the last, partial
-// one takes `alone` (what a workgroup takes with nothing beside it) while the busy compute units
-// are few, and more as they grow many: the part is power-limited under matrix work, its clock
-// falls from 2.3 GHz with half the units busy to 1.7 GHz with all of them.  Fitted to 3000 timed
-// calls: 14 layers from 2560 x 2048 to 57344 x 8192 at 48 to 2050 tokens, every shape below, one
-// to six slices, on rotating weights inside HIP graphs.  The choice by this table is 1.1 % slower
-// than the best measured plan on average (9 % at worst but for two), and 9 % faster than the fill
-// rules it replaces on the same kernels.
-struct TileCost { double fixed, alone, full, slice0, slice1; };
+// What a verify-mode plan costs, in microseconds: fixed, `again` for every round of workgroups after the first,
+// groups per slice x the rounds' cost per group, and with K-slices the exchange.  A round's cost per
+// group rises with the workgroups per compute unit: `one` with one on every unit, less in proportion
+// down to `alone` (what a workgroup takes with nothing beside it; the part is power-limited under matrix
+// work, its clock falls from 2.3 GHz with half the units busy to 1.7 GHz with all of them), from `above1`
+// with the first second workgroup to `two` with two everywhere, and from `above2` to `three`.  `places`
+// workgroups fit a unit; what lies past that is a further round.
+// Fitted to 38000 timed plans of 1716 problems: 16 to 128256 outputs from 128 to 28672 inputs at 33 to 2050
+// tokens and some up to 9000, every shape below, one to eight slices, on rotating weights inside HIP
+// graphs.  The choice is 0.6 % slower than the best of them on average and 19 % at most (368 outputs from 3584 at
+// 1002 tokens), and 1.2 % (18 %) on 228 more with long inputs or up to 9000 tokens; profiles/verify_plan_times.txt
+// lists a sample, the worst ones included.  (A table of five numbers a shape fitted to 14 large layers, without
+// the further rounds' cost and without 128 x 128 and 128 x 64 blocks in a single round, left 2.3 % on average and
+// was up to 39 % slower than the fill rules before both on short inputs: 28672 outputs from 512 at 256 tokens
+// 21.0 us, 15.1 by the rules, 14.0 now.)
+struct TileCost { double fixed, again, alone, one, above1, two, above2, three, slice0, slice1; int places; };
 constexpr TileCost kCost16[] = {
-    {2.2, 1.00, 1.91, 0.0, 0.0},   // 0: only where more than one round of it is needed (plan_tile16)
-    {4.3, 0.47, 0.64, 3.5, 0.65},  // 1
-    {3.4, 0.42, 0.69, 2.8, 0.65},  // 2
-    {6.1, 0.72, 1.05, 5.0, 0.80},  // 3
-    {8.1, 1.08, 1.90, 7.1, 1.65},  // 4
-    {6.2, 0.43, 0.59, 2.1, 1.00},  // 5
-    {2.2, 0.78, 1.29, 0.0, 0.0},   // 6: only up to 64 tokens on more than one round
-    {12.0, 1.98, 3.52, 0.0, 0.0},  // 7
+    {5.589, 3.537, 0.754, 0.95, 1.471, 1.772, 0, 0, 3.471, 1.33, 2},  // 0
+    {4.841, 3.47, 0.386, 0.492, 0.752, 0.986, 0, 0, 2.296, 0.76, 2},  // 1
+    {4.043, 2.084, 0.328, 0.375, 0.538, 0.607, 0, 0, 1.775, 0.341, 2},  // 2
+    {6.318, 5.271, 0.618, 0.876, 0, 0, 0, 0, 3.248, 1.093, 1},  // 3
+    {5.485, 4.333, 1.091, 1.622, 0, 0, 0, 0, 6.502, 2.209, 1},  // 4
+    {5.966, 4.565, 0.368, 0.472, 0, 0, 0, 0, 2.282, 0.677, 1},  // 5
+    {3.8, 2.407, 0.561, 0.596, 0.806, 1.027, 1.471, 1.723, 2.248, 0.773, 3},  // 6
+    {11.468, 8.47, 2.1, 2.909, 0, 0, 0, 0, 0, 0, 1},  // 7
 };
 constexpr TileShape kShapes4[] = {      // draft mode (gemm_tile4w_kernel): TN, TMW count 32 x 32 tiles; NW = NS = 3
     {1, 4, 4, 1, 3, 3, 2},   // 0: 128 outputs x 128 tokens
@@ -387,28 +393,37 @@ bool tile_override(bool w4a4, int* shape, int* S) {
   return *shape >= 0 && *shape < (w4a4 ? kNumTileShapes : kNumShapes16) && *S >= 1;
 }
 
+// Cost per group of a round with f workgroups per compute unit (0 < f <= places).
+double round_cost16(const TileCost& c, double f) {
+  if (f <= 1.0) return c.one * f;
+  if (f <= 2.0) return c.above1 + (c.two - c.above1) * (f - 1.0);
+  return c.above2 + (c.three - c.above2) * (f - 2.0);
+}
+
 // Cheapest verify-mode plan by kCost16.
 void plan_tile16(int M, int N, int G, int* shape, int* slices) {
   double best = 1e30;
   for (int i = 0; i < kNumShapes16; ++i) {
     const TileShape& t = kShapes16[i];
     const TileCost& c = kCost16[i];
-    const long long blocks = (long long)((N + 32 * t.TN * t.WGN - 1) / (32 * t.TN * t.WGN)) * ((M + 32 * t.TMW * t.WGM - 1) / (32 * t.TMW * t.WGM));
-    const int places = t.OCC * kNumCU;
-    if ((i == 0 || i == 6) && blocks <= places) continue;       // (one round: the K-dealing shapes of the same block are faster)
-    if (i == 6 && M > 64) continue;
+    const int bn = 32 * t.TN * t.WGN, bm = 32 * t.TMW * t.WGM;
+    const long long mb = (M + bm - 1) / bm, blocks = (N + bn - 1) / bn * mb;
+    const double used = 0.8 + 0.2 * M / (mb * bm);             // (rows past M are zeros or stale: they cost time, less power)
+    const auto per_group = [&](double f) { const double r = round_cost16(c, f) * used; return r > c.alone ? r : c.alone; };
     for (int S : {1, 2, 3, 4, 6, 8}) {
-      // K-slices only while all workgroups have a compute unit of their own, of six groups at least
-      if (S > 1 && (c.slice0 == 0.0 || blocks * S > kNumCU || G / S < 6)) break;
-      const long long full = blocks * S / places, rest = blocks * S % places;
-      double round = full * c.full;
-      if (rest > 0) {
-        if (t.OCC > 1) round += rest > kNumCU ? c.full : c.alone;
-        else round += c.full * rest / places > c.alone ? c.full * rest / places : c.alone;
-      }
+      // K-slices only while all workgroups have a compute unit of their own (and the partial sums
+      // fit 32 MiB), of four groups at least
+      if (S > 1 && (c.slice0 == 0.0 || blocks * S > kNumCU || G / S < 4)) break;
+      const long long wgs = blocks * S, load = (long long)c.places * kNumCU, full = wgs / load, rest = wgs % load;
+      const double rounds = (full ? full * per_group(c.places) : 0.0) + (rest ? per_group((double)rest / kNumCU) : 0.0);
       // (the exchange of few workgroups is cheaper: 48 of 64 x 64 in two slices 3.1 us, 240 of them 4.0)
-      const double xch = S > 1 ? (c.slice0 + c.slice1 * S) * (0.7 + 0.3 * blocks * S / kNumCU) : 0.0;
-      const double cost = c.fixed + round * G / S + xch;
+      const double xch = S > 1 ? (c.slice0 + c.slice1 * S) * (0.7 + 0.3 * wgs / kNumCU) : 0.0;
+      double cost = c.fixed + c.again * (full + (rest ? 1 : 0) - 1) + rounds * G / S + xch;
+      // An XCD fetches a group's activations of every token block it works on: on narrow layers that
+      // bounds the plan (512 x 1920 at 1767 tokens: 64 x 64 blocks 14.0 us, 128 x 64 10.7)
+      const long long rows = bm * (mb < (wgs + 7) / 8 ? mb : (wgs + 7) / 8);
+      const double fetch = c.fixed + 0.000276 * rows * G / S;
+      if (fetch > cost) cost = fetch;
       if (cost < best) { best = cost; *shape = i; *slices = S; }
     }
   }
