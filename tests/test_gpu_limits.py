@@ -25,7 +25,7 @@ def rel_err(y, ref):
     return float(np.max(np.abs(y.astype(np.float64) - ref)) / max(np.max(np.abs(ref)), 1e-30))
 
 
-def test_weight_tensor_just_under_two_gib(env):
+def test_weight_tensor_just_under_two_gib(env, plan):
     torch, B = env
     N, K = 32800, 130944                      # N*K/2 = 2 147 481 600 bytes of codes (limit: 2^31 - 2)
     assert N * K // 2 < 2 ** 31 - 1 <= (N + 16) * K // 2
@@ -62,6 +62,15 @@ def test_weight_tensor_just_under_two_gib(env):
         e16 = rel_err(y16[:, cols], orc.gemm_w4a16(x, c_h, s_h))
         print(f"   rel err w4a4 {e4:.2e}  w4a16 {e16:.2e}", flush=True)
         assert e4 <= TOL and e16 <= TOL
+    # the last M again on the shapes of the verify mode that its plan does not take: 512 x 128 blocks, the K
+    # groups dealt to sets of wavefronts, alone and in slices
+    ref16 = orc.gemm_w4a16(x, c_h, s_h)
+    for forced in ("7,1", "0,1", "1,1", "2,1", "3,1", "5,2", "6,1"):
+        plan("QSPEC_TILE_W4A16", forced)
+        y16 = B.gemm_w4a16(blob, xd, N).cpu().numpy()
+        e16 = rel_err(y16[:, cols], ref16)
+        print(f"   {forced}: {B.describe_kernel(False, M, N, K)} {e16:.2e}", flush=True)
+        assert np.isfinite(y16).all() and e16 <= TOL
 
 
 def test_one_row_too_many_is_refused(env):
@@ -74,9 +83,9 @@ def test_one_row_too_many_is_refused(env):
     torch.cuda.synchronize()
 
 
-def test_twenty_thousand_tokens(env):
+def test_twenty_thousand_tokens(env, plan):
     torch, B = env
-    M, N, K = 20001, 48, 1024                 # 157 token blocks of 128, the last with one row
+    M, N, K = 20001, 48, 1024                 # 157 token blocks of 128 or 313 of 64, the last with one or 33 rows
     rng = np.random.default_rng(79)
     codes = rng.integers(-8, 8, (N, K), dtype=np.int8)
     scales = rng.uniform(0.002, 0.01, (N, K // 128)).astype(np.float16)
@@ -89,4 +98,28 @@ def test_twenty_thousand_tokens(env):
     y4 = B.gemm_w4a4(blob, qa, sa, N).cpu().numpy()
     y16 = B.gemm_w4a16(blob, xd, N).cpu().numpy()
     assert rel_err(y4, orc.gemm_w4a4(q_ref, s_ref, codes, scales)) <= TOL
-    assert rel_err(y16, orc.gemm_w4a16(x, codes, scales)) <= TOL
+    ref16 = orc.gemm_w4a16(x, codes, scales)
+    assert rel_err(y16, ref16) <= TOL
+    for shape in range(8):                    # whatever the plan, every block shape of the verify mode
+        plan("QSPEC_TILE_W4A16", f"{shape},1")
+        assert rel_err(B.gemm_w4a16(blob, xd, N).cpu().numpy(), ref16) <= TOL, shape
+
+
+def test_activations_just_under_two_gib(env, plan):
+    """Row offsets near 2^31: every block shape on the last rows of an activation matrix of 2 GiB."""
+    torch, B = env
+    K, N = 16384, 16
+    M = (2 ** 31 - 2) // (2 * K)              # 65535 tokens: M * K * 2 = 2^31 - 32768 bytes
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(80)
+    x = torch.randn((M, K), device="cuda", generator=gen, dtype=torch.float16)
+    rng = np.random.default_rng(81)
+    codes = rng.integers(-8, 8, (N, K), dtype=np.int8)
+    scales = rng.uniform(0.002, 0.01, (N, K // 128)).astype(np.float16)
+    blob = B.pack_weights(torch.from_numpy(codes).cuda(), torch.from_numpy(scales).cuda())
+    rows = np.r_[0:8, M // 2:M // 2 + 8, M - 140:M]
+    ref = orc.gemm_w4a16(x[torch.from_numpy(rows).cuda()].cpu().numpy(), codes, scales)
+    for forced in [None] + [f"{shape},1" for shape in range(8)]:
+        plan("QSPEC_TILE_W4A16", forced)
+        y = B.gemm_w4a16(blob, x, N).cpu().numpy()
+        assert np.isfinite(y).all() and rel_err(y[rows], ref) <= TOL, forced

@@ -196,20 +196,20 @@ def test_all_sixteen_codes_dequantise_exactly(env):
 
 # ------------------------------------------------------------------ tiled kernels (M > 32)
 @pytest.mark.parametrize("S", [1, 3])
-@pytest.mark.parametrize("shape", range(7))
+@pytest.mark.parametrize("shape", range(8))
 def test_tile_kernels_every_workgroup_shape(env, plan, shape, S):
     """Every instantiated workgroup shape, alone and with 3 K-slices that meet in
     the workspace, on a problem with ragged M, a ragged last n-block and a group
     count (7) that does not divide by the slice count."""
     torch, B = env
     M, N, K = 150, 304, 896
-    plan("QSPEC_TILE_W4A4", f"{shape % 4},{S}")      # 4 draft-mode shapes, 7 verify-mode shapes
+    plan("QSPEC_TILE_W4A4", f"{shape % 4},{S}")      # 4 draft-mode shapes, 8 verify-mode shapes (7: never in slices)
     plan("QSPEC_TILE_W4A16", f"{shape},{S}")
     codes, scales, x = synth.generic_case(600 + shape, M, N, K)
     blob = B.pack_weights(dev(torch, codes), dev(torch, scales))
     qa, sa, q_ref, s_ref = _check_quant(torch, B, x)
     need = B.workspace_bytes(M, N, K)
-    assert (need > 0) == (S > 1)
+    assert (need > 0) == (S > 1)          # (the draft mode's slices where the verify mode has none)
     ws = B.alloc_workspace(need)
     ref4 = orc.gemm_w4a4(q_ref, s_ref, codes, scales)
     ref16 = orc.gemm_w4a16(x, codes, scales)

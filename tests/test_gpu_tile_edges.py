@@ -43,6 +43,13 @@ def test_k_groups_dealt_to_sets_of_wavefronts(plan, shape, S, G):
     _case(plan, shape, S, 129, 208, G)
 
 
+@pytest.mark.parametrize("S,G", [(5, 11), (6, 13), (7, 7), (8, 8), (8, 37)])
+@pytest.mark.parametrize("shape", range(7))
+def test_more_slices_than_are_read_at_once(plan, shape, S, G):
+    """The last workgroup of an output block reads four slices at a time: the second trip, whole or not."""
+    _case(plan, shape, S, 129, 272, G)
+
+
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 9])
 @pytest.mark.parametrize("shape", [0, 4, 6])
 def test_groups_left_over_behind_the_loop(plan, shape, G):
