@@ -214,7 +214,9 @@ __global__ __launch_bounds__(kRowMaxThreads) void rmsnorm_quant_kernel(const uin
 // bounds the SiLU kernel at large M, so: Taylor polynomial of degree 11 after one reduction by
 // n ln 2 (relative error 2^-46 with |r| <= ln 2 / 2), the power of two added to the exponent
 // field, and a reciprocal estimate with two Newton steps instead of a division.  That is the
-// correctly rounded result for every fp16 g (there are 63488: the tests walk all of them).
+// correctly rounded result for every fp16 g (there are 63488).  The tests walk all of them, and where an
+// up value puts the product within a unit of an fp16 rounding point, at a sixth of them on either
+// side, the binary32 value itself shows in the result.
 // g outside +-700 is held there for the exponential, which changes nothing: the result is g
 // or underflows to zero.  -inf gives NaN (-inf / inf).
 // (128 x 28672 outputs, with the quantiser's divisions by reciprocal: 11.4 -> 10.2 us.)

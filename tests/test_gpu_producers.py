@@ -117,6 +117,33 @@ def test_silu_mul_quant_whole_gate_range(env):
     run_silu(env, gu[finite])
 
 
+@pytest.mark.parametrize("side", [-1, 1])
+def test_silu_one_unit_off_in_binary32_would_show(env, side):
+    """The binary32 value of SiLU itself: for every gate the up value in [1, 2) is taken, if there is one, with
+    which a SiLU one unit in the last place lower (higher) would round to another fp16 product."""
+    bits = np.concatenate([np.arange(0, 0x7C00, dtype=np.uint16), np.arange(0x8000, 0xFC00, dtype=np.uint16)])
+    gate = bits.view(np.float16)
+    g = gate.astype(np.float64)
+    with np.errstate(over="ignore"):
+        s = (g / (1.0 + np.exp(-g))).astype(np.float32)
+    off = np.nextafter(s, np.float32(side * np.inf))
+    up = (1.0 + np.arange(1024) / 1024).astype(np.float32)
+    pick, seen = np.zeros(gate.size, np.int64), np.zeros(gate.size, bool)
+    with np.errstate(over="ignore"):
+        for i in range(0, gate.size, 4096):
+            c = slice(i, i + 4096)
+            differs = (s[c, None] * up).astype(np.float16) != (off[c, None] * up).astype(np.float16)
+            pick[c], seen[c] = differs.argmax(axis=1), differs.any(axis=1)
+    assert seen.mean() > 0.1                                # one candidate in 8192 / 1.5 is within a unit: a sixth of the gates
+    n = seen.sum() // 128 * 128
+    where = np.flatnonzero(seen)[:n]
+    gu = np.concatenate([gate[where].reshape(-1, 128), up[pick[where]].astype(np.float16).reshape(-1, 128)], axis=1)
+    with np.errstate(over="ignore", invalid="ignore"):
+        finite = np.isfinite(prod.silu_mul_f16(gu).astype(np.float32)).all(axis=1)
+    assert finite.mean() > 0.9
+    run_silu(env, gu[finite])
+
+
 def test_quotients_next_to_rounding_points_of_every_scale(env):
     """One group per positive finite fp16 maximum (every scale there is), filled with the fp16
     values nearest (k + 1/2) s and their neighbours: the codes of the correctly rounded quotient."""
