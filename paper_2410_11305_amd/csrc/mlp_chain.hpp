@@ -215,9 +215,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 1) void mlp_draft_kernel(MlpArgs
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const double g = (double)(float)gh[e];
-        const float s = (float)(g / (1.0 + exp(-g)));
-        v[e] = (float)(_Float16)rounded_f32(s * (float)uh[e]);
+        v[e] = (float)(_Float16)rounded_f32(silu_f32((float)gh[e]) * (float)uh[e]);
       }
       const size_t idx = (size_t)m * (size_t)(I / 8) + (size_t)j * 16 + l;   // word index in [M][I/8]
       finish_unit(v, false, live, idx, reinterpret_cast<uint32_t*>(p.qa_i), p.sa_i, nullptr);
