@@ -12,7 +12,7 @@
 // wavefronts, 19.0 on eight; 5120 x 5120 at 384: 29.1 -> 25.8).
 //   - Activations: the BM x 128 fp16 block of a group travels global -> LDS
 //     with buffer loads that write LDS directly (no registers, no ds_write),
-//     NS-1 groups ahead, into NS stages that are separate arrays (the compiler
+//     one group ahead, into two stages that are separate arrays (the compiler
 //     then knows that a transfer into one never aliases a read of another
 //     and inserts no wait between them).  A wave-wide transfer fills 1 KB of
 //     LDS linearly (lane l -> bytes 16l..16l+15) = four token rows; the
@@ -57,11 +57,8 @@ namespace qspec {
 constexpr int waitcnt_vm(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
 // the same with lgkmcnt(0): every LDS (and scalar-memory) operation of the wave has completed too
 constexpr int waitcnt_vm_lgkm0(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4); }
-#ifndef QSPEC_TILE16_EARLY
-#define QSPEC_TILE16_EARLY 1
-#endif
 
-template <int PN, int PM, int WGN, int WGM, int WGK, int NW, int NS, int OCC>
+template <int PN, int PM, int WGN, int WGM, int WGK, int NW, int OCC>
 __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel(TileArgs p) {
   constexpr int kWaves = WGN * WGM * WGK;
   constexpr int kTileWaves = WGN * WGM;                // the waves that cover the output block once
@@ -70,14 +67,10 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   constexpr int U = BM * 256 / 1024 / kTileWaves;      // wave-wide transfers per wave and group
   static_assert(BM * 256 % (1024 * kTileWaves) == 0, "the stage divides evenly among the waves");
   static_assert(NW == 2 || NW == 4, "the stage of a group must follow from its ring slot");
-  static_assert(NS == 2 || (NS == 4 && NW == 4), "stage = ring slot % NS");
-  constexpr int D = NS - 1;                            // activations are fetched D groups ahead
-  // NS stages, each an array of its own (see the head of this file)
+  // two stages, each an array of its own (see the head of this file)
   __shared__ __attribute__((aligned(1024))) uint8_t xs0[kStageBytes];
   __shared__ __attribute__((aligned(1024))) uint8_t xs1[kStageBytes];
-  __shared__ __attribute__((aligned(1024))) uint8_t xs2[NS > 2 ? kStageBytes : 16];
-  __shared__ __attribute__((aligned(1024))) uint8_t xs3[NS > 2 ? kStageBytes : 16];
-  auto stage_ptr = [&](int i) -> uint8_t* { return i == 0 ? xs0 : i == 1 ? xs1 : i == 2 ? xs2 : xs3; };
+  auto stage_ptr = [&](int i) -> uint8_t* { return i == 0 ? xs0 : xs1; };
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -106,8 +99,8 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   // the load's scalar offset, so that a group costs no vector address arithmetic.  Requests past
   // the end go through an empty buffer descriptor: zeros, no traffic, no branch.
 
-  // ---- activations: global -> LDS.  Transfer u of this wave fills block q = wave +
-  // u*kTileWaves (1 KB = rows 4q..4q+3).  Lane l writes slot l%16 of row 4q + l/16 and so
+  // ---- activations: global -> LDS.  Transfer u of this wave fills block q = wt +
+  // u*kTileWaves of its set's stage (1 KB = rows 4q..4q+3).  Lane l writes slot l%16 of row 4q + l/16 and so
   // must fetch k-chunk (l%16) ^ (row%16).  Rows past M are out of range: no traffic, and
   // whatever the stage holds there reaches only outputs that are not stored.
   uint32_t x_voff[U];
@@ -157,8 +150,7 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
 
 #pragma unroll
   for (int d = 0; d < NW; ++d) load_w(d, d);
-#pragma unroll
-  for (int d = 0; d < D; ++d) dma_x(d, stage_ptr(d));
+  dma_x(0, xs0);
 
   v2h s2[PN], s2n[PN], wa0[PN][4];
 #pragma unroll
@@ -183,8 +175,8 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   // the end did (everyone is done with this stage, everyone's transfers of the next stage
   // have landed), and the first operands of the next group are read under the last
   // k-step's MFMAs: no wave starts a group by waiting for LDS with nothing to issue.
-  constexpr bool EARLY = QSPEC_TILE16_EARLY && PN * PM >= 4;
-  constexpr int XB = EARLY ? 2 : (PN * PM >= 8 ? 2 : (PN * PM >= 4 ? 3 : 4));
+  constexpr bool EARLY = PN * PM >= 4;
+  constexpr int XB = EARLY ? 2 : 4;
   uint4 xb[XB][PM];
   // this lane's k-chunk of step s is 2 s + h: s only flips bits of a lane's address
   const int x_lane = wk * (BM * 256) + (mw0 + m32) * 256 + ((h ^ (m32 & 15)) << 4);
@@ -200,11 +192,10 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   auto group_body = [&](auto slot_c, int g, auto left_over_c) __attribute__((always_inline)) {
     constexpr int SLOT = decltype(slot_c)::value;
     constexpr bool LEFT_OVER = decltype(left_over_c)::value;
-    constexpr int kYounger = LEFT_OVER ? 0 : (D - 1) * (U + 3 * PN) + 3 * PN;   // loads issued after those activations
+    constexpr int kYounger = LEFT_OVER ? 0 : 3 * PN;   // loads issued after those activations: the ring slot's
     constexpr int NEXT = (SLOT + 1) % NW;
-    const uint8_t* xl = stage_ptr(SLOT % NS);
-    const uint8_t* xl_next = stage_ptr((SLOT + 1) % NS);
-    uint8_t* xnext = stage_ptr((SLOT + D) % NS);   // last read in the group before this one
+    const uint8_t* xl = stage_ptr(SLOT % 2);
+    uint8_t* xl_next = stage_ptr((SLOT + 1) % 2);      // last read in the group before this one
     auto read_step = [&](int s, uint4 (&dst)[PM]) { read_step_from(xl, s, dst); };
     auto word_of_step = [&](int d, int j, int s) -> uint32_t {
       const uint4& q = (s & 1) ? whi[d][j] : wlo[d][j];
@@ -239,7 +230,7 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
         // every wave has passed the barrier that ended the last group reading that
         // stage; issued here rather than at the top so that the first MFMAs of the
         // group do not queue behind the address computations
-        dma_x(g + D, xnext);
+        dma_x(g + 1, xl_next);
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
@@ -278,11 +269,10 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
     }
 #pragma unroll
     for (int j = 0; j < PN; ++j) s2[j] = s2n[j];
-    // The next group's activations were requested D-1 groups ago, before D-1 further
-    // batches of U transfers and D batches of 3*PN ring loads.  Loads complete in
-    // order: at most that many outstanding means those activations have landed.  (No
-    // store may sit between them - stores complete out of order with loads - so this
-    // kernel must compile without register spills in the loop.)
+    // The next group's activations were requested before the 3*PN loads that refill the ring
+    // slot.  Loads complete in order: at most that many outstanding means those activations
+    // have landed.  (No store may sit between them - stores complete out of order with
+    // loads - so this kernel must compile without register spills in the loop.)
     if constexpr (!EARLY) {
       __builtin_amdgcn_s_waitcnt(waitcnt_vm(kYounger));
       __builtin_amdgcn_s_barrier();
@@ -317,7 +307,7 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   if constexpr (WGK == 1) {
     tile_store32<PN, PM, 64 * kWaves>(p, tc, acc, n0, m0 + mw0);
   } else {
-    // Each of the WGK waves of an output tile set finishes PM / WGK of its tiles.  All partial
+    // Each of the WGK waves of an output tile set finishes PN * PM / WGK of its tiles.  All partial
     // sums go through LDS (a wave's own too: which tiles it finishes is not known at compile
     // time); the stages are dead, the barrier that ended the last group is behind every read of
     // them, and requests past the end have landed.

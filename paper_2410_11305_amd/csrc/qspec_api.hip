@@ -329,18 +329,18 @@ int launch_stream(StreamArgs a, void* workspace, hipStream_t s) {
 
 // ---------------------------------------------------------------- tiled (M > 32) kernels
 // Workgroup shapes the tiled kernels are instantiated for: TN x TMW MFMA tiles per
-// wavefront, WGN x WGM wavefronts per workgroup, weight ring of NW groups and NS
-// activation stages (verify mode), OCC workgroups per compute unit (the register budget the compiler is held to).
-struct TileShape { int TN, TMW, WGN, WGM, NW, NS, OCC, WGK = 1; };
+// wavefront, WGN x WGM wavefronts per workgroup, weight ring of NW groups, OCC workgroups per compute
+// unit (the register budget the compiler is held to), K groups dealt to WGK sets of such wavefronts.
+struct TileShape { int TN, TMW, WGN, WGM, NW, OCC, WGK = 1; };
 constexpr TileShape kShapes16[] = {     // verify mode (gemm_tile16w_kernel): TN, TMW count 32 x 32 tiles
-    {1, 4, 4, 1, 4, 2, 2},      // 0: 128 outputs x 128 tokens
-    {1, 2, 4, 1, 2, 2, 1, 2},   // 1: 128 x 64, the K groups dealt to two sets of four wavefronts
-    {1, 2, 2, 1, 2, 2, 2, 2},   // 2: 64 x 64, the K groups dealt to two pairs of wavefronts
-    {1, 4, 4, 1, 2, 2, 1, 2},   // 3: 128 x 128, the K groups dealt to two sets of four wavefronts
-    {1, 4, 8, 1, 2, 2, 1},      // 4: 256 x 128, eight wavefronts, one workgroup per compute unit
-    {2, 2, 2, 1, 2, 2, 1, 4},   // 5: 128 x 64, the K groups dealt to four pairs of wavefronts
-    {1, 2, 4, 1, 2, 2, 3},      // 6: 128 x 64, three workgroups per compute unit
-    {2, 4, 8, 1, 2, 2, 1},      // 7: 512 x 128 (gemm_tile16w2_kernel), never in K-slices
+    {1, 4, 4, 1, 4, 2},      // 0: 128 outputs x 128 tokens
+    {1, 2, 4, 1, 2, 1, 2},   // 1: 128 x 64, the K groups dealt to two sets of four wavefronts
+    {1, 2, 2, 1, 2, 2, 2},   // 2: 64 x 64, the K groups dealt to two pairs of wavefronts
+    {1, 4, 4, 1, 2, 1, 2},   // 3: 128 x 128, the K groups dealt to two sets of four wavefronts
+    {1, 4, 8, 1, 2, 1},      // 4: 256 x 128, eight wavefronts, one workgroup per compute unit
+    {2, 2, 2, 1, 2, 1, 4},   // 5: 128 x 64, the K groups dealt to four pairs of wavefronts
+    {1, 2, 4, 1, 2, 3},      // 6: 128 x 64, three workgroups per compute unit
+    {2, 4, 8, 1, 2, 1},      // 7: 512 x 128 (gemm_tile16w2_kernel), never in K-slices
 };
 // What a verify-mode plan costs, in microseconds: fixed, `again` for every round of workgroups after the first,
 // groups per slice x the rounds' cost per group, and with K-slices the exchange.  A round's cost per
@@ -368,11 +368,11 @@ constexpr TileCost kCost16[] = {
     {3.8, 2.407, 0.561, 0.596, 0.806, 1.027, 1.471, 1.723, 2.248, 0.773, 3},  // 6
     {11.468, 8.47, 2.1, 2.909, 0, 0, 0, 0, 0, 0, 1},  // 7
 };
-constexpr TileShape kShapes4[] = {      // draft mode (gemm_tile4w_kernel): TN, TMW count 32 x 32 tiles; NW = NS = 3
-    {1, 4, 4, 1, 3, 3, 2},   // 0: 128 outputs x 128 tokens
-    {1, 2, 4, 1, 3, 3, 2},   // 1: 128 x 64
-    {1, 2, 2, 1, 3, 3, 2},   // 2: 64 x 64
-    {1, 4, 8, 1, 3, 3, 1},   // 3: 256 x 128, eight wavefronts, one workgroup per compute unit
+constexpr TileShape kShapes4[] = {      // draft mode (gemm_tile4w_kernel): TN, TMW count 32 x 32 tiles
+    {1, 4, 4, 1, 3, 2},   // 0: 128 outputs x 128 tokens
+    {1, 2, 4, 1, 3, 2},   // 1: 128 x 64
+    {1, 2, 2, 1, 3, 2},   // 2: 64 x 64
+    {1, 4, 8, 1, 3, 1},   // 3: 256 x 128, eight wavefronts, one workgroup per compute unit
 };
 constexpr int kNumTileShapes = 4;
 constexpr int kNumShapes16 = 8;
@@ -552,9 +552,9 @@ int launch_tile4w_inst(const TileArgs& a, bool wide, hipStream_t s) {
   return QSPEC_OK;
 }
 
-template <int PN, int PM, int WGN, int WGM, int NW, int NS, int OCC, int WGK = 1>
+template <int PN, int PM, int WGN, int WGM, int NW, int OCC, int WGK = 1>
 int launch_tile16w_inst(const TileArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_tile16w_kernel<PN, PM, WGN, WGM, WGK, NW, NS, OCC>), dim3(a.nb * a.mb * a.S),
+  hipLaunchKernelGGL((gemm_tile16w_kernel<PN, PM, WGN, WGM, WGK, NW, OCC>), dim3(a.nb * a.mb * a.S),
                      dim3(64 * WGN * WGM * WGK), 0, s, a);
   return QSPEC_OK;
 }
@@ -573,13 +573,13 @@ int launch_tile(const TilePlan& plan, TileArgs a, void* workspace, hipStream_t s
     }
   }
   switch (plan.shape) {
-    case 0: return launch_tile16w_inst<1, 4, 4, 1, 4, 2, 2>(a, s);
-    case 1: return launch_tile16w_inst<1, 2, 4, 1, 2, 2, 1, 2>(a, s);
-    case 2: return launch_tile16w_inst<1, 2, 2, 1, 2, 2, 2, 2>(a, s);
-    case 3: return launch_tile16w_inst<1, 4, 4, 1, 2, 2, 1, 2>(a, s);
-    case 4: return launch_tile16w_inst<1, 4, 8, 1, 2, 2, 1>(a, s);
-    case 5: return launch_tile16w_inst<2, 2, 2, 1, 2, 2, 1, 4>(a, s);
-    case 6: return launch_tile16w_inst<1, 2, 4, 1, 2, 2, 3>(a, s);
+    case 0: return launch_tile16w_inst<1, 4, 4, 1, 4, 2>(a, s);
+    case 1: return launch_tile16w_inst<1, 2, 4, 1, 2, 1, 2>(a, s);
+    case 2: return launch_tile16w_inst<1, 2, 2, 1, 2, 2, 2>(a, s);
+    case 3: return launch_tile16w_inst<1, 4, 4, 1, 2, 1, 2>(a, s);
+    case 4: return launch_tile16w_inst<1, 4, 8, 1, 2, 1>(a, s);
+    case 5: return launch_tile16w_inst<2, 2, 2, 1, 2, 1, 4>(a, s);
+    case 6: return launch_tile16w_inst<1, 2, 4, 1, 2, 3>(a, s);
     default:
       hipLaunchKernelGGL(gemm_tile16w2_kernel, dim3(a.nb * a.mb), dim3(512), 0, s, a);
       return QSPEC_OK;
@@ -1082,7 +1082,7 @@ int qspec_describe_kernel(int mode_w4a4, int M, int N, int K, int group, char* o
       const TileShape& t = shape_of(mode_w4a4 != 0, plan_tile(mode_w4a4 != 0, M, N, K).shape);
       if (mode_w4a4) snprintf(out, cap, "gemm_tile4w_kernel<%d, %d, %d, %d, %d, false>", t.TN, t.TMW, t.WGN, t.WGM, t.OCC);
       else if (t.TN == 2 && t.TMW == 4) snprintf(out, cap, "gemm_tile16w2_kernel");
-      else snprintf(out, cap, "gemm_tile16w_kernel<%d, %d, %d, %d, %d, %d, %d, %d>", t.TN, t.TMW, t.WGN, t.WGM, t.WGK, t.NW, t.NS, t.OCC);
+      else snprintf(out, cap, "gemm_tile16w_kernel<%d, %d, %d, %d, %d, %d, %d>", t.TN, t.TMW, t.WGN, t.WGM, t.WGK, t.NW, t.OCC);
     } else if (mode_w4a4) snprintf(out, cap, "gemm_w4a4_generic<%d, 4, false>", pick_tm(M));
     else snprintf(out, cap, "gemm_w4a16_generic<%d, 4>", pick_tm(M));
   }
