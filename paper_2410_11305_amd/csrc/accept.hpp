@@ -41,7 +41,7 @@ __device__ inline v2s half_order_pair(uint32_t w) {
   const uint32_t mag = (w & 0x7FFF7FFFu) ^ __builtin_bit_cast(uint32_t, neg);
   return __builtin_bit_cast(v2s, mag) - neg;
 }
-__device__ inline uint32_t half_order_of(int k) { return (uint32_t)(k + 0x8000); }   // as half_order_key counts
+__device__ inline uint32_t half_order_of(int k) { return (uint32_t)(k + 0x8000); }   // the same order, unsigned (half_order_key's is one lower for negative values)
 
 // Maximum over the 64 lanes (all active), wave-uniform.  DPP moves inside rows of 16 and
 // across them: six vector operations where six ds_bpermute are six trips through LDS.
@@ -73,7 +73,7 @@ struct ArgmaxArgs {
 // The scan costs two vector operations per logit (packed order, packed maximum); only the
 // lanes that hold the wave's maximum then look for its lowest index.  (One comparison and
 // two selects per logit, ten operations in all, took as long as the memory reads: 512 rows of
-// 32000 logits 10.2 -> 8.2 us.)
+// 32000 logits, median of 31 traced launches 9.8 -> 8.4 us.)
 template <bool VEC>
 __global__ __launch_bounds__(kArgmaxThreads) void argmax_partial_kernel(ArgmaxArgs p) {
   constexpr int U = kArgmaxLoads;
@@ -147,8 +147,9 @@ struct AcceptArgs {
 
 // One workgroup per sequence, one wavefront per row, kAcceptRows rows at a time (the loop of
 // further rows is for longer drafts): the rows' keys arrive together.  (One wavefront walking the
-// rows paid a trip to memory for each: the stores of the tokens keep the loads behind them;
-// 128 sequences of 4 rows 4.1 -> 3.3 us.)
+// rows paid a trip to memory for each: the stores of the tokens keep the loads behind them.  Both
+// launches over 1000 logits a row, where the walk is most of it, back to back in a graph: 128
+// sequences of 4 rows 6.3 -> 4.9 us, of 17 rows 13.1 -> 6.9; with 32000 logits 12.1 -> 7.8 and the scan.)
 constexpr int kAcceptRows = 16;
 __global__ __launch_bounds__(64 * kAcceptRows) void accept_kernel(AcceptArgs p) {
   __shared__ int32_t tops[kAcceptRows];

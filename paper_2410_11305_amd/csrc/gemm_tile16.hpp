@@ -8,8 +8,8 @@
 // same block, set wk takes every WGK-th group, and the sets' partial sums meet in LDS at
 // the end.  That is how eight wavefronts work on a block of 128 x 64 or 64 x 64 where the
 // problem has no more blocks than compute units: with four (one per SIMD) every wait of a
-// wave idles its SIMD (12288 x 4096 at 128 tokens, 192 blocks: 23.5 us on four
-// wavefronts, 19.0 on eight; 5120 x 5120 at 384: 29.1 -> 25.8).
+// wave idles its SIMD (128 x 64 blocks, 12288 x 4096 at 128 tokens, 192 blocks: 22.3 us on four
+// wavefronts, 18.5 on eight; 5120 x 5120 at 384, 240 blocks: 27.6 and 24.3).
 //   - Activations: the BM x 128 fp16 block of a group travels global -> LDS
 //     with buffer loads that write LDS directly (no registers, no ds_write),
 //     one group ahead, into two stages that are separate arrays (the compiler
@@ -26,14 +26,16 @@
 //     reads of a later k-step first, then the MFMAs of this k-step with the
 //     dequantisation of the NEXT k-step cut into stages of independent operations
 //     between them.  Left to itself the compiler puts every LDS read next to its first use.
-//   - What bounds the loop where the power limit does not: issue slots.  A SIMD issues a
-//     matrix or vector instruction every 4.9 cycles when both kinds mix, an MFMA takes 32, so
-//     six vector operations per MFMA are free and every further one costs; a 64-token
-//     wave tile needs 6.5 for the dequantisation alone.  Hence no address arithmetic in the
-//     loop: what moves with the group is a scalar offset of the load, LDS addresses differ
-//     from a lane's fixed one by constant bits (8.5 -> 7.0 vector operations per MFMA,
-//     12288 x 4096 at 128 tokens 21.4 -> 19.5 us, 57344 x 8192 at 512 448 -> 430 on 128 x 128
-//     blocks).
+//   - What bounds the loop where the power limit does not: issue slots.  Between the MFMAs (32
+//     cycles each) two wavefronts of a SIMD fit six independent vector operations, one wavefront
+//     alone four; every further one costs 4.9 cycles (a loop of MFMAs with n packed fp16
+//     products behind each, ns per MFMA of a SIMD: 15.7 up to n = 3, 17 at 4 to 6, 18.9 at 7, 24.0
+//     at 10; one wavefront: 34.5 cycles at n = 0, 38 at 4, 48 at 6, 62 at 10).  A 64-token wave tile
+//     needs 6.5 for the dequantisation alone.  Hence no address arithmetic in the loop: what
+//     moves with the group is a scalar offset of the load, LDS addresses differ from a lane's
+//     fixed one by constant bits (vector operations per MFMA in the compiled loops: 7.5 -> 6.5 on
+//     64-token wave tiles, 4.0 -> 3.3 on 128-token ones; on the same 128 x 128 blocks 57344 x 8192
+//     at 512 tokens 455 -> 442 us, 11008 -> 4096 at 2050 238 -> 227).
 //
 // A operand (32 rows x 16 k): lane l supplies 8 consecutive k of row l % 32,
 // lanes 0..31 the first 8 k of the step, lanes 32..63 the second 8.  In the blob

@@ -2,16 +2,16 @@
 // wavefronts, 64 x 128 per wavefront.  Same data layout, staging and dequantisation as
 // gemm_tile16w_kernel (see there); no K-slices.
 //
-// What bounds it: the power limit.  The matrix loops of this part run at 1.7 PFLOP/s on operands
-// like these with nothing else in the loop, whatever the instruction rate would allow; every
-// vector operation per v_mfma_f32_32x32x16_f16 costs 3.7 % of that and every 1 KB operand read from
-// LDS about 12 %.  So the wave tile is chosen for energy, not for issue slots: with two 32-wide
-// feature tiles per wavefront an activation operand is read from LDS once for two matrix
-// instructions instead of for one (32 x 128 wave tiles), and 512 outputs per workgroup halve
-// the activation bytes that enter a compute unit per output against 256.  Both need the
-// registers of one workgroup per compute unit: 128 of 256 are accumulators.
-// Measured at 57344 x 8192 and 512 tokens: 448 us (128 x 128 blocks) and 445 us (256 x 128) before,
-// 384 us with this kernel (1.25 PFLOP/s); 11008 -> 4096 at 2050 tokens 231 -> 185 us.
+// What bounds it: the power limit.  The matrix loop of this part runs at 1.62 PFLOP/s on operands
+// like these with nothing else in the loop, whatever the instruction rate would allow, and every
+// vector operation and operand read beside it takes from that.  So the wave tile is chosen for
+// energy, not for issue slots: with two 32-wide feature tiles per wavefront an activation operand
+// is read from LDS once for two matrix instructions instead of for one (32 x 128 wave tiles), and
+// 512 outputs per workgroup halve the activation bytes that enter a compute unit per output
+// against 256.  Both need the registers of one workgroup per compute unit: 128 of 256 are
+// accumulators.
+// Measured at 57344 x 8192 and 512 tokens, one run: 442 us on 128 x 128 blocks, 445 on 256 x 128, 408
+// with this kernel (381 on another machine, 1.26 PFLOP/s); 11008 -> 4096 at 2050 tokens 227, 247 and 216.
 //
 // Order inside a k-step: token tile by token tile, both feature tiles of it one after the other,
 // then the operand register quad of that token tile is refilled for the next k-step (six matrix
@@ -19,7 +19,8 @@
 // k-step: by then the wave's reads of the stage have completed, and half a k-step of matrix
 // instructions covers the first reads of the next stage.  The two waves of a SIMD take turns
 // by progress (a wave's priority falls over a group): left to the hardware the older wave
-// runs ahead to the barrier and the younger one then runs alone (411 against 417 us).
+// runs ahead to the barrier and the younger one then runs alone (384.7 us without the priorities,
+// 380.8 with them; 11008 -> 4096 at 2050 tokens 191.1 and 185.6).
 #pragma once
 #include "gemm_tile16.hpp"
 
