@@ -414,6 +414,8 @@ void plan_tile16(int M, int N, int G, int* shape, int* slices) {
       // K-slices only while all workgroups have a compute unit of their own (and the partial sums
       // fit 32 MiB), of four groups at least
       if (S > 1 && (c.slice0 == 0.0 || blocks * S > kNumCU || G / S < 4)) break;
+      // (every eager call plans; no plan is cheaper than one round of workgroups with nothing beside them)
+      if (c.fixed + c.alone * G / S >= best) continue;
       const long long wgs = blocks * S, load = (long long)c.places * kNumCU, full = wgs / load, rest = wgs % load;
       const double rounds = (full ? full * per_group(c.places) : 0.0) + (rest ? per_group((double)rest / kNumCU) : 0.0);
       // (the exchange of few workgroups is cheaper: 48 of 64 x 64 in two slices 3.1 us, 240 of them 4.0)
