@@ -1,24 +1,41 @@
 // Memory-bound (small M) kernels for both modes, wave-autonomous form.
 //
-// A workgroup of 8 wavefronts owns NT adjacent weight tiles (16 outputs each)
-// over the whole of K.  Wave w takes the K groups g = w, w+8, w+16, ...; for
-// each of them it loads the activation operand of that group ONCE into
-// registers (straight from global memory: the activations are small and stay
-// in L2) and re-uses it against the NT weight tiles, which stream from HBM
-// exactly once.  Nothing is staged in LDS, so there is no barrier in the
-// streaming loop and no split-K pass over a workspace: the eight per-wave
-// fp32 sums of a tile are combined through LDS at the very end and stored as
-// fp16.
+// A workgroup of 8 wavefronts owns NT adjacent weight tiles (16 outputs each) over the whole
+// of K and 16 TM token rows.  The K groups are dealt to the wavefronts; a wavefront loads the
+// activations of its groups once and uses them against the NT weight tiles, which stream from
+// HBM exactly once.  There is no barrier in the streaming loop: everything a wavefront stages
+// sits in a part of LDS that is its own (LDS executes a wavefront's accesses in order).  The
+// eight fp32 sums of a tile are combined through LDS at the very end and stored as fp16.
 //
-// All global loads are unconditional buffer loads (work that does not exist
-// gets an out-of-range offset, which reads as zero without memory traffic;
-// a load inside a branch would make the compiler drain the whole memory
-// pipeline at every use) and two register sets alternate, so that the loads
-// of the next group are in flight while the current one is computed.
+// What bounds it is the read of the weights, and next to that the number of cache LINES its
+// loads touch: the vector L1 looks up one 128-byte line per clock and quarter wavefront, so a
+// load whose 16 lanes hit 16 rows costs 16 lookups however few bytes it brings.  Hence:
+//  - activations are loaded with adjacent lanes on adjacent bytes of a row and turned into the
+//    MFMA operand through LDS.  (Loaded in operand layout, with one token scale per row and
+//    load, the draft mode at 64 tokens, 15360 x 5120, did 24200 lookups per compute unit
+//    = 11.5 us of its 19; now 14.9 us.  5120 x 13824: 22.9 -> 17.7; 4096 x 11008 at 32 tokens:
+//    10.8 -> 8.3.)
+//  - the scales of up to 16 groups come in a few wide loads at the start and wait in LDS.
+//  - neighbouring tile blocks run on the same XCD, whose L2 then serves the 128-byte lines of
+//    weight scales that four tiles share (0.2 to 0.8 us of every call).
+//  - no load is issued for work that does not exist, except in the last step of a wavefront
+//    with an odd number of groups: loads past the end cost the same issue time as others
+//    (a set of six: 0.35 us).
+// A weight tile's registers are refilled, with the same tile of the next step, as soon as its
+// codes are widened.  Two or three steps in flight are slower everywhere (22016 x 4096 at 32
+// tokens 12.0 -> 13.4 us; the reads only queue up).
 //
-// MFMA operand roles: A = weights (row = n % 16), B = activations (column =
-// m % 16), k-block = lane / 16; D[i][j]: lane holds rows 4*(lane/16)+r.
+// MFMA roles: A = activations (row = token), B = weights (column = output feature); lane
+// (r16 = lane % 16, kb = lane / 16) of D holds tokens 4 kb .. 4 kb + 3 of output r16.  So a lane
+// needs ONE weight scale per tile and group.  Draft mode: the MFMA chain starts from the bit
+// pattern of 1.5 * 2^23, the finished int32 register READ AS A FLOAT is 12582912 + 256 P exactly
+// (|256 P| <= 2^21), t = fma(that, sw, -12582912 sw) is the correctly rounded 256 P sw, and
+// acc = fma(t, sa 2^-8, acc) takes its token scale through the DPP row broadcast (lane i of a row
+// of 16 lanes holds the scale of token 4 kb + i).  Verify mode: the operands are the exact integer
+// codes, and the scale goes onto the fp32 group sum.
 #pragma once
+#include <type_traits>
+
 #include "buffer.hpp"
 #include "exchange.hpp"
 #include "common.hpp"
@@ -31,223 +48,76 @@ struct StreamArgs {
   const void* act;           // W4A4: qa bytes [M][K/2]; W4A16: x fp16 [M][K]
   const float* sa;           // W4A4: [M][G]
   uint16_t* y;               // fp16 [M][N]
-  float* ws;                 // S > 1: fp32 partial sums [S][tile block][output fragment]
+  float* ws;                 // S > 1: fp32 partial sums [S][tile block][output tile of 256]
   unsigned* tickets;         // S > 1: one arrival counter per tile block, zero on entry and on exit
   int M, N, K, G;
-  int S;                     // K-slices: workgroup b owns tile block b / S, slice b % S
+  int S;                     // K-slices: tile block b / S, slice b % S
 };
 
 constexpr int kStreamWaves = 8;
 
-struct StreamRsrc {
-  rsrc_t codes, scales, act, sa;
+template <bool W4A4, int TM, int NT>
+struct StreamShape {
+  static constexpr int W = kStreamWaves;
+  // Groups per step.  Two adjacent ones where few tiles per step would leave too few bytes in
+  // flight (4096 x 11008 at one token 8.8 -> 6.9 us); their activations fill whole cache lines.
+  static constexpr int QS = NT <= 2 && TM <= 4 ? 2 : 1;
+  static constexpr int CH = TM >= 4 ? 8 : 16;               // groups of a wavefront whose scales are in LDS at a time
+  static constexpr int kActTile = W4A4 ? 1024 : 4096;       // bytes of 16 token rows of one group
+  static constexpr int kChunk = NT * TM < W ? NT * TM : W;  // output tiles combined per pass
+  static constexpr int GPL = 64 / (2 * NT);                 // groups per weight-scale load
+  static constexpr int kSwN = (CH + GPL - 1) / GPL;         // weight-scale loads of a full chunk
+  static constexpr int kSaOff = QS * TM * kActTile;
+  static constexpr int kSwOff = kSaOff + (W4A4 ? CH * 16 * TM * 4 : 0);
+  static constexpr int kStage = kSwOff + kSwN * GPL * NT * 32;
+  static constexpr int kRed = kChunk * 1024;
+  // LDS of one wavefront: activations of a step, scales; at the end its sums
+  static constexpr int kRegion = ((kStage > kRed ? kStage : kRed) + 255) / 256 * 256;
 };
 
-// From this many tiles per workgroup on, the scales of two groups come in one load
-// (below that the two ds_bpermute per tile cost more than the load they replace).
-#ifndef QSPEC_PAIR_SCALES_MIN_NT
-#define QSPEC_PAIR_SCALES_MIN_NT 2
-#endif
-__device__ __host__ inline constexpr bool pair_scales(int nt) { return nt >= QSPEC_PAIR_SCALES_MIN_NT; }
-
-template <bool W4A4, int TM, int NT>
-struct GroupRegs {
-  uint4 w[NT];                      // one weight tile slice per n-tile
-  uint2 sw[NT];                     // 4 fp16 weight scales (rows 4*kb .. 4*kb+3 of the tile); unused with pair scales
-  uint4 a[W4A4 ? TM : TM * 4];      // activation operand(s) of this group
-  float sa[W4A4 ? TM : 1];          // activation scales (W4A4)
-};
-
-// Issue every load of group g (valid == false: all offsets out of range, no traffic).
-// wlds != nullptr: the weight tiles of this workgroup were copied to LDS beforehand, tile j
-// of group g at wlds + (j * G + g) * 1024, and are read from there.
-template <bool W4A4, int TM, int NT>
-__device__ inline void load_group(GroupRegs<W4A4, TM, NT>& R, const StreamRsrc& rs, const StreamArgs& p, int g,
-                                  bool valid, int T0, int nt_valid, int lane, const uint8_t* wlds = nullptr) {
-  const int r16 = lane & 15, kb = lane >> 4;
-  // activations first: loads return in order, and the (L2-resident) activations
-  // must not queue behind the HBM weight tiles
-#pragma unroll
-  for (int t = 0; t < TM; ++t) {
-    const uint32_t m = 16 * t + r16;               // rows past M lie past the end of the buffer: they read as 0
-    if (W4A4) {
-      R.a[t] = buf_load16(rs.act, valid ? m * (uint32_t)(p.K / 2) + 64u * g + 16u * kb : kOutOfRange);
-      R.sa[t] = buf_load_f32(rs.sa, valid ? (m * p.G + g) * 4u : kOutOfRange);
-    } else {
-      // Coalesced form: load u = 4t + i covers token rows 4u .. 4u+3, 256 contiguous
-      // bytes (one group) per row, 16 lanes per row.  compute_group turns this into
-      // the MFMA operand layout through a wave-private LDS buffer.  (Loading the
-      // operand layout directly touches 16 rows x 64 bytes at a 2K-byte stride per
-      // instruction, which the caches serve at a fraction of their bandwidth.)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t row = 4u * (4 * t + i) + kb;
-        R.a[t * 4 + i] = buf_load16(rs.act, valid ? (row * (uint32_t)p.K + (uint32_t)g * kGroup) * 2u + r16 * 16u
-                                                  : kOutOfRange);
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const bool ok = valid && j < nt_valid;
-    const uint32_t T = (uint32_t)(T0 + j);
-    if (wlds != nullptr) {
-      R.w[j] = ok ? *reinterpret_cast<const uint4*>(wlds + ((size_t)(j * p.G + g) * 1024u + lane * 16u)) : uint4{0u, 0u, 0u, 0u};
-    } else {
-      R.w[j] = buf_load16_stream(rs.codes, ok ? (T * p.G + g) * 1024u + lane * 16u : kOutOfRange);
-    }
-    if (!pair_scales(NT)) R.sw[j] = buf_load8(rs.scales, ok ? ((uint32_t)g * p.N + T * 16u + 4u * kb) * 2u : kOutOfRange);
-  }
-}
-
-// Weight scales of a PAIR of groups (ga: the even step, gb: the odd one) and all NT
-// tiles in one load instruction: lane (c = lane % 16, kb = lane / 16) fetches the four
-// fp16 scales of rows 4*kb .. 4*kb+3 of tile c % NT of group ga (c < NT) or gb
-// (NT <= c < 2*NT).  compute_group fetches them from that lane with ds_bpermute (no
-// LDS memory involved).  Measured: every further load instruction per group costs
-// streaming time even when it hits in cache (the vector memory queue, not DRAM, is
-// what it occupies), so 2*NT small loads per pair became one.
-template <int NT>
-__device__ inline uint2 load_pair_scales(const StreamRsrc& rs, const StreamArgs& p, int ga, int gb, bool va, bool vb,
-                                         int T0, int nt_valid, int lane) {
-  static_assert(2 * NT <= 16, "one lane row holds both groups of all tiles");
-  const int c = lane & 15, kb = lane >> 4;
-  const int q = c / NT, j = c - q * NT;
-  const bool ok = (q == 0 ? va : (q == 1 && vb)) && j < nt_valid;
-  const uint32_t g = (uint32_t)(q == 0 ? ga : gb);
-  return buf_load8(rs.scales, ok ? (g * (uint32_t)p.N + (uint32_t)(T0 + j) * 16u + 4u * kb) * 2u : kOutOfRange);
-}
-
-// The scales of tile j in step Q (0: even, 1: odd) of the pair, from the lane that loaded them.
-template <int NT, int Q>
-__device__ inline uint2 pair_scales_of(uint2 swp, int j, int lane) {
-  const int idx = ((lane & 48) + Q * NT + j) << 2;
-  uint2 r;
-  r.x = (uint32_t)__builtin_amdgcn_ds_bpermute(idx, (int)swp.x);
-  r.y = (uint32_t)__builtin_amdgcn_ds_bpermute(idx, (int)swp.y);
-  return r;
-}
-
-constexpr int kXPitch = 256 + 16;     // bytes per token row of the transpose buffer (odd number of 16-byte slots)
-
-template <bool W4A4, int TM, int NT, int Q>
-__device__ inline void compute_group(const GroupRegs<W4A4, TM, NT>& R, uint2 swp, float (&facc)[NT][TM][4],
-                                     uint8_t* xbuf, int lane) {
-  if (W4A4) {
-    // weight operands and scales of all NT tiles first, then token tile by token tile
-    // (one unpacked activation operand live at a time: TM goes up to 8)
-    I8Pair a[NT];
-    float sw[NT][4];
-    // With two or more token tiles the int32 -> fp32 conversion is folded away: the MFMA
-    // chain starts from the bit pattern of 1.5 * 2^23, so the finished int32 register READ
-    // AS A FLOAT is 12582912 + 256 P exactly (|256 P| <= 2^21: inside the binade, one unit
-    // in the last place = 1), and fma(that, sw, -12582912 * sw) is the correctly rounded
-    // 256 P * sw (the constant is exact: sw has 11 significant bits, 1.5 * 2^23 two).  Two
-    // vector instructions per output and group instead of three, plus one per weight row
-    // and group that the TM token tiles share.
-    constexpr bool kMagic = TM >= 2;
-    constexpr int kMagicBits = 0x4B400000;              // 12582912.0f
-    float swc[NT][4];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      a[j] = unpack_i8(R.w[j]);
-      const uint2 sq = pair_scales(NT) ? pair_scales_of<NT, Q>(swp, j, lane) : R.sw[j];
-      // both int8 operands carry a factor 16: fold 2^-8 into the weight scale (exact)
-      sw[j][0] = half_bits_to_float((uint16_t)(sq.x & 0xFFFF)) * 0.00390625f;
-      sw[j][1] = half_bits_to_float((uint16_t)(sq.x >> 16)) * 0.00390625f;
-      sw[j][2] = half_bits_to_float((uint16_t)(sq.y & 0xFFFF)) * 0.00390625f;
-      sw[j][3] = half_bits_to_float((uint16_t)(sq.y >> 16)) * 0.00390625f;
-      if (kMagic) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) swc[j][r] = sw[j][r] * -12582912.0f;
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < TM; ++t) {
-      const I8Pair b = unpack_i8(R.a[t]);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        v4i acc = kMagic ? v4i{kMagicBits, kMagicBits, kMagicBits, kMagicBits} : v4i{0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[j].lo, b.lo, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[j].hi, b.hi, acc, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (kMagic) {
-            const int bits = acc[r];                    // (a copy: bit_cast of a vector element lvalue reads element 0)
-            facc[j][t][r] = __builtin_fmaf(__builtin_fmaf(__builtin_bit_cast(float, bits), sw[j][r], swc[j][r]),
-                                           R.sa[t], facc[j][t][r]);
-          } else {
-            facc[j][t][r] += (float)acc[r] * (R.sa[t] * sw[j][r]);
-          }
-        }
-      }
-    }
-  } else {
-    // rows x 256 B (as loaded) -> operand layout: lane (r16, kb), step i reads the
-    // 16 bytes of row 16t + r16 that hold k = 32i + 8kb .. +8.  Only this wave
-    // touches xbuf and LDS executes a wave's accesses in order: no barrier.
-    const int r16 = lane & 15, kb = lane >> 4;
-#pragma unroll
-    for (int u = 0; u < TM * 4; ++u)
-      *reinterpret_cast<uint4*>(xbuf + (4 * u + kb) * kXPitch + r16 * 16) = R.a[u];
-    uint4 xb[TM * 4];
-#pragma unroll
-    for (int t = 0; t < TM; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        xb[t * 4 + i] = *reinterpret_cast<const uint4*>(xbuf + (16 * t + r16) * kXPitch + (4 * i + kb) * 16);
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      v8h wa[4];
-      wa[0] = dequant_word(R.w[j].x);
-      wa[1] = dequant_word(R.w[j].y);
-      wa[2] = dequant_word(R.w[j].z);
-      wa[3] = dequant_word(R.w[j].w);
-      const uint2 sq = pair_scales(NT) ? pair_scales_of<NT, Q>(swp, j, lane) : R.sw[j];
-      float sw[4];
-      sw[0] = half_bits_to_float((uint16_t)(sq.x & 0xFFFF));
-      sw[1] = half_bits_to_float((uint16_t)(sq.x >> 16));
-      sw[2] = half_bits_to_float((uint16_t)(sq.y & 0xFFFF));
-      sw[3] = half_bits_to_float((uint16_t)(sq.y >> 16));
-#pragma unroll
-      for (int t = 0; t < TM; ++t) {
-        v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[i], __builtin_bit_cast(v8h, xb[t * 4 + i]), acc, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) facc[j][t][r] += acc[r] * sw[r];
-      }
-    }
-  }
+// acc += S[lane R of this row of 16 lanes] * t.  S comes straight from LDS: a vector ALU instruction
+// must not have written it in the two instructions before.
+template <int R>
+__device__ __forceinline__ void fmac_row16(float& acc, float S, float t) {
+  asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(S), "v"(t), "n"(R));
 }
 
 template <bool W4A4, int TM, int NT>
-__global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_kernel(StreamArgs p) {
-  constexpr int W = kStreamWaves;
-  // LDS: per-wave transpose buffers while streaming (verify mode), re-used as the
-  // split-K reduction buffer at the end
-  constexpr int kChunk = NT * TM < W ? NT * TM : W;      // output tiles combined per pass, one per wave
-  constexpr int kRedBytes = W * kChunk * 4 * kWave * 4;
-  constexpr int kXBytes = W4A4 ? 0 : W * TM * 16 * kXPitch;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kRedBytes > kXBytes ? kRedBytes : kXBytes];
-  float (*red)[kChunk * 4][kWave] = reinterpret_cast<float (*)[kChunk * 4][kWave]>(lds);
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(StreamArgs p) {
+  using C = StreamShape<W4A4, TM, NT>;
+  constexpr int W = C::W, kChunk = C::kChunk, QS = C::QS, CH = C::CH;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[W * C::kRegion];
+  __shared__ unsigned ticket;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kb = lane >> 4;
-  const int tb = blockIdx.x / p.S, slice = blockIdx.x - tb * p.S;
-  const int T0 = tb * NT;
-  const int nt_valid = min(NT, p.N / 16 - T0);        // >= 1 by construction of the grid
+  // workgroups go to the eight XCDs in turn: each XCD gets a run of adjacent tile blocks
+  const int nblk = gridDim.x, xcd = blockIdx.x & 7, qx = nblk >> 3, rx = nblk & 7;
+  const int bx = xcd * qx + (xcd < rx ? xcd : rx) + (blockIdx.x >> 3);
   const int G = p.G;
-  // token-row blocks along gridDim.y (only without K-slices): this workgroup owns rows m_base .. m_base + 16*TM - 1
+  int tb = bx, slice = 0, s0 = 0, s1 = G;
+  if (p.S > 1) {
+    tb = bx / p.S; slice = bx - tb * p.S;
+    s0 = (int)(((long long)slice * G) / p.S); s1 = (int)(((long long)(slice + 1) * G) / p.S);
+  }
+  const int T0 = tb * NT;
+  const int nt_valid = min(NT, p.N / 16 - T0);
+  // token-row blocks along gridDim.y (only without K-slices)
   const int m_base = (int)blockIdx.y * (16 * TM);
   const int Mloc = p.M - m_base;
   if (Mloc <= 0) return;                           // (the whole workgroup: uniform)
   uint16_t* const yloc = p.y + (size_t)m_base * p.N;
-  const int g0 = (int)(((long long)slice * G) / p.S), g1 = (int)(((long long)(slice + 1) * G) / p.S);
-  // groups of this wave: g0 + wave, g0 + wave + W, ...  (n_g of them, possibly none)
-  const int n_g = max(0, (g1 - g0 - wave + W - 1) / W);
+  // group i of this wavefront, and how many it has: dealt round robin, QS adjacent ones at a time
+  // (contiguous ranges per wavefront read the weights 10 to 20 % slower)
+  auto grp = [&](int i) -> int { return QS == 1 ? s0 + wave + W * i : s0 + 2 * (wave + W * (i >> 1)) + (i & 1); };
+  int n_g;
+  if (QS == 1) n_g = (s1 - s0 - wave + W - 1) / W;
+  else {
+    const int left = s1 - s0 - 2 * wave;
+    const int full = left >= 0 ? left / (2 * W) : 0, rest = left - full * 2 * W;
+    n_g = 2 * full + (rest <= 0 ? 0 : rest >= 2 ? 2 : 1);
+  }
 
   float facc[NT][TM][4];
 #pragma unroll
@@ -257,110 +127,298 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gemm_stream_kernel(StreamAr
 #pragma unroll
       for (int r = 0; r < 4; ++r) facc[j][t][r] = 0.0f;
 
-  uint8_t* xbuf = lds + (W4A4 ? 0 : wave * TM * 16 * kXPitch);
+  uint8_t* const mine = lds + wave * C::kRegion;
   if (n_g > 0) {
-    StreamRsrc rs;
-    rs.codes = make_rsrc(p.codes, (uint32_t)((size_t)p.N * p.K / 2));
-    rs.scales = make_rsrc(p.scalesT, (uint32_t)((size_t)p.N * G * 2));
-    const uint8_t* act0 = static_cast<const uint8_t*>(p.act) + (size_t)m_base * (W4A4 ? p.K / 2 : p.K * 2);
-    rs.act = make_rsrc(act0, (uint32_t)(W4A4 ? (size_t)Mloc * p.K / 2 : (size_t)Mloc * p.K * 2));
-    rs.sa = make_rsrc(W4A4 ? (const void*)(p.sa + (size_t)m_base * G) : (const void*)act0, (uint32_t)((size_t)Mloc * G * 4));
-    // Workgroups start at different points of their K sequence so that the 256
-    // CUs do not all ask L2 for the same activation lines at the same moment.
-    const int rot = (int)(blockIdx.x % (unsigned)n_g);
-    auto grp = [&](int it) { int q = it + rot; q = q >= n_g ? q - n_g : q; return g0 + wave + q * W; };
-    // Two register sets alternate: the loads of the next group are in flight
-    // while one group is computed.  (A third set was measured and is slower: the
-    // memory system is throughput-bound here, more requests in flight only
-    // queue up.)  The scheduling barriers pin the order "issue loads, then
-    // compute": without them the compiler sinks the loads below the arithmetic.
-    GroupRegs<W4A4, TM, NT> A, B;
-    uint2 sw_cur = {0u, 0u}, sw_nxt = {0u, 0u};
-    if (pair_scales(NT)) sw_cur = load_pair_scales<NT>(rs, p, grp(0), grp(1), true, 1 < n_g, T0, nt_valid, lane);
-    load_group<W4A4, TM, NT>(A, rs, p, grp(0), true, T0, nt_valid, lane);
-    for (int it = 0; it < n_g; it += 2) {
-      // the scales of the next pair go out ahead of this pair's second group: they are
-      // back (loads return in order) long before the register move at the bottom
-      if (pair_scales(NT)) sw_nxt = load_pair_scales<NT>(rs, p, grp(it + 2), grp(it + 3), it + 2 < n_g, it + 3 < n_g, T0, nt_valid, lane);
-      load_group<W4A4, TM, NT>(B, rs, p, grp(it + 1), it + 1 < n_g, T0, nt_valid, lane);
+    const uint32_t codes_bytes = (uint32_t)((size_t)p.N * p.K / 2);
+    const uint32_t scales_bytes = (uint32_t)((size_t)p.N * G * 2);
+    const uint32_t row_bytes = W4A4 ? (uint32_t)p.K / 2 : (uint32_t)p.K * 2;
+    const uint8_t* const act = static_cast<const uint8_t*>(p.act) + (size_t)m_base * row_bytes;
+    const rsrc_t r_act = make_rsrc(act, (uint32_t)((size_t)Mloc * row_bytes));
+    const rsrc_t r_scales = make_rsrc(p.scalesT, scales_bytes);
+    const rsrc_t r_sa = make_rsrc(W4A4 ? (const void*)(p.sa + (size_t)m_base * G) : (const void*)act, (uint32_t)((size_t)Mloc * G * 4));
+    const uint32_t w_voff = lane * 16u;
+    // activation loads of a step: kA of them, 1 KB each
+    constexpr int kA = W4A4 ? QS * TM : QS * TM * 4;
+    uint32_t a_voff, st_off, rd_off[W4A4 ? QS : 4];
+    if (W4A4) {
+      if (QS == 2) {                                         // 8 rows x 128 bytes (two groups) a load
+        const int row = lane >> 3, sw = (r16 & 7) ^ (r16 >> 3);
+        a_voff = (uint32_t)row * row_bytes + (lane & 7) * 16u;
+        st_off = row * 128 + (((lane & 7) ^ row) << 4);      // rows 8 .. 15: the slot gets ^ 1
+#pragma unroll
+        for (int q = 0; q < QS; ++q) rd_off[q] = r16 * 128 + (((4 * q + kb) ^ sw) << 4);
+      } else {                                               // 16 rows x 64 bytes
+        const int row = lane >> 2;
+        a_voff = (uint32_t)row * row_bytes + (lane & 3) * 16u;
+        st_off = row * 64 + (((lane & 3) ^ ((row >> 1) & 3) ^ (row >> 3)) << 4);
+        rd_off[0] = r16 * 64 + ((kb ^ ((r16 >> 1) & 3) ^ (r16 >> 3)) << 4);
+      }
+    } else {                                                 // 4 rows x 256 bytes
+      a_voff = (uint32_t)kb * row_bytes + r16 * 16u;
+      st_off = kb * 256 + ((r16 ^ kb) << 4);                 // rows 4u + kb: the slot gets ^ 4 (u % 4)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rd_off[i] = r16 * 256 + (((4 * i + kb) ^ r16) << 4);
+    }
+    // token scales: a load covers 16 tokens x 4 groups, four lines per quarter wavefront
+    const int s_tok = 4 * kb + (lane & 3);
+    const int s_grp = (lane >> 2) & 3;
+    const uint32_t sa_voff = (uint32_t)s_tok * (uint32_t)G * 4u;
+    const int z_grp = lane / (2 * NT), z_piece = lane - z_grp * (2 * NT);      // weight scales: 2 NT lanes per group
+
+    uint4 w[QS][NT], ar[kA];
+
+    for (int c0 = 0; c0 < n_g; c0 += CH) {
+      const int n = min(CH, n_g - c0);                       // groups of this chunk
+      const int n_s = (n + QS - 1) / QS;
+      auto load_tile = [&](int s, int q, int j) __attribute__((always_inline)) {
+        // (a tile past N or a group past the end: an empty buffer, zeros)
+        const bool ok = (QS == 1 || s * QS + q < n) && j < nt_valid;
+        const uint32_t soff = ((uint32_t)(T0 + j) * (uint32_t)G + (uint32_t)grp(c0 + s * QS + q)) * 1024u;
+        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(p.codes, ok ? codes_bytes : 0u), w_voff, ok ? soff : 0u, 2);
+        w[q][j] = uint4{v.x, v.y, v.z, v.w};
+      };
+      auto load_act = [&](int s) __attribute__((always_inline)) {
+        if (W4A4) {
+          const uint32_t gb = a_voff + (uint32_t)grp(c0 + s * QS) * 64u;
+#pragma unroll
+          for (int u = 0; u < kA; ++u) ar[u] = buf_load16(r_act, gb + (uint32_t)((QS == 2 ? 8 : 16) * u) * row_bytes);
+        } else {
+          const uint32_t gb = a_voff + (uint32_t)grp(c0 + s * QS) * 256u;
+#pragma unroll
+          for (int q = 0; q < QS; ++q)
+#pragma unroll
+            for (int u = 0; u < 4 * TM; ++u) ar[q * 4 * TM + u] = buf_load16(r_act, gb + q * 256u + (uint32_t)(4 * u) * row_bytes);
+        }
+      };
+      auto stage = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kA; ++u) {
+          uint32_t off = st_off;
+          if (W4A4 && QS == 2 && (u & 1)) off ^= 16;
+          if (!W4A4) off ^= (u & 3) << 6;
+          *reinterpret_cast<uint4*>(mine + u * 1024 + off) = ar[u];
+        }
+      };
+      // scales of the chunk (zeros for groups and tiles that do not exist); token scales times 2^-8, exact
+      constexpr int kSaN = CH / 4;
+      float sar[W4A4 ? kSaN : 1][TM];
+      uint4 swr[C::kSwN];
+      if (W4A4) {
+#pragma unroll
+        for (int k = 0; k < kSaN; ++k)
+          if (4 * k < n) {
+            const int i = 4 * k + s_grp;
+            const uint32_t gone = (uint32_t)((n - 1 - i) >> 31) << 31;
+#pragma unroll
+            for (int t = 0; t < TM; ++t) sar[k][t] = buf_load_f32(r_sa, (sa_voff + (uint32_t)(16 * t * G + grp(c0 + i)) * 4u) | gone);
+          }
+      }
+#pragma unroll
+      for (int k = 0; k < C::kSwN; ++k)
+        if (C::GPL * k < n) {
+          const int i = C::GPL * k + z_grp;
+          const uint32_t gone = (uint32_t)(((n - 1 - i) | (2 * nt_valid - 1 - z_piece)) >> 31) << 31;
+          swr[k] = buf_load16(r_scales, (((uint32_t)grp(c0 + i) * (uint32_t)p.N + (uint32_t)T0 * 16u) * 2u + z_piece * 16u) | gone);
+        }
+      load_act(0);
+#pragma unroll
+      for (int q = 0; q < QS; ++q)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) load_tile(0, q, j);
       __builtin_amdgcn_sched_barrier(0);
-      compute_group<W4A4, TM, NT, 0>(A, sw_cur, facc, xbuf, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      load_group<W4A4, TM, NT>(A, rs, p, grp(it + 2), it + 2 < n_g, T0, nt_valid, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      if (it + 1 < n_g) compute_group<W4A4, TM, NT, 1>(B, sw_cur, facc, xbuf, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      sw_cur = sw_nxt;
+      if (W4A4) {
+#pragma unroll
+        for (int k = 0; k < kSaN; ++k)
+          if (4 * k < n) {
+#pragma unroll
+            for (int t = 0; t < TM; ++t)
+              *reinterpret_cast<float*>(mine + C::kSaOff + ((4 * k + s_grp) * (16 * TM) + 16 * t + s_tok) * 4) = sar[k][t] * 0.00390625f;
+          }
+      }
+#pragma unroll
+      for (int k = 0; k < C::kSwN; ++k)
+        if (C::GPL * k < n && z_grp < C::GPL)
+          *reinterpret_cast<uint4*>(mine + C::kSwOff + (C::GPL * k + z_grp) * (NT * 32) + z_piece * 16) = swr[k];
+
+      constexpr int kSeed = 0x4B400000;                       // 12582912.0f
+      v4i seed = {kSeed, kSeed, kSeed, kSeed};
+      if (W4A4) asm volatile("" : "+v"(seed));
+      auto rescale = [&](const v4i& acc, float sw, float swc, float S, float (&f)[4]) __attribute__((always_inline)) {
+        const int b0 = acc[0], b1 = acc[1], b2 = acc[2], b3 = acc[3];
+        fmac_row16<0>(f[0], S, __builtin_fmaf(__builtin_bit_cast(float, b0), sw, swc));
+        fmac_row16<1>(f[1], S, __builtin_fmaf(__builtin_bit_cast(float, b1), sw, swc));
+        fmac_row16<2>(f[2], S, __builtin_fmaf(__builtin_bit_cast(float, b2), sw, swc));
+        fmac_row16<3>(f[3], S, __builtin_fmaf(__builtin_bit_cast(float, b3), sw, swc));
+      };
+      const uint32_t sa_rd = C::kSaOff + (4 * kb + (lane & 3)) * 4;
+      const uint32_t sw_rd = C::kSwOff + r16 * 2;
+      // one step: groups QS s .. QS s + QS - 1 of the chunk.  (With an odd number of them the draft mode
+      // multiplies the missing group's zeros, the verify mode skips it: zeros times an infinite activation.)
+      auto step = [&](int s, auto refill_c) __attribute__((always_inline)) {
+        constexpr bool kRefill = decltype(refill_c)::value;
+        stage();
+        if constexpr (kRefill) load_act(s + 1);
+        float swf[QS][NT];
+        if constexpr (W4A4) {
+          constexpr int D = 2;                              // an output tile is rescaled while the next D are in the matrix unit
+          constexpr bool kTokenOuter = TM > NT;             // keep the fewer operands widened
+          v4i acc[D + 1];
+          float S[QS][TM], swc[QS][NT];
+          auto finish = [&](int e) __attribute__((always_inline)) {
+            const int q = e / (NT * TM), j = kTokenOuter ? e % NT : e / TM % NT, t = kTokenOuter ? e / NT % TM : e % TM;
+            rescale(acc[e % (D + 1)], swf[q][j], swc[q][j], S[q][t], facc[j][t]);
+          };
+#pragma unroll
+          for (int q = 0; q < QS; ++q) {
+            const int i = s * QS + q;
+#pragma unroll
+            for (int t = 0; t < TM; ++t) S[q][t] = *reinterpret_cast<const float*>(mine + sa_rd + i * (64 * TM) + t * 64);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) swf[q][j] = half_bits_to_float(*reinterpret_cast<const uint16_t*>(mine + sw_rd + i * (NT * 32) + j * 32));
+            if constexpr (kTokenOuter) {
+              I8Pair b[NT];
+#pragma unroll
+              for (int j = 0; j < NT; ++j) {
+                b[j] = unpack_i8(w[q][j]);
+                if constexpr (kRefill) load_tile(s + 1, q, j);
+                swc[q][j] = swf[q][j] * -12582912.0f;
+              }
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int t = 0; t < TM; ++t) {
+                const I8Pair a = unpack_i8(*reinterpret_cast<const uint4*>(mine + t * (QS * 1024) + rd_off[q]));
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                  const int e = (q * TM + t) * NT + j;
+                  acc[e % (D + 1)] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.lo, b[j].lo, seed, 0, 0, 0);
+                  acc[e % (D + 1)] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.hi, b[j].hi, acc[e % (D + 1)], 0, 0, 0);
+                  if (e >= D) finish(e - D);
+                }
+              }
+            } else {
+              I8Pair a[TM];
+#pragma unroll
+              for (int t = 0; t < TM; ++t) a[t] = unpack_i8(*reinterpret_cast<const uint4*>(mine + t * (QS * 1024) + rd_off[q]));
+#pragma unroll
+              for (int j = 0; j < NT; ++j) {
+                const I8Pair b = unpack_i8(w[q][j]);
+                if constexpr (kRefill) load_tile(s + 1, q, j);
+                swc[q][j] = swf[q][j] * -12582912.0f;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int t = 0; t < TM; ++t) {
+                  const int e = (q * NT + j) * TM + t;
+                  acc[e % (D + 1)] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[t].lo, b.lo, seed, 0, 0, 0);
+                  acc[e % (D + 1)] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[t].hi, b.hi, acc[e % (D + 1)], 0, 0, 0);
+                  if (e >= D) finish(e - D);
+                }
+              }
+            }
+          }
+#pragma unroll
+          for (int e = QS * NT * TM - D; e < QS * NT * TM; ++e) if (e >= 0) finish(e);
+        } else {
+          v4f acc[2][TM];
+          auto finish = [&](int e) __attribute__((always_inline)) {
+            const int q = e / NT, j = e % NT;
+#pragma unroll
+            for (int t = 0; t < TM; ++t)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) facc[j][t][r] = __builtin_fmaf(acc[e & 1][t][r], swf[q][j], facc[j][t][r]);
+          };
+#pragma unroll
+          for (int q = 0; q < QS; ++q) {
+            const int i = s * QS + q;
+            if (!kRefill && q > 0 && i >= n) { finish(q * NT - 1); return; }
+#pragma unroll
+            for (int j = 0; j < NT; ++j) swf[q][j] = half_bits_to_float(*reinterpret_cast<const uint16_t*>(mine + sw_rd + i * (NT * 32) + j * 32));
+            v8h a[TM][4];
+#pragma unroll
+            for (int t = 0; t < TM; ++t)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) a[t][k] = *reinterpret_cast<const v8h*>(mine + (q * TM + t) * 4096 + rd_off[k]);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+              const int e = q * NT + j;
+              const v8h b[4] = {dequant_word(w[q][j].x), dequant_word(w[q][j].y), dequant_word(w[q][j].z), dequant_word(w[q][j].w)};
+              if constexpr (kRefill) load_tile(s + 1, q, j);
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int t = 0; t < TM; ++t) acc[e & 1][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int t = 0; t < TM; ++t) acc[e & 1][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[t][k], b[k], acc[e & 1][t], 0, 0, 0);
+              if (e > 0) finish(e - 1);
+            }
+          }
+          finish(QS * NT - 1);
+        }
+      };
+      int s = 0;
+      for (; s + 1 < n_s; ++s) step(s, std::integral_constant<bool, true>{});
+      step(s, std::integral_constant<bool, false>{});
     }
   }
 
-  // ---- combine the eight per-wave sums of every output tile, kChunk tiles per pass
-  // through LDS (the transpose buffers are dead from here on).  With K-slices the
-  // sums go to the workspace first (one 16-byte piece per lane and output tile,
-  // contiguous per wavefront); the workgroup that arrives last at the tile block's
-  // counter adds the slices in slice order and stores fp16.
-  __shared__ unsigned ticket;
-  const int nblocks = gridDim.x / p.S;
-  auto frag = [&](int c, int o) -> float* {
-    return p.ws + ((((size_t)c * nblocks + tb) * (NT * TM) + o) * kWave + lane) * 4;
+  // ---- combine the eight wavefronts through LDS, kChunk output tiles per pass; a thread adds four
+  // adjacent outputs of one token.  Rows past M take no part (8 tokens: half the LDS traffic).  With
+  // K-slices the sums go to the workspace first, and the workgroup that arrives last at the tile
+  // block's counter adds the slices in slice order.
+  auto store_unit = [&](int o, int i, int l4, float4 s) __attribute__((always_inline)) {
+    const int j = o / TM, t = o - j * TM;
+    const int m = 16 * t + 4 * (l4 >> 2) + i;
+    if (j < nt_valid && m < Mloc) {
+      uint2 out;
+      out.x = (uint32_t)float_to_half_bits(s.x) | ((uint32_t)float_to_half_bits(s.y) << 16);
+      out.y = (uint32_t)float_to_half_bits(s.z) | ((uint32_t)float_to_half_bits(s.w) << 16);
+      *reinterpret_cast<uint2*>(yloc + (size_t)m * p.N + (T0 + j) * 16 + 4 * (l4 & 3)) = out;
+    }
   };
+  const int uc = tid >> 6, ui = (tid >> 4) & 3, ul = tid & 15;
 #pragma unroll
   for (int base = 0; base < NT * TM; base += kChunk) {
-    // the buffer must be free: the last pass has been read, and (verify mode) every
-    // wave is done with its transpose buffer, which the sums overwrite
-    if (!W4A4 || base > 0) __syncthreads();
+    // (the first pass overwrites only what this wavefront itself has read)
+    if (base > 0) __syncthreads();
 #pragma unroll
     for (int c = 0; c < kChunk; ++c) {
-      const int o = base + c;                      // compile-time: facc stays in registers
+      const int o = base + c;
       if (o < NT * TM) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave][c * 4 + r][lane] = facc[o / TM][o % TM][r];
+        for (int i = 0; i < 4; ++i)
+          if (16 * (o % TM) + 4 * kb + i < Mloc) *reinterpret_cast<float*>(mine + (c * 4 + i) * 256 + lane * 4) = facc[o / TM][o % TM][i];
       }
     }
     __syncthreads();
-    const int o = base + wave;
-    if (wave < kChunk && o < NT * TM) {
-      const int j = o / TM, t = o - j * TM;
-      float s[4];
+    const int o = base + uc;
+    if (uc < kChunk && o < NT * TM && 16 * (o % TM) + 4 * (ul >> 2) + ui < Mloc) {
+      float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float v = 0.0f;
-#pragma unroll
-        for (int w = 0; w < W; ++w) v += red[w][wave * 4 + r][lane];
-        s[r] = v;
+      for (int w = 0; w < W; ++w) {
+        const float4 v = *reinterpret_cast<const float4*>(lds + w * C::kRegion + (uc * 4 + ui) * 256 + ul * 16);
+        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
       }
       if (p.S > 1) {
-        float* f = frag(slice, o);
-        store_shared_f2(f, s[0], s[1]);
-        store_shared_f2(f + 2, s[2], s[3]);
+        float* f = p.ws + (((size_t)slice * (nblk / p.S) + tb) * (NT * TM) + o) * 256 + ui * 64 + ul * 4;
+        store_shared_f2(f, s.x, s.y);
+        store_shared_f2(f + 2, s.z, s.w);
       } else {
-        const int m = 16 * t + r16;
-        if (j < nt_valid && m < Mloc) {
-          uint2 out;
-          out.x = (uint32_t)float_to_half_bits(s[0]) | ((uint32_t)float_to_half_bits(s[1]) << 16);
-          out.y = (uint32_t)float_to_half_bits(s[2]) | ((uint32_t)float_to_half_bits(s[3]) << 16);
-          *reinterpret_cast<uint2*>(yloc + (size_t)m * p.N + (T0 + j) * 16 + 4 * kb) = out;
-        }
+        store_unit(o, ui, ul, s);
       }
     }
   }
   if (p.S == 1) return;
   if (!last_arrival(p.tickets, p.S, (unsigned)tb, &ticket)) return;
-  for (int o = wave; o < NT * TM; o += W) {
-    const int j = o / TM, t = o - j * TM;
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int o = uc; o < NT * TM; o += W) {
+    if (16 * (o % TM) + 4 * (ul >> 2) + ui >= Mloc) continue;
+    float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int c = 0; c < p.S; ++c) {            // fixed order: the result does not depend on who came last
-      const float* f = frag(c, o);
+      const float* f = p.ws + (((size_t)c * (nblk / p.S) + tb) * (NT * TM) + o) * 256 + ui * 64 + ul * 4;
       const float2 a = load_shared_f2(f), b = load_shared_f2(f + 2);
-      s[0] += a.x; s[1] += a.y; s[2] += b.x; s[3] += b.y;
+      s.x += a.x; s.y += a.y; s.z += b.x; s.w += b.y;
     }
-    const int m = 16 * t + r16;
-    if (j < nt_valid && m < Mloc) {
-      uint2 out;
-      out.x = (uint32_t)float_to_half_bits(s[0]) | ((uint32_t)float_to_half_bits(s[1]) << 16);
-      out.y = (uint32_t)float_to_half_bits(s[2]) | ((uint32_t)float_to_half_bits(s[3]) << 16);
-      *reinterpret_cast<uint2*>(yloc + (size_t)m * p.N + (T0 + j) * 16 + 4 * kb) = out;
-    }
+    store_unit(o, ui, ul, s);
   }
 }
 

@@ -6,8 +6,8 @@
 // cost rather than by arithmetic.  The grid is one workgroup of eight wavefronts per
 // compute unit, all resident at once; a workgroup keeps its place through both projections.
 //
-//   stage 1   a workgroup streams its share of the gate/up weight tiles (the streaming
-//             kernel's loop) and stores its fp16 outputs with write-through stores;
+//   stage 1   a workgroup streams its share of the gate/up weight tiles (the loop
+//             below) and stores its fp16 outputs with write-through stores;
 //   between   every quantisation group of 128 intermediate features has an arrival counter
 //             that counts the 16 output tiles (8 gate, 8 up) it is made of.  The workgroup
 //             whose tiles complete a group computes SiLU(gate) * up for it, quantises it
@@ -104,28 +104,143 @@ __device__ __forceinline__ void mlp_reduce_store(float (&facc)[NT][TM][4], float
   }
 }
 
-// The streaming loop of gemm_stream_kernel for one block of NT tiles over groups 0 .. G-1
-// (wave w takes groups w, w + 8, ...), draft mode.
+// ---- streaming loop of one projection: wavefront w takes groups w, w + 8, ...; per group it loads the
+// activation operand once and uses it against the NT weight tiles.  Two register sets alternate.
+struct MlpRsrc {
+  rsrc_t codes, scales, act, sa;
+};
+
+// From this many tiles per workgroup on, the scales of two groups come in one load
+// (below that the two ds_bpermute per tile cost more than the load they replace).
+__device__ __host__ inline constexpr bool pair_scales(int nt) { return nt >= 2; }
+
 template <int TM, int NT>
-__device__ __forceinline__ void mlp_stream(const StreamArgs& p, const StreamRsrc& rs, int T0, int nt_valid, int wave, int lane,
+struct MlpGroupRegs {
+  uint4 w[NT];                      // one weight tile slice per n-tile
+  uint2 sw[NT];                     // 4 fp16 weight scales (rows 4*kb .. 4*kb+3 of the tile); unused with pair scales
+  uint4 a[TM];                      // activation operand(s) of this group
+  float sa[TM];                     // activation scales
+};
+
+// Issue every load of group g (valid == false: all offsets out of range, no traffic).
+// wlds != nullptr: the weight tiles of this workgroup were copied to LDS beforehand, tile j
+// of group g at wlds + (j * G + g) * 1024, and are read from there.
+template <int TM, int NT>
+__device__ inline void mlp_load_group(MlpGroupRegs<TM, NT>& R, const MlpRsrc& rs, const StreamArgs& p, int g,
+                                      bool valid, int T0, int nt_valid, int lane, const uint8_t* wlds) {
+  const int r16 = lane & 15, kb = lane >> 4;
+  // activations first: loads return in order, and the (L2-resident) activations
+  // must not queue behind the HBM weight tiles
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    const uint32_t m = 16 * t + r16;               // rows past M lie past the end of the buffer: they read as 0
+    R.a[t] = buf_load16(rs.act, valid ? m * (uint32_t)(p.K / 2) + 64u * g + 16u * kb : kOutOfRange);
+    R.sa[t] = buf_load_f32(rs.sa, valid ? (m * p.G + g) * 4u : kOutOfRange);
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const bool ok = valid && j < nt_valid;
+    const uint32_t T = (uint32_t)(T0 + j);
+    if (wlds != nullptr) {
+      R.w[j] = ok ? *reinterpret_cast<const uint4*>(wlds + ((size_t)(j * p.G + g) * 1024u + lane * 16u)) : uint4{0u, 0u, 0u, 0u};
+    } else {
+      R.w[j] = buf_load16_stream(rs.codes, ok ? (T * p.G + g) * 1024u + lane * 16u : kOutOfRange);
+    }
+    if (!pair_scales(NT)) R.sw[j] = buf_load8(rs.scales, ok ? ((uint32_t)g * p.N + T * 16u + 4u * kb) * 2u : kOutOfRange);
+  }
+}
+
+// Weight scales of a PAIR of groups (ga: the even step, gb: the odd one) and all NT
+// tiles in one load instruction: lane (c = lane % 16, kb = lane / 16) fetches the four
+// fp16 scales of rows 4*kb .. 4*kb+3 of tile c % NT of group ga (c < NT) or gb
+// (NT <= c < 2*NT); mlp_compute_group fetches them from that lane with ds_bpermute.
+template <int NT>
+__device__ inline uint2 load_pair_scales(const MlpRsrc& rs, const StreamArgs& p, int ga, int gb, bool va, bool vb,
+                                         int T0, int nt_valid, int lane) {
+  static_assert(2 * NT <= 16, "one lane row holds both groups of all tiles");
+  const int c = lane & 15, kb = lane >> 4;
+  const int q = c / NT, j = c - q * NT;
+  const bool ok = (q == 0 ? va : (q == 1 && vb)) && j < nt_valid;
+  const uint32_t g = (uint32_t)(q == 0 ? ga : gb);
+  return buf_load8(rs.scales, ok ? (g * (uint32_t)p.N + (uint32_t)(T0 + j) * 16u + 4u * kb) * 2u : kOutOfRange);
+}
+
+// The scales of tile j in step Q (0: even, 1: odd) of the pair, from the lane that loaded them.
+template <int NT, int Q>
+__device__ inline uint2 pair_scales_of(uint2 swp, int j, int lane) {
+  const int idx = ((lane & 48) + Q * NT + j) << 2;
+  uint2 r;
+  r.x = (uint32_t)__builtin_amdgcn_ds_bpermute(idx, (int)swp.x);
+  r.y = (uint32_t)__builtin_amdgcn_ds_bpermute(idx, (int)swp.y);
+  return r;
+}
+
+// MFMA roles A = weights, B = activations: lane (r16, kb) of D holds outputs 4 kb .. 4 kb + 3 of token r16.
+template <int TM, int NT, int Q>
+__device__ inline void mlp_compute_group(const MlpGroupRegs<TM, NT>& R, uint2 swp, float (&facc)[NT][TM][4], int lane) {
+  I8Pair a[NT];
+  float sw[NT][4];
+  // With two token tiles the int32 -> fp32 conversion is folded away (the seeded accumulator of gemm_stream.hpp)
+  constexpr bool kMagic = TM >= 2;
+  constexpr int kMagicBits = 0x4B400000;              // 12582912.0f
+  float swc[NT][4];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    a[j] = unpack_i8(R.w[j]);
+    const uint2 sq = pair_scales(NT) ? pair_scales_of<NT, Q>(swp, j, lane) : R.sw[j];
+    // both int8 operands carry a factor 16: fold 2^-8 into the weight scale (exact)
+    sw[j][0] = half_bits_to_float((uint16_t)(sq.x & 0xFFFF)) * 0.00390625f;
+    sw[j][1] = half_bits_to_float((uint16_t)(sq.x >> 16)) * 0.00390625f;
+    sw[j][2] = half_bits_to_float((uint16_t)(sq.y & 0xFFFF)) * 0.00390625f;
+    sw[j][3] = half_bits_to_float((uint16_t)(sq.y >> 16)) * 0.00390625f;
+    if (kMagic) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) swc[j][r] = sw[j][r] * -12582912.0f;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    const I8Pair b = unpack_i8(R.a[t]);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      v4i acc = kMagic ? v4i{kMagicBits, kMagicBits, kMagicBits, kMagicBits} : v4i{0, 0, 0, 0};
+      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[j].lo, b.lo, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[j].hi, b.hi, acc, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (kMagic) {
+          const int bits = acc[r];                    // (a copy: bit_cast of a vector element lvalue reads element 0)
+          facc[j][t][r] = __builtin_fmaf(__builtin_fmaf(__builtin_bit_cast(float, bits), sw[j][r], swc[j][r]),
+                                         R.sa[t], facc[j][t][r]);
+        } else {
+          facc[j][t][r] += (float)acc[r] * (R.sa[t] * sw[j][r]);
+        }
+      }
+    }
+  }
+}
+
+// The loop for one block of NT tiles over groups 0 .. G-1.
+template <int TM, int NT>
+__device__ __forceinline__ void mlp_stream(const StreamArgs& p, const MlpRsrc& rs, int T0, int nt_valid, int wave, int lane,
                                            float (&facc)[NT][TM][4], const uint8_t* wlds) {
   constexpr int W = kStreamWaves;
   const int n_g = max(0, (p.G - wave + W - 1) / W);
   if (n_g <= 0 || nt_valid <= 0) return;
   auto grp = [&](int it) { return wave + it * W; };
-  GroupRegs<true, TM, NT> A, B;
+  MlpGroupRegs<TM, NT> A, B;
   uint2 sw_cur = {0u, 0u}, sw_nxt = {0u, 0u};
   if (pair_scales(NT)) sw_cur = load_pair_scales<NT>(rs, p, grp(0), grp(1), true, 1 < n_g, T0, nt_valid, lane);
-  load_group<true, TM, NT>(A, rs, p, grp(0), true, T0, nt_valid, lane, wlds);
+  mlp_load_group<TM, NT>(A, rs, p, grp(0), true, T0, nt_valid, lane, wlds);
   for (int it = 0; it < n_g; it += 2) {
     if (pair_scales(NT)) sw_nxt = load_pair_scales<NT>(rs, p, grp(it + 2), grp(it + 3), it + 2 < n_g, it + 3 < n_g, T0, nt_valid, lane);
-    load_group<true, TM, NT>(B, rs, p, grp(it + 1), it + 1 < n_g, T0, nt_valid, lane, wlds);
+    mlp_load_group<TM, NT>(B, rs, p, grp(it + 1), it + 1 < n_g, T0, nt_valid, lane, wlds);
     __builtin_amdgcn_sched_barrier(0);
-    compute_group<true, TM, NT, 0>(A, sw_cur, facc, nullptr, lane);
+    mlp_compute_group<TM, NT, 0>(A, sw_cur, facc, lane);
     __builtin_amdgcn_sched_barrier(0);
-    load_group<true, TM, NT>(A, rs, p, grp(it + 2), it + 2 < n_g, T0, nt_valid, lane, wlds);
+    mlp_load_group<TM, NT>(A, rs, p, grp(it + 2), it + 2 < n_g, T0, nt_valid, lane, wlds);
     __builtin_amdgcn_sched_barrier(0);
-    if (it + 1 < n_g) compute_group<true, TM, NT, 1>(B, sw_cur, facc, nullptr, lane);
+    if (it + 1 < n_g) mlp_compute_group<TM, NT, 1>(B, sw_cur, facc, lane);
     __builtin_amdgcn_sched_barrier(0);
     sw_cur = sw_nxt;
   }
@@ -157,7 +272,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 1) void mlp_draft_kernel(MlpArgs
   {
     StreamArgs a{};
     a.M = M; a.N = p.N1; a.K = p.K1; a.G = p.K1 / kGroup; a.S = 1;
-    StreamRsrc rs;
+    MlpRsrc rs;
     rs.codes = make_rsrc(p.codes1, (uint32_t)((size_t)p.N1 * p.K1 / 2));
     rs.scales = make_rsrc(p.scales1T, (uint32_t)((size_t)p.N1 * a.G * 2));
     rs.act = make_rsrc(p.qa_h, (uint32_t)((size_t)M * p.K1 / 2));
@@ -269,7 +384,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 1) void mlp_draft_kernel(MlpArgs
   {
     StreamArgs a{};
     a.M = M; a.N = p.N2; a.K = p.K2; a.G = G2; a.S = 1;
-    StreamRsrc rs;
+    MlpRsrc rs;
     rs.codes = make_rsrc(p.codes2, (uint32_t)((size_t)p.N2 * p.K2 / 2));
     rs.scales = make_rsrc(p.scales2T, (uint32_t)((size_t)p.N2 * G2 * 2));
     rs.act = make_rsrc(p.qa_i, (uint32_t)((size_t)M * p.K2 / 2));
