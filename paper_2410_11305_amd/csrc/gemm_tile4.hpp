@@ -132,8 +132,6 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
   const int m0 = tc.mblk * BM;
   const int mw0 = wm * (PM * 32);
 
-  const rsrc_t r_codes = make_rsrc(p.codes, (uint32_t)((size_t)p.N * p.K / 2));
-  const rsrc_t r_scales = make_rsrc(p.scalesT, (uint32_t)((size_t)p.N * G * 2));
   const rsrc_t r_act = make_rsrc(p.act, (uint32_t)((size_t)p.M * p.K / (WIDE ? 1 : 2)));
   const rsrc_t r_sa = make_rsrc(p.sa, (uint32_t)((size_t)p.M * G * 4));
   // Work that does not exist gets bit 31 in its load offset (out of range: zeros, no
@@ -195,13 +193,11 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
   const int drow = lane >> 3;
   const uint32_t xw_voff = (uint32_t)(m0 + 8 * wave + drow) * (uint32_t)p.K + (uint32_t)((((lane & 7) ^ drow ^ (wave & 1))) << 4);
   auto dma_x = [&](int q, uint8_t* stage) {
-    const uint32_t gone = past_end(q);
-    const uint32_t gbase = (uint32_t)(g0 + q) * 128u;
+    const int g = g0 + q;
+    const uint32_t bytes = g < g1 ? (uint32_t)((size_t)p.M * p.K) : 0u;
 #pragma unroll
-    for (int u = 0; u < UD; ++u) {
-      const uint32_t off = (xw_voff + gbase + (uint32_t)(u * 8 * kWaves) * (uint32_t)p.K) | gone;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r_act, (lds_ptr_t)(stage + (wave + u * kWaves) * 1024), 16, off, 0, 0, 0);
-    }
+    for (int u = 0; u < UD; ++u)
+      buf_load16_lds(p.act, bytes, stage + (wave + u * kWaves) * 1024, xw_voff + (uint32_t)(u * 8 * kWaves) * (uint32_t)p.K, (uint32_t)g * 128u);
   };
   auto store_sa = [&](int stage) {
     if (tid < BM) scale_ptr(stage)[tid] = sas[stage] * 0.00390625f;
@@ -212,17 +208,25 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
   uint4 wlo[NW][PN], whi[NW][PN];
   uint32_t sq[NW][PN];
   const int n_lane = n0 + l32;          // this lane's weight row in pair 0
-  const uint32_t w_voff = (uint32_t)(n_lane >> 4) * G * 1024u + (uint32_t)((n_lane & 15) + 16 * h) * 16u;
+  // (a lane's part of an address is fixed, what moves with the group is a scalar offset, work past the
+  // end goes through an empty buffer: 9.9 instead of 10.6 vector instructions per MFMA as compiled.
+  // 57344 x 8192 at 128 tokens 78.0 -> 76.4 us, 22016 x 4096 at 256: 36.6 -> 35.7; bit 31 of an
+  // offset: a row past N)
+  uint32_t w_voff[PN], s_voff[PN];
+#pragma unroll
+  for (int j = 0; j < PN; ++j) {
+    const uint32_t none = n_lane + 32 * j >= p.N ? kOutOfRange : 0u;
+    w_voff[j] = ((uint32_t)((n_lane >> 4) + 2 * j) * G * 1024u + (uint32_t)((n_lane & 15) + 16 * h) * 16u) | none;
+    s_voff[j] = (uint32_t)(n_lane + 32 * j) * 2u | none;
+  }
   auto load_w = [&](int d, int q) {
-    const uint32_t gone = past_end(q);
     const int g = g0 + q;
+    const uint32_t cbytes = g < g1 ? (uint32_t)((size_t)p.N * p.K / 2) : 0u, sbytes = g < g1 ? (uint32_t)((size_t)p.N * G * 2) : 0u;
 #pragma unroll
     for (int j = 0; j < PN; ++j) {
-      const uint32_t skip = gone | ((uint32_t)((p.N - 1 - (n_lane + 32 * j)) >> 31) << 31);
-      const uint32_t wo = w_voff + (uint32_t)(2 * j) * G * 1024u + (uint32_t)g * 1024u;
-      wlo[d][j] = buf_load16(r_codes, wo | skip);
-      whi[d][j] = buf_load16(r_codes, (wo + 512u) | skip);
-      sq[d][j] = buf_load_u16(r_scales, (((uint32_t)g * (uint32_t)p.N + (uint32_t)(n_lane + 32 * j)) * 2u) | skip);
+      wlo[d][j] = buf_load16(p.codes, cbytes, w_voff[j], (uint32_t)g * 1024u);
+      whi[d][j] = buf_load16(p.codes, cbytes, w_voff[j] + 512u, (uint32_t)g * 1024u);
+      sq[d][j] = buf_load_u16(p.scalesT, sbytes, s_voff[j], (uint32_t)g * (uint32_t)p.N * 2u);
     }
   };
 
@@ -305,13 +309,18 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
   // request, and with the rest of group q to land before anyone waits for them), published
   // by the barrier that ends group q, first read at the end of group q + 1 (the operands
   // of a group's first token tile are fetched under the last tile of the group before).
-  auto group_body = [&](auto slot_c, int q) __attribute__((always_inline)) {
+  // LEFT_OVER: one of the last groups, behind the loop.  Whatever comes after it has been requested
+  // before; it refills nothing, so nothing is younger than those requests and the wait is for everything.
+  auto group_body = [&](auto slot_c, int q, auto left_over_c) __attribute__((always_inline)) {
     constexpr int SLOT = decltype(slot_c)::value;
+    constexpr bool LEFT_OVER = decltype(left_over_c)::value;
     const uint8_t* xl = stage_ptr(SLOT);
     const uint8_t* xl_next = stage_ptr((SLOT + 1) % NW);
     const float* sl = scale_ptr(SLOT);
     const float* sl_next = scale_ptr((SLOT + 1) % NW);
-    if constexpr (WIDE) {
+    if constexpr (LEFT_OVER) {
+      // (the activations of group q + 1, the last there can be, are in their stage or on the way)
+    } else if constexpr (WIDE) {
       // group q + 2 straight into its stage (last read in group q - 1); it has the whole of
       // this group to land, and the wait in front of this group's closing barrier counts the
       // loads issued after it: the scale triple (slot 0 only) and the ring refill
@@ -334,9 +343,14 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
       const I8Pair lo = unpack_i8(wlo[SLOT][j]), hi = unpack_i8(whi[SLOT][j]);
       b[j][0] = lo.lo; b[j][1] = lo.hi; b[j][2] = hi.lo; b[j][3] = hi.hi;
       swf[j] = half_bits_to_float((uint16_t)sq[SLOT][j]);
+      // (kept as a binary32 register: the compiler would fold the conversion into every
+      // multiply-add of the rescaling, and v_fma_mix_f32 takes 4.5 cycles of a SIMD where two
+      // wavefronts' v_fma_f32 take 2.75 each.  10240 x 8192 at 128 tokens 26.7 -> 26.0 us,
+      // 12288 x 4096 at 96: 19.3 -> 17.7)
+      asm volatile("" : "+v"(swf[j]));
       swc[j] = swf[j] * -12582912.0f;            // exact: 11 significant bits times 1.5 * 2^23
     }
-    load_w(SLOT, q + NW);                        // the slot's contents are in b[] and swf[] now
+    if constexpr (!LEFT_OVER) load_w(SLOT, q + NW);   // the slot's contents are in b[] and swf[] now
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int idx = 0; idx < kTiles; ++idx) {
@@ -370,21 +384,22 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
     read_scales(sl_next, 0, 0);                  // S[0] was token tile PM-2's: released
     // (loads complete in order; no store may sit between them, so the kernel must compile
     // without register spills)
-    if constexpr (WIDE) __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * PN + (SLOT == 0 ? 1 : 0)));
+    if constexpr (WIDE) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LEFT_OVER ? 0 : 3 * PN + (SLOT == 0 ? 1 : 0)));
     __syncthreads();
   };
 
-  // Three groups per trip (the ring slots are named statically), each a straight line;
-  // the loop is left between groups (every block inside keeps a single predecessor, so
-  // the compiler's wait-count bookkeeping stays exact).  Requests past the end of the
-  // slice are out of range: zeros, no traffic.
-  for (int q = 0; q < ng; q += NW) {
-    group_body(std::integral_constant<int, 0>{}, q);
-    if (q + 1 >= ng) break;
-    group_body(std::integral_constant<int, 1>{}, q + 1);
-    if (q + 2 >= ng) break;
-    group_body(std::integral_constant<int, 2>{}, q + 2);
+  // Three groups per trip (the ring slots are named statically), then the one or two left over in
+  // copies of their own: no exit inside the loop, nothing requested past the end by them.
+  std::false_type in_loop;
+  std::true_type left_over;
+  int q = 0;
+  for (; q + NW <= ng; q += NW) {
+    group_body(std::integral_constant<int, 0>{}, q, in_loop);
+    group_body(std::integral_constant<int, 1>{}, q + 1, in_loop);
+    group_body(std::integral_constant<int, 2>{}, q + 2, in_loop);
   }
+  if (q < ng) group_body(std::integral_constant<int, 0>{}, q, left_over);
+  if (q + 1 < ng) group_body(std::integral_constant<int, 1>{}, q + 1, left_over);
 #pragma unroll
   for (int part = 0; part < 4; ++part) rescale_quarter(P[(kTiles - 1) & 1], pend_sw, pend_swc, pend_S, acc[PN - 1][PM - 1], part);
 
