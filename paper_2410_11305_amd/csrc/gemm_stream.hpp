@@ -52,6 +52,8 @@ struct StreamArgs {
   unsigned* tickets;         // S > 1: one arrival counter per tile block, zero on entry and on exit
   int M, N, K, G;
   int S;                     // K-slices: tile block b / S, slice b % S
+  int ms;                    // token-row blocks (1 with K-slices)
+  uint32_t ms_rcp;           // 2^32 / ms, rounded up
 };
 
 constexpr int kStreamWaves = 8;
@@ -92,19 +94,22 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kb = lane >> 4;
-  // workgroups go to the eight XCDs in turn: each XCD gets a run of adjacent tile blocks
-  const int nblk = gridDim.x, xcd = blockIdx.x & 7, qx = nblk >> 3, rx = nblk & 7;
+  // Workgroups go to the eight XCDs in turn: each XCD gets a run of adjacent tile blocks, and of each of
+  // them all token-row blocks one after the other, so that they find its weights in that XCD's L2.
+  const int total = gridDim.x, xcd = blockIdx.x & 7, qx = total >> 3, rx = total & 7;
   const int bx = xcd * qx + (xcd < rx ? xcd : rx) + (blockIdx.x >> 3);
   const int G = p.G;
-  int tb = bx, slice = 0, s0 = 0, s1 = G;
+  int tb = bx, slice = 0, s0 = 0, s1 = G, row_block = 0;
   if (p.S > 1) {
     tb = bx / p.S; slice = bx - tb * p.S;
     s0 = (int)(((long long)slice * G) / p.S); s1 = (int)(((long long)(slice + 1) * G) / p.S);
+  } else if (p.ms > 1) {
+    tb = (int)__umulhi((unsigned)bx, p.ms_rcp);    // bx / ms (exact below 2^28 workgroups), in the scalar unit
+    row_block = bx - tb * p.ms;
   }
   const int T0 = tb * NT;
   const int nt_valid = min(NT, p.N / 16 - T0);
-  // token-row blocks along gridDim.y (only without K-slices)
-  const int m_base = (int)blockIdx.y * (16 * TM);
+  const int m_base = row_block * (16 * TM);
   const int Mloc = p.M - m_base;
   if (Mloc <= 0) return;                           // (the whole workgroup: uniform)
   uint16_t* const yloc = p.y + (size_t)m_base * p.N;
@@ -400,7 +405,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
       }
       if (p.S > 1) {
-        float* f = p.ws + (((size_t)slice * (nblk / p.S) + tb) * (NT * TM) + o) * 256 + ui * 64 + ul * 4;
+        float* f = p.ws + (((size_t)slice * (total / p.S) + tb) * (NT * TM) + o) * 256 + ui * 64 + ul * 4;
         store_shared_f2(f, s.x, s.y);
         store_shared_f2(f + 2, s.z, s.w);
       } else {
@@ -414,7 +419,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
     if (16 * (o % TM) + 4 * (ul >> 2) + ui >= Mloc) continue;
     float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int c = 0; c < p.S; ++c) {            // fixed order: the result does not depend on who came last
-      const float* f = p.ws + (((size_t)c * (nblk / p.S) + tb) * (NT * TM) + o) * 256 + ui * 64 + ul * 4;
+      const float* f = p.ws + (((size_t)c * (total / p.S) + tb) * (NT * TM) + o) * 256 + ui * 64 + ul * 4;
       const float2 a = load_shared_f2(f), b = load_shared_f2(f + 2);
       s.x += a.x; s.y += a.y; s.z += b.x; s.w += b.y;
     }

@@ -162,7 +162,7 @@ constexpr int kMaxTickets = (int)(kTicketBytes / 4);
 // "NT,S,MS" override the heuristic (benchmark A/B only).
 struct StreamPlan {
   int nt, S, blocks;
-  int ms;       // token-row blocks (gridDim.y); block y owns rows y*16*tm .. (y+1)*16*tm - 1
+  int ms;       // token-row blocks; block i owns rows i*16*tm .. (i+1)*16*tm - 1
   int tm;       // 16-token tiles per workgroup (the kernel's TM)
 };
 inline int stream_tm(int M) { return M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8; }   // 16-token tiles that cover M rows
@@ -294,7 +294,7 @@ bool use_stream(bool w4a4, int M, int N, int K) {
 // instantiated (a forced plan can name one) is refused: nothing is launched.
 template <bool W4A4, int TM>
 int launch_stream_tm(const StreamArgs& a, const StreamPlan& plan, hipStream_t s) {
-  dim3 grid(plan.blocks * plan.S, plan.ms), block(kStreamWaves * 64);
+  dim3 grid(plan.blocks * plan.S * plan.ms), block(kStreamWaves * 64);
   switch (plan.nt) {
     case 1: hipLaunchKernelGGL((gemm_stream_kernel<W4A4, TM, 1>), grid, block, 0, s, a); return QSPEC_OK;
     case 2: hipLaunchKernelGGL((gemm_stream_kernel<W4A4, TM, 2>), grid, block, 0, s, a); return QSPEC_OK;
@@ -316,6 +316,8 @@ int launch_stream(StreamArgs a, void* workspace, hipStream_t s) {
   const StreamPlan plan = plan_stream(W4A4, a.M, a.N, a.K);
   if ((long long)plan.ms * 16 * plan.tm < a.M) return QSPEC_ERR_UNSUPPORTED;      // the row blocks must cover M
   a.S = plan.S;
+  a.ms = plan.ms;
+  a.ms_rcp = (uint32_t)((0x100000000ull + plan.ms - 1) / plan.ms);
   a.tickets = static_cast<unsigned*>(workspace);
   a.ws = plan.S > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kTicketBytes) : nullptr;
   switch (plan.tm) {
