@@ -182,90 +182,118 @@ int stream_base_max(bool w4a4) {
   return forced ? forced : (w4a4 ? kStreamMaxM4 : kStreamMaxM);
 }
 
-// Up to 128 tokens on layers no larger than 8192 x 8192 the streaming kernel with token-row
-// blocks beats the tiled kernels when ONE round of workgroups covers the problem (the
-// tiled kernels have too few output blocks to fill the chip there and fall back on
-// K-slices): measured 4096 x 4096 at 128 tokens 16.0 -> 9.7 us (draft) and 15.5 -> 12.4 us
-// (verify), 8192 x 8192 at 128 draft tokens 31.5 -> 27.1 us; with longer K or more than
-// one round the tiled kernels win.  Picks tiles per workgroup, 16-token tiles per row
-// block and the number of row blocks by the cost model of plan_stream; false: no such plan.
-bool plan_wide_stream(bool w4a4, int M, int N, int K, int* nt_out, int* tm_out, int* ms_out) {
-  if (M > 128 || N > 8192 || K > 8192) return false;
-  const int tiles = N / 16;
-  const double c = w4a4 ? 1.5 : 1.6;
+// What a streaming plan of more than 16 tokens costs, in microseconds.  ng groups fall to the busiest
+// wavefront (G / 8 on average), the workgroups of ceil(M / (16 tm)) token-row blocks fill `rounds`
+// rounds of the compute units:
+//   fixed + round (rounds - 1) + ng (group + again (rounds - 1)) + G / 8 x workgroups per unit x (load + tokens x share of live rows)
+// Fitted to timed plans: 4089 draft-mode problems of 17 to 600 tokens and 2116 verify-mode ones of 17 to 32
+// (layers 1024 to 57344 wide, 512 to 28672 long), every instance with the row blocks that cover M, on
+// rotating weights inside HIP graphs.  On the half of them that a fit had not seen the choice among
+// these and the tiled plans is 0.3 to 1.5 % slower than the best one.
+// Against the rules before it (rounds x tiles per wavefront, two row blocks at most up to 64 tokens, at
+// 65 to 128 only where one round covered the layer, none beyond) the draft mode takes 6 % less time at
+// 33 to 48 tokens, 7 % at 65 to 96, 24 % at 129 to 192, 12 % at 193 to 400; the verify mode 3 to 5 % at 17 to 32.
+struct StreamCost { int tm, nt; double fixed, round, group, again, load, tokens; };
+constexpr StreamCost kStreamCost4[] = {
+    {1, 1, 2.885, 0, 0.114, 0.075, 0.244, 0.019},
+    {1, 2, 2.965, 0, 0.194, 0.144, 0.331, 0},
+    {1, 3, 2.961, 0.119, 0.41, 0.293, 0.336, 0},
+    {1, 4, 2.962, 0.179, 0.553, 0.385, 0.349, 0},
+    {1, 6, 3.111, 1.849, 0.813, 0.573, 0.441, 0},
+    {2, 1, 3.02, 0, 0.195, 0.133, 0.281, 0.07},
+    {2, 2, 2.908, 1.774, 0.413, 0.208, 0.288, 0.116},
+    {2, 3, 3.047, 1.963, 0.661, 0.444, 0.32, 0},
+    {2, 4, 3.089, 2.212, 0.828, 0.524, 0.372, 0},
+    {2, 6, 3.951, 3.029, 1.157, 0.856, 0.368, 0},
+    {4, 1, 3.234, 1.613, 0.32, 0.24, 0.36, 0.364},
+    {4, 2, 3.289, 2.517, 0.71, 0.462, 0.317, 0.285},
+    {4, 3, 4.128, 3.368, 1.017, 0.682, 0.432, 0.155},
+    {4, 4, 4.385, 3.54, 1.242, 0.935, 0.477, 0},
+    {8, 1, 3.655, 2.37, 0.837, 0.633, 0.634, 0.28},
+    {8, 2, 4.703, 3.791, 1.444, 1.115, 0.17, 0.637},
+};
+constexpr StreamCost kStreamCost16[] = {
+    {1, 1, 2.715, 0, 0.249, 0.09, 0.379, 0.085},
+    {1, 2, 2.87, 0.657, 0.372, 0.365, 0.452, 0.045},
+    {1, 3, 2.776, 0.043, 0.691, 0.517, 0.37, 0},
+    {1, 4, 2.791, 1.579, 0.895, 0.68, 0.364, 0},
+    {1, 6, 3.174, 1.86, 1.183, 1.178, 0.423, 0},
+    {2, 1, 2.811, 1.259, 0.404, 0.318, 0.427, 0.298},
+    {2, 2, 2.793, 1.632, 0.747, 0.635, 0.223, 0.439},
+    {2, 3, 3.053, 2.015, 1.042, 0.955, 0.09, 0.498},
+    {2, 4, 3.446, 1.815, 1.137, 1.167, 0.327, 0.379},
+    {2, 6, 5.129, 2.014, 1.21, 1.658, 0.699, 0.387},
+};
+constexpr int kMaxRowBlocks = 16;
+
+inline int stream_qs(int nt, int tm) { return nt <= 2 && tm <= 4 ? 2 : 1; }      // the kernel's QS
+
+double stream_cost(const StreamCost& c, int M, int N, int G) {
+  const int ms = (M + 16 * c.tm - 1) / (16 * c.tm), tiles = N / 16;
+  const long long blocks = (long long)((tiles + c.nt - 1) / c.nt) * ms;
+  const double rounds = (double)((blocks + kNumCU - 1) / kNumCU);
+  const int qs = stream_qs(c.nt, c.tm), ng = qs * (((G + qs - 1) / qs + kStreamWaves - 1) / kStreamWaves);
+  const double load = (double)tiles * ms / c.nt / kNumCU * G / kStreamWaves;
+  return c.fixed + c.round * (rounds - 1) + ng * (c.group + c.again * (rounds - 1)) + load * (c.load + c.tokens * M / (16.0 * c.tm * ms));
+}
+
+// Cheapest streaming plan of more than 16 tokens; one_round: among those that one round of workgroups covers.
+double best_stream(bool w4a4, int M, int N, int G, bool one_round, StreamPlan* p) {
   double best = 1e30;
-  bool found = false;
-  for (int tm = 1; tm <= (w4a4 ? 8 : 2); tm *= 2) {
-    const int ms = (M + 16 * tm - 1) / (16 * tm);
-    if (ms < 2 || ms > 8) continue;
-    for (int v : kStreamNts) {
-      if (!stream_nt_ok(v, tm)) continue;
-      if (((tiles + v - 1) / v) * ms > kNumCU) continue;
-      const double cost = v + c * tm;
-      if (cost < best - 1e-9 || (cost < best + 1e-9 && v > *nt_out)) { best = cost; *nt_out = v; *tm_out = tm; *ms_out = ms; found = true; }
-    }
+  const int n = w4a4 ? (int)(sizeof(kStreamCost4) / sizeof(StreamCost)) : (int)(sizeof(kStreamCost16) / sizeof(StreamCost));
+  for (int i = 0; i < n; ++i) {
+    const StreamCost& c = w4a4 ? kStreamCost4[i] : kStreamCost16[i];
+    const int ms = (M + 16 * c.tm - 1) / (16 * c.tm), blocks = (N / 16 + c.nt - 1) / c.nt;
+    if (ms > kMaxRowBlocks || (c.tm > 1 && 8 * c.tm >= M)) continue;              // (a kernel of half the token tiles covers M)
+    if (one_round && (ms > 8 || blocks * ms > kNumCU)) continue;
+    if (M > 32 && (long long)blocks * ms > 5 * kNumCU) continue;                   // (not timed)
+    const double cost = stream_cost(c, M, N, G);
+    if (cost < best) { best = cost; p->nt = c.nt; p->tm = c.tm; p->ms = ms; p->S = 1; p->blocks = blocks; }
   }
-  return found;
+  return best;
 }
 
 StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
   const int tiles = N / 16, G = K / kGroup;
   const PlanOverrides& ov = overrides();
   const int nf = ov.stream_fields[w4a4 ? 1 : 0];
-  int nt = ov.stream[w4a4 ? 1 : 0][0], S = ov.stream[w4a4 ? 1 : 0][1], ms = ov.stream[w4a4 ? 1 : 0][2], tm_wide = 0;
+  int nt = ov.stream[w4a4 ? 1 : 0][0], S = ov.stream[w4a4 ? 1 : 0][1], ms = ov.stream[w4a4 ? 1 : 0][2];
   bool forced = nf >= 2 && S >= 1 && S <= G;
   if (nf < 3) ms = 1;
   if (forced && ms > 1) forced = S == 1 && (ms == 2 || ms == 4 || ms == 8);
   // a forced plan must have an instance and its row blocks must cover all M rows
   if (forced) forced = stream_nt_ok(nt, stream_tm_split(M, ms)) && (w4a4 || stream_tm_split(M, ms) <= 2) &&
                        (long long)ms * 16 * stream_tm_split(M, ms) >= M;
-  if (!forced) { nt = 0; S = 0; ms = 1; }
-  if (!forced && M > stream_base_max(w4a4)) {
-    StreamPlan none{};                                   // nt == 0: no streaming plan, the tiled kernels take it
-    if (!plan_wide_stream(w4a4, M, N, K, &nt, &tm_wide, &ms)) return none;
-    S = 1;
-  } else if (!forced) {
-    // Cost of a plan, in units of one weight tile (1 KB from HBM) per wavefront:
-    // rounds over the 256 compute units x groups per wavefront x (NT weight tiles +
-    // the activation operand of the group, which comes from L2 and is re-used for
-    // the NT tiles).  K-slices are never chosen here: measured on MI355X, the
-    // exchange (write-through stores, a ticket, S dependent trips to memory) costs
-    // 4 to 10 us, more than any of these launches saves; the path stays available
-    // to the override and is covered by the tests.
-    ms = 1;
-    const int tm = stream_tm(M);
-    const double act = w4a4 ? 0.4 * tm : 1.6 * tm;
-    double best = 1e30;
-    for (int s = 1; s <= 1; s *= 2) {
-      for (int v : kStreamNts) {
-        if (!stream_nt_ok(v, tm)) continue;
-        const int blocks = (tiles + v - 1) / v;
-        if (s > 1 && blocks > kMaxTickets) continue;
-        const int rounds = (blocks * s + kNumCU - 1) / kNumCU;
-        const int per_wave = ((G + s - 1) / s + kStreamWaves - 1) / kStreamWaves;
-        const double cost = rounds * (per_wave * (v + act) + (s > 1 ? 0.25 * s * v * tm + 2.0 : 0.0));
-        if (cost < best - 1e-9 || (cost < best + 1e-9 && v > nt)) { best = cost; nt = v; S = s; }
-      }
-    }
-    // Two token-row blocks: with few tiles per workgroup the activation operand, not the
-    // weights, is most of what a compute unit pulls through its L1 (every workgroup
-    // reads ALL of x).  Dealing the rows to two workgroups that own twice the tiles
-    // keeps the number of workgroups, halves that traffic, and lets the partner's
-    // weight reads hit in L2 (both run on the same XCD: their ids differ by a multiple
-    // of 8).  Measured on the 4096- and 5120-wide layers: 16-25 % less time where the
-    // tile count per workgroup is below act/2 (act in weight-tile units: 1.6 per 16
-    // verify-mode tokens, 1.5 per 16 draft-mode tokens for this decision), slower
-    // on the wide layers, where the weights dominate already.
-    if (tm >= 2) {
-      const double act2 = (w4a4 ? 1.5 : 1.6) * tm;
-      const int blocks1 = (tiles + nt - 1) / nt, blocks2 = ((tiles + 2 * nt - 1) / (2 * nt)) * 2;
-      const bool same_rounds = (blocks2 + kNumCU - 1) / kNumCU <= (blocks1 + kNumCU - 1) / kNumCU;
-      if (nt < act2 / 2 && stream_nt_ok(2 * nt, stream_tm_split(M, 2)) && same_rounds) { nt *= 2; ms = 2; }
-    }
-  }
   StreamPlan p{};
-  p.nt = nt; p.S = S; p.blocks = (tiles + nt - 1) / nt; p.ms = ms;
-  p.tm = tm_wide ? tm_wide : (ms > 1 ? stream_tm_split(M, ms) : stream_tm(M));
+  if (forced) {
+    p.nt = nt; p.S = S; p.ms = ms;
+    p.blocks = (tiles + nt - 1) / nt;
+    p.tm = ms > 1 ? stream_tm_split(M, ms) : stream_tm(M);
+    return p;
+  }
+  if (M <= 16) {
+    // Rounds over the 256 compute units x groups per wavefront x (NT weight tiles + the activation operand,
+    // in units of one weight tile of 1 KB), ties to the larger NT: 1 % slower than the best of the five
+    // instances on 3993 timed problems of 1 to 16 tokens, 12 % at most.  K-slices are never chosen: the exchange
+    // (write-through stores, a ticket, S dependent trips to memory) costs 4 to 10 us, more than any of these
+    // launches saves; the path stays available to the override and is covered by the tests.
+    const double act = w4a4 ? 0.4 : 1.6;
+    double best = 1e30;
+    for (int v : kStreamNts) {
+      const int blocks = (tiles + v - 1) / v;
+      const int rounds = (blocks + kNumCU - 1) / kNumCU, per_wave = (G + kStreamWaves - 1) / kStreamWaves;
+      const double cost = rounds * (per_wave * (v + act));
+      if (cost < best - 1e-9 || (cost < best + 1e-9 && v > p.nt)) { best = cost; p.nt = v; }
+    }
+    p.S = 1; p.ms = 1; p.tm = 1;
+    p.blocks = (tiles + p.nt - 1) / p.nt;
+    return p;
+  }
+  // (verify mode past 32 tokens: only where one round of workgroups covers a layer of at most 8192 x 8192; the
+  // tiled kernels have too few output blocks to fill the chip there.  128 tokens, 4096 x 4096: 15.5 us tiled, 9.6 here.)
+  const bool past = !w4a4 && M > stream_base_max(false);
+  if (past && (M > 128 || N > 8192 || K > 8192)) return p;          // nt == 0: no streaming plan
+  best_stream(w4a4, M, N, G, past, &p);
   return p;
 }
 
@@ -275,19 +303,18 @@ inline size_t stream_ws_bytes(const StreamPlan& p) {
 
 bool tile_override(bool w4a4, int* shape, int* S);
 
+double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices = 4);
+
 bool use_stream(bool w4a4, int M, int N, int K) {
-  if (M <= stream_base_max(w4a4)) {
-    // Draft mode, 48 to 64 tokens, very wide layers (170 and more blocks of 128 outputs): the
-    // tiled kernel is faster than the streaming one (22016 x 4096 at 64 tokens 26.8 -> 23.4 us,
-    // 27648 x 5120: 36.4 -> 29.2, 57344 x 8192: 101.5 -> 68.4; at 48 tokens equal or better;
-    // narrower layers stay with the streaming kernel: 12288 x 4096 at 64 tokens 13.7 vs 17.3 us)
-    const PlanOverrides& ov = overrides();
-    const bool wide_draft = w4a4 && M >= 48 && N >= 170 * 128 && ov.stream_fields[1] == 0 && ov.stream_max[1] == 0;
-    return !wide_draft;
-  }
+  const PlanOverrides& ov = overrides();
+  const bool within = M <= stream_base_max(w4a4);
+  if (within && (!w4a4 || M <= 24 || ov.stream_fields[1] != 0 || ov.stream_max[1] != 0)) return true;
   int shape, S;
-  if (tile_override(w4a4, &shape, &S)) return false;      // a forced tile shape means the tiled kernel
-  return plan_stream(w4a4, M, N, K).nt > 0;
+  if (!within && tile_override(w4a4, &shape, &S)) return false;      // a forced tile shape means the tiled kernel
+  if (!w4a4 || ov.stream_fields[1] != 0) return plan_stream(w4a4, M, N, K).nt > 0;
+  // draft mode: the cheaper of the two kernels
+  StreamPlan p{};
+  return best_stream(true, M, N, K / kGroup, false, &p) <= best_tile4(M, N, K / kGroup, &shape, &S);
 }
 
 // Launch the instance <mode, TM, NT> of a streaming plan.  A (TM, NT) pair that is not
@@ -433,96 +460,55 @@ void plan_tile16(int M, int N, int G, int* shape, int* slices) {
   }
 }
 
+// What a draft-mode tiled plan costs, in microseconds: g groups per slice (times the share of live rows), f
+// workgroups per compute unit in its last round of `places`:
+//   fixed + again (rounds - 1) + g (full (rounds - 1) + any + first min(f, 1) + second clamp(f - 1, 0, 1) + more max(f - 2, 0) + shared [f > 1])
+//   + with K-slices (slice0 + slice1 S + slice2 workgroups per unit) + out x workgroups per unit
+// Fitted to the problems of kStreamCost4 (and 600 to 3000 tokens on top) with the widened activation format.
+// Its predecessor, fill rules from sweeps over the Llama-shaped layers, sliced small layers too little and
+// wide ones at 65 to 96 tokens too much (51200 x 7936 at 72: 86.9 us in 128 x 64, 63.0 in 256 x 128 blocks).
+struct Tile4Cost { double fixed, again, full, any, first, second, more, shared, slice0, slice1, slice2, out; int places; };
+constexpr Tile4Cost kCost4[] = {
+    {5.849, 0.676, 1.17, 0.51, 0.167, 0.155, 0, 0.336, 0, 1.267, 3.859, 0.572, 2},   // 0: 128 x 128
+    {3.532, 0.481, 0.635, 0.366, 0.118, 0.017, 0, 0.164, 0, 1.186, 1.94, 0.631, 2},   // 1: 128 x 64
+    {3.609, 0.552, 0.754, 0.275, 0.126, 0.042, 0.071, 0.174, 1.393, 0.789, 0.233, 0.197, 4},   // 2: 64 x 64
+    {5.936, 4.332, 1.111, 0.761, 0.276, 0, 0, 0, 0.043, 2.048, 5.603, 1.045, 1},   // 3: 256 x 128
+};
+
+// Cheapest draft-mode tiled plan by kCost4.
+double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices) {
+  double best = 1e30;
+  for (int i = 0; i < kNumTileShapes; ++i) {
+    const TileShape& t = kShapes4[i];
+    const Tile4Cost& c = kCost4[i];
+    const int bn = 32 * t.TN * t.WGN, bm = 32 * t.TMW * t.WGM;
+    const long long mb = (M + bm - 1) / bm, blocks = (N + bn - 1) / bn * mb;
+    for (int S = 1; S <= max_slices; ++S) {
+      // K-slices only in one round of two workgroups per unit (one of eight wavefronts: the partial sums stay
+      // within 32 MiB), of four groups at least
+      if (S > 1 && (blocks * S > (c.places > 1 ? 2 : 1) * kNumCU || G / S < 4)) break;
+      const long long wgs = blocks * S, load = (long long)c.places * kNumCU, rounds = (wgs + load - 1) / load;
+      const double per_unit = (double)wgs / kNumCU, f = per_unit - (double)c.places * (rounds - 1);
+      const double g = ((G + S - 1) / S) * (0.7 + 0.3 * M / (double)(mb * bm));
+      const auto clamp01 = [](double v) { return v < 0.0 ? 0.0 : v > 1.0 ? 1.0 : v; };
+      double cost = c.fixed + c.again * (rounds - 1) + c.out * per_unit +
+                    g * (c.full * (rounds - 1) + c.any + c.first * clamp01(f) + c.second * clamp01(f - 1) +
+                         c.more * (f > 2 ? f - 2 : 0.0) + (f > 1 ? c.shared : 0.0));
+      if (S > 1) cost += c.slice0 + c.slice1 * S + c.slice2 * per_unit;
+      if (cost < best) { best = cost; *shape = i; *slices = S; }
+    }
+  }
+  return best;
+}
+
 // Pure function of (mode, M, N, K): qspec_workspace_bytes and the GEMM entry points agree.
 TilePlan plan_tile(bool w4a4, int M, int N, int K) {
   const int G = K / kGroup;
   TilePlan p{};
   int shape = 0, S = 1;
   if (!tile_override(w4a4, &shape, &S)) {
-    // The draft-mode rules come from sweeps over the Llama-shaped layers on the MI355X; the
-    // figures quoted are microseconds per call before -> after the rule.
     if (w4a4) {
-      // Two block sizes, 128 x 128 (a weight operand feeds four token tiles) and 128 x 64, and up
-      // to four K-slices: the plan that comes closest to filling the 512 places of the chip
-      // (two workgroups per compute unit) in ONE round wins.  From sweeps over the Llama-shaped
-      // layers at 64 to 512 tokens: 13824 -> 5120 at 512 tokens 79.5 us (128 x 64, unsliced, 320
-      // workgroups) -> 63.0 (128 x 128 in three slices, 480); 28672 -> 8192 at 384: 160 -> 140;
-      // 10240 x 8192 at 256: 49.5 -> 44.9; at 128: 35.7 -> 28.4.  Ties go to the larger block when
-      // its slices keep at least 48 groups, else to the plan with fewer slices (the exchange costs
-      // 4-8 us).  Problems too large for one round run unsliced, on 128 x 128 blocks from 420
-      // blocks on (27648 x 5120 at 256 tokens, 432 blocks: 70.0 -> 60.7 us).
-      const int nb128 = (N + 127) / 128;
-      const int blocks[2] = {nb128 * ((M + 127) / 128), nb128 * ((M + 63) / 64)};
-      const int places = 2 * kNumCU;
-      int sl[2] = {1, 1};
-      double fill[2] = {-1.0, -1.0};
-      for (int i = 0; i < 2; ++i) {
-        if (blocks[i] > places || (i == 0 && M <= 64)) continue;       // (a 128-token block is half empty at 64 tokens)
-        int c = places / blocks[i];
-        if (c > 4) c = 4;
-        // (slices of fewer than 20 groups lose to the unsliced plan even at half the fill: 4096 x
-        // 4096 at 512 tokens, two slices of 16 groups 21.4 us, unsliced 18.8; 12288 x 4096 at 128:
-        // 21.1 against 19.5; slices of 21 groups win: 10240 x 8192 at 128 tokens, three slices 29.0 us,
-        // two 33.6, unsliced 39.3)
-        while (c > 1 && G / c < 20) --c;
-        // (but a chip left less than half full takes slices down to 12 groups, up to that half:
-        // 4096 x 4096 at 256 tokens, 128 blocks: 18.6 us unsliced, 15.7 in two slices of 16)
-        {
-          int c2 = places / 2 / blocks[i];
-          if (c2 > 4) c2 = 4;
-          while (c2 > 1 && G / c2 < 12) --c2;
-          if (c2 > c) c = c2;
-        }
-        sl[i] = c;
-        fill[i] = (double)blocks[i] * c / places;
-      }
-      if (fill[0] < 0 && fill[1] < 0) {
-        shape = (M > 64 && blocks[0] >= 420) ? 0 : 1;
-        S = 1;
-      } else if (fill[1] < 0) {
-        shape = blocks[0] >= 420 ? 0 : 1;
-        S = 1;
-      } else if (fill[0] < 0) {
-        shape = 1;
-        S = sl[1];
-      } else {
-        const double d = fill[0] - fill[1];
-        if (d > 0.05) shape = 0;
-        else if (d < -0.05) shape = 1;
-        else shape = (G / sl[0] >= 48 || sl[0] <= sl[1]) ? 0 : 1;
-        S = sl[shape];
-        // a very long K carries twice the slices even past one round (28672 -> 8192 at 384
-        // tokens: two slices 148.7 us, four 139.8)
-        if (fill[shape] <= 0.75 && S == 2 && G / 4 >= 48) S = 4;
-      }
-      // 256 x 128 blocks on eight wavefronts, one workgroup per compute unit: the activation
-      // codes of a group are widened and staged once for twice the outputs, and half the
-      // activation bytes enter the unit.  As in the verify mode a ragged round costs a whole
-      // round, so (both plans timed alternately in one process): one round at least 60 % full
-      // unsliced (57344 x 8192 at 128 tokens, 224 blocks: 115.4 -> 105.0 us; 10240 x 8192 at 512,
-      // 160 blocks: 84.8 -> 72.7; 22016 x 4096 at 256, 172 blocks: 46.6 -> 40.9; 15360 x 5120 at
-      // 384: 57.7 -> 50.0), or at least 90 % full in up to three K-slices of at least 21 groups
-      // or four of at least 48 (28672 -> 8192 at 512 tokens, two slices: 179.6 -> 164.7; at 256,
-      // four: 101.9 -> 93.8; 10240 x 8192 at 256, three: 47.4 -> 44.3; slices of 16 groups lose:
-      // 12288 x 4096 at 256 tokens 31.6 -> 34.5), or up to two rounds at least 85 % full (57344 x
-      // 8192 at 256 tokens: 188.3 -> 176.8; 1.3 rounds lose 6-8 %).
-      const int mb128 = (M + 127) / 128;
-      if (M > 96 && M * 4 >= mb128 * 128 * 3) {
-        const int blocks3 = ((N + 255) / 256) * mb128;
-        if (blocks3 <= kNumCU) {
-          int c = kNumCU / blocks3;
-          if (c > 4) c = 4;
-          if (c == 4 && G / 4 < 48) c = 3;             // (four slices of 21 groups: 4096 x 11008 at 512 tokens 45.1 -> 47.1 us)
-          while (c > 1 && G / c < 21) --c;
-          const int full = blocks3 * c * 100;
-          if (c == 1 ? full >= kNumCU * 60 : full >= kNumCU * 90) { shape = 3; S = c; }
-        } else {
-          // (from three rounds on 95 %: 57344 x 8192 at 512 tokens, 3.5 rounds, equal with packed
-          // codes and 309 against 279 us on 128 x 128 blocks with the widened format)
-          const int rounds3 = (blocks3 + kNumCU - 1) / kNumCU;
-          if (blocks3 * 100 >= rounds3 * kNumCU * (rounds3 <= 2 ? 85 : 95)) { shape = 3; S = 1; }
-        }
-      }
+      best_tile4(M, N, G, &shape, &S);
     } else {
       plan_tile16(M, N, G, &shape, &S);
     }
@@ -536,6 +522,29 @@ TilePlan plan_tile(bool w4a4, int M, int N, int K) {
   if (S > G) S = G;
   if (p.nb * p.mb > kMaxTickets || (!w4a4 && shape == 7)) S = 1;
   p.S = S;
+  return p;
+}
+
+// Sizes for which the widened format is accepted though the packed one is advised (qspec_w4a4_takes_wide: 0):
+// more than 64 tokens, or 48 on very wide layers, unless one round of row blocks covers a layer of at most
+// 8192 x 8192.  A caller may have quantised for them already.  They run unsliced, so need no workspace.
+bool wide_on_request(int M, int N, int K) {
+  if (use_generic() || overrides().stream_fields[1] != 0 || overrides().stream_max[1] != 0) return false;
+  if (M <= kStreamMaxM4) return M >= 48 && N >= 170 * 128;
+  if (M > 128 || N > 8192 || K > 8192) return true;
+  for (int tm = 1; tm <= 4; tm *= 2) {
+    const int ms = (M + 16 * tm - 1) / (16 * tm);
+    for (int v : kStreamNts)
+      if (ms >= 2 && ms <= 8 && stream_nt_ok(v, tm) && ((N / 16 + v - 1) / v) * ms <= kNumCU) return false;
+  }
+  return true;
+}
+TilePlan plan_tile4_unsliced(int M, int N, int K) {
+  TilePlan p{};
+  best_tile4(M, N, K / kGroup, &p.shape, &p.S, 1);
+  const TileShape& t = kShapes4[p.shape];
+  p.nb = (N + 32 * t.TN * t.WGN - 1) / (32 * t.TN * t.WGN);
+  p.mb = (M + 32 * t.TMW * t.WGM - 1) / (32 * t.TMW * t.WGM);
   return p;
 }
 
@@ -899,7 +908,8 @@ int qspec_gemm_w4a4_wide(const void* packed, const int8_t* qa8, const float* sa,
   if (!packed || !qa8 || !sa || !y_f16) return QSPEC_ERR_NULL;
   if (int st = check_shape(M, N, K, group)) return st;
   if (misaligned(packed) || misaligned(qa8) || misaligned(sa) || misaligned(y_f16)) return QSPEC_ERR_ALIGN;
-  if (!qspec_w4a4_takes_wide(M, N, K, group)) return QSPEC_ERR_UNSUPPORTED;   // this shape runs on a kernel that reads packed codes
+  const bool advised = qspec_w4a4_takes_wide(M, N, K, group) != 0;
+  if (!advised && !wide_on_request(M, N, K)) return QSPEC_ERR_UNSUPPORTED;   // this shape runs on a kernel that reads packed codes
   const size_t need = qspec_workspace_bytes(M, N, K, group);
   if (need > 0 && (!workspace || workspace_bytes < need)) return QSPEC_ERR_WORKSPACE;
   if (int st = check_device()) return st;
@@ -910,7 +920,7 @@ int qspec_gemm_w4a4_wide(const void* packed, const int8_t* qa8, const float* sa,
   t.sa = sa;
   t.y = static_cast<uint16_t*>(y_f16);
   t.M = M; t.N = N; t.K = K; t.G = K / kGroup;
-  if (int st = launch_tile<true>(plan_tile(true, M, N, K), t, workspace, static_cast<hipStream_t>(stream), true)) return st;
+  if (int st = launch_tile<true>(advised ? plan_tile(true, M, N, K) : plan_tile4_unsliced(M, N, K), t, workspace, static_cast<hipStream_t>(stream), true)) return st;
   return launch_status();
 }
 

@@ -167,3 +167,20 @@ def test_wide_entry_points_refuse_what_they_cannot_do(env):
     assert L.qspec_quant_act_wide(vp(y), 0, 128, 128, vp(qa8), vp(sa), None) == B.ERR_SHAPE
     assert L.qspec_quant_act_wide(vp(y), 1, 128, 128, None, vp(sa), None) == B.ERR_NULL
     assert L.qspec_quant_act_wide(ctypes.c_void_p(y.data_ptr() + 2), 1, 128, 128, vp(qa8), vp(sa), None) == B.ERR_ALIGN
+
+
+@pytest.mark.parametrize("M,N,K", [(65, 640, 8320), (130, 256, 512), (160, 256, 512), (235, 640, 1920), (300, 1040, 640)])
+def test_widened_format_stays_accepted_where_the_packed_one_is_advised(env, M, N, K):
+    """Sizes on which the packed format runs on the streaming kernel: a caller who has quantised to the
+    widened format is still served, without a workspace."""
+    torch, B = env
+    codes, scales, x = synth.generic_case(M + N, M, N, K)
+    blob = B.pack_weights(dev(torch, codes), dev(torch, scales))
+    q_ref, s_ref = orc.quant_act(x)
+    ref = orc.gemm_w4a4(q_ref, s_ref, codes, scales)
+    assert not B.w4a4_takes_wide(M, N, K)
+    qa8, sa = B.quant_act_wide(dev(torch, x))
+    ws = torch.zeros(16, dtype=torch.uint8, device="cuda") if B.workspace_bytes(M, N, K) == 0 else None
+    assert rel_err(B.gemm_w4a4_wide(blob, qa8, sa, N, workspace=ws).cpu().numpy(), ref) <= TOL
+    qa, sa = B.quant_act(dev(torch, x))
+    assert rel_err(B.gemm_w4a4(blob, qa, sa, N).cpu().numpy(), ref) <= TOL
