@@ -139,8 +139,16 @@ def _dev(t: torch.Tensor, dtype, name: str) -> int:
     return t.data_ptr()
 
 
+# The current stream's handle without building a torch.cuda.Stream object (1.3 us of the 8 that an
+# eager call used to cost the host; the two functions are what torch.cuda.current_stream() itself asks).
+_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _check(status: int, where: str) -> None:
@@ -156,8 +164,8 @@ def alloc_workspace(nbytes: int) -> torch.Tensor:
 
 
 def _workspace(M, N, K, group, workspace):
-    need = workspace_bytes(M, N, K, group)
-    if workspace is None:
+    if workspace is None:                 # (one that is given is held against the need by the entry point itself)
+        need = workspace_bytes(M, N, K, group)
         if need == 0:
             return None, 0
         # convenience for tests: hot loops pass a workspace from alloc_workspace instead
