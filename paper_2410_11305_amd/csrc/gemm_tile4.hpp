@@ -1,4 +1,5 @@
-// Tiled draft-mode (W4A4) kernel for M > 64 on v_mfma_i32_32x32x32_i8 (paper
+// Tiled draft-mode (W4A4) kernel on v_mfma_i32_32x32x32_i8, from 25 tokens where its plan
+// is the cheaper one, always where the streaming kernel's row blocks end (paper
 // Sec. 1 item (2): both operands stay 4-bit integers on the low-precision matrix
 // units; Sec. 4.1: groups of 128).
 //

@@ -174,8 +174,8 @@ inline bool stream_nt_ok(int nt, int tm) {
 // tiles per workgroup when the rows are dealt to ms blocks: ceil(M / ms) rows, in whole tiles
 inline int stream_tm_split(int M, int ms) { return stream_tm(16 * (((M + ms - 1) / ms + 15) / 16)); }
 
-// Largest M the streaming kernels take without token-row blocks: 32 verify-mode tokens, 64
-// draft-mode tokens (a draft-mode activation operand is a quarter of a verify-mode one).
+// Largest M that is the streaming kernels' without a look at the tiled ones' shapes: 32 verify-mode tokens,
+// 64 draft-mode tokens where the tiled kernel has no cheaper plan (use_stream).
 // The QSPEC_STREAM_MAX_* overrides replace the bound (benchmark A/B only).
 int stream_base_max(bool w4a4) {
   const int forced = overrides().stream_max[w4a4 ? 1 : 0];
