@@ -330,10 +330,12 @@ int qspec_kv_overwrite(const void* kv_verify_f16, const int32_t* n_accept, const
 /*
  * Debug entry (benchmark A/B and tests): force the kernel plan the GEMM entry points
  * and qspec_workspace_bytes use, instead of the library's own choice.  `name` is one of
- *   "QSPEC_KERNEL"            value "generic": untiled reference kernels for M > 32
+ *   "QSPEC_KERNEL"            value "generic": untiled reference kernels for M > 32, in both modes
+ *                             and before any other override (qspec_gemm_w4a4_wide: refused)
  *   "QSPEC_STREAM_W4A4",  "QSPEC_STREAM_W4A16"   value "NT,S" or "NT,S,MS": tiles per
  *                             workgroup, K-slices, token-row blocks of the streaming kernels
- *   "QSPEC_STREAM_MAX_W4A4"   largest M the draft-mode streaming kernel takes (32..128)
+ *   "QSPEC_STREAM_MAX_W4A4"   32..128: the draft-mode streaming kernel takes every M up to
+ *                             this one and none above
  *   "QSPEC_TILE_W4A4",    "QSPEC_TILE_W4A16"     value "shape,S": workgroup shape, K-slices
  *   "QSPEC_MLP_SPIN"          polls before a workgroup of qspec_mlp_draft gives up waiting
  * `value` NULL (or unparsable) clears that override; both are host strings.  The same

@@ -91,9 +91,9 @@ constexpr int kNumCU = 256;
 // Plan overrides (benchmark A/B and tests only).  They are parsed ONCE: from the
 // environment at the first use, and afterwards only through qspec_debug_set_plan.  The
 // launch path reads plain integers; no entry point calls getenv.
-//   QSPEC_KERNEL=generic            route M > 32 to the untiled reference kernels
+//   QSPEC_KERNEL=generic            route M > 32 to the untiled reference kernels, whatever else is set
 //   QSPEC_STREAM_W4A4 / _W4A16      "NT,S" or "NT,S,MS": tiles per workgroup, K-slices, token-row blocks
-//   QSPEC_STREAM_MAX_W4A4 / _W4A16  largest M of the streaming kernels without token-row blocks
+//   QSPEC_STREAM_MAX_W4A4 / _W4A16  the streaming kernels take every M up to this one and none above
 //   QSPEC_TILE_W4A4 / _W4A16        "shape,S": workgroup shape index, K-slices
 struct PlanOverrides {
   bool generic = false;
@@ -176,11 +176,7 @@ inline int stream_tm_split(int M, int ms) { return stream_tm(16 * (((M + ms - 1)
 
 // Largest M that is the streaming kernels' without a look at the tiled ones' shapes: 32 verify-mode tokens,
 // 64 draft-mode tokens where the tiled kernel has no cheaper plan (use_stream).
-// The QSPEC_STREAM_MAX_* overrides replace the bound (benchmark A/B only).
-int stream_base_max(bool w4a4) {
-  const int forced = overrides().stream_max[w4a4 ? 1 : 0];
-  return forced ? forced : (w4a4 ? kStreamMaxM4 : kStreamMaxM);
-}
+int stream_base_max(bool w4a4) { return w4a4 ? kStreamMaxM4 : kStreamMaxM; }
 
 // What a streaming plan of more than 16 tokens costs, in microseconds.  ng groups fall to the busiest
 // wavefront (G / 8 on average), the workgroups of ceil(M / (16 tm)) token-row blocks fill `rounds`
@@ -246,7 +242,7 @@ double best_stream(bool w4a4, int M, int N, int G, bool one_round, StreamPlan* p
     const int ms = (M + 16 * c.tm - 1) / (16 * c.tm), blocks = (N / 16 + c.nt - 1) / c.nt;
     if (ms > kMaxRowBlocks || (c.tm > 1 && 8 * c.tm >= M)) continue;              // (a kernel of half the token tiles covers M)
     if (one_round && (ms > 8 || blocks * ms > kNumCU)) continue;
-    if (M > 32 && (long long)blocks * ms > 5 * kNumCU) continue;                   // (not timed)
+    if (M > 32 && !overrides().stream_max[w4a4] && (long long)blocks * ms > 5 * kNumCU) continue;   // (not timed)
     const double cost = stream_cost(c, M, N, G);
     if (cost < best) { best = cost; p->nt = c.nt; p->tm = c.tm; p->ms = ms; p->S = 1; p->blocks = blocks; }
   }
@@ -307,8 +303,10 @@ double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices =
 
 bool use_stream(bool w4a4, int M, int N, int K) {
   const PlanOverrides& ov = overrides();
+  if (ov.generic && M > kStreamMaxM) return false;
+  if (ov.stream_max[w4a4]) return M <= ov.stream_max[w4a4];
   const bool within = M <= stream_base_max(w4a4);
-  if (within && (!w4a4 || M <= 24 || ov.stream_fields[1] != 0 || ov.stream_max[1] != 0)) return true;
+  if (within && (!w4a4 || M <= 24 || ov.stream_fields[1] != 0 || ov.generic)) return true;
   int shape, S;
   if (!within && tile_override(w4a4, &shape, &S)) return false;      // a forced tile shape means the tiled kernel
   if (!w4a4 || ov.stream_fields[1] != 0) return plan_stream(w4a4, M, N, K).nt > 0;

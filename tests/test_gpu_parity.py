@@ -514,3 +514,17 @@ def test_random_shapes_take_every_plan_and_match(env):
     for k in sorted(seen):
         print(f"  {seen[k]:4d}  {k}", flush=True)
     assert len(seen) >= 12            # the sample reaches a broad set of instances
+
+
+@pytest.mark.parametrize("M", [33, 64, 150, 200])
+def test_untiled_reference_kernels(env, plan, M):
+    """QSPEC_KERNEL=generic: both modes on the kernels it names, at token counts that the streaming kernels take otherwise."""
+    torch, B = env
+    N, K = 304, 896
+    plan("QSPEC_KERNEL", "generic")
+    codes, scales, x = synth.generic_case(950 + M, M, N, K)
+    blob = B.pack_weights(dev(torch, codes), dev(torch, scales))
+    qa, sa, q_ref, s_ref = _check_quant(torch, B, x)
+    assert B.describe_kernel(True, M, N, K).startswith("gemm_w4a4_generic<") and B.describe_kernel(False, M, N, K).startswith("gemm_w4a16_generic<")
+    assert rel_err(B.gemm_w4a4(blob, qa, sa, N).cpu().numpy(), orc.gemm_w4a4(q_ref, s_ref, codes, scales)) <= TOL
+    assert rel_err(B.gemm_w4a16(blob, dev(torch, x), N).cpu().numpy(), orc.gemm_w4a16(x, codes, scales)) <= TOL

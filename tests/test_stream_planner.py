@@ -51,3 +51,24 @@ def test_draft_partial_sums_fit_the_built_in_scratch(plan, M, N, K):
     plan("QSPEC_TILE_W4A16", "0,1")
     if M * K * 2 < 2 ** 31:
         assert B.workspace_bytes(M, N, K) <= (32 << 20) + 16384
+
+
+@pytest.mark.parametrize("M", [33, 48, 64, 65, 100, 128, 200, 300, 600, 2000])
+@pytest.mark.parametrize("N,K", [(400, 1408), (1024, 1024), (4096, 4096), (22016, 4096)])
+def test_generic_override_leaves_nothing_above_32_tokens_to_the_other_kernels(plan, M, N, K):
+    plan("QSPEC_KERNEL", "generic")
+    for draft in (True, False):
+        assert re.match(r"gemm_w4a(4|16)_generic<", B.describe_kernel(draft, M, N, K))
+    assert not B.w4a4_takes_wide(M, N, K) and B.workspace_bytes(M, N, K) == 0
+    assert B.describe_kernel(True, 32, N, K).startswith("gemm_stream") and B.describe_kernel(False, 32, N, K).startswith("gemm_stream")
+
+
+@pytest.mark.parametrize("bound", [32, 64, 100, 128])
+@pytest.mark.parametrize("N,K", [(400, 1408), (1024, 1024), (4096, 4096), (22016, 4096), (57344, 8192)])
+def test_stream_max_override_is_a_bound_from_both_sides(plan, bound, N, K):
+    plan("QSPEC_STREAM_MAX_W4A4", str(bound))
+    for M in (17, 30, bound - 1, bound):
+        m = re.match(r"gemm_stream_kernel<true, (\d+), (\d+)>", B.describe_kernel(True, M, N, K))
+        assert m and int(m.group(1)) > 0 and int(m.group(2)) > 0       # (0: a plan that the launch refuses)
+    for M in (bound + 1, 300, 1500):
+        assert B.describe_kernel(True, M, N, K).startswith("gemm_tile4w_kernel")
