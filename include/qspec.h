@@ -58,7 +58,7 @@ typedef enum {
   QSPEC_ERR_NULL = 1,        /* a required pointer is NULL                    */
   QSPEC_ERR_SHAPE = 2,       /* M, N, K or group outside what is supported    */
   QSPEC_ERR_ALIGN = 3,       /* a pointer is not 16-byte aligned              */
-  QSPEC_ERR_WORKSPACE = 4,   /* workspace smaller than qspec_workspace_bytes  */
+  QSPEC_ERR_WORKSPACE = 4,   /* workspace smaller than this call needs        */
   QSPEC_ERR_HIP = 5,         /* the HIP runtime refused the launch            */
   QSPEC_ERR_UNSUPPORTED = 6  /* not gfx950; a forced plan has no kernel; a shape outside what a variant entry point takes */
 } qspec_status;
@@ -73,9 +73,10 @@ int qspec_version(void);
  * supported. */
 size_t qspec_packed_weight_bytes(int N, int K, int group);
 
-/* Scratch the GEMM entry points need for an (M,N,K) problem (partial sums of
- * K-slices that several workgroups produce); 0 when none is needed.  Returns 0
- * for unsupported shapes as well (the GEMM call reports those).
+/* Scratch that is enough for every GEMM entry point on an (M,N,K) problem (partial
+ * sums of K-slices that several workgroups produce); 0 when none of them needs any.
+ * (A call that gets less is held against the need of its own mode.)  Returns 0 for
+ * unsupported shapes as well (the GEMM call reports those).
  * Workspace rule: the first 16 KiB of a workspace hold arrival counters.  They
  * must be ZERO when the first GEMM call that uses the workspace is enqueued;
  * every GEMM call leaves them zero again, so one zero-filled allocation serves

@@ -163,14 +163,16 @@ def alloc_workspace(nbytes: int) -> torch.Tensor:
     return torch.zeros(max(int(nbytes), 16), dtype=torch.uint8, device="cuda")
 
 
-def _workspace(M, N, K, group, workspace):
-    if workspace is None:                 # (one that is given is held against the need by the entry point itself)
-        need = workspace_bytes(M, N, K, group)
-        if need == 0:
-            return None, 0
-        # convenience for tests: hot loops pass a workspace from alloc_workspace instead
-        workspace = alloc_workspace(need)
-    return _dev(workspace, torch.uint8, "workspace"), workspace.numel()
+def _with_workspace(call, args, M, N, K, group, workspace) -> int:
+    """The status of call(*args, workspace, its size, stream).  Without a workspace one is allocated if the call asks
+    for it (convenience for tests: hot loops pass one from alloc_workspace instead)."""
+    if workspace is not None:
+        return call(*args, _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream())
+    status = call(*args, None, 0, _stream())
+    if status == ERR_WORKSPACE:
+        workspace = alloc_workspace(workspace_bytes(M, N, K, group))
+        status = call(*args, workspace.data_ptr(), workspace.numel(), _stream())
+    return status
 
 
 def pack_weights(codes: torch.Tensor, scales: torch.Tensor, packed: torch.Tensor = None,
@@ -306,11 +308,9 @@ def gemm_w4a4(packed: torch.Tensor, qa: torch.Tensor, sa: torch.Tensor, N: int,
     M, K = qa.shape[0], qa.shape[1] * 2
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=qa.device)
-    ws, ws_bytes = _workspace(M, N, K, group, workspace)
-    _check(lib().qspec_gemm_w4a4(_dev(packed, torch.uint8, "packed"), _dev(qa, torch.uint8, "qa"),
-                                 _dev(sa, torch.float32, "sa"), M, N, K, group,
-                                 _dev(y, torch.float16, "y"), ws, ws_bytes, _stream()),
-           "qspec_gemm_w4a4")
+    args = (_dev(packed, torch.uint8, "packed"), _dev(qa, torch.uint8, "qa"), _dev(sa, torch.float32, "sa"),
+            M, N, K, group, _dev(y, torch.float16, "y"))
+    _check(_with_workspace(lib().qspec_gemm_w4a4, args, M, N, K, group, workspace), "qspec_gemm_w4a4")
     return y
 
 
@@ -319,11 +319,9 @@ def gemm_w4a4_wide(packed: torch.Tensor, qa8: torch.Tensor, sa: torch.Tensor, N:
     M, K = qa8.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=qa8.device)
-    ws, ws_bytes = _workspace(M, N, K, group, workspace)
-    _check(lib().qspec_gemm_w4a4_wide(_dev(packed, torch.uint8, "packed"), _dev(qa8, torch.int8, "qa8"),
-                                      _dev(sa, torch.float32, "sa"), M, N, K, group,
-                                      _dev(y, torch.float16, "y"), ws, ws_bytes, _stream()),
-           "qspec_gemm_w4a4_wide")
+    args = (_dev(packed, torch.uint8, "packed"), _dev(qa8, torch.int8, "qa8"), _dev(sa, torch.float32, "sa"),
+            M, N, K, group, _dev(y, torch.float16, "y"))
+    _check(_with_workspace(lib().qspec_gemm_w4a4_wide, args, M, N, K, group, workspace), "qspec_gemm_w4a4_wide")
     return y
 
 
@@ -332,10 +330,9 @@ def gemm_w4a16(packed: torch.Tensor, x: torch.Tensor, N: int, y: torch.Tensor = 
     M, K = x.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    ws, ws_bytes = _workspace(M, N, K, group, workspace)
-    _check(lib().qspec_gemm_w4a16(_dev(packed, torch.uint8, "packed"), _dev(x, torch.float16, "x"),
-                                  M, N, K, group, _dev(y, torch.float16, "y"), ws, ws_bytes, _stream()),
-           "qspec_gemm_w4a16")
+    args = (_dev(packed, torch.uint8, "packed"), _dev(x, torch.float16, "x"),
+            M, N, K, group, _dev(y, torch.float16, "y"))
+    _check(_with_workspace(lib().qspec_gemm_w4a16, args, M, N, K, group, workspace), "qspec_gemm_w4a16")
     return y
 
 

@@ -147,8 +147,6 @@ PlanOverrides& overrides() {
   return o;
 }
 
-bool use_generic() { return overrides().generic; }
-
 // ---------------------------------------------------------------- streaming (small-M) kernel
 constexpr int kStreamMaxM = 32;
 constexpr int kStreamMaxM4 = 64;
@@ -173,10 +171,6 @@ inline bool stream_nt_ok(int nt, int tm) {
 }
 // tiles per workgroup when the rows are dealt to ms blocks: ceil(M / ms) rows, in whole tiles
 inline int stream_tm_split(int M, int ms) { return stream_tm(16 * (((M + ms - 1) / ms + 15) / 16)); }
-
-// Largest M that is the streaming kernels' without a look at the tiled ones' shapes: 32 verify-mode tokens,
-// 64 draft-mode tokens where the tiled kernel has no cheaper plan (use_stream).
-int stream_base_max(bool w4a4) { return w4a4 ? kStreamMaxM4 : kStreamMaxM; }
 
 // What a streaming plan of more than 16 tokens costs, in microseconds.  ng groups fall to the busiest
 // wavefront (G / 8 on average), the workgroups of ceil(M / (16 tm)) token-row blocks fill `rounds`
@@ -224,13 +218,16 @@ constexpr int kMaxRowBlocks = 16;
 
 inline int stream_qs(int nt, int tm) { return nt <= 2 && tm <= 4 ? 2 : 1; }      // the kernel's QS
 
-double stream_cost(const StreamCost& c, int M, int N, int G) {
+// `over` or more once the first terms alone reach it (every eager call plans)
+double stream_cost(const StreamCost& c, int M, int N, int G, double over) {
+  const int qs = stream_qs(c.nt, c.tm), ng = qs * ((G + qs * kStreamWaves - 1) / (qs * kStreamWaves));
+  const double start = c.fixed + ng * c.group;
+  if (start >= over) return start;
   const int ms = (M + 16 * c.tm - 1) / (16 * c.tm), tiles = N / 16;
   const long long blocks = (long long)((tiles + c.nt - 1) / c.nt) * ms;
-  const double rounds = (double)((blocks + kNumCU - 1) / kNumCU);
-  const int qs = stream_qs(c.nt, c.tm), ng = qs * (((G + qs - 1) / qs + kStreamWaves - 1) / kStreamWaves);
+  const double again = (double)((blocks + kNumCU - 1) / kNumCU - 1);
   const double load = (double)tiles * ms / c.nt / kNumCU * G / kStreamWaves;
-  return c.fixed + c.round * (rounds - 1) + ng * (c.group + c.again * (rounds - 1)) + load * (c.load + c.tokens * M / (16.0 * c.tm * ms));
+  return start + again * (c.round + ng * c.again) + load * (c.load + c.tokens * M / (16.0 * c.tm * ms));
 }
 
 // Cheapest streaming plan of more than 16 tokens; one_round: among those that one round of workgroups covers.
@@ -243,7 +240,7 @@ double best_stream(bool w4a4, int M, int N, int G, bool one_round, StreamPlan* p
     if (ms > kMaxRowBlocks || (c.tm > 1 && 8 * c.tm >= M)) continue;              // (a kernel of half the token tiles covers M)
     if (one_round && (ms > 8 || blocks * ms > kNumCU)) continue;
     if (M > 32 && !overrides().stream_max[w4a4] && (long long)blocks * ms > 5 * kNumCU) continue;   // (not timed)
-    const double cost = stream_cost(c, M, N, G);
+    const double cost = stream_cost(c, M, N, G, best);
     if (cost < best) { best = cost; p->nt = c.nt; p->tm = c.tm; p->ms = ms; p->S = 1; p->blocks = blocks; }
   }
   return best;
@@ -287,7 +284,7 @@ StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
   }
   // (verify mode past 32 tokens: only where one round of workgroups covers a layer of at most 8192 x 8192; the
   // tiled kernels have too few output blocks to fill the chip there.  128 tokens, 4096 x 4096: 15.5 us tiled, 9.6 here.)
-  const bool past = !w4a4 && M > stream_base_max(false);
+  const bool past = !w4a4 && M > kStreamMaxM;
   if (past && (M > 128 || N > 8192 || K > 8192)) return p;          // nt == 0: no streaming plan
   best_stream(w4a4, M, N, G, past, &p);
   return p;
@@ -295,24 +292,6 @@ StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
 
 inline size_t stream_ws_bytes(const StreamPlan& p) {
   return p.S > 1 ? kTicketBytes + (size_t)p.S * p.blocks * p.nt * p.tm * 1024 : 0;
-}
-
-bool tile_override(bool w4a4, int* shape, int* S);
-
-double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices = 4);
-
-bool use_stream(bool w4a4, int M, int N, int K) {
-  const PlanOverrides& ov = overrides();
-  if (ov.generic && M > kStreamMaxM) return false;
-  if (ov.stream_max[w4a4]) return M <= ov.stream_max[w4a4];
-  const bool within = M <= stream_base_max(w4a4);
-  if (within && (!w4a4 || M <= 24 || ov.stream_fields[1] != 0 || ov.generic)) return true;
-  int shape, S;
-  if (!within && tile_override(w4a4, &shape, &S)) return false;      // a forced tile shape means the tiled kernel
-  if (!w4a4 || ov.stream_fields[1] != 0) return plan_stream(w4a4, M, N, K).nt > 0;
-  // draft mode: the cheaper of the two kernels
-  StreamPlan p{};
-  return best_stream(true, M, N, K / kGroup, false, &p) <= best_tile4(M, N, K / kGroup, &shape, &S);
 }
 
 // Launch the instance <mode, TM, NT> of a streaming plan.  A (TM, NT) pair that is not
@@ -337,8 +316,7 @@ int launch_stream_tm(const StreamArgs& a, const StreamPlan& plan, hipStream_t s)
 }
 
 template <bool W4A4>
-int launch_stream(StreamArgs a, void* workspace, hipStream_t s) {
-  const StreamPlan plan = plan_stream(W4A4, a.M, a.N, a.K);
+int launch_stream(const StreamPlan& plan, StreamArgs a, void* workspace, hipStream_t s) {
   if ((long long)plan.ms * 16 * plan.tm < a.M) return QSPEC_ERR_UNSUPPORTED;      // the row blocks must cover M
   a.S = plan.S;
   a.ms = plan.ms;
@@ -415,9 +393,11 @@ inline const TileShape& shape_of(bool w4a4, int i) { return w4a4 ? kShapes4[i] :
 bool tile_override(bool w4a4, int* shape, int* S) {
   const PlanOverrides& ov = overrides();
   if (!ov.tile_set[w4a4 ? 1 : 0]) return false;
-  *shape = ov.tile[w4a4 ? 1 : 0][0];
-  *S = ov.tile[w4a4 ? 1 : 0][1];
-  return *shape >= 0 && *shape < (w4a4 ? kNumTileShapes : kNumShapes16) && *S >= 1;
+  const int* f = ov.tile[w4a4 ? 1 : 0];
+  if (f[0] < 0 || f[0] >= (w4a4 ? kNumTileShapes : kNumShapes16) || f[1] < 1) return false;
+  *shape = f[0];
+  *S = f[1];
+  return true;
 }
 
 // Cost per group of a round with f workgroups per compute unit (0 < f <= places).
@@ -473,9 +453,8 @@ constexpr Tile4Cost kCost4[] = {
     {5.936, 4.332, 1.111, 0.761, 0.276, 0, 0, 0, 0.043, 2.048, 5.603, 1.045, 1},   // 3: 256 x 128
 };
 
-// Cheapest draft-mode tiled plan by kCost4.
-double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices) {
-  double best = 1e30;
+// Cheapest draft-mode tiled plan by kCost4 among those below `best`; without one, shape and slices stay as they are.
+double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices = 4, double best = 1e30) {
   for (int i = 0; i < kNumTileShapes; ++i) {
     const TileShape& t = kShapes4[i];
     const Tile4Cost& c = kCost4[i];
@@ -485,9 +464,10 @@ double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices) 
       // K-slices only in one round of two workgroups per unit (one of eight wavefronts: the partial sums stay
       // within 32 MiB), of four groups at least
       if (S > 1 && (blocks * S > (c.places > 1 ? 2 : 1) * kNumCU || G / S < 4)) break;
+      const double g = ((G + S - 1) / S) * (0.7 + 0.3 * M / (double)(mb * bm));
+      if (c.fixed + c.any * g >= best) continue;
       const long long wgs = blocks * S, load = (long long)c.places * kNumCU, rounds = (wgs + load - 1) / load;
       const double per_unit = (double)wgs / kNumCU, f = per_unit - (double)c.places * (rounds - 1);
-      const double g = ((G + S - 1) / S) * (0.7 + 0.3 * M / (double)(mb * bm));
       const auto clamp01 = [](double v) { return v < 0.0 ? 0.0 : v > 1.0 ? 1.0 : v; };
       double cost = c.fixed + c.again * (rounds - 1) + c.out * per_unit +
                     g * (c.full * (rounds - 1) + c.any + c.first * clamp01(f) + c.second * clamp01(f - 1) +
@@ -499,21 +479,11 @@ double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices) 
   return best;
 }
 
-// Pure function of (mode, M, N, K): qspec_workspace_bytes and the GEMM entry points agree.
-TilePlan plan_tile(bool w4a4, int M, int N, int K) {
-  const int G = K / kGroup;
-  TilePlan p{};
-  int shape = 0, S = 1;
-  if (!tile_override(w4a4, &shape, &S)) {
-    if (w4a4) {
-      best_tile4(M, N, G, &shape, &S);
-    } else {
-      plan_tile16(M, N, G, &shape, &S);
-    }
-  }
+TilePlan tile_plan(bool w4a4, int M, int N, int K, int shape, int S) {
   const TileShape& t = shape_of(w4a4, shape);
   const int edge = 32;                  // MFMA tile edge
-  const int bn = edge * t.TN * t.WGN, bm = edge * t.TMW * t.WGM;
+  const int bn = edge * t.TN * t.WGN, bm = edge * t.TMW * t.WGM, G = K / kGroup;
+  TilePlan p{};
   p.shape = shape;
   p.nb = (N + bn - 1) / bn;
   p.mb = (M + bm - 1) / bm;
@@ -523,11 +493,30 @@ TilePlan plan_tile(bool w4a4, int M, int N, int K) {
   return p;
 }
 
+inline size_t plan_ws_bytes(bool w4a4, const TilePlan& p) {
+  if (p.S <= 1) return 0;
+  const TileShape& t = shape_of(w4a4, p.shape);
+  const int edge = 32;
+  const size_t block_floats = (size_t)(edge * t.TN * t.WGN) * (edge * t.TMW * t.WGM);   // whole blocks, ragged or not
+  return kTicketBytes + (size_t)p.S * p.nb * p.mb * block_floats * 4;
+}
+
+// ---------------------------------------------------------------- the plan of a product
+enum Product { kVerify, kDraft, kDraftWide };      // W4A16; W4A4 on packed codes; W4A4 on widened codes
+enum class Kernel { none, stream, tile, generic };
+struct Plan {
+  Kernel kernel;      // none: not a size this product takes
+  StreamPlan stream;
+  TilePlan tile;
+  size_t need;        // bytes of workspace
+};
+
 // Sizes for which the widened format is accepted though the packed one is advised (qspec_w4a4_takes_wide: 0):
 // more than 64 tokens, or 48 on very wide layers, unless one round of row blocks covers a layer of at most
-// 8192 x 8192.  A caller may have quantised for them already.  They run unsliced, so need no workspace.
+// 8192 x 8192.  A caller may have quantised for them already.
 bool wide_on_request(int M, int N, int K) {
-  if (use_generic() || overrides().stream_fields[1] != 0 || overrides().stream_max[1] != 0) return false;
+  const PlanOverrides& ov = overrides();
+  if (ov.stream_fields[1] != 0 || ov.stream_max[1] != 0) return false;
   if (M <= kStreamMaxM4) return M >= 48 && N >= 170 * 128;
   if (M > 128 || N > 8192 || K > 8192) return true;
   for (int tm = 1; tm <= 4; tm *= 2) {
@@ -537,21 +526,53 @@ bool wide_on_request(int M, int N, int K) {
   }
   return true;
 }
-TilePlan plan_tile4_unsliced(int M, int N, int K) {
-  TilePlan p{};
-  best_tile4(M, N, K / kGroup, &p.shape, &p.S, 1);
-  const TileShape& t = kShapes4[p.shape];
-  p.nb = (N + 32 * t.TN * t.WGN - 1) / (32 * t.TN * t.WGN);
-  p.mb = (M + 32 * t.TMW * t.WGM - 1) / (32 * t.TMW * t.WGM);
-  return p;
-}
 
-inline size_t plan_ws_bytes(bool w4a4, const TilePlan& p) {
-  if (p.S <= 1) return 0;
-  const TileShape& t = shape_of(w4a4, p.shape);
-  const int edge = 32;
-  const size_t block_floats = (size_t)(edge * t.TN * t.WGN) * (edge * t.TMW * t.WGM);   // whole blocks, ragged or not
-  return kTicketBytes + (size_t)p.S * p.nb * p.mb * block_floats * 4;
+// A pure function of its arguments and the overrides, worked out once per call: the entry points launch what it
+// says and ask for the workspace it needs, qspec_workspace_bytes gives the most that any product of the size needs.
+Plan plan_product(Product product, int M, int N, int K) {
+  const bool w4a4 = product != kVerify;
+  const PlanOverrides& ov = overrides();
+  const int G = K / kGroup;
+  Plan p{};
+  if (ov.generic && M > kStreamMaxM) {
+    p.kernel = product == kDraftWide ? Kernel::none : Kernel::generic;
+    return p;
+  }
+  // up to here the streaming kernels have it without a look at the tiled ones' shapes: 32 verify-mode tokens, 64
+  // draft-mode tokens where the tiled kernel has no cheaper plan
+  const bool within = M <= (w4a4 ? kStreamMaxM4 : kStreamMaxM);
+  int shape = 0, S = 0;                            // S == 0: no tiled plan yet
+  const bool forced_tile = tile_override(w4a4, &shape, &S);
+  bool stream = true;
+  if (ov.stream_max[w4a4]) stream = M <= ov.stream_max[w4a4];
+  else if (within && (!w4a4 || M <= 24 || ov.stream_fields[1] != 0 || ov.generic)) stream = true;
+  else if (!within && forced_tile) stream = false;
+  else if (!w4a4 || ov.stream_fields[1] != 0) {
+    p.stream = plan_stream(w4a4, M, N, K);
+    stream = p.stream.nt > 0;
+  } else {                                         // draft mode: the cheaper of the two kernels
+    int best_shape = 0, best_S = 0;
+    best_tile4(M, N, G, &best_shape, &best_S, 4, best_stream(true, M, N, G, false, &p.stream));
+    stream = best_S == 0;
+    if (!forced_tile) { shape = best_shape; S = best_S; }
+  }
+  if (stream && product != kDraftWide) {
+    p.kernel = Kernel::stream;
+    if (p.stream.nt == 0) p.stream = plan_stream(w4a4, M, N, K);
+    p.need = stream_ws_bytes(p.stream);
+    return p;
+  }
+  if (stream) {
+    if (!wide_on_request(M, N, K)) return p;
+    best_tile4(M, N, G, &shape, &S, 1);
+  } else if (S == 0) {
+    if (w4a4) best_tile4(M, N, G, &shape, &S);
+    else plan_tile16(M, N, G, &shape, &S);
+  }
+  p.kernel = Kernel::tile;
+  p.tile = tile_plan(w4a4, M, N, K, shape, S);
+  p.need = plan_ws_bytes(w4a4, p.tile);
+  return p;
 }
 
 template <int PN, int PM, int WGN, int WGM, int OCC>
@@ -694,6 +715,57 @@ inline int check_accept_shape(int B, int gamma, int V) {
   return QSPEC_OK;
 }
 
+// ---------------------------------------------------------------- the three products
+int check_gemm(const void* packed, const void* act, const float* sa, int M, int N, int K, int group, void* y_f16) {
+  if (!packed || !act || !y_f16) return QSPEC_ERR_NULL;
+  if (int st = check_shape(M, N, K, group)) return st;
+  if (misaligned(packed) || misaligned(act) || misaligned(sa) || misaligned(y_f16)) return QSPEC_ERR_ALIGN;
+  return QSPEC_OK;
+}
+
+int launch_product(Product product, const Plan& plan, const void* packed, const void* act, const float* sa,
+                   int M, int N, int K, void* y_f16, void* workspace, hipStream_t s) {
+  const bool w4a4 = product != kVerify;
+  const auto operands = [&](auto& a) {
+    a.codes = static_cast<const uint4*>(packed);
+    a.scalesT = blob_scales(packed, N, K);
+    a.act = act;
+    a.sa = sa;
+    a.y = static_cast<uint16_t*>(y_f16);
+    a.M = M; a.N = N; a.K = K; a.G = K / kGroup;
+  };
+  if (plan.kernel == Kernel::stream) {
+    StreamArgs a{};
+    operands(a);
+    if (int st = w4a4 ? launch_stream<true>(plan.stream, a, workspace, s) : launch_stream<false>(plan.stream, a, workspace, s)) return st;
+  } else if (plan.kernel == Kernel::tile) {
+    TileArgs a{};
+    operands(a);
+    if (int st = w4a4 ? launch_tile<true>(plan.tile, a, workspace, s, product == kDraftWide)
+                      : launch_tile<false>(plan.tile, a, workspace, s)) return st;
+  } else {
+    GemmArgs a{};
+    operands(a);
+    switch (pick_tm(M)) {
+      case 1: w4a4 ? launch_w4a4<1>(a, s) : launch_w4a16<1>(a, s); break;
+      case 2: w4a4 ? launch_w4a4<2>(a, s) : launch_w4a16<2>(a, s); break;
+      case 4: w4a4 ? launch_w4a4<4>(a, s) : launch_w4a16<4>(a, s); break;
+      default: w4a4 ? launch_w4a4<8>(a, s) : launch_w4a16<8>(a, s); break;
+    }
+  }
+  return launch_status();
+}
+
+int gemm(Product product, const void* packed, const void* act, const float* sa, int M, int N, int K, int group,
+         void* y_f16, void* workspace, size_t workspace_bytes, void* stream) {
+  if (int st = check_gemm(packed, act, sa, M, N, K, group, y_f16)) return st;
+  const Plan plan = plan_product(product, M, N, K);
+  if (plan.kernel == Kernel::none) return QSPEC_ERR_UNSUPPORTED;   // this shape runs on a kernel that reads packed codes
+  if (plan.need > 0 && (!workspace || workspace_bytes < plan.need)) return QSPEC_ERR_WORKSPACE;
+  if (int st = check_device()) return st;
+  return launch_product(product, plan, packed, act, sa, M, N, K, y_f16, workspace, static_cast<hipStream_t>(stream));
+}
+
 }  // namespace
 
 extern "C" {
@@ -721,13 +793,8 @@ size_t qspec_packed_weight_bytes(int N, int K, int group) {
 size_t qspec_workspace_bytes(int M, int N, int K, int group) {
   if (check_shape(M, N, K, group) != QSPEC_OK) return 0;
   // the larger of what the two modes need for this shape
-  size_t need[2];
-  for (int w4a4 = 0; w4a4 < 2; ++w4a4) {
-    if (use_stream(w4a4 != 0, M, N, K)) need[w4a4] = stream_ws_bytes(plan_stream(w4a4 != 0, M, N, K));
-    else if (use_generic()) need[w4a4] = 0;
-    else need[w4a4] = plan_ws_bytes(w4a4 != 0, plan_tile(w4a4 != 0, M, N, K));
-  }
-  return need[0] > need[1] ? need[0] : need[1];
+  const size_t draft = plan_product(kDraft, M, N, K).need, verify = plan_product(kVerify, M, N, K).need;
+  return draft > verify ? draft : verify;
 }
 
 int qspec_pack_weights(const int8_t* codes, const void* scales_f16, int N, int K, int group,
@@ -778,7 +845,7 @@ int qspec_quant_act(const void* x_f16, int M, int K, int group, uint8_t* qa, flo
 
 int qspec_w4a4_takes_wide(int M, int N, int K, int group) {
   if (check_shape(M, N, K, group) != QSPEC_OK) return 0;
-  return (!use_stream(true, M, N, K) && !use_generic()) ? 1 : 0;
+  return plan_product(kDraft, M, N, K).kernel == Kernel::tile ? 1 : 0;
 }
 
 int qspec_quant_act_wide(const void* x_f16, int M, int K, int group, int8_t* qa8, float* sa, void* stream) {
@@ -864,119 +931,36 @@ int qspec_reorder_quant(const void* x_f16, const int32_t* perm, int M, int K, in
 
 int qspec_gemm_w4a4(const void* packed, const uint8_t* qa, const float* sa, int M, int N, int K, int group,
                     void* y_f16, void* workspace, size_t workspace_bytes, void* stream) {
-  if (!packed || !qa || !sa || !y_f16) return QSPEC_ERR_NULL;
-  if (int st = check_shape(M, N, K, group)) return st;
-  if (misaligned(packed) || misaligned(qa) || misaligned(sa) || misaligned(y_f16)) return QSPEC_ERR_ALIGN;
-  const size_t need = qspec_workspace_bytes(M, N, K, group);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return QSPEC_ERR_WORKSPACE;
-  if (int st = check_device()) return st;
-  GemmArgs a{};
-  a.codes = static_cast<const uint4*>(packed);
-  a.scalesT = blob_scales(packed, N, K);
-  a.act = qa;
-  a.sa = sa;
-  a.y = static_cast<uint16_t*>(y_f16);
-  a.M = M; a.N = N; a.K = K; a.G = K / kGroup;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (use_stream(true, M, N, K)) {
-    StreamArgs st{};
-    st.codes = a.codes; st.scalesT = a.scalesT; st.act = qa; st.sa = sa; st.y = a.y;
-    st.M = M; st.N = N; st.K = K; st.G = a.G;
-    if (int err = launch_stream<true>(st, workspace, s)) return err;
-    return launch_status();
-  }
-  if (!use_generic()) {
-    TileArgs t{};
-    t.codes = a.codes; t.scalesT = a.scalesT; t.act = qa; t.sa = sa; t.y = a.y;
-    t.M = M; t.N = N; t.K = K; t.G = a.G;
-    if (int st = launch_tile<true>(plan_tile(true, M, N, K), t, workspace, s)) return st;
-    return launch_status();
-  }
-  switch (pick_tm(M)) {
-    case 1: launch_w4a4<1>(a, s); break;
-    case 2: launch_w4a4<2>(a, s); break;
-    case 4: launch_w4a4<4>(a, s); break;
-    default: launch_w4a4<8>(a, s); break;
-  }
-  return launch_status();
+  if (!sa) return QSPEC_ERR_NULL;
+  return gemm(kDraft, packed, qa, sa, M, N, K, group, y_f16, workspace, workspace_bytes, stream);
 }
 
 int qspec_gemm_w4a4_wide(const void* packed, const int8_t* qa8, const float* sa, int M, int N, int K, int group,
                          void* y_f16, void* workspace, size_t workspace_bytes, void* stream) {
-  if (!packed || !qa8 || !sa || !y_f16) return QSPEC_ERR_NULL;
-  if (int st = check_shape(M, N, K, group)) return st;
-  if (misaligned(packed) || misaligned(qa8) || misaligned(sa) || misaligned(y_f16)) return QSPEC_ERR_ALIGN;
-  const bool advised = qspec_w4a4_takes_wide(M, N, K, group) != 0;
-  if (!advised && !wide_on_request(M, N, K)) return QSPEC_ERR_UNSUPPORTED;   // this shape runs on a kernel that reads packed codes
-  const size_t need = qspec_workspace_bytes(M, N, K, group);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return QSPEC_ERR_WORKSPACE;
-  if (int st = check_device()) return st;
-  TileArgs t{};
-  t.codes = static_cast<const uint4*>(packed);
-  t.scalesT = blob_scales(packed, N, K);
-  t.act = qa8;
-  t.sa = sa;
-  t.y = static_cast<uint16_t*>(y_f16);
-  t.M = M; t.N = N; t.K = K; t.G = K / kGroup;
-  if (int st = launch_tile<true>(advised ? plan_tile(true, M, N, K) : plan_tile4_unsliced(M, N, K), t, workspace, static_cast<hipStream_t>(stream), true)) return st;
-  return launch_status();
+  if (!sa) return QSPEC_ERR_NULL;
+  return gemm(kDraftWide, packed, qa8, sa, M, N, K, group, y_f16, workspace, workspace_bytes, stream);
 }
 
 int qspec_gemm_w4a16(const void* packed, const void* x_f16, int M, int N, int K, int group,
                      void* y_f16, void* workspace, size_t workspace_bytes, void* stream) {
-  if (!packed || !x_f16 || !y_f16) return QSPEC_ERR_NULL;
-  if (int st = check_shape(M, N, K, group)) return st;
-  if (misaligned(packed) || misaligned(x_f16) || misaligned(y_f16)) return QSPEC_ERR_ALIGN;
-  const size_t need = qspec_workspace_bytes(M, N, K, group);
-  if (need > 0 && (!workspace || workspace_bytes < need)) return QSPEC_ERR_WORKSPACE;
-  if (int st = check_device()) return st;
-  GemmArgs a{};
-  a.codes = static_cast<const uint4*>(packed);
-  a.scalesT = blob_scales(packed, N, K);
-  a.act = x_f16;
-  a.y = static_cast<uint16_t*>(y_f16);
-  a.M = M; a.N = N; a.K = K; a.G = K / kGroup;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (use_stream(false, M, N, K)) {
-    StreamArgs st{};
-    st.codes = a.codes; st.scalesT = a.scalesT; st.act = x_f16; st.y = a.y;
-    st.M = M; st.N = N; st.K = K; st.G = a.G;
-    if (int err = launch_stream<false>(st, workspace, s)) return err;
-    return launch_status();
-  }
-  if (!use_generic()) {
-    TileArgs t{};
-    t.codes = a.codes; t.scalesT = a.scalesT; t.act = x_f16; t.y = a.y;
-    t.M = M; t.N = N; t.K = K; t.G = a.G;
-    if (int st = launch_tile<false>(plan_tile(false, M, N, K), t, workspace, s)) return st;
-    return launch_status();
-  }
-  switch (pick_tm(M)) {
-    case 1: launch_w4a16<1>(a, s); break;
-    case 2: launch_w4a16<2>(a, s); break;
-    case 4: launch_w4a16<4>(a, s); break;
-    default: launch_w4a16<8>(a, s); break;
-  }
-  return launch_status();
+  return gemm(kVerify, packed, x_f16, nullptr, M, N, K, group, y_f16, workspace, workspace_bytes, stream);
 }
 
 int qspec_gemm_w4a16_noalloc(const void* packed, const void* x_f16, int M, int N, int K, int group,
                              void* y_f16, void* stream) {
-  if (!packed || !x_f16 || !y_f16) return QSPEC_ERR_NULL;
-  if (int st = check_shape(M, N, K, group)) return st;
-  if (misaligned(packed) || misaligned(x_f16) || misaligned(y_f16)) return QSPEC_ERR_ALIGN;
-  const size_t need = qspec_workspace_bytes(M, N, K, group);
-  if (need > kScratchBytes) return QSPEC_ERR_WORKSPACE;       // beyond the built-in scratch: use qspec_gemm_w4a16
+  if (int st = check_gemm(packed, x_f16, nullptr, M, N, K, group, y_f16)) return st;
+  const Plan plan = plan_product(kVerify, M, N, K);
+  if (plan.need > kScratchBytes) return QSPEC_ERR_WORKSPACE;       // beyond the built-in scratch: use qspec_gemm_w4a16
   if (int st = check_device()) return st;
   int st = QSPEC_OK;
   void* ws = scratch_of_device(&st);
   if (!ws) return st;
-  if (need > 0) {
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  if (plan.need > 0) {
     // the counters must start at zero whatever an earlier (possibly failed) call left
-    hipLaunchKernelGGL(clear_tickets_kernel, dim3(kMaxTickets / 256), dim3(256), 0, static_cast<hipStream_t>(stream),
-                       static_cast<unsigned*>(ws), kMaxTickets);
+    hipLaunchKernelGGL(clear_tickets_kernel, dim3(kMaxTickets / 256), dim3(256), 0, s, static_cast<unsigned*>(ws), kMaxTickets);
   }
-  return qspec_gemm_w4a16(packed, x_f16, M, N, K, group, y_f16, ws, kScratchBytes, stream);
+  return launch_product(kVerify, plan, packed, x_f16, nullptr, M, N, K, y_f16, ws, s);
 }
 
 size_t qspec_mlp_draft_workspace_bytes(int M, int H, int I, int group) {
@@ -1086,18 +1070,16 @@ int qspec_describe_kernel(int mode_w4a4, int M, int N, int K, int group, char* o
   if (!out || cap == 0) return QSPEC_ERR_NULL;
   if (int st = check_shape(M, N, K, group)) return st;
   const char* b = mode_w4a4 ? "true" : "false";
-  if (use_stream(mode_w4a4 != 0, M, N, K)) {
-    const StreamPlan sp = plan_stream(mode_w4a4 != 0, M, N, K);
-    snprintf(out, cap, "gemm_stream_kernel<%s, %d, %d>", b, sp.tm, sp.nt);
-  } else {
-    if (!use_generic()) {
-      const TileShape& t = shape_of(mode_w4a4 != 0, plan_tile(mode_w4a4 != 0, M, N, K).shape);
-      if (mode_w4a4) snprintf(out, cap, "gemm_tile4w_kernel<%d, %d, %d, %d, %d, false>", t.TN, t.TMW, t.WGN, t.WGM, t.OCC);
-      else if (t.TN == 2 && t.TMW == 4) snprintf(out, cap, "gemm_tile16w2_kernel");
-      else snprintf(out, cap, "gemm_tile16w_kernel<%d, %d, %d, %d, %d, %d, %d>", t.TN, t.TMW, t.WGN, t.WGM, t.WGK, t.NW, t.OCC);
-    } else if (mode_w4a4) snprintf(out, cap, "gemm_w4a4_generic<%d, 4, false>", pick_tm(M));
-    else snprintf(out, cap, "gemm_w4a16_generic<%d, 4>", pick_tm(M));
-  }
+  const Plan plan = plan_product(mode_w4a4 ? kDraft : kVerify, M, N, K);
+  if (plan.kernel == Kernel::stream) {
+    snprintf(out, cap, "gemm_stream_kernel<%s, %d, %d>", b, plan.stream.tm, plan.stream.nt);
+  } else if (plan.kernel == Kernel::tile) {
+    const TileShape& t = shape_of(mode_w4a4 != 0, plan.tile.shape);
+    if (mode_w4a4) snprintf(out, cap, "gemm_tile4w_kernel<%d, %d, %d, %d, %d, false>", t.TN, t.TMW, t.WGN, t.WGM, t.OCC);
+    else if (t.TN == 2 && t.TMW == 4) snprintf(out, cap, "gemm_tile16w2_kernel");
+    else snprintf(out, cap, "gemm_tile16w_kernel<%d, %d, %d, %d, %d, %d, %d>", t.TN, t.TMW, t.WGN, t.WGM, t.WGK, t.NW, t.OCC);
+  } else if (mode_w4a4) snprintf(out, cap, "gemm_w4a4_generic<%d, 4, false>", pick_tm(M));
+  else snprintf(out, cap, "gemm_w4a16_generic<%d, 4>", pick_tm(M));
   return QSPEC_OK;
 }
 

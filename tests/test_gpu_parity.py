@@ -458,6 +458,32 @@ def test_missing_workspace_is_refused(env, plan):
     assert bool((y == 7.0).all())
 
 
+@pytest.mark.parametrize("sliced", ["draft", "verify"])
+def test_workspace_is_held_against_the_calls_own_need(env, plan, sliced):
+    """One mode runs in K-slices, the other does not: without a workspace the first is refused, the second runs."""
+    torch, B = env
+    M, N, K = 100, 64, 1024
+    plan("QSPEC_TILE_W4A4", "1,2" if sliced == "draft" else "1,1")
+    plan("QSPEC_TILE_W4A16", "2,2" if sliced == "verify" else "2,1")
+    codes, scales, x = synth.generic_case(81, M, N, K)
+    blob = B.pack_weights(dev(torch, codes), dev(torch, scales))
+    qa, sa, q_ref, s_ref = _check_quant(torch, B, x)
+    qa8, xd, L = B.quant_act_wide(dev(torch, x))[0], dev(torch, x), B.lib()
+    assert B.workspace_bytes(M, N, K) > 16384
+    y4, y8, y16 = (torch.full((M, N), 7.0, dtype=torch.float16, device="cuda") for _ in range(3))
+    rc = (L.qspec_gemm_w4a4(blob.data_ptr(), qa.data_ptr(), sa.data_ptr(), M, N, K, 128, y4.data_ptr(), None, 0, None),
+          L.qspec_gemm_w4a4_wide(blob.data_ptr(), qa8.data_ptr(), sa.data_ptr(), M, N, K, 128, y8.data_ptr(), None, 0, None),
+          L.qspec_gemm_w4a16(blob.data_ptr(), xd.data_ptr(), M, N, K, 128, y16.data_ptr(), None, 0, None))
+    torch.cuda.synchronize()
+    if sliced == "draft":
+        assert rc == (B.ERR_WORKSPACE, B.ERR_WORKSPACE, B.OK) and bool((y4 == 7.0).all()) and bool((y8 == 7.0).all())
+    else:
+        assert rc == (B.OK, B.OK, B.ERR_WORKSPACE) and bool((y16 == 7.0).all()) and torch.equal(y4, y8)
+        assert rel_err(y4.cpu().numpy(), orc.gemm_w4a4(q_ref, s_ref, codes, scales)) <= TOL
+    y16 = B.gemm_w4a16(blob, xd, N)                  # (the binding allocates what a call asks for)
+    assert rel_err(y16.cpu().numpy(), orc.gemm_w4a16(x, codes, scales)) <= TOL
+
+
 def test_bad_arguments_are_refused_on_device(env):
     torch, B = env
     M, N, K = 4, 64, 256
