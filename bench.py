@@ -255,9 +255,8 @@ class Bench:
                     us=round(t / L * 1e6, 3), TBps=round(ab(M, lin.N, lin.K) * L / t / 1e12, 3),
                     hbm_frac=round(ab(M, lin.N, lin.K) * L / t / 1e9 / HBM_PEAK_GBS, 4),
                     mfma_frac=round(fl * L / t / 1e12 / MFMA_PEAK_TFLOPS[kind], 4))
-                name = B.describe_kernel(kind == "w4a4", M, lin.N, lin.K)          # the profiler's symbol
-                if kind == "w4a4" and wide_d[i]:
-                    name = name.replace(", false>", ", true>")                     # (the instance that takes widened codes)
+                # the profiler's symbol
+                name = B.describe_kernel(kind == "w4a4", M, lin.N, lin.K, wide=kind == "w4a4" and wide_d[i])
                 k = kernels.setdefault(name, dict(launches=0, seconds=0.0, bytes=0, flops=0, mode=kind))
                 k["launches"] += L
                 k["seconds"] += t
@@ -405,7 +404,7 @@ class Bench:
         out = {}
         for i, lin in enumerate(lins):
             G = lin.K // 128
-            name = B.describe_kernel(True, Md, lin.N, lin.K)
+            name = B.describe_kernel(True, Md, lin.N, lin.K, wide=B.w4a4_takes_wide(Md, lin.N, lin.K))
             nbytes = lin.N * lin.K // 2            # the code tiles; whole 1 KB tiles
             if name.startswith("gemm_stream_kernel"):
                 per = int(name.split(",")[-1].strip(" >")) * G       # NT tiles per workgroup over all of K

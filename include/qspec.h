@@ -196,8 +196,8 @@ int qspec_gemm_w4a4(const void* packed, const uint8_t* qa, const float* sa,
 
 /*
  * The same quantiser and the same draft-mode product (paper Sec. 1, W4A4; Sec. 4.1,
- * groups of 128) with the activation codes kept in a second device format for the shapes
- * whose product runs on the tiled kernel (wide layers from about 33 tokens on, others later):
+ * groups of 128) with the activation codes kept in a second device format, the one the tiled
+ * kernel reads (it runs where there are tokens enough; the streaming kernel reads packed codes):
  * every code in a byte of its own, as int8 16 * code, 128 bytes per token row and group in
  * the order of that kernel's LDS rows (byte b of the packed group's 64 bytes gives byte b
  * = 16 * its low-nibble code and byte 64 + b = 16 * its high-nibble code).  The kernel then
@@ -206,11 +206,11 @@ int qspec_gemm_w4a4(const void* packed, const uint8_t* qa, const float* sa,
  *   qspec_w4a4_takes_wide   1 if this format is the faster one for this shape, else 0 (also 0
  *                           for a shape the library refuses);
  *   qspec_quant_act_wide    x_f16 fp16 [M,K];  qa8 out, M*K bytes;  sa out, fp32 [M,G];
- *   qspec_gemm_w4a4_wide    arguments as qspec_gemm_w4a4 with qa8 in place of qa;
- *                           QSPEC_ERR_UNSUPPORTED (nothing launched) for a shape whose
- *                           product runs on a kernel that reads packed codes, unless it has
- *                           more than 64 tokens (48 on very wide layers) and no plan of one
- *                           round of row blocks on that kernel.
+ *   qspec_gemm_w4a4_wide    arguments as qspec_gemm_w4a4 with qa8 in place of qa.  Takes every
+ *                           shape of 25 tokens or more; QSPEC_ERR_UNSUPPORTED (nothing
+ *                           launched) below, and where a debug override asks for another
+ *                           kernel.  Where qspec_w4a4_takes_wide is 0 it needs no workspace,
+ *                           but is up to 3 times as fast with one of qspec_workspace_bytes.
  */
 int qspec_w4a4_takes_wide(int M, int N, int K, int group);
 int qspec_quant_act_wide(const void* x_f16, int M, int K, int group,
@@ -351,7 +351,8 @@ int qspec_debug_set_plan(const char* name, const char* value);
 /*
  * Debug entry: name of the device kernel the GEMM entry points select for an
  * (M,N,K) problem, e.g. "gemm_stream_kernel<false, 2, 3>" (mode 0 = W4A16
- * verify, 1 = W4A4 draft).  It matches the symbol a profiler reports, so that
+ * verify, 1 = W4A4 draft, 2 = W4A4 draft on widened codes: QSPEC_ERR_UNSUPPORTED
+ * where that is refused).  It matches the symbol a profiler reports, so that
  * benchmark timings can be set beside profiler output.  Writes a NUL-terminated
  * string of at most cap-1 characters to `out` (host memory); returns a status.
  */

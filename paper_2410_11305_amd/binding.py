@@ -123,9 +123,10 @@ def debug_set_plan(name: str, value: str = None) -> None:
            "qspec_debug_set_plan")
 
 
-def describe_kernel(w4a4: bool, M: int, N: int, K: int, group: int = GROUP) -> str:
+def describe_kernel(w4a4: bool, M: int, N: int, K: int, group: int = GROUP, wide: bool = False) -> str:
+    """`wide`: the draft-mode product on widened codes."""
     buf = ctypes.create_string_buffer(128)
-    _check(lib().qspec_describe_kernel(1 if w4a4 else 0, M, N, K, group, buf, 128), "qspec_describe_kernel")
+    _check(lib().qspec_describe_kernel(2 if wide else 1 if w4a4 else 0, M, N, K, group, buf, 128), "qspec_describe_kernel")
     return buf.value.decode()
 
 
@@ -213,8 +214,8 @@ def quant_act(x: torch.Tensor, qa: torch.Tensor = None, sa: torch.Tensor = None,
 
 
 def w4a4_takes_wide(M: int, N: int, K: int, group: int = GROUP) -> bool:
-    """True when the draft-mode GEMM of this shape runs on the kernel that can take the widened
-    activation format (quant_act_wide -> gemm_w4a4_wide)."""
+    """True when the widened activation format (quant_act_wide -> gemm_w4a4_wide) is the faster one for the
+    draft-mode GEMM of this shape.  It is accepted from 25 tokens on either way."""
     return bool(lib().qspec_w4a4_takes_wide(M, N, K, group))
 
 
@@ -321,6 +322,9 @@ def gemm_w4a4_wide(packed: torch.Tensor, qa8: torch.Tensor, sa: torch.Tensor, N:
         y = torch.empty((M, N), dtype=torch.float16, device=qa8.device)
     args = (_dev(packed, torch.uint8, "packed"), _dev(qa8, torch.int8, "qa8"), _dev(sa, torch.float32, "sa"),
             M, N, K, group, _dev(y, torch.float16, "y"))
+    need = workspace_bytes(M, N, K, group) if workspace is None else 0
+    if need:                              # (the call does not ask for one everywhere that it is faster with it)
+        workspace = alloc_workspace(need)
     _check(_with_workspace(lib().qspec_gemm_w4a4_wide, args, M, N, K, group, workspace), "qspec_gemm_w4a4_wide")
     return y
 

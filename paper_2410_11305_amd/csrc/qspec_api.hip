@@ -509,23 +509,11 @@ struct Plan {
   StreamPlan stream;
   TilePlan tile;
   size_t need;        // bytes of workspace
+  bool optional;      // runs unsliced, so without any, where the workspace does not hold that
 };
-
-// Sizes for which the widened format is accepted though the packed one is advised (qspec_w4a4_takes_wide: 0):
-// more than 64 tokens, or 48 on very wide layers, unless one round of row blocks covers a layer of at most
-// 8192 x 8192.  A caller may have quantised for them already.
-bool wide_on_request(int M, int N, int K) {
-  const PlanOverrides& ov = overrides();
-  if (ov.stream_fields[1] != 0 || ov.stream_max[1] != 0) return false;
-  if (M <= kStreamMaxM4) return M >= 48 && N >= 170 * 128;
-  if (M > 128 || N > 8192 || K > 8192) return true;
-  for (int tm = 1; tm <= 4; tm *= 2) {
-    const int ms = (M + 16 * tm - 1) / (16 * tm);
-    for (int v : kStreamNts)
-      if (ms >= 2 && ms <= 8 && stream_nt_ok(v, tm) && ((N / 16 + v - 1) / v) * ms <= kNumCU) return false;
-  }
-  return true;
-}
+// Tokens from which the draft mode may run on the tiled kernel (the streaming one is always the faster below) and
+// the widened format is accepted
+constexpr int kTileMinM4 = 25;
 
 // A pure function of its arguments and the overrides, worked out once per call: the entry points launch what it
 // says and ask for the workspace it needs, qspec_workspace_bytes gives the most that any product of the size needs.
@@ -545,7 +533,7 @@ Plan plan_product(Product product, int M, int N, int K) {
   const bool forced_tile = tile_override(w4a4, &shape, &S);
   bool stream = true;
   if (ov.stream_max[w4a4]) stream = M <= ov.stream_max[w4a4];
-  else if (within && (!w4a4 || M <= 24 || ov.stream_fields[1] != 0 || ov.generic)) stream = true;
+  else if (within && (!w4a4 || M < kTileMinM4 || ov.stream_fields[1] != 0 || ov.generic)) stream = true;
   else if (!within && forced_tile) stream = false;
   else if (!w4a4 || ov.stream_fields[1] != 0) {
     p.stream = plan_stream(w4a4, M, N, K);
@@ -563,9 +551,12 @@ Plan plan_product(Product product, int M, int N, int K) {
     return p;
   }
   if (stream) {
-    if (!wide_on_request(M, N, K)) return p;
-    best_tile4(M, N, G, &shape, &S, 1);
-  } else if (S == 0) {
+    // A caller that has quantised to the widened format before it knew the size is served by the tiled kernel, in
+    // the slices it would have there (1024 outputs from 28672 at 300 tokens 32.1 us, unsliced 84.2).
+    if (M < kTileMinM4 || ov.stream_fields[1] != 0 || ov.stream_max[1] != 0) return p;
+    p.optional = true;
+  }
+  if (S == 0) {
     if (w4a4) best_tile4(M, N, G, &shape, &S);
     else plan_tile16(M, N, G, &shape, &S);
   }
@@ -759,9 +750,14 @@ int launch_product(Product product, const Plan& plan, const void* packed, const 
 int gemm(Product product, const void* packed, const void* act, const float* sa, int M, int N, int K, int group,
          void* y_f16, void* workspace, size_t workspace_bytes, void* stream) {
   if (int st = check_gemm(packed, act, sa, M, N, K, group, y_f16)) return st;
-  const Plan plan = plan_product(product, M, N, K);
-  if (plan.kernel == Kernel::none) return QSPEC_ERR_UNSUPPORTED;   // this shape runs on a kernel that reads packed codes
-  if (plan.need > 0 && (!workspace || workspace_bytes < plan.need)) return QSPEC_ERR_WORKSPACE;
+  Plan plan = plan_product(product, M, N, K);
+  if (plan.kernel == Kernel::none) return QSPEC_ERR_UNSUPPORTED;   // too few tokens for the widened format
+  if (plan.need > 0 && (!workspace || workspace_bytes < plan.need)) {
+    if (!plan.optional) return QSPEC_ERR_WORKSPACE;
+    int shape = 0, S = 1;
+    best_tile4(M, N, K / kGroup, &shape, &S, 1);
+    plan.tile = tile_plan(true, M, N, K, shape, S);
+  }
   if (int st = check_device()) return st;
   return launch_product(product, plan, packed, act, sa, M, N, K, y_f16, workspace, static_cast<hipStream_t>(stream));
 }
@@ -792,9 +788,12 @@ size_t qspec_packed_weight_bytes(int N, int K, int group) {
 
 size_t qspec_workspace_bytes(int M, int N, int K, int group) {
   if (check_shape(M, N, K, group) != QSPEC_OK) return 0;
-  // the larger of what the two modes need for this shape
-  const size_t draft = plan_product(kDraft, M, N, K).need, verify = plan_product(kVerify, M, N, K).need;
-  return draft > verify ? draft : verify;
+  size_t most = 0;
+  for (Product product : {kVerify, kDraft, kDraftWide}) {
+    const size_t need = plan_product(product, M, N, K).need;
+    if (need > most) most = need;
+  }
+  return most;
 }
 
 int qspec_pack_weights(const int8_t* codes, const void* scales_f16, int N, int K, int group,
@@ -845,7 +844,8 @@ int qspec_quant_act(const void* x_f16, int M, int K, int group, uint8_t* qa, flo
 
 int qspec_w4a4_takes_wide(int M, int N, int K, int group) {
   if (check_shape(M, N, K, group) != QSPEC_OK) return 0;
-  return plan_product(kDraft, M, N, K).kernel == Kernel::tile ? 1 : 0;
+  const Plan plan = plan_product(kDraftWide, M, N, K);
+  return plan.kernel == Kernel::tile && !plan.optional ? 1 : 0;
 }
 
 int qspec_quant_act_wide(const void* x_f16, int M, int K, int group, int8_t* qa8, float* sa, void* stream) {
@@ -1070,12 +1070,14 @@ int qspec_describe_kernel(int mode_w4a4, int M, int N, int K, int group, char* o
   if (!out || cap == 0) return QSPEC_ERR_NULL;
   if (int st = check_shape(M, N, K, group)) return st;
   const char* b = mode_w4a4 ? "true" : "false";
-  const Plan plan = plan_product(mode_w4a4 ? kDraft : kVerify, M, N, K);
+  const bool wide = mode_w4a4 == 2;
+  const Plan plan = plan_product(wide ? kDraftWide : mode_w4a4 ? kDraft : kVerify, M, N, K);
+  if (plan.kernel == Kernel::none) return QSPEC_ERR_UNSUPPORTED;
   if (plan.kernel == Kernel::stream) {
     snprintf(out, cap, "gemm_stream_kernel<%s, %d, %d>", b, plan.stream.tm, plan.stream.nt);
   } else if (plan.kernel == Kernel::tile) {
     const TileShape& t = shape_of(mode_w4a4 != 0, plan.tile.shape);
-    if (mode_w4a4) snprintf(out, cap, "gemm_tile4w_kernel<%d, %d, %d, %d, %d, false>", t.TN, t.TMW, t.WGN, t.WGM, t.OCC);
+    if (mode_w4a4) snprintf(out, cap, "gemm_tile4w_kernel<%d, %d, %d, %d, %d, %s>", t.TN, t.TMW, t.WGN, t.WGM, t.OCC, wide ? "true" : "false");
     else if (t.TN == 2 && t.TMW == 4) snprintf(out, cap, "gemm_tile16w2_kernel");
     else snprintf(out, cap, "gemm_tile16w_kernel<%d, %d, %d, %d, %d, %d, %d>", t.TN, t.TMW, t.WGN, t.WGM, t.WGK, t.NW, t.OCC);
   } else if (mode_w4a4) snprintf(out, cap, "gemm_w4a4_generic<%d, 4, false>", pick_tm(M));

@@ -169,18 +169,36 @@ def test_wide_entry_points_refuse_what_they_cannot_do(env):
     assert L.qspec_quant_act_wide(ctypes.c_void_p(y.data_ptr() + 2), 1, 128, 128, vp(qa8), vp(sa), None) == B.ERR_ALIGN
 
 
-@pytest.mark.parametrize("M,N,K", [(65, 640, 8320), (130, 256, 512), (160, 256, 512), (235, 640, 1920), (300, 1040, 640)])
-def test_widened_format_stays_accepted_where_the_packed_one_is_advised(env, M, N, K):
+@pytest.mark.parametrize("M,N,K", [(25, 48, 1024), (40, 512, 2048), (65, 640, 8320), (130, 256, 512), (160, 256, 512),
+                                   (235, 640, 1920), (300, 1040, 640), (300, 1024, 4096)])
+def test_widened_format_is_accepted_where_the_packed_one_is_advised(env, M, N, K):
     """Sizes on which the packed format runs on the streaming kernel: a caller who has quantised to the
-    widened format is still served, without a workspace."""
+    widened format is served, with a workspace in the K-slices of the tiled kernel's plan, without one unsliced."""
     torch, B = env
     codes, scales, x = synth.generic_case(M + N, M, N, K)
     blob = B.pack_weights(dev(torch, codes), dev(torch, scales))
     q_ref, s_ref = orc.quant_act(x)
     ref = orc.gemm_w4a4(q_ref, s_ref, codes, scales)
     assert not B.w4a4_takes_wide(M, N, K)
+    assert B.describe_kernel(True, M, N, K, wide=True).startswith("gemm_tile4w_kernel<")
     qa8, sa = B.quant_act_wide(dev(torch, x))
-    ws = torch.zeros(16, dtype=torch.uint8, device="cuda") if B.workspace_bytes(M, N, K) == 0 else None
+    ws = B.alloc_workspace(max(B.workspace_bytes(M, N, K), 16))
     assert rel_err(B.gemm_w4a4_wide(blob, qa8, sa, N, workspace=ws).cpu().numpy(), ref) <= TOL
+    assert int(ws[:16384].count_nonzero()) == 0
+    y = torch.full((M, N), 7.0, dtype=torch.float16, device="cuda")
+    vp = lambda t: ctypes.c_void_p(t.data_ptr())
+    for short in (None, torch.zeros(1024, dtype=torch.uint8, device="cuda")):
+        rc = B.lib().qspec_gemm_w4a4_wide(vp(blob), vp(qa8), vp(sa), M, N, K, 128, vp(y), None if short is None else vp(short),
+                                          0 if short is None else 1024, ctypes.c_void_p(B._stream()))
+        assert rc == B.OK and rel_err(y.cpu().numpy(), ref) <= TOL
     qa, sa = B.quant_act(dev(torch, x))
     assert rel_err(B.gemm_w4a4(blob, qa, sa, N).cpu().numpy(), ref) <= TOL
+
+
+def test_slices_of_the_widened_product_where_the_packed_format_is_advised(env):
+    """qspec_workspace_bytes covers them, so a caller that asks gets them."""
+    torch, B = env
+    for M, N, K in [(300, 1024, 28672), (256, 4096, 11008), (214, 480, 24960)]:
+        assert not B.w4a4_takes_wide(M, N, K) and B.workspace_bytes(M, N, K) > 16384
+    with pytest.raises(B.QSpecError):                # below 25 tokens the format is refused
+        B.describe_kernel(True, 24, 512, 2048, wide=True)
