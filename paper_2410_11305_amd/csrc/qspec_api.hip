@@ -172,47 +172,65 @@ inline bool stream_nt_ok(int nt, int tm) {
 // tiles per workgroup when the rows are dealt to ms blocks: ceil(M / ms) rows, in whole tiles
 inline int stream_tm_split(int M, int ms) { return stream_tm(16 * (((M + ms - 1) / ms + 15) / 16)); }
 
-// What a streaming plan of more than 16 tokens costs, in microseconds.  ng groups fall to the busiest
-// wavefront (G / 8 on average), the workgroups of ceil(M / (16 tm)) token-row blocks fill `rounds`
-// rounds of the compute units:
+// What a streaming plan costs, in microseconds.  ng groups fall to the busiest wavefront (G / 8 on average), the
+// workgroups of ceil(M / (16 tm)) token-row blocks fill `rounds` rounds of the compute units:
 //   fixed + round (rounds - 1) + ng (group + again (rounds - 1)) + G / 8 x workgroups per unit x (load + tokens x share of live rows)
-// Fitted to timed plans: 4089 draft-mode problems of 17 to 600 tokens and 2116 verify-mode ones of 17 to 32
-// (layers 1024 to 57344 wide, 512 to 28672 long), every instance with the row blocks that cover M, on
-// rotating weights inside HIP graphs.  On the half of them that a fit had not seen the choice among
-// these and the tiled plans is 0.3 to 1.5 % slower than the best one.
-// Against the rules before it (rounds x tiles per wavefront, two row blocks at most up to 64 tokens, at
-// 65 to 128 only where one round covered the layer, none beyond) the draft mode takes 6 % less time at
-// 33 to 48 tokens, 7 % at 65 to 96, 24 % at 129 to 192, 12 % at 193 to 400; the verify mode 3 to 5 % at 17 to 32.
+// Fitted to timed plans, on rotating weights inside HIP graphs: in the draft mode 5500 problems of layers 128 to 57344
+// wide and 128 to 28672 long at 1 to 2050 tokens and 1400 layers of Llama-shaped blocks at 1 to 256, in the verify mode
+// 3300 and 1200 at 1 to 128, every instance with the row blocks that cover M.  On 520 problems timed afterwards
+// (profiles/stream_plan_times.txt) the choice among these and the tiled plans is 0.9 % slower than the best one on average and
+// 15 % at most (verify mode past 32 tokens, where a rule bounds it: 1.6 and 32 %), and takes no more than 1.12 times
+// what the kernels and rules before the cost tables took.  (Tables fitted to 17 to 600 tokens and layers from 512 long
+// and 1024 wide alone were too low where few workgroups or few groups leave nothing to hide the latency behind: 224
+// outputs from 10240 at 1200 tokens 17.1 us tiled, 23.4 as chosen; 11696 from 1152 at 43 tokens 8.6 us, 6.7 now.  A rule for up
+// to 16 tokens, rounds x groups per wavefront x (NT + activations), was 0.4 % behind the best instance on average on the
+// blocks' layers and 1.0 % on the others, 35 % at most; now 0.2, 0.4 and 16 %.)
 struct StreamCost { int tm, nt; double fixed, round, group, again, load, tokens; };
+// up to 16 tokens
+constexpr StreamCost kStreamFew4[] = {
+    {1, 1, 2.863, 0.51, 0.199, 0.093, 0.185, 0.081},
+    {1, 2, 2.956, 0.323, 0.277, 0.222, 0.31, 0.094},
+    {1, 3, 3.012, 0.167, 0.516, 0.519, 0.35, 0.087},
+    {1, 4, 3.145, 0.085, 0.581, 0.659, 0.501, 0.153},
+    {1, 6, 3.21, 1.465, 0.856, 1.045, 0.744, 0.248},
+};
+constexpr StreamCost kStreamFew16[] = {
+    {1, 1, 2.466, 0.476, 0.393, 0.135, 0.228, 0.187},
+    {1, 2, 2.503, 0.818, 0.555, 0.441, 0.277, 0.225},
+    {1, 3, 2.787, 0.255, 0.712, 0.566, 0.246, 0.346},
+    {1, 4, 2.875, 1.143, 0.865, 0.809, 0.303, 0.395},
+    {1, 6, 2.937, 1.552, 1.213, 1.185, 0.53, 0.435},
+};
+// from 17 tokens on
 constexpr StreamCost kStreamCost4[] = {
-    {1, 1, 2.885, 0, 0.114, 0.075, 0.244, 0.019},
-    {1, 2, 2.965, 0, 0.194, 0.144, 0.331, 0},
-    {1, 3, 2.961, 0.119, 0.41, 0.293, 0.336, 0},
-    {1, 4, 2.962, 0.179, 0.553, 0.385, 0.349, 0},
-    {1, 6, 3.111, 1.849, 0.813, 0.573, 0.441, 0},
-    {2, 1, 3.02, 0, 0.195, 0.133, 0.281, 0.07},
-    {2, 2, 2.908, 1.774, 0.413, 0.208, 0.288, 0.116},
-    {2, 3, 3.047, 1.963, 0.661, 0.444, 0.32, 0},
-    {2, 4, 3.089, 2.212, 0.828, 0.524, 0.372, 0},
-    {2, 6, 3.951, 3.029, 1.157, 0.856, 0.368, 0},
-    {4, 1, 3.234, 1.613, 0.32, 0.24, 0.36, 0.364},
-    {4, 2, 3.289, 2.517, 0.71, 0.462, 0.317, 0.285},
-    {4, 3, 4.128, 3.368, 1.017, 0.682, 0.432, 0.155},
-    {4, 4, 4.385, 3.54, 1.242, 0.935, 0.477, 0},
-    {8, 1, 3.655, 2.37, 0.837, 0.633, 0.634, 0.28},
-    {8, 2, 4.703, 3.791, 1.444, 1.115, 0.17, 0.637},
+    {1, 1, 2.545, 0.603, 0.238, 0.058, 0.204, 0},
+    {1, 2, 2.689, 0.575, 0.338, 0.124, 0.263, 0},
+    {1, 3, 2.908, 0.53, 0.536, 0.318, 0.249, 0},
+    {1, 4, 2.991, 0.504, 0.655, 0.405, 0.303, 0},
+    {1, 6, 3.22, 1.846, 0.95, 0.685, 0.307, 0},
+    {2, 1, 2.718, 0.624, 0.344, 0.111, 0.263, 0},
+    {2, 2, 2.97, 1.497, 0.467, 0.223, 0.375, 0},
+    {2, 3, 3.23, 1.894, 0.713, 0.488, 0.28, 0},
+    {2, 4, 3.352, 2.102, 0.864, 0.588, 0.334, 0},
+    {2, 6, 4.038, 2.866, 1.159, 0.803, 0.461, 0},
+    {4, 1, 2.887, 1.754, 0.639, 0.346, 0.339, 0.101},
+    {4, 2, 3.084, 2.145, 0.907, 0.585, 0.339, 0.135},
+    {4, 3, 4.091, 2.881, 1.24, 0.939, 0.225, 0.169},
+    {4, 4, 4.347, 3.215, 1.379, 1.046, 0.332, 0.081},
+    {8, 1, 3.39, 2.165, 1.349, 0.945, 0, 0.635},
+    {8, 2, 4.401, 3.307, 1.802, 1.41, 0, 0.579},
 };
 constexpr StreamCost kStreamCost16[] = {
-    {1, 1, 2.715, 0, 0.249, 0.09, 0.379, 0.085},
-    {1, 2, 2.87, 0.657, 0.372, 0.365, 0.452, 0.045},
-    {1, 3, 2.776, 0.043, 0.691, 0.517, 0.37, 0},
-    {1, 4, 2.791, 1.579, 0.895, 0.68, 0.364, 0},
-    {1, 6, 3.174, 1.86, 1.183, 1.178, 0.423, 0},
-    {2, 1, 2.811, 1.259, 0.404, 0.318, 0.427, 0.298},
-    {2, 2, 2.793, 1.632, 0.747, 0.635, 0.223, 0.439},
-    {2, 3, 3.053, 2.015, 1.042, 0.955, 0.09, 0.498},
-    {2, 4, 3.446, 1.815, 1.137, 1.167, 0.327, 0.379},
-    {2, 6, 5.129, 2.014, 1.21, 1.658, 0.699, 0.387},
+    {1, 1, 2.429, 0.103, 0.412, 0.139, 0.286, 0.058},
+    {1, 2, 2.53, 0.892, 0.582, 0.497, 0.18, 0.144},
+    {1, 3, 2.817, 0.332, 0.758, 0.578, 0.309, 0},
+    {1, 4, 2.938, 1.033, 0.877, 0.78, 0.404, 0},
+    {1, 6, 3.288, 1.359, 1.122, 1.13, 0.551, 0},
+    {2, 1, 2.391, 0.393, 0.702, 0.58, 0.093, 0.344},
+    {2, 2, 2.806, 0.87, 0.741, 0.73, 0.201, 0.517},
+    {2, 3, 3.165, 1.349, 1.03, 1.03, 0.074, 0.609},
+    {2, 4, 3.279, 1.416, 1.199, 1.246, 0.229, 0.515},
+    {2, 6, 3.969, 2.063, 1.388, 1.529, 0.979, 0.225},
 };
 constexpr int kMaxRowBlocks = 16;
 
@@ -230,20 +248,24 @@ double stream_cost(const StreamCost& c, int M, int N, int G, double over) {
   return start + again * (c.round + ng * c.again) + load * (c.load + c.tokens * M / (16.0 * c.tm * ms));
 }
 
-// Cheapest streaming plan of more than 16 tokens; one_round: among those that one round of workgroups covers.
-double best_stream(bool w4a4, int M, int N, int G, bool one_round, StreamPlan* p) {
+// Cheapest streaming plan; one_round: among those that one round of workgroups covers.
+template <size_t COUNT>
+double best_stream(const StreamCost (&costs)[COUNT], int M, int N, int G, bool one_round, bool bounded, StreamPlan* p) {
   double best = 1e30;
-  const int n = w4a4 ? (int)(sizeof(kStreamCost4) / sizeof(StreamCost)) : (int)(sizeof(kStreamCost16) / sizeof(StreamCost));
-  for (int i = 0; i < n; ++i) {
-    const StreamCost& c = w4a4 ? kStreamCost4[i] : kStreamCost16[i];
+  for (const StreamCost& c : costs) {
     const int ms = (M + 16 * c.tm - 1) / (16 * c.tm), blocks = (N / 16 + c.nt - 1) / c.nt;
     if (ms > kMaxRowBlocks || (c.tm > 1 && 8 * c.tm >= M)) continue;              // (a kernel of half the token tiles covers M)
     if (one_round && (ms > 8 || blocks * ms > kNumCU)) continue;
-    if (M > 32 && !overrides().stream_max[w4a4] && (long long)blocks * ms > 5 * kNumCU) continue;   // (not timed)
+    if (bounded && (long long)blocks * ms > 5 * kNumCU) continue;   // (the best of no timed problem past 32 tokens)
     const double cost = stream_cost(c, M, N, G, best);
     if (cost < best) { best = cost; p->nt = c.nt; p->tm = c.tm; p->ms = ms; p->S = 1; p->blocks = blocks; }
   }
   return best;
+}
+double best_stream(bool w4a4, int M, int N, int G, bool one_round, StreamPlan* p) {
+  const bool bounded = M > 32 && !overrides().stream_max[w4a4];
+  if (M <= 16) return w4a4 ? best_stream(kStreamFew4, M, N, G, one_round, bounded, p) : best_stream(kStreamFew16, M, N, G, one_round, bounded, p);
+  return w4a4 ? best_stream(kStreamCost4, M, N, G, one_round, bounded, p) : best_stream(kStreamCost16, M, N, G, one_round, bounded, p);
 }
 
 StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
@@ -262,24 +284,6 @@ StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
     p.nt = nt; p.S = S; p.ms = ms;
     p.blocks = (tiles + nt - 1) / nt;
     p.tm = ms > 1 ? stream_tm_split(M, ms) : stream_tm(M);
-    return p;
-  }
-  if (M <= 16) {
-    // Rounds over the 256 compute units x groups per wavefront x (NT weight tiles + the activation operand,
-    // in units of one weight tile of 1 KB), ties to the larger NT: 1 % slower than the best of the five
-    // instances on 3993 timed problems of 1 to 16 tokens, 12 % at most.  K-slices are never chosen: the exchange
-    // (write-through stores, a ticket, S dependent trips to memory) costs 4 to 10 us, more than any of these
-    // launches saves; the path stays available to the override and is covered by the tests.
-    const double act = w4a4 ? 0.4 : 1.6;
-    double best = 1e30;
-    for (int v : kStreamNts) {
-      const int blocks = (tiles + v - 1) / v;
-      const int rounds = (blocks + kNumCU - 1) / kNumCU, per_wave = (G + kStreamWaves - 1) / kStreamWaves;
-      const double cost = rounds * (per_wave * (v + act));
-      if (cost < best - 1e-9 || (cost < best + 1e-9 && v > p.nt)) { best = cost; p.nt = v; }
-    }
-    p.S = 1; p.ms = 1; p.tm = 1;
-    p.blocks = (tiles + p.nt - 1) / p.nt;
     return p;
   }
   // (verify mode past 32 tokens: only where one round of workgroups covers a layer of at most 8192 x 8192; the
@@ -442,19 +446,24 @@ void plan_tile16(int M, int N, int G, int* shape, int* slices) {
 // workgroups per compute unit in its last round of `places`:
 //   fixed + again (rounds - 1) + g (full (rounds - 1) + any + first min(f, 1) + second clamp(f - 1, 0, 1) + more max(f - 2, 0) + shared [f > 1])
 //   + with K-slices (slice0 + slice1 S + slice2 workgroups per unit) + out x workgroups per unit
-// Fitted to the problems of kStreamCost4 (and 600 to 3000 tokens on top) with the widened activation format.
-// Its predecessor, fill rules from sweeps over the Llama-shaped layers, sliced small layers too little and
-// wide ones at 65 to 96 tokens too much (51200 x 7936 at 72: 86.9 us in 128 x 64, 63.0 in 256 x 128 blocks).
-struct Tile4Cost { double fixed, again, full, any, first, second, more, shared, slice0, slice1, slice2, out; int places; };
+// Fitted to the problems of kStreamCost4 and 500 larger ones of up to 3000 tokens, with the widened activation format.
+// On packed codes, which the kernel widens in registers, the groups take `packed` times as long: that decides between
+// this kernel and the streaming one for a caller who has packed codes (34 tokens, 16656 outputs from 5248: streaming 19.9 us,
+// this kernel 22.2 on widened codes, 27.3 on packed ones).  Fill rules from sweeps over the Llama-shaped layers, its
+// predecessor, sliced small layers too little and wide ones at 65 to 96 tokens too much (51200 x 7936 at 72: 86.9 us in
+// 128 x 64, 63.0 in 256 x 128 blocks).
+struct Tile4Cost { double fixed, again, full, any, first, second, more, shared, slice0, slice1, slice2, out, packed; int places; };
 constexpr Tile4Cost kCost4[] = {
-    {5.849, 0.676, 1.17, 0.51, 0.167, 0.155, 0, 0.336, 0, 1.267, 3.859, 0.572, 2},   // 0: 128 x 128
-    {3.532, 0.481, 0.635, 0.366, 0.118, 0.017, 0, 0.164, 0, 1.186, 1.94, 0.631, 2},   // 1: 128 x 64
-    {3.609, 0.552, 0.754, 0.275, 0.126, 0.042, 0.071, 0.174, 1.393, 0.789, 0.233, 0.197, 4},   // 2: 64 x 64
-    {5.936, 4.332, 1.111, 0.761, 0.276, 0, 0, 0, 0.043, 2.048, 5.603, 1.045, 1},   // 3: 256 x 128
+    {4.673, 0.694, 1.09, 0.635, 0.035, 0.109, 0, 0.375, 1.134, 0.815, 3.458, 1.812, 1.175, 2},   // 0: 128 x 128
+    {3.582, 0.745, 0.609, 0.415, 0.034, 0.032, 0, 0.18, 1.453, 0.308, 1.841, 1.104, 1.177, 2},   // 1: 128 x 64
+    {3.43, 0.109, 0.736, 0.364, 0.038, 0.021, 0.073, 0.177, 1.761, 0.166, 0.682, 0.599, 1.282, 4},   // 2: 64 x 64
+    {5.255, 2.734, 1.03, 0.855, 0.152, 0, 0, 0, 3.027, 1.428, 3.697, 2.475, 1.105, 1},   // 3: 256 x 128
 };
 
-// Cheapest draft-mode tiled plan by kCost4 among those below `best`; without one, shape and slices stay as they are.
-double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices = 4, double best = 1e30) {
+struct Tile4Choice { int shape, S; double wide, packed; };      // S == 0: none
+// Cheapest draft-mode tiled plan on widened codes among those below `best`, and what it costs on either format.
+Tile4Choice best_tile4(int M, int N, int G, int max_slices = 4, double best = 1e30) {
+  Tile4Choice choice{0, 0, best, best};
   for (int i = 0; i < kNumTileShapes; ++i) {
     const TileShape& t = kShapes4[i];
     const Tile4Cost& c = kCost4[i];
@@ -465,18 +474,18 @@ double best_tile4(int M, int N, int G, int* shape, int* slices, int max_slices =
       // within 32 MiB), of four groups at least
       if (S > 1 && (blocks * S > (c.places > 1 ? 2 : 1) * kNumCU || G / S < 4)) break;
       const double g = ((G + S - 1) / S) * (0.7 + 0.3 * M / (double)(mb * bm));
-      if (c.fixed + c.any * g >= best) continue;
+      if (c.fixed + c.any * g >= choice.wide) continue;
       const long long wgs = blocks * S, load = (long long)c.places * kNumCU, rounds = (wgs + load - 1) / load;
       const double per_unit = (double)wgs / kNumCU, f = per_unit - (double)c.places * (rounds - 1);
       const auto clamp01 = [](double v) { return v < 0.0 ? 0.0 : v > 1.0 ? 1.0 : v; };
-      double cost = c.fixed + c.again * (rounds - 1) + c.out * per_unit +
-                    g * (c.full * (rounds - 1) + c.any + c.first * clamp01(f) + c.second * clamp01(f - 1) +
-                         c.more * (f > 2 ? f - 2 : 0.0) + (f > 1 ? c.shared : 0.0));
+      const double groups = g * (c.full * (rounds - 1) + c.any + c.first * clamp01(f) + c.second * clamp01(f - 1) +
+                                 c.more * (f > 2 ? f - 2 : 0.0) + (f > 1 ? c.shared : 0.0));
+      double cost = c.fixed + c.again * (rounds - 1) + c.out * per_unit + groups;
       if (S > 1) cost += c.slice0 + c.slice1 * S + c.slice2 * per_unit;
-      if (cost < best) { best = cost; *shape = i; *slices = S; }
+      if (cost < choice.wide) choice = Tile4Choice{i, S, cost, cost + (c.packed - 1.0) * groups};
     }
   }
-  return best;
+  return choice;
 }
 
 TilePlan tile_plan(bool w4a4, int M, int N, int K, int shape, int S) {
@@ -539,10 +548,10 @@ Plan plan_product(Product product, int M, int N, int K) {
     p.stream = plan_stream(w4a4, M, N, K);
     stream = p.stream.nt > 0;
   } else {                                         // draft mode: the cheaper of the two kernels
-    int best_shape = 0, best_S = 0;
-    best_tile4(M, N, G, &best_shape, &best_S, 4, best_stream(true, M, N, G, false, &p.stream));
-    stream = best_S == 0;
-    if (!forced_tile) { shape = best_shape; S = best_S; }
+    const double streaming = best_stream(true, M, N, G, false, &p.stream);
+    const Tile4Choice tiled = best_tile4(M, N, G, 4, streaming);
+    stream = tiled.S == 0 || (product == kDraft && tiled.packed >= streaming);
+    if (!forced_tile) { shape = tiled.shape; S = tiled.S; }
   }
   if (stream && product != kDraftWide) {
     p.kernel = Kernel::stream;
@@ -556,9 +565,11 @@ Plan plan_product(Product product, int M, int N, int K) {
     if (M < kTileMinM4 || ov.stream_fields[1] != 0 || ov.stream_max[1] != 0) return p;
     p.optional = true;
   }
-  if (S == 0) {
-    if (w4a4) best_tile4(M, N, G, &shape, &S);
-    else plan_tile16(M, N, G, &shape, &S);
+  if (S == 0 && w4a4) {
+    const Tile4Choice tiled = best_tile4(M, N, G);
+    shape = tiled.shape; S = tiled.S;
+  } else if (S == 0) {
+    plan_tile16(M, N, G, &shape, &S);
   }
   p.kernel = Kernel::tile;
   p.tile = tile_plan(w4a4, M, N, K, shape, S);
@@ -754,9 +765,7 @@ int gemm(Product product, const void* packed, const void* act, const float* sa, 
   if (plan.kernel == Kernel::none) return QSPEC_ERR_UNSUPPORTED;   // too few tokens for the widened format
   if (plan.need > 0 && (!workspace || workspace_bytes < plan.need)) {
     if (!plan.optional) return QSPEC_ERR_WORKSPACE;
-    int shape = 0, S = 1;
-    best_tile4(M, N, K / kGroup, &shape, &S, 1);
-    plan.tile = tile_plan(true, M, N, K, shape, S);
+    plan.tile = tile_plan(true, M, N, K, best_tile4(M, N, K / kGroup, 1).shape, 1);
   }
   if (int st = check_device()) return st;
   return launch_product(product, plan, packed, act, sa, M, N, K, y_f16, workspace, static_cast<hipStream_t>(stream));

@@ -1,7 +1,7 @@
 """The choice between the streaming and tiled kernels, and of their plans, against timed plans
-(profiles/stream_plan_times.txt): draft mode at 17 to 600 tokens, verify mode at 17 to 32.  Needs no GPU: the
-choice is a pure function of the sizes.  Bounds: the timings repeat within 3 %; the cost tables leave 1 % on
-average and 15 % at most on problems they were not fitted to."""
+(profiles/stream_plan_times.txt): the draft mode on both activation formats at 1 to 2050 tokens, the verify mode at
+1 to 128.  Needs no GPU: the choice is a pure function of the sizes.  Bounds: the timings repeat within 3 % (a few
+within 10 %); the cost tables leave 1 % on average, and 20 % at most but for a few per cent of layers with few groups."""
 import math
 import os
 import re
@@ -14,34 +14,58 @@ TABLE = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 BLOCK4 = [(128, 128, "1, 4, 4"), (128, 64, "1, 2, 4"), (64, 64, "1, 2, 2"), (256, 128, "1, 4, 8")]
 
 
-def _chosen(draft, M, N, K):
-    name = B.describe_kernel(draft, M, N, K)
+def _rows():
+    fitted = True
+    for line in open(TABLE):
+        if line.startswith("#"):
+            fitted = fitted and "not fitted to" not in line
+            continue
+        size, before, plans = line.split("|")
+        mode, M, N, K = size.split()
+        yield fitted, mode, int(M), int(N), int(K), float(before), {k: float(v) for k, v in (p.split(":") for p in plans.split())}
+
+
+def _chosen(mode, M, N, K):
+    wide = mode == "draft" and B.w4a4_takes_wide(M, N, K)      # (the advised format)
+    name = B.describe_kernel(mode != "verify", M, N, K, wide=wide)
     m = re.match(r"gemm_stream_kernel<\w+, (\d+), (\d+)>", name)
     if m:
         return f"stream{m.group(1)}.{m.group(2)}"
+    if mode == "verify":
+        return "tile"
     need = B.workspace_bytes(M, N, K)
     for shape, (bn, bm, args) in enumerate(BLOCK4):
         if f"<{args}, 1," in name:
             return f"tile{shape}.{max(1, (need - 16384) // (-(-N // bn) * -(-M // bm) * bn * bm * 4))}"
 
 
-def test_chosen_plans_are_near_the_best(plan):
-    plan("QSPEC_TILE_W4A16", "0,1")                       # (the verify mode's own workspace need is kept at none)
-    logs, slower, n = [], [], 0
-    for line in open(TABLE):
-        if line.startswith("#"):
-            continue
-        size, before, plans = line.split("|")
-        mode, M, N, K = size.split()
-        M, N, K, before = int(M), int(N), int(K), float(before)
-        times = {k: float(v) for k, v in (p.split(":") for p in plans.split())}
-        t = times.get(_chosen(mode == "draft", M, N, K), math.inf)    # a plan more than 20 % off the best is not listed
+def _judge(plan, rows, slower_bound):
+    logs, slower = [], []
+    for _, mode, M, N, K, before, times in rows:
+        plan("QSPEC_TILE_W4A16", None if mode == "verify" else "0,1")   # (draft: the verify mode's own workspace need at none)
+        t = times.get(_chosen(mode, M, N, K), math.inf)                 # a plan far off the best is not listed
         logs.append(math.log(t / min(times.values())))
-        if t > 1.12 * before:
-            slower.append((size, t, before))
-        n += 1
-    assert n == 320 and not slower, slower[:5]
-    assert max(logs) <= math.log(1.2) and sum(logs) / n <= math.log(1.02)
+        if t > slower_bound * before:
+            slower.append((mode, M, N, K, t, before))
+    return logs, slower
+
+
+def test_chosen_plans_are_near_the_best(plan):
+    rows = [r for r in _rows() if r[0]]
+    logs, slower = _judge(plan, rows, 1.12)
+    assert len(rows) == 320 and not slower, slower[:5]
+    assert max(logs) <= math.log(1.2) and sum(logs) / len(logs) <= math.log(1.02)
+
+
+@pytest.mark.parametrize("mode,count", [("draft", 150), ("packed", 220), ("verify", 150)])
+def test_chosen_plans_are_near_the_best_on_problems_no_fit_has_seen(plan, mode, count):
+    """The draft mode in its advised format and on packed codes alone (callers whose quantiser writes no other), layers
+    of a few groups, more than 600 tokens, and the verify mode past 32 tokens.  There the streaming kernel is
+    bounded by a rule, not by cost: up to 32 % behind the best plan, but no slower than with the kernels before."""
+    rows = [r for r in _rows() if not r[0] and r[1] == mode]
+    logs, slower = _judge(plan, rows, 1.12)
+    assert len(rows) == count and not slower, slower[:5]
+    assert max(logs) <= math.log(1.35 if mode == "verify" else 1.2) and sum(logs) / len(logs) <= math.log(1.02)
 
 
 @pytest.mark.parametrize("M", [17, 33, 48, 64, 65, 128, 129, 256, 512, 600, 2050, 20001])
