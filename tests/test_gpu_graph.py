@@ -33,7 +33,7 @@ def rel_err(y, ref):
     return float(np.max(np.abs(y.astype(np.float64) - ref.astype(np.float64))) / max(np.max(np.abs(ref.astype(np.float64))), 1e-30))
 
 
-@pytest.mark.parametrize("M,N,K,forced", [(150, 304, 896, "3"), (8, 512, 1024, None), (130, 2048, 4096, None)])
+@pytest.mark.parametrize("M,N,K,forced", [(150, 304, 896, "3"), (8, 512, 1024, None), (130, 2048, 4096, None), (100, 8288, 4224, None)])
 def test_graph_replays_match_eager(env, plan, M, N, K, forced):
     torch, B = env
     if forced:
@@ -42,6 +42,8 @@ def test_graph_replays_match_eager(env, plan, M, N, K, forced):
     codes, scales, x0 = synth.generic_case(1234 + M, M, N, K)
     blob = B.pack_weights(dev(torch, codes), dev(torch, scales))
     wide = B.w4a4_takes_wide(M, N, K)
+    assert wide == (M in (150, 100))                     # (100: the library's own plan, in K-slices on either format)
+    assert M != 100 or B.workspace_bytes(M, N, K) > 16384
     x = dev(torch, x0)
     qa = torch.empty((M, K // 2), dtype=torch.uint8, device="cuda")
     qa8 = torch.empty((M, K), dtype=torch.int8, device="cuda")

@@ -37,7 +37,8 @@ def rel_err(y, ref):
 SMALL_SHAPES = [(1, 128, 128), (3, 256, 256), (4, 1152, 1024), (5, 128, 1024), (16, 256, 128),
                 (17, 1152, 256), (33, 144, 384), (70, 272, 640), (130, 48, 1280), (200, 80, 256),
                 (40, 64, 128), (100, 32, 256), (65, 16, 128),
-                (1100, 144, 256), (2050, 272, 384)]          # prefill-sized M: many ragged token blocks
+                (1100, 144, 256), (2050, 272, 384),          # prefill-sized M: many ragged token blocks
+                (33, 8208, 256), (65, 8272, 256)]            # the draft mode's tiled kernel, 64 x 64 and 128 x 64 blocks
 
 
 # ------------------------------------------------------------------ pack
@@ -500,15 +501,15 @@ def test_bad_arguments_are_refused_on_device(env):
 
 # ------------------------------------------------------------------ many shapes
 def test_random_shapes_take_every_plan_and_match(env):
-    """150 seeded shapes across the planner's regimes (streaming kernels with 1..6 tiles,
-    K-slices, token-row blocks, the wide one-round plans, tiled kernels of every size
-    class): both modes against the oracle, and the set of kernels that ran is reported."""
+    """180 seeded shapes across the planner's regimes (streaming kernels with 1..6 tiles and up to
+    8 token tiles, K-slices, token-row blocks, small blocks of the tiled kernels): both modes against the
+    oracle, and the set of kernels that ran is reported."""
     torch, B = env
     rng = np.random.default_rng(2024)
     seen = {}
     worst = (0.0, None)
-    for case in range(150):
-        regime = case % 5
+    for case in range(180):
+        regime = case % 6
         if regime == 0:      # decoding batch, wide and narrow layers
             M, N, K = int(rng.integers(1, 33)), 16 * int(rng.integers(1, 700)), 128 * int(rng.integers(1, 24))
         elif regime == 1:    # mid batch
@@ -517,6 +518,8 @@ def test_random_shapes_take_every_plan_and_match(env):
             M, N, K = int(rng.integers(130, 700)), 16 * int(rng.integers(1, 80)), 128 * int(rng.integers(1, 10))
         elif regime == 3:    # long K, few columns (K-slices)
             M, N, K = int(rng.integers(1, 140)), 16 * int(rng.integers(1, 24)), 128 * int(rng.integers(24, 90))
+        elif regime == 4:    # wide layers, few groups (the draft mode's tiled kernel)
+            M, N, K = int(rng.integers(33, 140)), 16 * int(rng.integers(450, 900)), 128 * int(rng.integers(1, 4))
         else:                # tiny
             M, N, K = int(rng.integers(1, 20)), 16 * int(rng.integers(1, 6)), 128 * int(rng.integers(1, 4))
         while M * N * K > 3e8:
@@ -539,7 +542,8 @@ def test_random_shapes_take_every_plan_and_match(env):
     print("worst", worst, flush=True)
     for k in sorted(seen):
         print(f"  {seen[k]:4d}  {k}", flush=True)
-    assert len(seen) >= 12            # the sample reaches a broad set of instances
+    assert len(seen) >= 16            # the sample reaches a broad set of instances
+    assert sum(k.startswith("gemm_tile4w") for k in seen) >= 2 and sum(k.startswith("gemm_tile16w") for k in seen) >= 2
 
 
 @pytest.mark.parametrize("M", [33, 64, 150, 200])

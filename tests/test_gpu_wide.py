@@ -129,13 +129,12 @@ def test_wide_product_integer_stage_bit_exact(env, plan, shape, S):
 
 
 def test_wide_product_library_plans_and_ragged_shapes(env):
-    """The library's own plans on shapes that reach each tiled instance, with ragged tails."""
+    """The library's own plans on shapes that reach each tiled instance and K-slices, with ragged tails."""
     torch, B = env
-    seen = set()
-    for seed, (M, N, K) in enumerate([(65, 2064, 1024), (128, 12288, 1024), (200, 640, 3072), (257, 1040, 2048),
-                                      (512, 4096, 2048), (130, 39680, 256), (384, 8192, 5376)]):
-        if not B.w4a4_takes_wide(M, N, K):
-            continue
+    seen, sliced = set(), 0
+    for seed, (M, N, K) in enumerate([(33, 8208, 256), (65, 8272, 256), (128, 12288, 1024), (512, 4096, 2048), (130, 39680, 256),
+                                      (384, 8192, 5376), (100, 8288, 4224), (200, 36880, 256), (65, 39648, 256), (65, 16512, 6912)]):
+        assert B.w4a4_takes_wide(M, N, K), (M, N, K)
         codes, scales, x = synth.generic_case(900 + seed, M, N, K)
         blob = B.pack_weights(dev(torch, codes), dev(torch, scales))
         q_ref, s_ref = orc.quant_act(x)
@@ -143,8 +142,13 @@ def test_wide_product_library_plans_and_ragged_shapes(env):
         y = B.gemm_w4a4_wide(blob, qa8, sa, N).cpu().numpy()
         ref = orc.gemm_w4a4(q_ref, s_ref, codes, scales)
         assert rel_err(y, ref) <= TOL, (M, N, K)
-        seen.add(B.describe_kernel(True, M, N, K))
-    assert len(seen) >= 2, seen
+        seen.add(B.describe_kernel(True, M, N, K, wide=True))
+        y2 = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        rc = B.lib().qspec_gemm_w4a4_wide(blob.data_ptr(), qa8.data_ptr(), sa.data_ptr(), M, N, K, 128, y2.data_ptr(), None, 0, None)
+        sliced += rc == B.ERR_WORKSPACE                   # (only a plan with K-slices asks for one)
+        torch.cuda.synchronize()
+    assert seen == {f"gemm_tile4w_kernel<{block}, true>" for block in ("1, 2, 2, 1, 2", "1, 2, 4, 1, 2", "1, 4, 4, 1, 2", "1, 4, 8, 1, 1")}
+    assert sliced == 2
 
 
 def test_wide_entry_points_refuse_what_they_cannot_do(env):
