@@ -12,12 +12,13 @@ is off the token path) and is reported separately.
 
 The default run measures ALL five configurations in one process.  The headline
 (`value`, `ms_per_step`, `roofline`, `cpu_baseline` at the top level) is the
-largest one, configuration 5 (Llama-70B-shaped, batch 128); `configs` holds the
-same objects for every configuration, `ceilings` what the machine itself sustains
-(bare streaming reads, matrix-instruction loops) measured by a bench-only HIP
-library in the same run.
+largest one, configuration 5 (Llama-70B-shaped, batch 128); `configs` holds value,
+ms_per_step and microseconds per call of every configuration.
 
-Prints ONE JSON line:  value = algorithmic bytes of a step / time, in TB/s.
+Prints ONE JSON line on stdout:  value = algorithmic bytes of a step / time, in TB/s.
+On stderr, one JSON object a line: `ceilings`, what the machine itself sustains (bare
+streaming reads, matrix-instruction loops) measured by a bench-only HIP library in the
+same run, and everything measured for each configuration.
 """
 from __future__ import annotations
 
@@ -792,9 +793,14 @@ def main() -> int:
         "roofline": h["roofline"],
         "cpu_baseline": h["cpu_baseline"],
         "pack_weights_GBps": round(bench.pack_bytes / bench.t_pack / 1e9, 1) if bench.t_pack > 0 else None,
-        "ceilings": ceilings,
-        "configs": {str(ci): r for ci, r in results.items()},
+        "configs": {str(ci): {"value": r["value"], "ms_per_step": r["ms_per_step"],
+                              "us_per_call": {name: c["us"] for name, c in r["calls"].items()}} for ci, r in results.items()},
     }
+    # Everything else that was measured goes to stderr, one object a line: whoever keeps the end of stdout keeps the whole line.
+    print(json.dumps({"ceilings": ceilings}), file=sys.stderr)
+    for ci, r in results.items():
+        print(json.dumps({"config": ci, **r}), file=sys.stderr)
+    sys.stderr.flush()
     print(json.dumps(out))
     return 0
 
