@@ -164,11 +164,9 @@ def alloc_workspace(nbytes: int) -> torch.Tensor:
     return torch.zeros(max(int(nbytes), 16), dtype=torch.uint8, device="cuda")
 
 
-def _with_workspace(call, args, M, N, K, group, workspace) -> int:
-    """The status of call(*args, workspace, its size, stream).  Without a workspace one is allocated if the call asks
-    for it (convenience for tests: hot loops pass one from alloc_workspace instead)."""
-    if workspace is not None:
-        return call(*args, _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream())
+def _without_workspace(call, args, M, N, K, group) -> int:
+    """The status of call(*args, workspace, its size, stream) with a workspace of its own if the call asks for
+    one (convenience for tests: hot loops pass one from alloc_workspace instead)."""
     status = call(*args, None, 0, _stream())
     if status == ERR_WORKSPACE:
         workspace = alloc_workspace(workspace_bytes(M, N, K, group))
@@ -309,9 +307,14 @@ def gemm_w4a4(packed: torch.Tensor, qa: torch.Tensor, sa: torch.Tensor, N: int,
     M, K = qa.shape[0], qa.shape[1] * 2
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=qa.device)
-    args = (_dev(packed, torch.uint8, "packed"), _dev(qa, torch.uint8, "qa"), _dev(sa, torch.float32, "sa"),
-            M, N, K, group, _dev(y, torch.float16, "y"))
-    _check(_with_workspace(lib().qspec_gemm_w4a4, args, M, N, K, group, workspace), "qspec_gemm_w4a4")
+    if workspace is None:
+        args = (_dev(packed, torch.uint8, "packed"), _dev(qa, torch.uint8, "qa"), _dev(sa, torch.float32, "sa"), M, N, K, group, _dev(y, torch.float16, "y"))
+        status = _without_workspace(lib().qspec_gemm_w4a4, args, M, N, K, group)
+    else:
+        status = lib().qspec_gemm_w4a4(_dev(packed, torch.uint8, "packed"), _dev(qa, torch.uint8, "qa"), _dev(sa, torch.float32, "sa"),
+                                       M, N, K, group, _dev(y, torch.float16, "y"),
+                                       _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream())
+    _check(status, "qspec_gemm_w4a4")
     return y
 
 
@@ -320,12 +323,12 @@ def gemm_w4a4_wide(packed: torch.Tensor, qa8: torch.Tensor, sa: torch.Tensor, N:
     M, K = qa8.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=qa8.device)
-    args = (_dev(packed, torch.uint8, "packed"), _dev(qa8, torch.int8, "qa8"), _dev(sa, torch.float32, "sa"),
-            M, N, K, group, _dev(y, torch.float16, "y"))
     need = workspace_bytes(M, N, K, group) if workspace is None else 0
     if need:                              # (the call does not ask for one everywhere that it is faster with it)
         workspace = alloc_workspace(need)
-    _check(_with_workspace(lib().qspec_gemm_w4a4_wide, args, M, N, K, group, workspace), "qspec_gemm_w4a4_wide")
+    ws = (None, 0) if workspace is None else (_dev(workspace, torch.uint8, "workspace"), workspace.numel())
+    _check(lib().qspec_gemm_w4a4_wide(_dev(packed, torch.uint8, "packed"), _dev(qa8, torch.int8, "qa8"), _dev(sa, torch.float32, "sa"),
+                                      M, N, K, group, _dev(y, torch.float16, "y"), *ws, _stream()), "qspec_gemm_w4a4_wide")
     return y
 
 
@@ -334,9 +337,14 @@ def gemm_w4a16(packed: torch.Tensor, x: torch.Tensor, N: int, y: torch.Tensor = 
     M, K = x.shape
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    args = (_dev(packed, torch.uint8, "packed"), _dev(x, torch.float16, "x"),
-            M, N, K, group, _dev(y, torch.float16, "y"))
-    _check(_with_workspace(lib().qspec_gemm_w4a16, args, M, N, K, group, workspace), "qspec_gemm_w4a16")
+    if workspace is None:
+        args = (_dev(packed, torch.uint8, "packed"), _dev(x, torch.float16, "x"), M, N, K, group, _dev(y, torch.float16, "y"))
+        status = _without_workspace(lib().qspec_gemm_w4a16, args, M, N, K, group)
+    else:
+        status = lib().qspec_gemm_w4a16(_dev(packed, torch.uint8, "packed"), _dev(x, torch.float16, "x"),
+                                       M, N, K, group, _dev(y, torch.float16, "y"),
+                                       _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream())
+    _check(status, "qspec_gemm_w4a16")
     return y
 
 
