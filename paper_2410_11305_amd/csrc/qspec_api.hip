@@ -221,16 +221,16 @@ constexpr StreamCost kStreamCost4[] = {
     {8, 2, 4.401, 3.307, 1.802, 1.41, 0, 0.579},
 };
 constexpr StreamCost kStreamCost16[] = {
-    {1, 1, 2.429, 0.103, 0.412, 0.139, 0.286, 0.058},
-    {1, 2, 2.53, 0.892, 0.582, 0.497, 0.18, 0.144},
-    {1, 3, 2.817, 0.332, 0.758, 0.578, 0.309, 0},
-    {1, 4, 2.938, 1.033, 0.877, 0.78, 0.404, 0},
-    {1, 6, 3.288, 1.359, 1.122, 1.13, 0.551, 0},
-    {2, 1, 2.391, 0.393, 0.702, 0.58, 0.093, 0.344},
-    {2, 2, 2.806, 0.87, 0.741, 0.73, 0.201, 0.517},
-    {2, 3, 3.165, 1.349, 1.03, 1.03, 0.074, 0.609},
-    {2, 4, 3.279, 1.416, 1.199, 1.246, 0.229, 0.515},
-    {2, 6, 3.969, 2.063, 1.388, 1.529, 0.979, 0.225},
+    {1, 1, 2.427, 0.048, 0.422, 0.153, 0.268, 0.056},
+    {1, 2, 2.566, 0.872, 0.562, 0.493, 0.192, 0.147},
+    {1, 3, 2.846, 0.359, 0.73, 0.544, 0.336, 0},
+    {1, 4, 2.93, 1.039, 0.87, 0.778, 0.407, 0},
+    {1, 6, 3.288, 1.369, 1.108, 1.131, 0.556, 0},
+    {2, 1, 2.459, 0.483, 0.651, 0.531, 0.157, 0.331},
+    {2, 2, 2.796, 0.892, 0.736, 0.732, 0.194, 0.52},
+    {2, 3, 3.152, 1.367, 1.024, 1.028, 0.101, 0.573},
+    {2, 4, 3.289, 1.449, 1.17, 1.215, 0.268, 0.5},
+    {2, 6, 4.03, 2.05, 1.346, 1.505, 1.009, 0.225},
 };
 constexpr int kMaxRowBlocks = 16;
 
