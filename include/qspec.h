@@ -24,7 +24,7 @@
  *   - Shapes: group must be 128, K a positive multiple of 128, N a positive
  *     multiple of 16, M >= 1.  Anything else is QSPEC_ERR_SHAPE.
  *   - Input and output ranges must not overlap.
- *   - Non-finite activations: behaviour unspecified.
+ *   - Non-finite activations or weight scales: behaviour unspecified.
  *
  * Packed weight blob (written by qspec_pack_weights, N*K/2 + N*G*2 bytes)
  *   codes  : tiles of 16 output rows x 128 input features (one group), 1024
@@ -75,7 +75,7 @@ size_t qspec_packed_weight_bytes(int N, int K, int group);
 
 /* Scratch that is enough for every GEMM entry point on an (M,N,K) problem (partial
  * sums of K-slices that several workgroups produce); 0 when none of them needs any.
- * (A call that gets less is held against the need of its own mode.)  Returns 0 for
+ * (A call that gets less is held against the need of its own mode and format.)  Returns 0 for
  * unsupported shapes as well (the GEMM call reports those).
  * Workspace rule: the first 16 KiB of a workspace hold arrival counters.  They
  * must be ZERO when the first GEMM call that uses the workspace is enqueued;
@@ -210,7 +210,10 @@ int qspec_gemm_w4a4(const void* packed, const uint8_t* qa, const float* sa,
  *                           shape of 25 tokens or more; QSPEC_ERR_UNSUPPORTED (nothing
  *                           launched) below, and where a debug override asks for another
  *                           kernel.  Where qspec_w4a4_takes_wide is 0 it needs no workspace,
- *                           but is up to 3 times as fast with one of qspec_workspace_bytes.
+ *                           but is up to 3 times as fast in K-slices, which it takes if the
+ *                           workspace holds them: 32 MiB + 16 KiB always do, and
+ *                           qspec_workspace_bytes does for more than 128 tokens, more than 64
+ *                           where N or K > 8192, 48 and more where N >= 21760.
  */
 int qspec_w4a4_takes_wide(int M, int N, int K, int group);
 int qspec_quant_act_wide(const void* x_f16, int M, int K, int group,

@@ -562,7 +562,7 @@ Plan plan_product(Product product, int M, int N, int K) {
   if (stream) {
     // A caller that has quantised to the widened format before it knew the size is served by the tiled kernel, in
     // the slices it would have there (1024 outputs from 28672 at 300 tokens 32.1 us, unsliced 84.2).
-    if (M < kTileMinM4 || ov.stream_fields[1] != 0 || ov.stream_max[1] != 0) return p;
+    if (M < kTileMinM4 || ov.stream_fields[1] != 0 || ov.stream_max[1] != 0 || ov.generic) return p;
     p.optional = true;
   }
   if (S == 0 && w4a4) {
@@ -575,6 +575,13 @@ Plan plan_product(Product product, int M, int N, int K) {
   p.tile = tile_plan(w4a4, M, N, K, shape, S);
   p.need = plan_ws_bytes(w4a4, p.tile);
   return p;
+}
+
+// Where qspec_workspace_bytes covers optional slices: sizes that ran on the tiled kernel before the streaming one took
+// row blocks of every size, so that programs hold widened codes for them.  Not everywhere: a caller on packed
+// codes would allocate 4 to 32 MiB for nothing (0.2 to 0.3 ms before the first call of two decoder blocks at 32 tokens).
+bool covers_optional(int M, int N, int K) {
+  return M > 128 || (M > 64 && (N > 8192 || K > 8192)) || (M >= 48 && N >= 170 * 128);
 }
 
 template <int PN, int PM, int WGN, int WGM, int OCC>
@@ -799,8 +806,9 @@ size_t qspec_workspace_bytes(int M, int N, int K, int group) {
   if (check_shape(M, N, K, group) != QSPEC_OK) return 0;
   size_t most = 0;
   for (Product product : {kVerify, kDraft, kDraftWide}) {
-    const size_t need = plan_product(product, M, N, K).need;
-    if (need > most) most = need;
+    const Plan plan = plan_product(product, M, N, K);
+    if (plan.optional && !covers_optional(M, N, K)) continue;
+    if (plan.need > most) most = plan.need;
   }
   return most;
 }

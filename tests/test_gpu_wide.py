@@ -186,9 +186,10 @@ def test_widened_format_is_accepted_where_the_packed_one_is_advised(env, M, N, K
     assert not B.w4a4_takes_wide(M, N, K)
     assert B.describe_kernel(True, M, N, K, wide=True).startswith("gemm_tile4w_kernel<")
     qa8, sa = B.quant_act_wide(dev(torch, x))
-    ws = B.alloc_workspace(max(B.workspace_bytes(M, N, K), 16))
-    assert rel_err(B.gemm_w4a4_wide(blob, qa8, sa, N, workspace=ws).cpu().numpy(), ref) <= TOL
-    assert int(ws[:16384].count_nonzero()) == 0
+    for size in (max(B.workspace_bytes(M, N, K), 16), B.NOALLOC_SCRATCH_BYTES):       # (the second holds every plan's slices)
+        ws = B.alloc_workspace(size)
+        assert rel_err(B.gemm_w4a4_wide(blob, qa8, sa, N, workspace=ws).cpu().numpy(), ref) <= TOL
+        assert int(ws[:16384].count_nonzero()) == 0
     y = torch.full((M, N), 7.0, dtype=torch.float16, device="cuda")
     vp = lambda t: ctypes.c_void_p(t.data_ptr())
     for short in (None, torch.zeros(1024, dtype=torch.uint8, device="cuda")):
@@ -204,5 +205,6 @@ def test_slices_of_the_widened_product_where_the_packed_format_is_advised(env):
     torch, B = env
     for M, N, K in [(300, 1024, 28672), (256, 4096, 11008), (214, 480, 24960)]:
         assert not B.w4a4_takes_wide(M, N, K) and B.workspace_bytes(M, N, K) > 16384
+    assert B.workspace_bytes(32, 4096, 4096) == 0        # (nothing a caller on packed codes has no use for at few tokens)
     with pytest.raises(B.QSpecError):                # below 25 tokens the format is refused
         B.describe_kernel(True, 24, 512, 2048, wide=True)

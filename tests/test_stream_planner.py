@@ -39,7 +39,7 @@ def _chosen(mode, M, N, K):
             return f"tile{shape}.{max(1, (need - 16384) // (-(-N // bn) * -(-M // bm) * bn * bm * 4))}"
 
 
-def _judge(plan, rows, slower_bound):
+def _against(plan, rows, slower_bound):
     logs, slower = [], []
     for _, mode, M, N, K, before, times in rows:
         plan("QSPEC_TILE_W4A16", None if mode == "verify" else "0,1")   # (draft: the verify mode's own workspace need at none)
@@ -52,7 +52,7 @@ def _judge(plan, rows, slower_bound):
 
 def test_chosen_plans_are_near_the_best(plan):
     rows = [r for r in _rows() if r[0]]
-    logs, slower = _judge(plan, rows, 1.12)
+    logs, slower = _against(plan, rows, 1.12)
     assert len(rows) == 320 and not slower, slower[:5]
     assert max(logs) <= math.log(1.2) and sum(logs) / len(logs) <= math.log(1.02)
 
@@ -63,7 +63,7 @@ def test_chosen_plans_are_near_the_best_on_problems_no_fit_has_seen(plan, mode, 
     of a few groups, more than 600 tokens, and the verify mode past 32 tokens.  There the streaming kernel is
     bounded by a rule, not by cost: up to 32 % behind the best plan, but no slower than with the kernels before."""
     rows = [r for r in _rows() if not r[0] and r[1] == mode]
-    logs, slower = _judge(plan, rows, 1.12)
+    logs, slower = _against(plan, rows, 1.12)
     assert len(rows) == count and not slower, slower[:5]
     assert max(logs) <= math.log(1.35 if mode == "verify" else 1.2) and sum(logs) / len(logs) <= math.log(1.02)
 
@@ -85,6 +85,9 @@ def test_generic_override_leaves_nothing_above_32_tokens_to_the_other_kernels(pl
         assert re.match(r"gemm_w4a(4|16)_generic<", B.describe_kernel(draft, M, N, K))
     assert not B.w4a4_takes_wide(M, N, K) and B.workspace_bytes(M, N, K) == 0
     assert B.describe_kernel(True, 32, N, K).startswith("gemm_stream") and B.describe_kernel(False, 32, N, K).startswith("gemm_stream")
+    for m in (30, M):
+        with pytest.raises(B.QSpecError):                 # (no untiled kernel reads widened codes)
+            B.describe_kernel(True, m, N, K, wide=True)
 
 
 @pytest.mark.parametrize("bound", [32, 64, 100, 128])
