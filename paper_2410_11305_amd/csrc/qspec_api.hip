@@ -322,9 +322,12 @@ int launch_stream_tm(const StreamArgs& a, const StreamPlan& plan, hipStream_t s)
 template <bool W4A4>
 int launch_stream(const StreamPlan& plan, StreamArgs a, void* workspace, hipStream_t s) {
   if ((long long)plan.ms * 16 * plan.tm < a.M) return QSPEC_ERR_UNSUPPORTED;      // the row blocks must cover M
-  a.S = plan.S;
+  a.S = plan.S; a.per_slice = a.G / plan.S; a.more_slice = a.G % plan.S;
+  a.blocks = plan.blocks;
   a.ms = plan.ms;
   a.ms_rcp = (uint32_t)((0x100000000ull + plan.ms - 1) / plan.ms);
+  a.per_xcd = plan.blocks * plan.S * plan.ms >> 3;
+  a.more_xcd = plan.blocks * plan.S * plan.ms & 7;
   a.tickets = static_cast<unsigned*>(workspace);
   a.ws = plan.S > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kTicketBytes) : nullptr;
   switch (plan.tm) {
