@@ -20,6 +20,8 @@ HIPCC_FLAGS = [
     "-Rpass-analysis=kernel-resource-usage",
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # kernel arguments in scalar registers when a wavefront starts, where a kernel takes them one by one
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wno-unused-function",
 ]
 

@@ -65,7 +65,7 @@ struct StreamArgs {
   int ms;                    // token-row blocks (1 with K-slices)
   uint32_t ms_rcp;           // 2^32 / ms, rounded up
   int blocks;                // tile blocks
-  int per_xcd, more_xcd;     // workgroups / 8, workgroups % 8
+  uint32_t xcds;             // number of workgroups, as the kernel takes it
 };
 
 constexpr int kStreamWaves = 8;
@@ -105,8 +105,21 @@ __device__ __forceinline__ uint2 quad_transpose(float4 s, int lane) {
                __builtin_amdgcn_perm(got, v, odd ? 0x03020706u : 0x07060100u)};
 }
 
+// The first 14 dwords of the arguments arrive in scalar registers with the wavefront (build flag
+// amdgpu-kernarg-preload-count; only arguments passed one by one do): what the first loads need.  The rest is read
+// when it is needed.  (12288 x 4096 at 32 draft tokens 7.65 -> 7.35 us, 27648 x 5120 at 64: 24.2 -> 24.0.)
+struct StreamRest {
+  uint16_t* y;
+  float* ws;
+  unsigned* tickets;
+  int S, per_slice, more_slice, blocks;
+};
+
+// xcds: the number of workgroups (each XCD gets an eighth of them, the first ones one more); ms == 0: K-slices.
 template <bool W4A4, int TM, int NT>
-__global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(StreamArgs p) {
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(
+    const uint4* codes, const uint16_t* scalesT, const void* act_rows, const float* sa, int M, int N, int K, uint32_t xcds, int ms,
+    uint32_t ms_rcp, StreamRest rest) {
   using C = StreamShape<W4A4, TM, NT>;
   constexpr int W = C::W, QS = C::QS, CH = C::CH, T = NT * TM;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[W * C::kRegion];
@@ -117,20 +130,20 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
   // Workgroups go to the eight XCDs in turn: each XCD gets a run of adjacent tile blocks, and of each of
   // them all token-row blocks one after the other, so that they find its weights in that XCD's L2.
   const int xcd = blockIdx.x & 7;
-  const int bx = xcd * p.per_xcd + min(xcd, p.more_xcd) + (int)(blockIdx.x >> 3);
-  const int G = p.G;
-  const bool sliced = p.S > 1;
+  const int bx = xcd * (int)(xcds >> 3) + min(xcd, (int)(xcds & 7)) + (int)(blockIdx.x >> 3);
+  const int G = (int)((unsigned)K / kGroup);
+  const bool sliced = ms == 0;
   int tb = bx, slice = 0, s0 = 0, s1 = G, m_base = 0;
   if (__builtin_expect(sliced, 0)) {
-    tb = (int)((unsigned)bx / (unsigned)p.S); slice = bx - tb * p.S;
-    s0 = slice * p.per_slice + min(slice, p.more_slice); s1 = s0 + p.per_slice + (slice < p.more_slice ? 1 : 0);
-  } else if (p.ms > 1) {
-    tb = (int)__umulhi((unsigned)bx, p.ms_rcp);    // bx / ms (exact below 2^28 workgroups), in the scalar unit
-    m_base = (bx - tb * p.ms) * (16 * TM);
+    tb = (int)((unsigned)bx / (unsigned)rest.S); slice = bx - tb * rest.S;
+    s0 = slice * rest.per_slice + min(slice, rest.more_slice); s1 = s0 + rest.per_slice + (slice < rest.more_slice ? 1 : 0);
+  } else if (ms > 1) {
+    tb = (int)__umulhi((unsigned)bx, ms_rcp);    // bx / ms (exact below 2^28 workgroups), in the scalar unit
+    m_base = (bx - tb * ms) * (16 * TM);
   }
   const int T0 = tb * NT;
-  const int nt_valid = min(NT, (p.N >> 4) - T0);
-  const int Mloc = p.M - m_base;
+  const int nt_valid = min(NT, (N >> 4) - T0);
+  const int Mloc = M - m_base;
   if (Mloc <= 0) return;                           // (the whole workgroup: uniform)
   // group i of this wavefront, and how many it has: dealt round robin, QS adjacent ones at a time
   // (contiguous ranges per wavefront read the weights 10 to 20 % slower; workgroups that start at different
@@ -152,12 +165,12 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
 
   uint8_t* const mine = lds + wave * C::kRegion;
   if (n_g > 0) {
-    const uint32_t codes_bytes = (uint32_t)(p.N >> 1) * (uint32_t)p.K;        // (all below 2^31)
-    const uint32_t row_bytes = W4A4 ? (uint32_t)p.K >> 1 : (uint32_t)p.K * 2;
-    const uint8_t* const act = static_cast<const uint8_t*>(p.act) + (uint32_t)m_base * row_bytes;
+    const uint32_t codes_bytes = (uint32_t)(N >> 1) * (uint32_t)K;        // (all below 2^31)
+    const uint32_t row_bytes = W4A4 ? (uint32_t)K >> 1 : (uint32_t)K * 2;
+    const uint8_t* const act = static_cast<const uint8_t*>(act_rows) + (uint32_t)m_base * row_bytes;
     const rsrc_t r_act = make_rsrc(act, (uint32_t)Mloc * row_bytes);
-    const rsrc_t r_scales = make_rsrc(p.scalesT, (uint32_t)p.N * (uint32_t)G * 2);
-    const rsrc_t r_sa = make_rsrc(W4A4 ? (const void*)(p.sa + (uint32_t)m_base * (uint32_t)G) : (const void*)act, (uint32_t)Mloc * (uint32_t)G * 4);
+    const rsrc_t r_scales = make_rsrc(scalesT, (uint32_t)N * (uint32_t)G * 2);
+    const rsrc_t r_sa = make_rsrc(W4A4 ? (const void*)(sa + (uint32_t)m_base * (uint32_t)G) : (const void*)act, (uint32_t)Mloc * (uint32_t)G * 4);
     const uint32_t w_voff = lane * 16u;
     // activation loads of a step: kA of them, 1 KB each: 8 rows x 128 bytes (draft mode, two groups), 16 x 64
     // (draft mode, one group) or 4 x 256 (verify mode)
@@ -178,7 +191,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
       const bool ok = (QS == 1 || s * QS + q < n_g) && j < nt_valid;
       const uint32_t soff = ((uint32_t)(T0 + j) * (uint32_t)G + (uint32_t)grp(s * QS + q)) * 1024u;
       typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(p.codes, ok ? codes_bytes : 0u), w_voff, ok ? soff : 0u, 2);
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(codes, ok ? codes_bytes : 0u), w_voff, ok ? soff : 0u, 2);
       w[q][j] = uint4{v.x, v.y, v.z, v.w};
     };
     auto load_act = [&](int s) __attribute__((always_inline)) {
@@ -214,7 +227,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
         if (c0 + C::GPL * k >= n_g) break;
         const int i = c0 + C::GPL * k + z_grp;
         const uint32_t gone = ((uint32_t)((n_g - 1 - i) >> 31) | z_gone) << 31;
-        swr[k] = buf_load16(r_scales, ((uint32_t)grp(i) * (uint32_t)p.N * 2u + sw_voff) | gone);
+        swr[k] = buf_load16(r_scales, ((uint32_t)grp(i) * (uint32_t)N * 2u + sw_voff) | gone);
       }
     };
     // (what takes the longest way first: with few rows the scales, whose lines nobody else has asked for; otherwise the
@@ -424,12 +437,12 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
   // K-slices the sums go to the workspace first, and the workgroup that arrives last at the tile
   // block's counter adds the slices in slice order.
   const int kb = lane >> 4;
-  uint16_t* const ytile = p.y + (size_t)m_base * p.N + (size_t)T0 * 16 + (lane & 12);
+  uint16_t* const ytile = rest.y + (size_t)m_base * N + (size_t)T0 * 16 + (lane & 12);
   auto store_tile = [&](int o, float4 s) __attribute__((always_inline)) {
     const int j = o / TM, t = o - j * TM;
     const int m = 16 * t + 4 * kb + (lane & 3);
     const uint2 out = quad_transpose(s, lane);
-    if (j < nt_valid && m < Mloc) *reinterpret_cast<uint2*>(ytile + (size_t)m * p.N + j * 16) = out;
+    if (j < nt_valid && m < Mloc) *reinterpret_cast<uint2*>(ytile + (size_t)m * N + j * 16) = out;
   };
   // (overwrites only what this wavefront itself has read)
 #pragma unroll
@@ -450,7 +463,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
 #pragma unroll
       for (int u = 0; u < W; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
       if (__builtin_expect(sliced, 0)) {
-        float* f = p.ws + (((size_t)slice * p.blocks + tb) * T + o) * 256 + lane * 4;
+        float* f = rest.ws + (((size_t)slice * rest.blocks + tb) * T + o) * 256 + lane * 4;
         store_shared_f2(f, s.x, s.y);
         store_shared_f2(f + 2, s.z, s.w);
       } else {
@@ -459,12 +472,12 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(Strea
     }
   }
   if (!sliced) return;
-  if (!last_arrival(p.tickets, p.S, (unsigned)tb, &ticket)) return;
+  if (!last_arrival(rest.tickets, rest.S, (unsigned)tb, &ticket)) return;
   for (int o = wave; o < T; o += W) {
     if (16 * (o % TM) + 4 * kb >= Mloc) continue;
     float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int c = 0; c < p.S; ++c) {            // fixed order: the result does not depend on who came last
-      const float* f = p.ws + (((size_t)c * p.blocks + tb) * T + o) * 256 + lane * 4;
+    for (int c = 0; c < rest.S; ++c) {            // fixed order: the result does not depend on who came last
+      const float* f = rest.ws + (((size_t)c * rest.blocks + tb) * T + o) * 256 + lane * 4;
       const float2 a = load_shared_f2(f), b = load_shared_f2(f + 2);
       s.x += a.x; s.y += a.y; s.z += b.x; s.w += b.y;
     }

@@ -302,18 +302,23 @@ inline size_t stream_ws_bytes(const StreamPlan& p) {
 // instantiated (a forced plan can name one) is refused: nothing is launched.
 template <bool W4A4, int TM>
 int launch_stream_tm(const StreamArgs& a, const StreamPlan& plan, hipStream_t s) {
-  dim3 grid(plan.blocks * plan.S * plan.ms), block(kStreamWaves * 64);
+  const auto launch = [&](auto kernel) {
+    const StreamRest rest{a.y, a.ws, a.tickets, a.S, a.per_slice, a.more_slice, a.blocks};
+    hipLaunchKernelGGL(kernel, dim3(a.xcds), dim3(kStreamWaves * 64), 0, s, a.codes, a.scalesT, a.act, a.sa, a.M, a.N, a.K,
+                       a.xcds, a.S > 1 ? 0 : a.ms, a.ms_rcp, rest);
+    return QSPEC_OK;
+  };
   switch (plan.nt) {
-    case 1: hipLaunchKernelGGL((gemm_stream_kernel<W4A4, TM, 1>), grid, block, 0, s, a); return QSPEC_OK;
-    case 2: hipLaunchKernelGGL((gemm_stream_kernel<W4A4, TM, 2>), grid, block, 0, s, a); return QSPEC_OK;
+    case 1: return launch(gemm_stream_kernel<W4A4, TM, 1>);
+    case 2: return launch(gemm_stream_kernel<W4A4, TM, 2>);
     case 3:
-      if constexpr (TM <= 4) { hipLaunchKernelGGL((gemm_stream_kernel<W4A4, TM, 3>), grid, block, 0, s, a); return QSPEC_OK; }
+      if constexpr (TM <= 4) { return launch(gemm_stream_kernel<W4A4, TM, 3>); }
       return QSPEC_ERR_UNSUPPORTED;
     case 4:
-      if constexpr (TM <= 4) { hipLaunchKernelGGL((gemm_stream_kernel<W4A4, TM, 4>), grid, block, 0, s, a); return QSPEC_OK; }
+      if constexpr (TM <= 4) { return launch(gemm_stream_kernel<W4A4, TM, 4>); }
       return QSPEC_ERR_UNSUPPORTED;
     case 6:
-      if constexpr (TM <= 2) { hipLaunchKernelGGL((gemm_stream_kernel<W4A4, TM, 6>), grid, block, 0, s, a); return QSPEC_OK; }
+      if constexpr (TM <= 2) { return launch(gemm_stream_kernel<W4A4, TM, 6>); }
       return QSPEC_ERR_UNSUPPORTED;
     default: return QSPEC_ERR_UNSUPPORTED;
   }
@@ -326,8 +331,7 @@ int launch_stream(const StreamPlan& plan, StreamArgs a, void* workspace, hipStre
   a.blocks = plan.blocks;
   a.ms = plan.ms;
   a.ms_rcp = (uint32_t)((0x100000000ull + plan.ms - 1) / plan.ms);
-  a.per_xcd = plan.blocks * plan.S * plan.ms >> 3;
-  a.more_xcd = plan.blocks * plan.S * plan.ms & 7;
+  a.xcds = (uint32_t)(plan.blocks * plan.S * plan.ms);
   a.tickets = static_cast<unsigned*>(workspace);
   a.ws = plan.S > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kTicketBytes) : nullptr;
   switch (plan.tm) {
@@ -857,8 +861,7 @@ int qspec_quant_act(const void* x_f16, int M, int K, int group, uint8_t* qa, flo
   if (int st = check_device()) return st;
   const size_t n_words = (size_t)M * K / 8;
   hipLaunchKernelGGL(quant_act_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint4*>(x_f16),
-                     reinterpret_cast<uint32_t*>(qa), sa, n_words);
+                     static_cast<hipStream_t>(stream), QuantArgs{static_cast<const uint4*>(x_f16), reinterpret_cast<uint32_t*>(qa), sa, n_words});
   return launch_status();
 }
 
@@ -875,8 +878,7 @@ int qspec_quant_act_wide(const void* x_f16, int M, int K, int group, int8_t* qa8
   if (int st = check_device()) return st;
   const size_t n_words = (size_t)M * K / 8;
   hipLaunchKernelGGL(quant_act_wide_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint4*>(x_f16),
-                     reinterpret_cast<uint32_t*>(qa8), sa, n_words);
+                     static_cast<hipStream_t>(stream), QuantArgs{static_cast<const uint4*>(x_f16), reinterpret_cast<uint32_t*>(qa8), sa, n_words});
   return launch_status();
 }
 

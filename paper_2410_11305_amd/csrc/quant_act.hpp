@@ -101,38 +101,41 @@ __device__ inline void quantise_unit_wide(const float (&v)[8], bool live, size_t
   }
 }
 
-__global__ __launch_bounds__(256) void quant_act_kernel(const uint4* __restrict__ x,
-                                                        uint32_t* __restrict__ qa_words,
-                                                        float* __restrict__ sa,
-                                                        size_t n_words) {
+// (Arguments in one struct: at the 1.7 us that no launch goes below, reading them ahead of the wavefronts costs what a
+// launch of two workgroups does not get back: 1.78 -> 1.87 us.)
+struct QuantArgs {
+  const uint4* x;
+  uint32_t* qa_words;
+  float* sa;
+  size_t n_words;
+};
+
+__global__ __launch_bounds__(256) void quant_act_kernel(QuantArgs p) {
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = idx < n_words;
+  const bool live = idx < p.n_words;
   uint4 raw = {0u, 0u, 0u, 0u};
-  if (live) raw = x[idx];
+  if (live) raw = p.x[idx];
   float v[8];
   {
     const v8h h = __builtin_bit_cast(v8h, raw);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = (float)h[e];
   }
-  quantise_unit(v, live, idx, qa_words, sa);
+  quantise_unit(v, live, idx, p.qa_words, p.sa);
 }
 
-__global__ __launch_bounds__(256) void quant_act_wide_kernel(const uint4* __restrict__ x,
-                                                             uint32_t* __restrict__ qa8_words,
-                                                             float* __restrict__ sa,
-                                                             size_t n_words) {
+__global__ __launch_bounds__(256) void quant_act_wide_kernel(QuantArgs p) {
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = idx < n_words;
+  const bool live = idx < p.n_words;
   uint4 raw = {0u, 0u, 0u, 0u};
-  if (live) raw = x[idx];
+  if (live) raw = p.x[idx];
   float v[8];
   {
     const v8h h = __builtin_bit_cast(v8h, raw);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = (float)h[e];
   }
-  quantise_unit_wide(v, live, idx, qa8_words, sa);
+  quantise_unit_wide(v, live, idx, p.qa_words, p.sa);
 }
 
 }  // namespace qspec
