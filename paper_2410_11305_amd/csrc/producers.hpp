@@ -135,13 +135,13 @@ __device__ inline void finish_unit(float (&v)[8], bool rotate, bool live, size_t
 }
 
 // 1/sqrt(v) in binary64 to within a few units in the last place, v > 0 and normal: the
-// hardware estimate and three Newton steps (each squares the relative error), instead of
-// the correctly rounded square root and division, whose long dependent chains would sit
+// hardware estimate (2^-24, by the instruction set's description) and two Newton steps (each squares the relative
+// error), instead of the correctly rounded square root and division, whose long dependent chains would sit
 // on this kernel's critical path.  The result is rounded to binary32 straight away.
 __device__ inline double rsqrt_f64(double v) {
   double y = __builtin_amdgcn_rsq(v);
 #pragma unroll
-  for (int it = 0; it < 3; ++it) {
+  for (int it = 0; it < 2; ++it) {
     const double e = fma(-v * y, y, 1.0);                  // 1 - v y^2
     y = fma(y * 0.5, e, y);                                // y (1 + e/2)
   }
@@ -186,8 +186,12 @@ __global__ __launch_bounds__(kRowMaxThreads) void rmsnorm_quant_kernel(const uin
   __shared__ double part[kRowMaxThreads / 64];
   if ((tid & 63) == 0) part[tid >> 6] = ss;
   __syncthreads();
-  double total = part[0];
-  for (int i = 1; i < (T >> 6); ++i) total += part[i];
+  // (one read, four folds inside a row of 16 lanes; a chain of reads and additions takes longer from four wavefronts on)
+  double total = (tid & 15) < (T >> 6) ? part[tid & 15] : 0.0;
+  total += dpp_f64<0xB1>(total);
+  total += dpp_f64<0x4E>(total);
+  total += dpp_f64<0x141>(total);
+  total += dpp_f64<0x140>(total);
   const double v = total * inv_K + (double)eps;
   // v == 0 only for a zero row with eps == 0: the outputs are 0 * r, and r = inf would make them NaN
   const float r = v > 0.0 ? (float)rsqrt_f64(v) : 0.0f;
@@ -246,28 +250,29 @@ __device__ inline float silu_f32(float g) {
   return g == -__builtin_inff() ? __builtin_nanf("") : s;
 }
 
-// gate_up: fp16 [M][2I], the gate in the first I columns.  One thread per 8 outputs,
-// n_words = M * I / 8.  h_out may be null.
-__global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint4* __restrict__ gate_up, int I8,
+// gate_up: fp16 [M][2I], the gate in the first I columns.  One thread per 8 outputs, a row of the grid per token
+// (its last workgroup ragged; a 64-bit division per thread to find the row costs more).  h_out may be null.
+__global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint4* __restrict__ gate_up, int I8, int M, int rotate,
                                                              uint32_t* __restrict__ qa_words,
-                                                             float* __restrict__ sa, uint4* __restrict__ h_out,
-                                                             size_t n_words, int rotate) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = idx < n_words;
-  uint4 graw = {0u, 0u, 0u, 0u}, uraw = {0u, 0u, 0u, 0u};
-  if (live) {
-    const size_t m = idx / (size_t)I8, p = idx - m * (size_t)I8;
-    graw = gate_up[m * 2 * (size_t)I8 + p];
-    uraw = gate_up[m * 2 * (size_t)I8 + (size_t)I8 + p];
-  }
-  const v8h gh = __builtin_bit_cast(v8h, graw);
-  const v8h uh = __builtin_bit_cast(v8h, uraw);
-  float v[8];
+                                                             float* __restrict__ sa, uint4* __restrict__ h_out) {
+  const int p = blockIdx.x * 256 + threadIdx.x;
+  const bool live = p < I8;
+  for (int m = blockIdx.y; m < M; m += gridDim.y) {        // (more than once past 65535 tokens only)
+    const uint4* const row = gate_up + (size_t)m * 2 * I8;
+    uint4 graw = {0u, 0u, 0u, 0u}, uraw = {0u, 0u, 0u, 0u};
+    if (live) {
+      graw = row[p];
+      uraw = row[I8 + p];
+    }
+    const v8h gh = __builtin_bit_cast(v8h, graw);
+    const v8h uh = __builtin_bit_cast(v8h, uraw);
+    float v[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    v[e] = (float)(_Float16)rounded_f32(silu_f32((float)gh[e]) * (float)uh[e]);
+    for (int e = 0; e < 8; ++e) {
+      v[e] = (float)(_Float16)rounded_f32(silu_f32((float)gh[e]) * (float)uh[e]);
+    }
+    finish_unit(v, (rotate & 1) != 0, live, (size_t)m * I8 + p, qa_words, sa, h_out, (rotate & 2) != 0);
   }
-  finish_unit(v, (rotate & 1) != 0, live, idx, qa_words, sa, h_out, (rotate & 2) != 0);
 }
 
 __global__ __launch_bounds__(256) void hadamard_quant_kernel(const uint4* __restrict__ x,
@@ -339,26 +344,21 @@ __global__ __launch_bounds__(256) void reorder_quant_kernel(const uint16_t* __re
   const size_t wbase = (m * (size_t)Gx + og) * 16 + wpos;
   const size_t hbase = (m * (size_t)Gx + og) * 16 + kw;   // 16-byte pieces of the fp16 row
   if (!outlier) {
-    const float s = a / 7.0f;
-    uint32_t w = 0;
-    if (a > 0.0f) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float t = rintf(v[e] / s);
-        t = fminf(fmaxf(t, -8.0f), 7.0f);
-        w |= ((uint32_t)(int)t & 0xFu) << (4 * nibble_pos(e));
-      }
-    }
-    qa_words[wbase] = w;
+    float s;
+    qa_words[wbase] = code_word(v, a, &s);
     if (kw == 0) sa[m * (size_t)Gx + og] = s;
     if (h_out != nullptr) h_out[hbase] = __builtin_bit_cast(uint4, raw);
   } else {
-    const float s = a / 119.0f;
+    const bool finite = a < __builtin_inff();
+    float s, y;
+    scale_and_reciprocal<119>(a, s, y);
+    s = finite ? s : a;
     uint32_t whi = 0, wlo = 0;
     if (a > 0.0f) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        float t = rintf(v[e] / s);
+        const float q = div_by_reciprocal(v[e], s, y);
+        float t = rintf(finite ? q : v[e] * 0.0f);
         t = fminf(fmaxf(t, -119.0f), 119.0f);
         const int q8 = (int)t;
         const int lo = ((q8 + 8) & 15) - 8;

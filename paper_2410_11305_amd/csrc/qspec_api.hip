@@ -915,10 +915,9 @@ int qspec_silu_mul_quant(const void* gate_up_f16, int M, int I, int group,
   if (rotate < 0 || rotate > 3) return QSPEC_ERR_SHAPE;
   if (misaligned(gate_up_f16) || misaligned(qa) || misaligned(sa) || misaligned(h_f16)) return QSPEC_ERR_ALIGN;
   if (int st = check_device()) return st;
-  const size_t n_words = (size_t)M * I / 8;
-  hipLaunchKernelGGL(silu_mul_quant_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint4*>(gate_up_f16), I / 8,
-                     reinterpret_cast<uint32_t*>(qa), sa, static_cast<uint4*>(h_f16), n_words, rotate);
+  hipLaunchKernelGGL(silu_mul_quant_kernel, dim3(blocks_for(I / 8, 256), M < 65535 ? M : 65535), dim3(256), 0,
+                     static_cast<hipStream_t>(stream), static_cast<const uint4*>(gate_up_f16), I / 8, M, rotate,
+                     reinterpret_cast<uint32_t*>(qa), sa, static_cast<uint4*>(h_f16));
   return launch_status();
 }
 

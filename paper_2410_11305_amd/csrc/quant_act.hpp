@@ -42,19 +42,30 @@ __device__ inline float div_by_reciprocal(float v, float s, float y) {
   return __builtin_fmaf(__builtin_fmaf(-q, s, v), y, q);
 }
 
-// quantise_word: the arithmetic alone.  v = this thread's 8 activations (fp16 values
-// widened to binary32); returns its code word (8 nibbles in the device nibble order)
+// s = a / L and 1 / s, both correctly rounded, for L = 7 or 119 and a finite fp16 value a > 0.  a / L: one remainder
+// step from the rounded reciprocal of L (Markstein).  1 / s: one from the hardware estimate (within one unit in the last
+// place), which rounds correctly unless every bit of the significand of s is set; the binary fractions of sevenths and
+// 119ths of 11-bit integers repeat every 3 and 24 digits and hold zeros in any 24.  (Checked for all 31743 values of a and
+// estimates one unit off on either side.)  Two divisions as the compiler expands them are a chain of some forty operations.
+template <int L>
+__device__ inline void scale_and_reciprocal(float a, float& s, float& y) {
+  constexpr float kRcp = 1.0f / L;
+  const float q = a * kRcp;
+  s = __builtin_fmaf(__builtin_fmaf(-q, (float)L, a), kRcp, q);
+  const float e = __builtin_amdgcn_rcpf(s);
+  y = __builtin_fmaf(__builtin_fmaf(-s, e, 1.0f), e, e);
+}
+
+// code_word, quantise_word: the arithmetic alone, with and without the largest magnitude a of the group.  v = this
+// thread's 8 activations (fp16 values widened to binary32); returns its code word (8 nibbles in the device nibble order)
 // and the group's scale.  Every lane of the wavefront must call it (the shuffles).
-__device__ inline uint32_t quantise_word(const float (&v)[8], float* s_out) {
-  float a = 0.0f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(v[e]));
-  a = row16_max(a);
-  const float s = a / 7.0f;
+__device__ inline uint32_t code_word(const float (&v)[8], float a, float* s_out) {
+  const bool finite = a < __builtin_inff();      // (an infinite scale: x / inf, which has no remainder)
+  float s, y;
+  scale_and_reciprocal<7>(a, s, y);
+  s = finite ? s : a;
   uint32_t w = 0;
   if (a > 0.0f) {
-    const bool finite = a < __builtin_inff();    // (an infinite scale: x / inf, which has no remainder)
-    const float y = 1.0f / s;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float q = div_by_reciprocal(v[e], s, y);
@@ -65,6 +76,13 @@ __device__ inline uint32_t quantise_word(const float (&v)[8], float* s_out) {
   }
   *s_out = s;
   return w;
+}
+
+__device__ inline uint32_t quantise_word(const float (&v)[8], float* s_out) {
+  float a = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(v[e]));
+  return code_word(v, row16_max(a), s_out);
 }
 
 // quantise_unit: quantise and store in the packed format.  idx = index of the thread's code

@@ -291,3 +291,14 @@ def test_bad_arguments_are_refused(env):
     with pytest.raises(B.QSpecError):
         B.hadamard_quant(torch.zeros((2, 192), dtype=torch.float16, device="cuda"))
     torch.cuda.synchronize()
+
+
+def test_silu_more_tokens_than_rows_of_the_grid(env):
+    """65535 rows of workgroups at most: the rows past that are the first rows' second trip."""
+    torch, B = env
+    M, I = 65535 + 70, 128
+    gu = (np.random.default_rng(5).standard_normal((M, 2 * I)) * 1.5).astype(np.float16)
+    qa, sa, _ = B.silu_mul_quant(dev(torch, gu))
+    rows = np.r_[0:3, 65530:M]
+    h_ref = prod.silu_mul_f16(gu[rows])
+    check_against(torch, qa[torch.from_numpy(rows).cuda()], sa[torch.from_numpy(rows).cuda()], None, h_ref)
