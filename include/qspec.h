@@ -355,7 +355,10 @@ int qspec_debug_set_plan(const char* name, const char* value);
  * Debug entry: name of the device kernel the GEMM entry points select for an
  * (M,N,K) problem, e.g. "gemm_stream_kernel<false, 2, 3>" (mode 0 = W4A16
  * verify, 1 = W4A4 draft, 2 = W4A4 draft on widened codes: QSPEC_ERR_UNSUPPORTED
- * where that is refused).  It matches the symbol a profiler reports, so that
+ * where that is refused).  A W4A16 product whose tokens do not fill whole
+ * blocks may run as two launches: mode 0 then names the kernel one launch would
+ * run on, 4 and 5 the first and the second launch (one launch: 4 its kernel, 5 an
+ * empty string).  It matches the symbol a profiler reports, so that
  * benchmark timings can be set beside profiler output.  Writes a NUL-terminated
  * string of at most cap-1 characters to `out` (host memory); returns a status.
  */

@@ -162,6 +162,7 @@ struct StreamPlan {
   int nt, S, blocks;
   int ms;       // token-row blocks; block i owns rows i*16*tm .. (i+1)*16*tm - 1
   int tm;       // 16-token tiles per workgroup (the kernel's TM)
+  double cost;  // microseconds by the cost tables; a forced plan has none
 };
 inline int stream_tm(int M) { return M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8; }   // 16-token tiles that cover M rows
 constexpr int kStreamNts[] = {1, 2, 3, 4, 6};
@@ -290,7 +291,7 @@ StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
   // tiled kernels have too few output blocks to fill the chip there.  128 tokens, 4096 x 4096: 15.5 us tiled, 9.6 here.)
   const bool past = !w4a4 && M > kStreamMaxM;
   if (past && (M > 128 || N > 8192 || K > 8192)) return p;          // nt == 0: no streaming plan
-  best_stream(w4a4, M, N, G, past, &p);
+  p.cost = best_stream(w4a4, M, N, G, past, &p);
   return p;
 }
 
@@ -418,8 +419,8 @@ double round_cost16(const TileCost& c, double f) {
   return c.above2 + (c.three - c.above2) * (f - 2.0);
 }
 
-// Cheapest verify-mode plan by kCost16.
-void plan_tile16(int M, int N, int G, int* shape, int* slices) {
+// Cheapest verify-mode plan by kCost16, and what it costs.
+double plan_tile16(int M, int N, int G, int* shape, int* slices) {
   double best = 1e30;
   for (int i = 0; i < kNumShapes16; ++i) {
     const TileShape& t = kShapes16[i];
@@ -447,6 +448,7 @@ void plan_tile16(int M, int N, int G, int* shape, int* slices) {
       if (cost < best) { best = cost; *shape = i; *slices = S; }
     }
   }
+  return best;
 }
 
 // What a draft-mode tiled plan costs, in microseconds: g groups per slice (times the share of live rows), f
@@ -526,6 +528,7 @@ struct Plan {
   TilePlan tile;
   size_t need;        // bytes of workspace
   bool optional;      // runs unsliced, so without any, where the workspace does not hold that
+  double cost;        // verify mode: microseconds by the cost tables; a forced plan has none
 };
 // Tokens from which the draft mode may run on the tiled kernel (the streaming one is always the faster below) and
 // the widened format is accepted
@@ -564,6 +567,7 @@ Plan plan_product(Product product, int M, int N, int K) {
     p.kernel = Kernel::stream;
     if (p.stream.nt == 0) p.stream = plan_stream(w4a4, M, N, K);
     p.need = stream_ws_bytes(p.stream);
+    p.cost = p.stream.cost;
     return p;
   }
   if (stream) {
@@ -576,12 +580,35 @@ Plan plan_product(Product product, int M, int N, int K) {
     const Tile4Choice tiled = best_tile4(M, N, G);
     shape = tiled.shape; S = tiled.S;
   } else if (S == 0) {
-    plan_tile16(M, N, G, &shape, &S);
+    p.cost = plan_tile16(M, N, G, &shape, &S);
   }
   p.kernel = Kernel::tile;
   p.tile = tile_plan(w4a4, M, N, K, shape, S);
   p.need = plan_ws_bytes(w4a4, p.tile);
   return p;
+}
+
+// A verify-mode product whose last block of 128 tokens is a short one can run as two launches: the whole blocks, and
+// the rows that are left on what is cheapest for so few.  The short block costs a workgroup as much as a full one,
+// and where it adds a round of workgroups or keeps a smaller shape from fitting one the rest is cheaper on its own, though
+// it reads the weights a second time: 11008 -> 4096 at 2050 tokens 190.8 us on 136 blocks of 512 x 128, 166.9 on
+// 256 of 256 x 128 and two rows on the streaming kernel; 21760 -> 7936 at 513 tokens 213 and 177.  The line lies at
+// 0.9 of the cost of the one launch: on 90 ragged products of 129 to 2050 tokens the second launch measures 0.06 more of it
+// than the tables say on average; of those below the line the slowest took 1.004 times the one launch, the mean 0.91.
+// No product needs more workspace for it.
+struct Split {
+  int rows;           // of the first launch; 0: one launch
+  Plan first, rest;
+};
+Split split_tokens(Product product, const Plan& whole, int M, int N, int K) {
+  Split s{};
+  const int rows = M / 128 * 128, left = M - rows;
+  if (product != kVerify || whole.kernel != Kernel::tile || whole.cost == 0.0 || rows == 0 || left == 0) return s;
+  s.first = plan_product(product, rows, N, K);
+  if (s.first.cost == 0.0 || s.first.cost >= 0.9 * whole.cost || s.first.need > whole.need) return s;
+  s.rest = plan_product(product, left, N, K);
+  if (s.rest.cost > 0.0 && s.rest.need <= whole.need && s.first.cost + s.rest.cost < 0.9 * whole.cost) s.rows = rows;
+  return s;
 }
 
 // Where qspec_workspace_bytes covers optional slices: sizes that ran on the tiled kernel before the streaming one took
@@ -772,6 +799,16 @@ int launch_product(Product product, const Plan& plan, const void* packed, const 
   return launch_status();
 }
 
+// One launch, or two (split_tokens).
+int launch_whole_or_split(Product product, const Plan& plan, const void* packed, const void* act, const float* sa,
+                          int M, int N, int K, void* y_f16, void* workspace, hipStream_t s) {
+  const Split split = split_tokens(product, plan, M, N, K);
+  if (split.rows == 0) return launch_product(product, plan, packed, act, sa, M, N, K, y_f16, workspace, s);
+  if (int st = launch_product(product, split.first, packed, act, sa, split.rows, N, K, y_f16, workspace, s)) return st;
+  return launch_product(product, split.rest, packed, static_cast<const uint8_t*>(act) + (size_t)split.rows * K * 2, sa,
+                        M - split.rows, N, K, static_cast<uint8_t*>(y_f16) + (size_t)split.rows * N * 2, workspace, s);
+}
+
 int gemm(Product product, const void* packed, const void* act, const float* sa, int M, int N, int K, int group,
          void* y_f16, void* workspace, size_t workspace_bytes, void* stream) {
   if (int st = check_gemm(packed, act, sa, M, N, K, group, y_f16)) return st;
@@ -782,7 +819,7 @@ int gemm(Product product, const void* packed, const void* act, const float* sa, 
     plan.tile = tile_plan(true, M, N, K, best_tile4(M, N, K / kGroup, 1).shape, 1);
   }
   if (int st = check_device()) return st;
-  return launch_product(product, plan, packed, act, sa, M, N, K, y_f16, workspace, static_cast<hipStream_t>(stream));
+  return launch_whole_or_split(product, plan, packed, act, sa, M, N, K, y_f16, workspace, static_cast<hipStream_t>(stream));
 }
 
 }  // namespace
@@ -981,7 +1018,7 @@ int qspec_gemm_w4a16_noalloc(const void* packed, const void* x_f16, int M, int N
     // the counters must start at zero whatever an earlier (possibly failed) call left
     hipLaunchKernelGGL(clear_tickets_kernel, dim3(kMaxTickets / 256), dim3(256), 0, s, static_cast<unsigned*>(ws), kMaxTickets);
   }
-  return launch_product(kVerify, plan, packed, x_f16, nullptr, M, N, K, y_f16, ws, s);
+  return launch_whole_or_split(kVerify, plan, packed, x_f16, nullptr, M, N, K, y_f16, ws, s);
 }
 
 size_t qspec_mlp_draft_workspace_bytes(int M, int H, int I, int group) {
@@ -1090,10 +1127,17 @@ int qspec_debug_set_plan(const char* name, const char* value) {
 int qspec_describe_kernel(int mode_w4a4, int M, int N, int K, int group, char* out, size_t cap) {
   if (!out || cap == 0) return QSPEC_ERR_NULL;
   if (int st = check_shape(M, N, K, group)) return st;
+  const int launch = mode_w4a4 == 4 || mode_w4a4 == 5 ? mode_w4a4 - 3 : 0;      // of the verify mode's launches: 0 the plan of one
+  if (launch) mode_w4a4 = 0;
   const char* b = mode_w4a4 ? "true" : "false";
   const bool wide = mode_w4a4 == 2;
-  const Plan plan = plan_product(wide ? kDraftWide : mode_w4a4 ? kDraft : kVerify, M, N, K);
+  Plan plan = plan_product(wide ? kDraftWide : mode_w4a4 ? kDraft : kVerify, M, N, K);
   if (plan.kernel == Kernel::none) return QSPEC_ERR_UNSUPPORTED;
+  if (launch) {
+    const Split split = split_tokens(kVerify, plan, M, N, K);
+    if (launch == 2 && split.rows == 0) { out[0] = 0; return QSPEC_OK; }
+    if (split.rows) { plan = launch == 1 ? split.first : split.rest; M = launch == 1 ? split.rows : M - split.rows; }
+  }
   if (plan.kernel == Kernel::stream) {
     snprintf(out, cap, "gemm_stream_kernel<%s, %d, %d>", b, plan.stream.tm, plan.stream.nt);
   } else if (plan.kernel == Kernel::tile) {
