@@ -61,7 +61,8 @@ constexpr int waitcnt_vm(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 
 constexpr int waitcnt_vm_lgkm0(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4); }
 
 template <int PN, int PM, int WGN, int WGM, int WGK, int NW, int OCC>
-__global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel(TileArgs p) {
+__global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel(QSPEC_TILE_PARAMS) {
+  const TileArgs p = QSPEC_TILE_ARGS;
   constexpr int kWaves = WGN * WGM * WGK;
   constexpr int kTileWaves = WGN * WGM;                // the waves that cover the output block once
   constexpr int BM = 32 * PM * WGM;
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   const int wn = wt % WGN, wm = wt / WGN;
   const int m32 = lane & 31, h = lane >> 5;
   const int G = p.G;
-  const TileCoord tc = tile_coord(p);
+  const TileCoord tc = tile_coord(p, total);
   const int g0 = tc.g0, g1 = tc.g1;
   const int n0 = (tc.nblk * (PN * WGN) + wn * PN) * 32;      // first output feature of this wave
   const int m0 = tc.mblk * BM;
@@ -150,9 +151,11 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.0f;
 
+  dma_x(0, xs0);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int d = 0; d < NW; ++d) load_w(d, d);
-  dma_x(0, xs0);
+  __builtin_amdgcn_sched_barrier(0);
 
   v2h s2[PN], s2n[PN], wa0[PN][4];
 #pragma unroll
@@ -163,7 +166,7 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
 #pragma unroll
     for (int hh = 0; hh < 4; ++hh) wa0[j][hh] = dequant_pair_scaled(wlo[0][j].x, hh, s2[j]);
   }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * PN * NW));       // (the activations; of the weights the first group has been waited for)
   __builtin_amdgcn_s_barrier();
 
   constexpr int Q = PN * PM;                   // MFMAs per k-step (16 k), one LDS read feeds PN of them
@@ -307,7 +310,11 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
   if (WGK > 1 && nmine < ng) __builtin_amdgcn_s_barrier();
 
   if constexpr (WGK == 1) {
-    tile_store32<PN, PM, 64 * kWaves>(p, tc, acc, n0, m0 + mw0);
+    // (every wave's reads of the stages are behind the last group's barrier; transfers past the end may still be under way)
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __syncthreads();
+    static_assert(kWaves * 4096 * PN <= kStageBytes, "4096 PN bytes of a stage for each wave");
+    tile_store32<PN, PM, 64 * kWaves>(p, tc, acc, n0, m0 + mw0, xs0 + wave * (4096 * PN));
   } else {
     // Each of the WGK waves of an output tile set finishes PN * PM / WGK of its tiles.  All partial
     // sums go through LDS (a wave's own too: which tiles it finishes is not known at compile
@@ -318,26 +325,35 @@ __global__ __launch_bounds__(64 * WGN * WGM * WGK, OCC) void gemm_tile16w_kernel
     static_assert(kTileWaves * WGK * (kT / 2) * 4096 <= kStageBytes, "half the tiles fit a stage");
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     __syncthreads();
-    // partial src of tile t: float e of lane l at e * 64 + l
-    auto slot = [&](int t, int src) -> float* {
+    // partial src of tile t: floats 4a .. 4a+3 of lane l at a * 256 + 4 l
+    auto slot = [&](int t, int src) -> float4* {
       const int i = ((t % (kT / 2)) * WGK + src) * kTileWaves + wt;
-      return reinterpret_cast<float*>(t < kT / 2 ? xs0 : xs1) + i * 1024 + lane;
+      return reinterpret_cast<float4*>(t < kT / 2 ? xs0 : xs1) + i * 256 + lane;
     };
 #pragma unroll
     for (int t = 0; t < kT; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) slot(t, wk)[r * 64] = acc[t / PM][t % PM][r];
+      for (int a = 0; a < 4; ++a) {
+        const v16f& v = acc[t / PM][t % PM];
+        slot(t, wk)[a * 64] = float4{v[4 * a], v[4 * a + 1], v[4 * a + 2], v[4 * a + 3]};
+      }
     __syncthreads();
     float fin[1][PF][16];
 #pragma unroll
     for (int f = 0; f < PF; ++f)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        fin[0][f][r] = 0.0f;
+      for (int a = 0; a < 4; ++a) {
+        float4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int src = 0; src < WGK; ++src) fin[0][f][r] += slot(wk * PF + f, src)[r * 64];
+        for (int src = 0; src < WGK; ++src) {
+          const float4 v = slot(wk * PF + f, src)[a * 64];
+          sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+        }
+        fin[0][f][4 * a] = sum.x; fin[0][f][4 * a + 1] = sum.y; fin[0][f][4 * a + 2] = sum.z; fin[0][f][4 * a + 3] = sum.w;
       }
-    tile_store32<1, PF, 64 * kWaves>(p, tc, fin, n0 + 32 * (wk * PF / PM), m0 + mw0 + 32 * (wk * PF % PM));
+    // (only this wave reads the partial sums of its tiles: one of them is its scratch now)
+    tile_store32<1, PF, 64 * kWaves>(p, tc, fin, n0 + 32 * (wk * PF / PM), m0 + mw0 + 32 * (wk * PF % PM),
+                                     reinterpret_cast<uint8_t*>(slot(wk * PF, 0) - lane));
   }
 }
 

@@ -26,7 +26,8 @@
 
 namespace qspec {
 
-__global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
+__global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(QSPEC_TILE_PARAMS) {
+  const TileArgs p = QSPEC_TILE_ARGS;
   constexpr int PN = 2, PM = 4, kWaves = 8;
   constexpr int BM = 32 * PM;
   constexpr int kStageBytes = BM * 256;
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m32 = lane & 31, h = lane >> 5;
   const int G = p.G;
-  const TileCoord tc = tile_coord(p);
+  const TileCoord tc = tile_coord(p, total);
   const int n0 = (tc.nblk * kWaves + wave) * (PN * 32);
   const int m0 = tc.mblk * BM;
 
@@ -83,9 +84,11 @@ __global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
     for (int t = 0; t < PM; ++t)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.0f;
+  dma_x(0, xs0);
+  __builtin_amdgcn_sched_barrier(0);
   load_w(0, 0);
   load_w(1, 1);
-  dma_x(0, xs0);
+  __builtin_amdgcn_sched_barrier(0);
   v2h s2[PN], s2n[PN], wa0[PN][4];
 #pragma unroll
   for (int j = 0; j < PN; ++j) {
@@ -95,7 +98,7 @@ __global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
 #pragma unroll
     for (int hh = 0; hh < 4; ++hh) wa0[j][hh] = dequant_pair_scaled(wlo[0][j].x, hh, s2[j]);
   }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * PN * 2));        // (the activations; of the weights the first group has been waited for)
   __builtin_amdgcn_s_barrier();
   const int x_lane = m32 * 256 + ((h ^ (m32 & 15)) << 4);
   v8h xb[PM];
@@ -173,7 +176,11 @@ __global__ __launch_bounds__(512, 1) void gemm_tile16w2_kernel(TileArgs p) {
     group_body(std::integral_constant<int, 1>{}, q + 1);
   }
   if (G & 1) group_body(std::integral_constant<int, 0>{}, G - 1);      // (no stage is read behind it: its counted wait guards nothing)
-  tile_write_fp16<PN, PM, true>(p, acc, n0, m0);
+  // (every wave's reads of the stages are behind the last group's barrier; transfers past the end may still be under way)
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __syncthreads();
+  static_assert(kWaves * 4096 * PN == 2 * kStageBytes, "4096 PN bytes of the stages for each wave");
+  tile_write_rows<PN, PM>(p, acc, n0, m0, (wave < kWaves / 2 ? xs0 : xs1) + (wave % (kWaves / 2)) * (4096 * PN));
 }
 
 }  // namespace qspec

@@ -95,7 +95,8 @@ __device__ __forceinline__ void fmac_row_bcast_r(float& acc, float S, float t, i
 __device__ __forceinline__ int act_swizzle(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
 template <int PN, int PM, int WGN, int WGM, int OCC, bool WIDE = false>
-__global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileArgs p) {
+__global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(QSPEC_TILE_PARAMS) {
+  const TileArgs p = QSPEC_TILE_ARGS;
   constexpr int kWaves = WGN * WGM;
   constexpr int kThreads = 64 * kWaves;
   constexpr int BM = 32 * PM * WGM;
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
   const int wn = wave % WGN, wm = wave / WGN;
   const int l32 = lane & 31, h = lane >> 5;
   const int G = p.G;
-  const TileCoord tc = tile_coord(p);
+  const TileCoord tc = tile_coord(p, total);
   const int g0 = tc.g0, g1 = tc.g1;
   const int ng = g1 - g0;
   const int n0 = (tc.nblk * (PN * WGN) + wn * PN) * 32;      // first output feature of this wave
@@ -285,12 +286,16 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(TileAr
   load_sa3(0);
   if constexpr (WIDE) {
     dma_x(0, stage0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(0, 0);
     dma_x(1, stage1);
-#pragma unroll
-    for (int d = 0; d < NW; ++d) load_w(d, d);
+    load_w(1, 1);
+    load_w(2, 2);
+    __builtin_amdgcn_sched_barrier(0);
     store_sa(0);
     store_sa(1);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    // (group 0; group 1 has its place in the wait that ends group 0)
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * PN * NW + UD));
   } else {
     load_x(0);
     store_x(0);

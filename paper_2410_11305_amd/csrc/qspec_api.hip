@@ -618,25 +618,31 @@ bool covers_optional(int M, int N, int K) {
   return M > 128 || (M > 64 && (N > 8192 || K > 8192)) || (M >= 48 && N >= 170 * 128);
 }
 
+template <typename Kernel>
+int launch_tile_kernel(Kernel kernel, int threads, const TileArgs& a, hipStream_t s) {
+  const uint32_t total = (uint32_t)(a.nb * a.mb * a.S);
+  hipLaunchKernelGGL(kernel, dim3(total), dim3(threads), 0, s, a.codes, a.act, a.sa, a.M, a.N, a.K, a.S, a.mb, total, a.row_rcp,
+                     TileRest{a.y, a.ws, a.tickets, a.nb});
+  return QSPEC_OK;
+}
+
 template <int PN, int PM, int WGN, int WGM, int OCC>
 int launch_tile4w_inst(const TileArgs& a, bool wide, hipStream_t s) {
-  if (wide) hipLaunchKernelGGL((gemm_tile4w_kernel<PN, PM, WGN, WGM, OCC, true>), dim3(a.nb * a.mb * a.S),
-                               dim3(64 * WGN * WGM), 0, s, a);
-  else hipLaunchKernelGGL((gemm_tile4w_kernel<PN, PM, WGN, WGM, OCC, false>), dim3(a.nb * a.mb * a.S),
-                          dim3(64 * WGN * WGM), 0, s, a);
-  return QSPEC_OK;
+  return wide ? launch_tile_kernel(gemm_tile4w_kernel<PN, PM, WGN, WGM, OCC, true>, 64 * WGN * WGM, a, s)
+              : launch_tile_kernel(gemm_tile4w_kernel<PN, PM, WGN, WGM, OCC, false>, 64 * WGN * WGM, a, s);
 }
 
 template <int PN, int PM, int WGN, int WGM, int NW, int OCC, int WGK = 1>
 int launch_tile16w_inst(const TileArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_tile16w_kernel<PN, PM, WGN, WGM, WGK, NW, OCC>), dim3(a.nb * a.mb * a.S),
-                     dim3(64 * WGN * WGM * WGK), 0, s, a);
-  return QSPEC_OK;
+  return launch_tile_kernel(gemm_tile16w_kernel<PN, PM, WGN, WGM, WGK, NW, OCC>, 64 * WGN * WGM * WGK, a, s);
 }
 
 template <bool W4A4>
 int launch_tile(const TilePlan& plan, TileArgs a, void* workspace, hipStream_t s, bool wide = false) {
   a.S = plan.S; a.nb = plan.nb; a.mb = plan.mb;
+  // exact while total x (mb S) stays below 2^32
+  const uint64_t per_row = (uint64_t)plan.mb * plan.S;
+  a.row_rcp = per_row > 1 && per_row * per_row * plan.nb < 0x100000000ull ? (uint32_t)((0x100000000ull + per_row - 1) / per_row) : 0u;
   a.tickets = static_cast<unsigned*>(workspace);
   a.ws = plan.S > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kTicketBytes) : nullptr;
   if (W4A4) {
@@ -656,8 +662,7 @@ int launch_tile(const TilePlan& plan, TileArgs a, void* workspace, hipStream_t s
     case 5: return launch_tile16w_inst<2, 2, 2, 1, 2, 1, 4>(a, s);
     case 6: return launch_tile16w_inst<1, 2, 4, 1, 2, 3>(a, s);
     default:
-      hipLaunchKernelGGL(gemm_tile16w2_kernel, dim3(a.nb * a.mb), dim3(512), 0, s, a);
-      return QSPEC_OK;
+      return launch_tile_kernel(gemm_tile16w2_kernel, 512, a, s);
   }
 }
 

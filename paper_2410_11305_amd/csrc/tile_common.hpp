@@ -26,7 +26,25 @@ struct TileArgs {
   int M, N, K, G;
   int S;                     // K-slices
   int nb, mb;                // output blocks along N and along M
+  uint32_t row_rcp;          // 2^32 / (mb S), rounded up; 0: not exact for these sizes, divide
 };
+
+// What a kernel needs late; the rest comes as arguments of its own, 13 dwords, in scalar registers when a wavefront
+// starts (build flag amdgpu-kernarg-preload-count).
+struct TileRest {
+  uint16_t* y;
+  float* ws;
+  unsigned* tickets;
+  int nb;
+};
+#define QSPEC_TILE_PARAMS \
+  const uint4 *codes, const void *act, const float *sa, int M, int N, int K, int slices, int mb, uint32_t total, uint32_t row_rcp, TileRest rest
+// (the scales follow the code tiles)
+#define QSPEC_TILE_ARGS                                                                                                     \
+  TileArgs {                                                                                                                \
+    codes, reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(codes) + (uint32_t)(N >> 1) * (uint32_t)K), act, sa, \
+        rest.y, rest.ws, rest.tickets, M, N, K, (int)((unsigned)K / kGroup), slices, rest.nb, mb, row_rcp                        \
+  }
 
 // Which output block and K-slice a workgroup owns.  Workgroup ids are dealt
 // round-robin to the 8 XCDs (each with its own L2): ids with the same id % 8 are
@@ -34,23 +52,28 @@ struct TileArgs {
 // n-block, all m-blocks and K-slices) run on one XCD and fetch it from HBM once.
 struct TileCoord { int nblk, mblk, slice, g0, g1; };
 
-__device__ __forceinline__ TileCoord tile_coord(const TileArgs& p) {
-  const int total = p.nb * p.mb * p.S;
-  int logical = blockIdx.x;
-  const int per = total >> 3;                   // ids per XCD in the part that divides evenly
-  if ((int)blockIdx.x < per * 8) logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+__device__ __forceinline__ TileCoord tile_coord(const TileArgs& p, uint32_t total) {
+  uint32_t logical = blockIdx.x;
+  const uint32_t per = total >> 3;              // ids per XCD in the part that divides evenly
+  if (blockIdx.x < per * 8) logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   TileCoord c;
-  c.nblk = logical / (p.mb * p.S);
-  const int rem = logical - c.nblk * (p.mb * p.S);
-  c.mblk = rem / p.S;
-  c.slice = rem - c.mblk * p.S;
-  // (the divisions run in the vector unit; what depends on them, buffer descriptors among it,
-  // has to be known to the compiler as wave-uniform)
-  c.nblk = __builtin_amdgcn_readfirstlane(c.nblk);
-  c.mblk = __builtin_amdgcn_readfirstlane(c.mblk);
-  c.slice = __builtin_amdgcn_readfirstlane(c.slice);
-  c.g0 = __builtin_amdgcn_readfirstlane((int)((unsigned)(c.slice * p.G) / (unsigned)p.S));
-  c.g1 = __builtin_amdgcn_readfirstlane((int)((unsigned)((c.slice + 1) * p.G) / (unsigned)p.S));
+  const uint32_t per_row = (uint32_t)(p.mb * p.S);
+  // (five divisions in the vector unit took 0.3 us in front of the first load)
+  uint32_t nblk = logical;
+  if (p.row_rcp) nblk = __umulhi(logical, p.row_rcp);
+  else if (per_row > 1) nblk = (uint32_t)__builtin_amdgcn_readfirstlane((int)(logical / per_row));
+  c.nblk = (int)nblk;
+  c.mblk = (int)(logical - nblk * per_row);
+  c.slice = 0; c.g0 = 0; c.g1 = p.G;
+  if (p.S > 1) {
+    // (the divisions run in the vector unit; what depends on them, buffer descriptors among it,
+    // has to be known to the compiler as wave-uniform)
+    const unsigned rem = (unsigned)c.mblk, S = (unsigned)p.S;
+    c.mblk = __builtin_amdgcn_readfirstlane((int)(rem / S));
+    c.slice = (int)rem - c.mblk * p.S;
+    c.g0 = __builtin_amdgcn_readfirstlane((int)((unsigned)(c.slice * p.G) / S));
+    c.g1 = __builtin_amdgcn_readfirstlane((int)((unsigned)((c.slice + 1) * p.G) / S));
+  }
   return c;
 }
 
@@ -155,6 +178,42 @@ __device__ __forceinline__ void tile_write_fp16(const TileArgs& p, const Acc (&a
     }
 }
 
+// The same for LANE_IS_TOKEN tiles through LDS (`scratch`: 4096 PN bytes that belong to the wave), so that whole
+// runs of 32 PN features of a token are stored 16 bytes per lane: a store in accumulator layout touches 32 lines with 16
+// bytes each, 256 lines for a tile pair of 64 features where 32 hold it (512 x 128 blocks: 3.6 to 6.2 us between the last
+// matrix instruction and the end of a workgroup).  The 16-byte slot s of row r sits at s ^ f(r), so that neither the
+// 8-byte writes of 32 rows nor the reads meet in a bank.
+template <int PN, int PM, typename Acc>
+__device__ __forceinline__ void tile_write_rows(const TileArgs& p, const Acc (&acc)[PN][PM], int n0, int mrow0, uint8_t* scratch) {
+  static_assert(PN <= 2, "slots of a row");
+  constexpr int kRow = 64 * PN, kSlots = kRow / 16, kShift = PN == 1 ? 2 : 1;
+  const int lane = threadIdx.x & 63;
+  const int m32 = lane & 31, h = lane >> 5;
+  const int wr = m32 * kRow + (((m32 >> kShift) & (kSlots - 1)) << 4) + 8 * h;
+  const int row = lane / kSlots, slot = lane % kSlots;
+  constexpr int kRows = 64 / kSlots;                       // token rows per store
+  const int n = n0 + 8 * slot;
+#pragma unroll
+  for (int t = 0; t < PM; ++t) {
+    uint8_t* const buf = scratch + (t & 1) * (32 * kRow);
+#pragma unroll
+    for (int j = 0; j < PN; ++j)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        uint2 out;
+        out.x = (uint32_t)float_to_half_bits(acc[j][t][4 * a + 0]) | ((uint32_t)float_to_half_bits(acc[j][t][4 * a + 1]) << 16);
+        out.y = (uint32_t)float_to_half_bits(acc[j][t][4 * a + 2]) | ((uint32_t)float_to_half_bits(acc[j][t][4 * a + 3]) << 16);
+        *reinterpret_cast<uint2*>(buf + (wr ^ ((4 * j + a) << 4))) = out;
+      }
+#pragma unroll
+    for (int i = 0; i < 32 / kRows; ++i) {
+      const int r = i * kRows + row, m = mrow0 + 32 * t + r;
+      const uint4 v = *reinterpret_cast<const uint4*>(buf + r * kRow + ((slot ^ ((r >> kShift) & (kSlots - 1))) << 4));
+      if (m < p.M && n < p.N) *reinterpret_cast<uint4*>(p.y + (size_t)m * p.N + n) = v;
+    }
+  }
+}
+
 // Add the K-slices of output block blk in the fixed order 0 .. S-1 whoever arrives last (its own
 // slice is read back like the others, so the result does not depend on timing) and store fp16.
 // The loads bypass the caches and each batch of them costs a trip to memory, so SB slices of
@@ -163,7 +222,7 @@ __device__ __forceinline__ void tile_write_fp16(const TileArgs& p, const Acc (&a
 // 13824 -> 5120 at 96 in four 27.7 -> 26.8; two slices take the narrow form (the empty loads of
 // the wide one cost 1.2 us).
 template <int PN, int PM, int kThreads, bool LANE_IS_TOKEN, int SB>
-__device__ __forceinline__ void tile_sum_slices(const TileArgs& p, unsigned blk, int n0, int mrow0) {
+__device__ __forceinline__ void tile_sum_slices(const TileArgs& p, unsigned blk, int n0, int mrow0, uint8_t* scratch) {
   constexpr int kAcc = PN * PM * 16;
   constexpr int TB = PM % 2 == 0 ? 2 : 1;
 #pragma unroll 1
@@ -193,7 +252,8 @@ __device__ __forceinline__ void tile_sum_slices(const TileArgs& p, unsigned blk,
 #pragma unroll
           for (int e = 0; e < 8; ++e) { sum[0][t][2 * e] += v[c][t][e].x; sum[0][t][2 * e + 1] += v[c][t][e].y; }
     }
-    tile_write_fp16<1, TB, LANE_IS_TOKEN>(p, sum, n0 + 32 * (q / PM), mrow0 + 32 * (q % PM));
+    if constexpr (LANE_IS_TOKEN) tile_write_rows<1, TB>(p, sum, n0 + 32 * (q / PM), mrow0 + 32 * (q % PM), scratch);
+    else tile_write_fp16<1, TB, LANE_IS_TOKEN>(p, sum, n0 + 32 * (q / PM), mrow0 + 32 * (q % PM));
   }
 }
 
@@ -201,10 +261,11 @@ __device__ __forceinline__ void tile_sum_slices(const TileArgs& p, unsigned blk,
 // head of this file.
 template <int PN, int PM, int kThreads, bool LANE_IS_TOKEN = true, typename Acc>
 __device__ __forceinline__ void tile_store32(const TileArgs& p, const TileCoord& tc, Acc (&acc)[PN][PM],
-                                             int n0, int mrow0) {
+                                             int n0, int mrow0, uint8_t* scratch = nullptr) {
   const int tid = threadIdx.x;
   if (p.S == 1) {
-    tile_write_fp16<PN, PM, LANE_IS_TOKEN>(p, acc, n0, mrow0);
+    if constexpr (LANE_IS_TOKEN) tile_write_rows<PN, PM>(p, acc, n0, mrow0, scratch);
+    else tile_write_fp16<PN, PM, LANE_IS_TOKEN>(p, acc, n0, mrow0);
     return;
   }
   const unsigned blk = (unsigned)(tc.nblk * p.mb + tc.mblk);
@@ -224,8 +285,8 @@ __device__ __forceinline__ void tile_store32(const TileArgs& p, const TileCoord&
       }
   __shared__ unsigned ticket32;
   if (!last_arrival(p.tickets, p.S, blk, &ticket32)) return;
-  if (p.S == 2) tile_sum_slices<PN, PM, kThreads, LANE_IS_TOKEN, 2>(p, blk, n0, mrow0);
-  else tile_sum_slices<PN, PM, kThreads, LANE_IS_TOKEN, 4>(p, blk, n0, mrow0);
+  if (p.S == 2) tile_sum_slices<PN, PM, kThreads, LANE_IS_TOKEN, 2>(p, blk, n0, mrow0, scratch);
+  else tile_sum_slices<PN, PM, kThreads, LANE_IS_TOKEN, 4>(p, blk, n0, mrow0, scratch);
 }
 
 }  // namespace qspec
