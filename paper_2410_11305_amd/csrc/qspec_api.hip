@@ -8,6 +8,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <tuple>
+
 #include "accept.hpp"
 #include "common.hpp"
 #include "gemm_generic.hpp"
@@ -60,6 +62,17 @@ int check_device() {
   return verdict[dev] == 1 ? QSPEC_OK : QSPEC_ERR_UNSUPPORTED;
 }
 
+// kernel<<<grid, block, lds, s>>>(a...) by the one runtime call that makes it up, without storing the launch
+// configuration and fetching it again first (two more calls).  A failure is left for launch_status().
+template <typename... P, typename... A>
+inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, unsigned lds, hipStream_t s, const A&... a) {
+  std::tuple<P...> values(a...);
+  std::apply([&](P&... v) {
+    void* args[] = {const_cast<void*>(static_cast<const void*>(&v))...};
+    (void)hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, args, lds, s);
+  }, values);
+}
+
 // QSPEC_ERR_HIP must mean "THIS call's launch failed": check_device(), which every entry
 // point calls after validating its arguments and before launching, drops whatever error an
 // unrelated earlier runtime call left behind; launch_status() then sees only this call's.
@@ -77,12 +90,12 @@ inline int pick_tm(int M) { return M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8; 
 template <int TM>
 void launch_w4a4(const GemmArgs& a, hipStream_t s) {
   dim3 grid(a.N / 16, (a.M + TM * 16 - 1) / (TM * 16));
-  hipLaunchKernelGGL((gemm_w4a4_generic<TM, 4, false>), grid, dim3(256), 0, s, a);
+  launch_kernel((gemm_w4a4_generic<TM, 4, false>), grid, dim3(256), 0, s, a);
 }
 template <int TM>
 void launch_w4a16(const GemmArgs& a, hipStream_t s) {
   dim3 grid(a.N / 16, (a.M + TM * 16 - 1) / (TM * 16));
-  hipLaunchKernelGGL((gemm_w4a16_generic<TM, 4>), grid, dim3(256), 0, s, a);
+  launch_kernel((gemm_w4a16_generic<TM, 4>), grid, dim3(256), 0, s, a);
 }
 
 
@@ -305,7 +318,7 @@ template <bool W4A4, int TM>
 int launch_stream_tm(const StreamArgs& a, const StreamPlan& plan, hipStream_t s) {
   const auto launch = [&](auto kernel) {
     const StreamRest rest{a.y, a.ws, a.tickets, a.S, a.per_slice, a.more_slice, a.blocks};
-    hipLaunchKernelGGL(kernel, dim3(a.xcds), dim3(kStreamWaves * 64), 0, s, a.codes, a.scalesT, a.act, a.sa, a.M, a.N, a.K,
+    launch_kernel(kernel, dim3(a.xcds), dim3(kStreamWaves * 64), 0, s, a.codes, a.scalesT, a.act, a.sa, a.M, a.N, a.K,
                        a.xcds, a.S > 1 ? 0 : a.ms, a.ms_rcp, rest);
     return QSPEC_OK;
   };
@@ -621,7 +634,7 @@ bool covers_optional(int M, int N, int K) {
 template <typename Kernel>
 int launch_tile_kernel(Kernel kernel, int threads, const TileArgs& a, hipStream_t s) {
   const uint32_t total = (uint32_t)(a.nb * a.mb * a.S);
-  hipLaunchKernelGGL(kernel, dim3(total), dim3(threads), 0, s, a.codes, a.act, a.sa, a.M, a.N, a.K, a.S, a.mb, total, a.row_rcp,
+  launch_kernel(kernel, dim3(total), dim3(threads), 0, s, a.codes, a.act, a.sa, a.M, a.N, a.K, a.S, a.mb, total, a.row_rcp,
                      TileRest{a.y, a.ws, a.tickets, a.nb});
   return QSPEC_OK;
 }
@@ -741,8 +754,8 @@ bool mlp_plan(int M, int H, int I, int nwg, int* nt1, int* nt2) {
 
 template <int TM, int NT1>
 int launch_mlp_nt2(const MlpArgs& a, int nt2, int nwg, hipStream_t s) {
-  if (nt2 == 1) hipLaunchKernelGGL((mlp_draft_kernel<TM, NT1, 1>), dim3(nwg), dim3(kStreamWaves * 64), 0, s, a);
-  else hipLaunchKernelGGL((mlp_draft_kernel<TM, NT1, 2>), dim3(nwg), dim3(kStreamWaves * 64), 0, s, a);
+  if (nt2 == 1) launch_kernel((mlp_draft_kernel<TM, NT1, 1>), dim3(nwg), dim3(kStreamWaves * 64), 0, s, a);
+  else launch_kernel((mlp_draft_kernel<TM, NT1, 2>), dim3(nwg), dim3(kStreamWaves * 64), 0, s, a);
   return QSPEC_OK;
 }
 template <int TM>
@@ -871,10 +884,10 @@ int qspec_pack_weights(const int8_t* codes, const void* scales_f16, int N, int K
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = K / kGroup;
   const size_t n_words = (size_t)N * K / 8;
-  hipLaunchKernelGGL(pack_codes_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0, s,
+  launch_kernel(pack_codes_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0, s,
                      codes, static_cast<uint32_t*>(packed), N, K, G);
   uint16_t* sc_out = reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(packed) + (size_t)N * K / 2);
-  hipLaunchKernelGGL(transpose_scales_kernel, dim3(blocks_for((size_t)N * G, 256)), dim3(256), 0, s,
+  launch_kernel(transpose_scales_kernel, dim3(blocks_for((size_t)N * G, 256)), dim3(256), 0, s,
                      static_cast<const uint16_t*>(scales_f16), sc_out, N, G);
   return launch_status();
 }
@@ -888,10 +901,10 @@ int qspec_unpack_weights(const void* packed, int N, int K, int group,
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = K / kGroup;
   const size_t n_words = (size_t)N * K / 8;
-  hipLaunchKernelGGL(unpack_codes_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0, s,
+  launch_kernel(unpack_codes_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0, s,
                      static_cast<const uint32_t*>(packed), codes, N, K, G);
   // [G][N] -> [N][G] is the same transpose with the roles swapped
-  hipLaunchKernelGGL(transpose_scales_kernel, dim3(blocks_for((size_t)N * G, 256)), dim3(256), 0, s,
+  launch_kernel(transpose_scales_kernel, dim3(blocks_for((size_t)N * G, 256)), dim3(256), 0, s,
                      blob_scales(packed, N, K), static_cast<uint16_t*>(scales_f16), G, N);
   return launch_status();
 }
@@ -902,7 +915,7 @@ int qspec_quant_act(const void* x_f16, int M, int K, int group, uint8_t* qa, flo
   if (misaligned(x_f16) || misaligned(qa) || misaligned(sa)) return QSPEC_ERR_ALIGN;
   if (int st = check_device()) return st;
   const size_t n_words = (size_t)M * K / 8;
-  hipLaunchKernelGGL(quant_act_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
+  launch_kernel(quant_act_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
                      static_cast<hipStream_t>(stream), QuantArgs{static_cast<const uint4*>(x_f16), reinterpret_cast<uint32_t*>(qa), sa, n_words});
   return launch_status();
 }
@@ -919,7 +932,7 @@ int qspec_quant_act_wide(const void* x_f16, int M, int K, int group, int8_t* qa8
   if (misaligned(x_f16) || misaligned(qa8) || misaligned(sa)) return QSPEC_ERR_ALIGN;
   if (int st = check_device()) return st;
   const size_t n_words = (size_t)M * K / 8;
-  hipLaunchKernelGGL(quant_act_wide_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
+  launch_kernel(quant_act_wide_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
                      static_cast<hipStream_t>(stream), QuantArgs{static_cast<const uint4*>(x_f16), reinterpret_cast<uint32_t*>(qa8), sa, n_words});
   return launch_status();
 }
@@ -943,10 +956,10 @@ int qspec_rmsnorm_quant(const void* x_f16, const void* weight_f16, float eps, in
   const int chunks = (kw + T - 1) / T;
   const double inv_K = 1.0 / (double)K;
   const dim3 grid(M), block(T);
-  if (chunks <= 1) hipLaunchKernelGGL(rmsnorm_quant_kernel<1>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
-  else if (chunks <= 2) hipLaunchKernelGGL(rmsnorm_quant_kernel<2>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
-  else if (chunks <= 4) hipLaunchKernelGGL(rmsnorm_quant_kernel<4>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
-  else hipLaunchKernelGGL(rmsnorm_quant_kernel<0>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
+  if (chunks <= 1) launch_kernel(rmsnorm_quant_kernel<1>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
+  else if (chunks <= 2) launch_kernel(rmsnorm_quant_kernel<2>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
+  else if (chunks <= 4) launch_kernel(rmsnorm_quant_kernel<4>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
+  else launch_kernel(rmsnorm_quant_kernel<0>, grid, block, 0, s, x, w, eps, K, inv_K, words, sa, h, rotate);
   return launch_status();
 }
 
@@ -957,7 +970,7 @@ int qspec_silu_mul_quant(const void* gate_up_f16, int M, int I, int group,
   if (rotate < 0 || rotate > 3) return QSPEC_ERR_SHAPE;
   if (misaligned(gate_up_f16) || misaligned(qa) || misaligned(sa) || misaligned(h_f16)) return QSPEC_ERR_ALIGN;
   if (int st = check_device()) return st;
-  hipLaunchKernelGGL(silu_mul_quant_kernel, dim3(blocks_for(I / 8, 256), M < 65535 ? M : 65535), dim3(256), 0,
+  launch_kernel(silu_mul_quant_kernel, dim3(blocks_for(I / 8, 256), M < 65535 ? M : 65535), dim3(256), 0,
                      static_cast<hipStream_t>(stream), static_cast<const uint4*>(gate_up_f16), I / 8, M, rotate,
                      reinterpret_cast<uint32_t*>(qa), sa, static_cast<uint4*>(h_f16));
   return launch_status();
@@ -970,7 +983,7 @@ int qspec_hadamard_quant(const void* x_f16, int M, int K, int group,
   if (misaligned(x_f16) || misaligned(qa) || misaligned(sa) || misaligned(h_f16)) return QSPEC_ERR_ALIGN;
   if (int st = check_device()) return st;
   const size_t n_words = (size_t)M * K / 8;
-  hipLaunchKernelGGL(hadamard_quant_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
+  launch_kernel(hadamard_quant_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
                      static_cast<hipStream_t>(stream), static_cast<const uint4*>(x_f16),
                      reinterpret_cast<uint32_t*>(qa), sa, static_cast<uint4*>(h_f16), n_words);
   return launch_status();
@@ -986,7 +999,7 @@ int qspec_reorder_quant(const void* x_f16, const int32_t* perm, int M, int K, in
     return QSPEC_ERR_ALIGN;
   if (int st = check_device()) return st;
   const size_t n_words = (size_t)M * K / 8;
-  hipLaunchKernelGGL(reorder_quant_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
+  launch_kernel(reorder_quant_kernel, dim3(blocks_for(n_words, 256)), dim3(256), 0,
                      static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(x_f16), perm, K,
                      n_outlier_groups, reinterpret_cast<uint32_t*>(qa), sa, static_cast<uint4*>(h_f16), n_words);
   return launch_status();
@@ -1021,7 +1034,7 @@ int qspec_gemm_w4a16_noalloc(const void* packed, const void* x_f16, int M, int N
   const hipStream_t s = static_cast<hipStream_t>(stream);
   if (plan.need > 0) {
     // the counters must start at zero whatever an earlier (possibly failed) call left
-    hipLaunchKernelGGL(clear_tickets_kernel, dim3(kMaxTickets / 256), dim3(256), 0, s, static_cast<unsigned*>(ws), kMaxTickets);
+    launch_kernel(clear_tickets_kernel, dim3(kMaxTickets / 256), dim3(256), 0, s, static_cast<unsigned*>(ws), kMaxTickets);
   }
   return launch_whole_or_split(kVerify, plan, packed, x_f16, nullptr, M, N, K, y_f16, ws, s);
 }
@@ -1080,7 +1093,7 @@ int qspec_gemm_w4a4_partials(const void* packed, const uint8_t* qa, int M, int N
   a.M = M; a.N = N; a.K = K; a.G = K / kGroup;
   a.n0 = n0; a.n_count = n_count;
   dim3 grid(n_count / 16, (M + 15) / 16);
-  hipLaunchKernelGGL((gemm_w4a4_generic<1, 4, true>), grid, dim3(256), 0,
+  launch_kernel((gemm_w4a4_generic<1, 4, true>), grid, dim3(256), 0,
                      static_cast<hipStream_t>(stream), a);
   return launch_status();
 }
@@ -1104,10 +1117,10 @@ int qspec_greedy_accept(const void* logits_f16, const int32_t* draft_tokens, int
   const ArgmaxPlan plan = plan_argmax(V);
   const int R = B * (gamma + 1);
   ArgmaxArgs a{static_cast<const uint16_t*>(logits_f16), static_cast<uint64_t*>(workspace), V, plan.C, plan.chunk};
-  if (V % 8 == 0) hipLaunchKernelGGL((argmax_partial_kernel<true>), dim3(plan.C, R), dim3(kArgmaxThreads), 0, s, a);
-  else hipLaunchKernelGGL((argmax_partial_kernel<false>), dim3(plan.C, R), dim3(kArgmaxThreads), 0, s, a);
+  if (V % 8 == 0) launch_kernel((argmax_partial_kernel<true>), dim3(plan.C, R), dim3(kArgmaxThreads), 0, s, a);
+  else launch_kernel((argmax_partial_kernel<false>), dim3(plan.C, R), dim3(kArgmaxThreads), 0, s, a);
   AcceptArgs f{static_cast<const uint64_t*>(workspace), draft_tokens, n_accept, out_tokens, gamma, plan.C};
-  hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64 * (gamma + 1 < kAcceptRows ? gamma + 1 : kAcceptRows)), 0, s, f);
+  launch_kernel(accept_kernel, dim3(B), dim3(64 * (gamma + 1 < kAcceptRows ? gamma + 1 : kAcceptRows)), 0, s, f);
   return launch_status();
 }
 
@@ -1120,7 +1133,7 @@ int qspec_kv_overwrite(const void* kv_verify_f16, const int32_t* n_accept, const
     return QSPEC_ERR_ALIGN;
   if (int st = check_device()) return st;
   KvArgs a{static_cast<const uint4*>(kv_verify_f16), static_cast<uint4*>(cache_f16), n_accept, pos, gamma, D / 8, S};
-  hipLaunchKernelGGL(kv_overwrite_kernel, dim3(B * (gamma + 1)), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+  launch_kernel(kv_overwrite_kernel, dim3(B * (gamma + 1)), dim3(256), 0, static_cast<hipStream_t>(stream), a);
   return launch_status();
 }
 
