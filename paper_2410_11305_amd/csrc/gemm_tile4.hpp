@@ -409,7 +409,12 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(QSPEC_
 #pragma unroll
   for (int part = 0; part < 4; ++part) rescale_quarter(P[(kTiles - 1) & 1], pend_sw, pend_swc, pend_S, acc[PN - 1][PM - 1], part);
 
-  tile_store32<PN, PM, kThreads, false>(p, tc, acc, n0, m0 + mw0);
+  // (every wave's reads of the stages are behind the last group's barrier; transfers past the end may still be under way)
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __syncthreads();
+  static_assert(kWaves * 4096 <= 2 * kActBytes, "4096 bytes of the first two stages for each wave");
+  constexpr int kFirst = kActBytes / 4096;
+  tile_store32<PN, PM, kThreads, false>(p, tc, acc, n0, m0 + mw0, wave < kFirst ? stage0 + wave * 4096 : stage1 + (wave - kFirst) * 4096);
 }
 
 }  // namespace qspec

@@ -139,46 +139,11 @@ __device__ inline uint32_t word_of(const uint4& q, int i) {
 __device__ __forceinline__ float* slice_frag(const TileArgs& p, int c, unsigned blk, int floats_per_block) {
   return p.ws + ((size_t)c * (p.nb * p.mb) + blk) * (size_t)floats_per_block;
 }
-// fp16 store of a wave's PN x PM accumulator tiles of 32 x 32 (first output feature n0,
-// first token row mrow0).  Two MFMA D layouts (h = lane / 32; a, r = 0..3; register 4a + r):
-//   LANE_IS_TOKEN   lane holds token m = lane % 32 and features 8a + 4h + r: four runs of
-//                   four consecutive output features of one token (8-byte stores);
-//   !LANE_IS_TOKEN  lane holds feature n = lane % 32 and tokens 8a + 4h + r: per register
-//                   the 32 lanes of a half write 64 contiguous bytes of one token row.
-template <int PN, int PM, bool LANE_IS_TOKEN, typename Acc>
-__device__ __forceinline__ void tile_write_fp16(const TileArgs& p, const Acc (&acc)[PN][PM], int n0, int mrow0) {
-  const int lane = threadIdx.x & 63;
-  const int l32 = lane & 31, h = lane >> 5;
-#pragma unroll
-  for (int j = 0; j < PN; ++j)
-#pragma unroll
-    for (int t = 0; t < PM; ++t) {
-      if (LANE_IS_TOKEN) {
-        const int m = mrow0 + 32 * t + l32;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const int n = n0 + 32 * j + 8 * a + 4 * h;
-          if (m < p.M && n < p.N) {
-            uint2 out;
-            out.x = (uint32_t)float_to_half_bits(acc[j][t][4 * a + 0]) | ((uint32_t)float_to_half_bits(acc[j][t][4 * a + 1]) << 16);
-            out.y = (uint32_t)float_to_half_bits(acc[j][t][4 * a + 2]) | ((uint32_t)float_to_half_bits(acc[j][t][4 * a + 3]) << 16);
-            *reinterpret_cast<uint2*>(p.y + (size_t)m * p.N + n) = out;
-          }
-        }
-      } else {
-        const int n = n0 + 32 * j + l32;
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int m = mrow0 + 32 * t + 8 * a + 4 * h + r;
-            if (m < p.M && n < p.N) p.y[(size_t)m * p.N + n] = float_to_half_bits(acc[j][t][4 * a + r]);
-          }
-      }
-    }
-}
-
-// The same for LANE_IS_TOKEN tiles through LDS (`scratch`: 4096 PN bytes that belong to the wave), so that whole
+// fp16 store of a wave's PN x PM accumulator tiles of 32 x 32 (first output feature n0, first token row mrow0).  Two MFMA
+// D layouts (h = lane / 32; a, r = 0..3; register 4a + r):
+//   LANE_IS_TOKEN   lane holds token m = lane % 32 and features 8a + 4h + r;
+//   !LANE_IS_TOKEN  lane holds feature n = lane % 32 and tokens 8a + 4h + r.
+// LANE_IS_TOKEN: through LDS (`scratch`: 4096 PN bytes that belong to the wave), so that whole
 // runs of 32 PN features of a token are stored 16 bytes per lane: a store in accumulator layout touches 32 lines with 16
 // bytes each, 256 lines for a tile pair of 64 features where 32 hold it (512 x 128 blocks: 3.6 to 6.2 us between the last
 // matrix instruction and the end of a workgroup).  The 16-byte slot s of row r sits at s ^ f(r), so that neither the
@@ -212,6 +177,40 @@ __device__ __forceinline__ void tile_write_rows(const TileArgs& p, const Acc (&a
       if (m < p.M && n < p.N) *reinterpret_cast<uint4*>(p.y + (size_t)m * p.N + n) = v;
     }
   }
+}
+
+// The same for !LANE_IS_TOKEN tiles: a lane holds one feature of 16 tokens, so neighbouring lanes first trade halves (each
+// gets two adjacent features of one token), and a row of 32 features is 64 bytes of LDS.
+template <int PN, int PM, typename Acc>
+__device__ __forceinline__ void tile_write_columns(const TileArgs& p, const Acc (&acc)[PN][PM], int n0, int mrow0, uint8_t* scratch) {
+  const int lane = threadIdx.x & 63;
+  const int l32 = lane & 31, h = lane >> 5, odd = lane & 1;
+  const int row = lane >> 2, slot = lane & 3;
+  // token 8a + 4h + r: its 16-byte slot is turned by bits 2 and 3 of the token
+  const int wr = (4 * h + odd) * 64 + (l32 & ~1) * 2;
+#pragma unroll
+  for (int j = 0; j < PN; ++j)
+#pragma unroll
+    for (int t = 0; t < PM; ++t) {
+      uint8_t* const buf = scratch + ((j * PM + t) & 1) * 2048;
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+          const uint32_t own = (uint32_t)float_to_half_bits(acc[j][t][4 * a + r]) | ((uint32_t)float_to_half_bits(acc[j][t][4 * a + r + 1]) << 16);
+          const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xF, 0xF, false);      // lane ^ 1
+          // even lane: token r of features n, n + 1; odd lane: token r + 1 of features n - 1, n
+          const uint32_t pair = __builtin_amdgcn_perm(other, own, odd ? 0x03020706u : 0x05040100u);
+          const int turn = ((2 * a + h) & 3) << 4;            // bits 2 and 3 of the token
+          *reinterpret_cast<uint32_t*>(buf + ((wr + (8 * a + r) * 64) ^ turn)) = pair;
+        }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int tok = 16 * i + row, m = mrow0 + 32 * t + tok, n = n0 + 32 * j + 8 * slot;
+        const uint4 v = *reinterpret_cast<const uint4*>(buf + tok * 64 + ((slot ^ ((tok >> 2) & 3)) << 4));
+        if (m < p.M && n < p.N) *reinterpret_cast<uint4*>(p.y + (size_t)m * p.N + n) = v;
+      }
+    }
 }
 
 // Add the K-slices of output block blk in the fixed order 0 .. S-1 whoever arrives last (its own
@@ -253,7 +252,7 @@ __device__ __forceinline__ void tile_sum_slices(const TileArgs& p, unsigned blk,
           for (int e = 0; e < 8; ++e) { sum[0][t][2 * e] += v[c][t][e].x; sum[0][t][2 * e + 1] += v[c][t][e].y; }
     }
     if constexpr (LANE_IS_TOKEN) tile_write_rows<1, TB>(p, sum, n0 + 32 * (q / PM), mrow0 + 32 * (q % PM), scratch);
-    else tile_write_fp16<1, TB, LANE_IS_TOKEN>(p, sum, n0 + 32 * (q / PM), mrow0 + 32 * (q % PM));
+    else tile_write_columns<1, TB>(p, sum, n0 + 32 * (q / PM), mrow0 + 32 * (q % PM), scratch);
   }
 }
 
@@ -265,7 +264,7 @@ __device__ __forceinline__ void tile_store32(const TileArgs& p, const TileCoord&
   const int tid = threadIdx.x;
   if (p.S == 1) {
     if constexpr (LANE_IS_TOKEN) tile_write_rows<PN, PM>(p, acc, n0, mrow0, scratch);
-    else tile_write_fp16<PN, PM, LANE_IS_TOKEN>(p, acc, n0, mrow0);
+    else tile_write_columns<PN, PM>(p, acc, n0, mrow0, scratch);
     return;
   }
   const unsigned blk = (unsigned)(tc.nblk * p.mb + tc.mblk);
