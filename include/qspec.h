@@ -336,7 +336,7 @@ int qspec_kv_overwrite(const void* kv_verify_f16, const int32_t* n_accept, const
  * and qspec_workspace_bytes use, instead of the library's own choice.  `name` is one of
  *   "QSPEC_KERNEL"            value "generic": untiled reference kernels for M > 32, in both modes
  *                             and before any other override (qspec_gemm_w4a4_wide: refused)
- *   "QSPEC_STREAM_W4A4",  "QSPEC_STREAM_W4A16"   value "NT,S" or "NT,S,MS": tiles per
+ *   "QSPEC_STREAM_W4A4",  "QSPEC_STREAM_W4A16"   value "NT,S", "NT,S,MS" or "NT,S,MS,W": tiles per
  *                             workgroup, K-slices, token-row blocks of the streaming kernels
  *   "QSPEC_STREAM_MAX_W4A4"   32..128: the draft-mode streaming kernel takes every M up to
  *                             this one and none above

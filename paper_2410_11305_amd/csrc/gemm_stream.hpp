@@ -72,7 +72,6 @@ constexpr int kStreamWaves = 8;
 
 template <bool W4A4, int TM, int NT>
 struct StreamShape {
-  static constexpr int W = kStreamWaves;
   // Groups per step.  Two adjacent ones where few tiles per step would leave too few bytes in
   // flight (4096 x 11008 at one token 8.8 -> 6.9 us); their activations fill whole cache lines.
   static constexpr int QS = NT <= 2 && TM <= 4 ? 2 : 1;
@@ -115,13 +114,15 @@ struct StreamRest {
   int S, per_slice, more_slice, blocks;
 };
 
+#define QSPEC_STREAM_PARAMS                                                                                               \
+  const uint4 *codes, const uint16_t *scalesT, const void *act_rows, const float *sa, int M, int N, int K, uint32_t xcds, \
+      int ms, uint32_t ms_rcp, StreamRest rest
+
 // xcds: the number of workgroups (each XCD gets an eighth of them, the first ones one more); ms == 0: K-slices.
-template <bool W4A4, int TM, int NT>
-__global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(
-    const uint4* codes, const uint16_t* scalesT, const void* act_rows, const float* sa, int M, int N, int K, uint32_t xcds, int ms,
-    uint32_t ms_rcp, StreamRest rest) {
+template <bool W4A4, int TM, int NT, int W>
+__device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
   using C = StreamShape<W4A4, TM, NT>;
-  constexpr int W = C::W, QS = C::QS, CH = C::CH, T = NT * TM;
+  constexpr int QS = C::QS, CH = C::CH, T = NT * TM;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[W * C::kRegion];
   __shared__ unsigned ticket;
   const int tid = threadIdx.x;
@@ -484,5 +485,21 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(
     store_tile(o, s);
   }
 }
+
+template <bool W4A4, int TM, int NT>
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(QSPEC_STREAM_PARAMS) {
+  stream_product<W4A4, TM, NT, kStreamWaves>(codes, scalesT, act_rows, sa, M, N, K, xcds, ms, ms_rcp, rest);
+}
+
+// The same on four wavefronts, for plans of between one and two (from two token tiles on: three) rounds of
+// workgroups.  The registers of eight wavefronts keep a second workgroup off a compute unit, so what comes before the
+// first loads and after the last group of the one stands in front of the other; two workgroups of four wavefronts
+// have it under each other's loops.  Measured against eight on the same plan: rule in qspec_api.hip.
+namespace waves4 {
+template <bool W4A4, int TM, int NT>
+__global__ __launch_bounds__(256, 2) void gemm_stream_kernel(QSPEC_STREAM_PARAMS) {
+  stream_product<W4A4, TM, NT, 4>(codes, scalesT, act_rows, sa, M, N, K, xcds, ms, ms_rcp, rest);
+}
+}  // namespace waves4
 
 }  // namespace qspec

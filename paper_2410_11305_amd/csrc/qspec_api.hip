@@ -105,13 +105,14 @@ constexpr int kNumCU = 256;
 // environment at the first use, and afterwards only through qspec_debug_set_plan.  The
 // launch path reads plain integers; no entry point calls getenv.
 //   QSPEC_KERNEL=generic            route M > 32 to the untiled reference kernels, whatever else is set
-//   QSPEC_STREAM_W4A4 / _W4A16      "NT,S" or "NT,S,MS": tiles per workgroup, K-slices, token-row blocks
+//   QSPEC_STREAM_W4A4 / _W4A16      "NT,S", "NT,S,MS" or "NT,S,MS,W": tiles per workgroup, K-slices, token-row blocks,
+//                                   wavefronts of a workgroup (8, or 4 where that instance exists)
 //   QSPEC_STREAM_MAX_W4A4 / _W4A16  the streaming kernels take every M up to this one and none above
 //   QSPEC_TILE_W4A4 / _W4A16        "shape,S": workgroup shape index, K-slices
 struct PlanOverrides {
   bool generic = false;
-  int stream_fields[2] = {0, 0};      // [w4a4]: how many of nt, S, ms were given (0: no override)
-  int stream[2][3] = {{0, 0, 0}, {0, 0, 0}};
+  int stream_fields[2] = {0, 0};      // [w4a4]: how many of nt, S, ms, waves were given (0: no override)
+  int stream[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
   int stream_max[2] = {0, 0};         // 0: the default bound
   bool tile_set[2] = {false, false};
   int tile[2][2] = {{0, 0}, {0, 0}};
@@ -125,8 +126,8 @@ bool apply_override(PlanOverrides& o, const char* name, const char* value) {
   for (int w4a4 = 0; w4a4 < 2; ++w4a4) {
     if (strcmp(name, w4a4 ? "QSPEC_STREAM_W4A4" : "QSPEC_STREAM_W4A16") == 0) {
       int* f = o.stream[w4a4];
-      f[0] = f[1] = 0; f[2] = 1;
-      const int nf = value ? sscanf(value, "%d,%d,%d", &f[0], &f[1], &f[2]) : 0;
+      f[0] = f[1] = 0; f[2] = 1; f[3] = 8;
+      const int nf = value ? sscanf(value, "%d,%d,%d,%d", &f[0], &f[1], &f[2], &f[3]) : 0;
       o.stream_fields[w4a4] = nf >= 2 ? nf : 0;
       if (nf < 3) f[2] = 1;
       return true;
@@ -176,6 +177,7 @@ struct StreamPlan {
   int ms;       // token-row blocks; block i owns rows i*16*tm .. (i+1)*16*tm - 1
   int tm;       // 16-token tiles per workgroup (the kernel's TM)
   double cost;  // microseconds by the cost tables; a forced plan has none
+  int waves;    // wavefronts of a workgroup: 8, or 4 (stream_waves)
 };
 inline int stream_tm(int M) { return M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8; }   // 16-token tiles that cover M rows
 constexpr int kStreamNts[] = {1, 2, 3, 4, 6};
@@ -282,6 +284,15 @@ double best_stream(bool w4a4, int M, int N, int G, bool one_round, StreamPlan* p
   return w4a4 ? best_stream(kStreamCost4, M, N, G, one_round, bounded, p) : best_stream(kStreamCost16, M, N, G, one_round, bounded, p);
 }
 
+// Four wavefronts or eight.  Time on four over time on eight, same tiles, 260 problems of Llama-shaped layers at 1 to 64
+// tokens, by rounds of workgroups: one 1.02 to 1.19, up to 1.25 rounds 1.02, from there to two rounds 0.97 (draft mode, one
+// token tile), 0.95 (verify mode), 0.92 (two and four token tiles, also 0.95 to 0.98 up to three rounds); beyond 1.00 to
+// 1.03; with one weight tile 1.00 to 1.13 everywhere.
+int stream_waves(const StreamPlan& p) {
+  const long long wgs = (long long)p.blocks * p.ms;
+  return p.nt >= 2 && p.tm <= 4 && 4 * wgs > 5 * kNumCU && wgs <= (p.tm >= 2 ? 3 : 2) * kNumCU ? 4 : kStreamWaves;
+}
+
 StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
   const int tiles = N / 16, G = K / kGroup;
   const PlanOverrides& ov = overrides();
@@ -298,6 +309,7 @@ StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
     p.nt = nt; p.S = S; p.ms = ms;
     p.blocks = (tiles + nt - 1) / nt;
     p.tm = ms > 1 ? stream_tm_split(M, ms) : stream_tm(M);
+    p.waves = ov.stream[w4a4 ? 1 : 0][3];     // (one that does not exist is refused at the launch)
     return p;
   }
   // (verify mode past 32 tokens: only where one round of workgroups covers a layer of at most 8192 x 8192; the
@@ -305,6 +317,7 @@ StreamPlan plan_stream(bool w4a4, int M, int N, int K) {
   const bool past = !w4a4 && M > kStreamMaxM;
   if (past && (M > 128 || N > 8192 || K > 8192)) return p;          // nt == 0: no streaming plan
   p.cost = best_stream(w4a4, M, N, G, past, &p);
+  p.waves = stream_waves(p);
   return p;
 }
 
@@ -314,26 +327,29 @@ inline size_t stream_ws_bytes(const StreamPlan& p) {
 
 // Launch the instance <mode, TM, NT> of a streaming plan.  A (TM, NT) pair that is not
 // instantiated (a forced plan can name one) is refused: nothing is launched.
-template <bool W4A4, int TM>
-int launch_stream_tm(const StreamArgs& a, const StreamPlan& plan, hipStream_t s) {
+template <bool W4A4, int TM, int NT>
+int launch_stream_inst(const StreamArgs& a, const StreamPlan& plan, hipStream_t s) {
   const auto launch = [&](auto kernel) {
     const StreamRest rest{a.y, a.ws, a.tickets, a.S, a.per_slice, a.more_slice, a.blocks};
-    launch_kernel(kernel, dim3(a.xcds), dim3(kStreamWaves * 64), 0, s, a.codes, a.scalesT, a.act, a.sa, a.M, a.N, a.K,
-                       a.xcds, a.S > 1 ? 0 : a.ms, a.ms_rcp, rest);
+    launch_kernel(kernel, dim3(a.xcds), dim3(plan.waves * 64), 0, s, a.codes, a.scalesT, a.act, a.sa, a.M, a.N, a.K,
+                  a.xcds, a.S > 1 ? 0 : a.ms, a.ms_rcp, rest);
     return QSPEC_OK;
   };
+  if constexpr (NT >= 2 && TM <= 4) {
+    if (plan.waves == 4) return launch(waves4::gemm_stream_kernel<W4A4, TM, NT>);
+  }
+  if (plan.waves != kStreamWaves) return QSPEC_ERR_UNSUPPORTED;
+  return launch(gemm_stream_kernel<W4A4, TM, NT>);
+}
+
+template <bool W4A4, int TM>
+int launch_stream_tm(const StreamArgs& a, const StreamPlan& plan, hipStream_t s) {
   switch (plan.nt) {
-    case 1: return launch(gemm_stream_kernel<W4A4, TM, 1>);
-    case 2: return launch(gemm_stream_kernel<W4A4, TM, 2>);
-    case 3:
-      if constexpr (TM <= 4) { return launch(gemm_stream_kernel<W4A4, TM, 3>); }
-      return QSPEC_ERR_UNSUPPORTED;
-    case 4:
-      if constexpr (TM <= 4) { return launch(gemm_stream_kernel<W4A4, TM, 4>); }
-      return QSPEC_ERR_UNSUPPORTED;
-    case 6:
-      if constexpr (TM <= 2) { return launch(gemm_stream_kernel<W4A4, TM, 6>); }
-      return QSPEC_ERR_UNSUPPORTED;
+    case 1: return launch_stream_inst<W4A4, TM, 1>(a, plan, s);
+    case 2: return launch_stream_inst<W4A4, TM, 2>(a, plan, s);
+    case 3: if constexpr (TM <= 4) return launch_stream_inst<W4A4, TM, 3>(a, plan, s); else return QSPEC_ERR_UNSUPPORTED;
+    case 4: if constexpr (TM <= 4) return launch_stream_inst<W4A4, TM, 4>(a, plan, s); else return QSPEC_ERR_UNSUPPORTED;
+    case 6: if constexpr (TM <= 2) return launch_stream_inst<W4A4, TM, 6>(a, plan, s); else return QSPEC_ERR_UNSUPPORTED;
     default: return QSPEC_ERR_UNSUPPORTED;
   }
 }
@@ -572,6 +588,7 @@ Plan plan_product(Product product, int M, int N, int K) {
     stream = p.stream.nt > 0;
   } else {                                         // draft mode: the cheaper of the two kernels
     const double streaming = best_stream(true, M, N, G, false, &p.stream);
+    p.stream.waves = stream_waves(p.stream);
     const Tile4Choice tiled = best_tile4(M, N, G, 4, streaming);
     stream = tiled.S == 0 || (product == kDraft && tiled.packed >= streaming);
     if (!forced_tile) { shape = tiled.shape; S = tiled.S; }
