@@ -563,6 +563,13 @@ struct Plan {
 // the widened format is accepted
 constexpr int kTileMinM4 = 25;
 
+// What the streaming kernels take of what kStreamCost4 says, beside the tiled ones and kCost4, since the tables were fitted
+// (loads sooner, sums combined in one pass, workgroups of four wavefronts; the tiled kernels gained less).  The medians
+// on 260 products are 0.94 and, on four wavefronts, 0.87, but they spread: at 64 tokens 27648 outputs from 5120 (0.96 of
+// the tiled cost by the tables) still take 24.0 us streaming and 23.4 on widened codes, 36864 from 6144 (0.99) 33.7 and
+// 41.2.  So only what the tables call a tie goes over.  Past 64 tokens and on fewer than 16 groups they decide alone.
+double stream_since(int M, int G) { return M <= 64 && G >= 16 ? 0.97 : 1.0; }
+
 // A pure function of its arguments and the overrides, worked out once per call: the entry points launch what it
 // says and ask for the workspace it needs, qspec_workspace_bytes gives the most that any product of the size needs.
 Plan plan_product(Product product, int M, int N, int K) {
@@ -587,8 +594,9 @@ Plan plan_product(Product product, int M, int N, int K) {
     p.stream = plan_stream(w4a4, M, N, K);
     stream = p.stream.nt > 0;
   } else {                                         // draft mode: the cheaper of the two kernels
-    const double streaming = best_stream(true, M, N, G, false, &p.stream);
+    double streaming = best_stream(true, M, N, G, false, &p.stream);
     p.stream.waves = stream_waves(p.stream);
+    streaming *= stream_since(M, G);
     const Tile4Choice tiled = best_tile4(M, N, G, 4, streaming);
     stream = tiled.S == 0 || (product == kDraft && tiled.packed >= streaming);
     if (!forced_tile) { shape = tiled.shape; S = tiled.S; }
@@ -644,7 +652,10 @@ Split split_tokens(Product product, const Plan& whole, int M, int N, int K) {
 // Where qspec_workspace_bytes covers optional slices: sizes that ran on the tiled kernel before the streaming one took
 // row blocks of every size, so that programs hold widened codes for them.  Not everywhere: a caller on packed
 // codes would allocate 4 to 32 MiB for nothing (0.2 to 0.3 ms before the first call of two decoder blocks at 32 tokens).
+// And where the tables alone, before the streaming kernels gained on them, advised that format.
 bool covers_optional(int M, int N, int K) {
+  StreamPlan stream{};
+  if (best_tile4(M, N, K / kGroup, 4, best_stream(true, M, N, K / kGroup, false, &stream)).S != 0) return true;
   return M > 128 || (M > 64 && (N > 8192 || K > 8192)) || (M >= 48 && N >= 170 * 128);
 }
 
