@@ -1,9 +1,9 @@
 // Activation quantiser of the draft mode (paper Sec. 1: W4A4 quantises the
 // activations to 4 bit as well; Sec. 4.1: groups of 128).  Per token and
 // group, all in binary32: a = max|x|, s = a / 7, q = clamp(rne(x / s), -8, 7),
-// ties to even.  Both quotients are the correctly rounded ones: the first by division, the
-// second from a reciprocal and two exact remainder steps (div_by_reciprocal), which for these
-// operands gives the IEEE quotient bit for bit.
+// ties to even.  Both quotients are the correctly rounded ones, the first from the rounded reciprocal
+// of 7 and one remainder step (scale_and_reciprocal), the second from 1 / s and two (div_by_reciprocal);
+// for these operands that gives the IEEE quotients bit for bit.
 #pragma once
 #include "common.hpp"
 
