@@ -294,8 +294,9 @@ __global__ __launch_bounds__(64 * WGN * WGM, OCC) void gemm_tile4w_kernel(QSPEC_
     __builtin_amdgcn_sched_barrier(0);
     store_sa(0);
     store_sa(1);
-    // (group 0; group 1 has its place in the wait that ends group 0)
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * PN * NW + UD));
+    // (groups 0 and 1: group 0 reads the first operands of group 1 before its own closing wait.  Younger than
+    // their transfers are the last two refills of the ring.)
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * PN * (NW - 1)));
   } else {
     load_x(0);
     store_x(0);
