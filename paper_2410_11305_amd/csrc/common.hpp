@@ -19,6 +19,14 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
+// Stands between accesses to LDS through which the lanes of ONE wavefront pass values to each other.  LDS executes a
+// wavefront's accesses in order, so there is nothing to wait for; but the compiler, which follows a single lane, must be
+// told not to move one access across another that it takes for a different place.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Bit position (in nibbles) of code e of an 8-code run inside its 32-bit word.
 // Chosen so that masking with 0x000F000F / 0x00F000F0 (before and after a
 // shift by 8) yields the fp16 pairs (c0,c1) (c2,c3) (c4,c5) (c6,c7) in order,

@@ -312,8 +312,11 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
     // draft mode multiplies the missing group's zeros, the verify mode skips it: zeros times an infinite activation.)
     auto step = [&](int s, int c0, auto refill_c) __attribute__((always_inline)) {
       constexpr bool kRefill = decltype(refill_c)::value;
+      wave_lds_order();
       stage();
-      if constexpr (kRefill) load_act(s + 1);
+      if constexpr (kRefill) load_act(s + 1);                // (in between: a load goes out as soon as its registers are free)
+      else __builtin_amdgcn_sched_barrier(0);                // (nothing that waits for weights in front of the stores)
+      wave_lds_order();
       float swf[QS][NT];
       if constexpr (W4A4) {
         constexpr int D = 2;                              // an output tile is rescaled while the next D are in the matrix unit
@@ -428,6 +431,7 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
         break;
       }
       load_scales(c0 + CH);                                  // (the loads of the next step are on the way meanwhile)
+      wave_lds_order();                                      // (the scales of this chunk have been read)
       put_scales(c0 + CH);
     }
   }
@@ -446,6 +450,7 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
     if (j < nt_valid && m < Mloc) *reinterpret_cast<uint2*>(ytile + (size_t)m * N + j * 16) = out;
   };
   // (overwrites only what this wavefront itself has read)
+  wave_lds_order();
 #pragma unroll
   for (int o = 0; o < T; ++o) {
     const float(&f)[4] = facc[o / TM][o % TM];

@@ -161,6 +161,7 @@ __device__ __forceinline__ void tile_write_rows(const TileArgs& p, const Acc (&a
 #pragma unroll
   for (int t = 0; t < PM; ++t) {
     uint8_t* const buf = scratch + (t & 1) * (32 * kRow);
+    wave_lds_order();
 #pragma unroll
     for (int j = 0; j < PN; ++j)
 #pragma unroll
@@ -170,6 +171,7 @@ __device__ __forceinline__ void tile_write_rows(const TileArgs& p, const Acc (&a
         out.y = (uint32_t)float_to_half_bits(acc[j][t][4 * a + 2]) | ((uint32_t)float_to_half_bits(acc[j][t][4 * a + 3]) << 16);
         *reinterpret_cast<uint2*>(buf + (wr ^ ((4 * j + a) << 4))) = out;
       }
+    wave_lds_order();
 #pragma unroll
     for (int i = 0; i < 32 / kRows; ++i) {
       const int r = i * kRows + row, m = mrow0 + 32 * t + r;
@@ -193,6 +195,7 @@ __device__ __forceinline__ void tile_write_columns(const TileArgs& p, const Acc 
 #pragma unroll
     for (int t = 0; t < PM; ++t) {
       uint8_t* const buf = scratch + ((j * PM + t) & 1) * 2048;
+      wave_lds_order();
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -204,6 +207,7 @@ __device__ __forceinline__ void tile_write_columns(const TileArgs& p, const Acc 
           const int turn = ((2 * a + h) & 3) << 4;            // bits 2 and 3 of the token
           *reinterpret_cast<uint32_t*>(buf + ((wr + (8 * a + r) * 64) ^ turn)) = pair;
         }
+      wave_lds_order();
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int tok = 16 * i + row, m = mrow0 + 32 * t + tok, n = n0 + 32 * j + 8 * slot;
