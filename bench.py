@@ -56,6 +56,7 @@ def alg_bytes_quant(M, K):
 def family(sym):
     """The kernel template and mode a profiler symbol belongs to (its instances differ in
     tiles per workgroup and the like, chosen per layer shape)."""
+    sym = sym.removeprefix("waves4::")             # (the streaming kernels on four wavefronts)
     if sym.startswith("gemm_stream_kernel<"):
         return "gemm_stream_kernel<" + ",".join(sym.split("<")[1].split(",")[:2]) + ", *>"
     return sym.split("<")[0] + ("<*>" if "<" in sym else "")
@@ -407,7 +408,7 @@ class Bench:
             G = lin.K // 128
             name = B.describe_kernel(True, Md, lin.N, lin.K, wide=B.w4a4_takes_wide(Md, lin.N, lin.K))
             nbytes = lin.N * lin.K // 2            # the code tiles; whole 1 KB tiles
-            if name.startswith("gemm_stream_kernel"):
+            if family(name).startswith("gemm_stream_kernel"):
                 per = int(name.split(",")[-1].strip(" >")) * G       # NT tiles per workgroup over all of K
             else:
                 per = max(1, nbytes // 1024 // 2048)                 # tiled kernels: about 2048 workgroups

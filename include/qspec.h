@@ -337,7 +337,9 @@ int qspec_kv_overwrite(const void* kv_verify_f16, const int32_t* n_accept, const
  *   "QSPEC_KERNEL"            value "generic": untiled reference kernels for M > 32, in both modes
  *                             and before any other override (qspec_gemm_w4a4_wide: refused)
  *   "QSPEC_STREAM_W4A4",  "QSPEC_STREAM_W4A16"   value "NT,S", "NT,S,MS" or "NT,S,MS,W": tiles per
- *                             workgroup, K-slices, token-row blocks of the streaming kernels
+ *                             workgroup, K-slices, token-row blocks and wavefronts per workgroup (8, the
+ *                             default, or 4; a kernel that does not exist is refused at the launch,
+ *                             QSPEC_ERR_UNSUPPORTED) of the streaming kernels
  *   "QSPEC_STREAM_MAX_W4A4"   32..128: the draft-mode streaming kernel takes every M up to
  *                             this one and none above
  *   "QSPEC_TILE_W4A4",    "QSPEC_TILE_W4A16"     value "shape,S": workgroup shape, K-slices
@@ -353,9 +355,10 @@ int qspec_debug_set_plan(const char* name, const char* value);
 
 /*
  * Debug entry: name of the device kernel the GEMM entry points select for an
- * (M,N,K) problem, e.g. "gemm_stream_kernel<false, 2, 3>" (mode 0 = W4A16
+ * (M,N,K) problem, without namespace qspec::, e.g. "gemm_stream_kernel<false, 2, 3>" (mode 0 = W4A16
  * verify, 1 = W4A4 draft, 2 = W4A4 draft on widened codes: QSPEC_ERR_UNSUPPORTED
- * where that is refused).  A W4A16 product whose tokens do not fill whole
+ * where that is refused); "waves4::gemm_stream_kernel<false, 2, 3>" is the one of four
+ * wavefronts per workgroup.  A W4A16 product whose tokens do not fill whole
  * blocks may run as two launches: mode 0 then names the kernel one launch would
  * run on, 4 and 5 the first and the second launch (one launch: 4 its kernel, 5 an
  * empty string).  It matches the symbol a profiler reports, so that

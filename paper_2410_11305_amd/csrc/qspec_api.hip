@@ -1185,7 +1185,7 @@ int qspec_describe_kernel(int mode_w4a4, int M, int N, int K, int group, char* o
     if (split.rows) { plan = launch == 1 ? split.first : split.rest; M = launch == 1 ? split.rows : M - split.rows; }
   }
   if (plan.kernel == Kernel::stream) {
-    snprintf(out, cap, "gemm_stream_kernel<%s, %d, %d>", b, plan.stream.tm, plan.stream.nt);
+    snprintf(out, cap, "%sgemm_stream_kernel<%s, %d, %d>", plan.stream.waves == 4 ? "waves4::" : "", b, plan.stream.tm, plan.stream.nt);
   } else if (plan.kernel == Kernel::tile) {
     const TileShape& t = shape_of(mode_w4a4 != 0, plan.tile.shape);
     if (mode_w4a4) snprintf(out, cap, "gemm_tile4w_kernel<%d, %d, %d, %d, %d, %s>", t.TN, t.TMW, t.WGN, t.WGM, t.OCC, wide ? "true" : "false");

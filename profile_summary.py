@@ -44,6 +44,7 @@ def _short(name: str) -> str:
 
 
 def _family(name: str) -> str:
+    name = name.removeprefix("waves4::")           # (the streaming kernels on four wavefronts)
     if name.startswith("gemm_stream_kernel<"):
         return "gemm_stream_kernel<" + ",".join(name.split("<")[1].split(",")[:2]) + ", *>"
     return name.split("<")[0] + ("<*>" if "<" in name else "")
@@ -60,7 +61,7 @@ def _counter_means(path):
 def main(in_dir: str, out_dir: str, tag: str = "bench_config2") -> None:
     os.makedirs(out_dir, exist_ok=True)
     cfg = "".join(ch for ch in tag if ch.isdigit()) or "2"
-    ours = ("gemm_", "quant_act", "pack_", "unpack_", "transpose_", "argmax_", "accept_", "kv_overwrite")
+    ours = ("gemm_", "waves4::gemm_", "quant_act", "pack_", "unpack_", "transpose_", "argmax_", "accept_", "kv_overwrite")
     lines = [f"# rocprofv3 kernel statistics, {tag}", f"# command: {CMD_KT.format(cfg=cfg)}",
              f"# {'kernel':68s} {'calls':>6s} {'avg_us':>9s} {'min_us':>9s} {'max_us':>9s} {'pct':>6s}"]
     fam = collections.OrderedDict()
@@ -70,7 +71,7 @@ def main(in_dir: str, out_dir: str, tag: str = "bench_config2") -> None:
             if n.startswith(ours):
                 lines.append(f"  {n:68s} {int(r['Calls']):6d} {float(r['AverageNs'])/1e3:9.2f} "
                              f"{float(r['MinNs'])/1e3:9.2f} {float(r['MaxNs'])/1e3:9.2f} {float(r['Percentage']):6.2f}")
-                if n.startswith("gemm_"):
+                if _family(n).startswith("gemm_"):
                     e = fam.setdefault(_family(n), [0, 0.0, 0.0])
                     e[0] += int(r["Calls"]); e[1] += float(r["TotalDurationNs"]); e[2] += float(r["Percentage"])
     lines.append("# the same, summed over the instances of one kernel template and mode (the unit bench.py's")
@@ -142,7 +143,7 @@ def sq_table(in_dir: str, out_dir: str, tag: str) -> None:
              f"# commands: {CMD_SQ.format(c=SQ_A, o='sqa', cfg=cfg)}",
              f"#           {CMD_SQ.format(c=SQ_B, o='sqb', cfg=cfg)}"]
     for k in sorted(agg):
-        if not k.startswith("gemm_"):
+        if not _family(k).startswith("gemm_"):
             continue
         m = {c: sum(v) / len(v) for c, v in agg[k].items()}
         lines.append(f"  {k}  ({len(next(iter(agg[k].values())))} dispatches)")

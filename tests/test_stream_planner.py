@@ -28,7 +28,7 @@ def _rows():
 def _chosen(mode, M, N, K):
     wide = mode == "draft" and B.w4a4_takes_wide(M, N, K)      # (the advised format)
     name = B.describe_kernel(mode != "verify", M, N, K, wide=wide)
-    m = re.match(r"gemm_stream_kernel<\w+, (\d+), (\d+)>", name)
+    m = re.match(r"(?:waves4::)?gemm_stream_kernel<\w+, (\d+), (\d+)>", name)
     if m:
         return f"stream{m.group(1)}.{m.group(2)}"
     if mode == "verify":
@@ -95,7 +95,7 @@ def test_generic_override_leaves_nothing_above_32_tokens_to_the_other_kernels(pl
 def test_stream_max_override_is_a_bound_from_both_sides(plan, bound, N, K):
     plan("QSPEC_STREAM_MAX_W4A4", str(bound))
     for M in (17, 30, bound - 1, bound):
-        m = re.match(r"gemm_stream_kernel<true, (\d+), (\d+)>", B.describe_kernel(True, M, N, K))
+        m = re.match(r"(?:waves4::)?gemm_stream_kernel<true, (\d+), (\d+)>", B.describe_kernel(True, M, N, K))
         assert m and int(m.group(1)) > 0 and int(m.group(2)) > 0       # (0: a plan that the launch refuses)
     for M in (bound + 1, 300, 1500):
         assert B.describe_kernel(True, M, N, K).startswith("gemm_tile4w_kernel")
