@@ -4,6 +4,7 @@
 within 10 %); the cost tables leave 1 % on average, and 20 % at most but for a few per cent of layers with few groups."""
 import math
 import os
+import random
 import re
 
 import pytest
@@ -99,3 +100,21 @@ def test_stream_max_override_is_a_bound_from_both_sides(plan, bound, N, K):
         assert m and int(m.group(1)) > 0 and int(m.group(2)) > 0       # (0: a plan that the launch refuses)
     for M in (bound + 1, 300, 1500):
         assert B.describe_kernel(True, M, N, K).startswith("gemm_tile4w_kernel")
+
+
+@pytest.mark.parametrize("draft", [True, False])
+def test_wavefronts_follow_the_rounds_of_workgroups(draft):
+    """Four where 256 compute units take more than 1.25 and at most two rounds of workgroups (three with two and more token
+    tiles) of two and more weight tiles; eight everywhere else."""
+    rng, seen = random.Random(7), {}
+    for _ in range(6000):
+        M, N, K = rng.randint(1, 128 if draft else 32), 16 * rng.randint(1, 4000), 128 * rng.choice((1, 2, 3, 5, 8, 16, 32, 64))
+        m = re.match(r"(waves4::)?gemm_stream_kernel<\w+, (\d+), (\d+)>", B.describe_kernel(draft, M, N, K))
+        if not m:
+            continue
+        tm, nt = int(m.group(2)), int(m.group(3))
+        rounds = -(-N // (16 * nt)) * -(-M // (16 * tm)) / 256
+        four = nt >= 2 and tm <= 4 and 1.25 < rounds <= (3 if tm >= 2 else 2)
+        assert four == bool(m.group(1)), (M, N, K, m.group(0))
+        seen[four, min(tm, 2)] = seen.get((four, min(tm, 2)), 0) + 1
+    assert all(seen.get((four, tm), 0) >= 30 for four in (True, False) for tm in (1, 2)), seen
