@@ -123,3 +123,29 @@ def test_activations_just_under_two_gib(env, plan):
         plan("QSPEC_TILE_W4A16", forced)
         y = B.gemm_w4a16(blob, x, N).cpu().numpy()
         assert np.isfinite(y).all() and rel_err(y[rows], ref) <= TOL, forced
+
+
+@pytest.mark.parametrize("blocks", [37837, 37838])
+def test_more_token_blocks_than_the_reciprocal_covers(env, plan, blocks):
+    """Tiled kernels find their output block by a reciprocal while blocks of tokens squared times blocks of outputs stays below
+    2^32, by a division from there on: the last size of the one and the first of the other, 64 x 64 blocks.  Token
+    rows repeat with a period that is no multiple of a block, so every row has to equal the same row of a small call."""
+    torch, B = env
+    M, N, K, period = 64 * blocks - 40, 176, 128, 8191
+    assert (blocks * blocks * 3 >= 2 ** 32) == (blocks == 37838)
+    rng = np.random.default_rng(83)
+    codes = rng.integers(-8, 8, (N, K), dtype=np.int8)
+    scales = rng.uniform(0.002, 0.01, (N, 1)).astype(np.float16)
+    x = rng.standard_normal((period, K)).astype(np.float16)
+    blob = B.pack_weights(torch.from_numpy(codes).cuda(), torch.from_numpy(scales).cuda())
+    few = torch.from_numpy(x).cuda()
+    rows = torch.arange(M, device="cuda") % period
+    many = few[rows]
+    plan("QSPEC_TILE_W4A16", "2,1")
+    plan("QSPEC_TILE_W4A4", "2,1")
+    for product, ref in ((lambda t: B.gemm_w4a16(blob, t, N), orc.gemm_w4a16(x, codes, scales)),
+                         (lambda t: B.gemm_w4a4(blob, *B.quant_act(t), N), orc.gemm_w4a4(*orc.quant_act(x), codes, scales)),
+                         (lambda t: B.gemm_w4a4_wide(blob, *B.quant_act_wide(t), N), orc.gemm_w4a4(*orc.quant_act(x), codes, scales))):
+        y = product(few)
+        assert rel_err(y.cpu().numpy(), ref) <= TOL
+        assert torch.equal(product(many), y[rows])
