@@ -54,9 +54,6 @@ __device__ inline uint2 buf_load8(rsrc_t r, uint32_t off) {
   const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
   return uint2{v.x, v.y};
 }
-__device__ inline uint16_t buf_load_u16(rsrc_t r, uint32_t off) {
-  return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
-}
 // three consecutive floats (4-byte aligned; each component is range-checked on its own)
 struct float3_t { float x, y, z; };
 __device__ inline float3_t buf_load_f32x3(rsrc_t r, uint32_t off) {

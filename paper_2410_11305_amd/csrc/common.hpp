@@ -9,7 +9,6 @@ namespace qspec {
 
 constexpr int kGroup = 128;        // quantisation group along K (paper Sec. 4.1)
 constexpr int kTileRows = 16;      // output rows per weight tile
-constexpr int kTileBytes = 1024;   // 16 rows x 128 codes x 4 bit
 constexpr int kWave = 64;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -17,7 +16,6 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
-typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
 // Stands between accesses to LDS through which the lanes of ONE wavefront pass values to each other.  LDS executes a
 // wavefront's accesses in order, so there is nothing to wait for; but the compiler, which follows a single lane, must be

@@ -1,20 +1,20 @@
 // Memory-bound (small M) kernels for both modes, wave-autonomous form.
 //
-// A workgroup of 8 wavefronts owns NT adjacent weight tiles (16 outputs each) over the whole
+// A workgroup of W wavefronts (8, or 4: namespace waves4) owns NT adjacent weight tiles (16 outputs each) over the whole
 // of K and 16 TM token rows.  The K groups are dealt to the wavefronts; a wavefront loads the
 // activations of its groups once and uses them against the NT weight tiles, which stream from
 // HBM exactly once.  There is no barrier in the streaming loop: everything a wavefront stages
 // sits in a part of LDS that is its own (LDS executes a wavefront's accesses in order).  The
-// eight fp32 sums of a tile are combined through LDS at the very end and stored as fp16.
+// W fp32 sums of a tile are combined through LDS at the very end and stored as fp16.
 //
 // A launch takes its time on the chip plus 1.1 us, and never less than 1.7.  Of 3.0 us on the chip (4096 x 4096 at
 // one token; a bare read 1.8) 0.5 are spent before the first loads are out and 0.45 after the last group, so
 //  - what the first loads need comes first and from the host's arguments where it can; LDS addresses are worked
 //    out while the loads are on the way;
-//  - a wavefront lays its sums down 16 bytes per lane, all tiles at once, and the eight sums of a tile are read
-//    together (four bytes per lane, eight tiles a pass and two sums at a time before);
+//  - a wavefront lays its sums down 16 bytes per lane, all tiles at once, and the W sums of a tile are read
+//    together;
 //  - the loads of the next step are issued across the end of a chunk of scales as well.
-// Together (us, one run): 4096 x 4096 at one token 4.4 -> 4.1, 12288 x 4096 7.1 -> 6.6, 22016 x 4096 at 32 tokens
+// Together (us on eight wavefronts, one run): 4096 x 4096 at one token 4.4 -> 4.1, 12288 x 4096 7.1 -> 6.6, 22016 x 4096 at 32 tokens
 // 11.9 -> 11.3, verify mode 14.5 -> 13.6; 27648 x 5120 at 64 tokens 27.1 -> 23.8.
 //
 // What bounds it is the read of the weights, and next to that the number of cache LINES its
@@ -65,7 +65,7 @@ struct StreamArgs {
   int ms;                    // token-row blocks (1 with K-slices)
   uint32_t ms_rcp;           // 2^32 / ms, rounded up
   int blocks;                // tile blocks
-  uint32_t xcds;             // number of workgroups, as the kernel takes it
+  uint32_t workgroups;
 };
 
 constexpr int kStreamWaves = 8;
@@ -115,10 +115,10 @@ struct StreamRest {
 };
 
 #define QSPEC_STREAM_PARAMS                                                                                               \
-  const uint4 *codes, const uint16_t *scalesT, const void *act_rows, const float *sa, int M, int N, int K, uint32_t xcds, \
+  const uint4 *codes, const uint16_t *scalesT, const void *act_rows, const float *sa, int M, int N, int K, uint32_t workgroups, \
       int ms, uint32_t ms_rcp, StreamRest rest
 
-// xcds: the number of workgroups (each XCD gets an eighth of them, the first ones one more); ms == 0: K-slices.
+// workgroups: how many (each XCD gets an eighth of them, the first ones one more); ms == 0: K-slices.
 template <bool W4A4, int TM, int NT, int W>
 __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
   using C = StreamShape<W4A4, TM, NT>;
@@ -131,7 +131,7 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
   // Workgroups go to the eight XCDs in turn: each XCD gets a run of adjacent tile blocks, and of each of
   // them all token-row blocks one after the other, so that they find its weights in that XCD's L2.
   const int xcd = blockIdx.x & 7;
-  const int bx = xcd * (int)(xcds >> 3) + min(xcd, (int)(xcds & 7)) + (int)(blockIdx.x >> 3);
+  const int bx = xcd * (int)(workgroups >> 3) + min(xcd, (int)(workgroups & 7)) + (int)(blockIdx.x >> 3);
   const int G = (int)((unsigned)K / kGroup);
   const bool sliced = ms == 0;
   int tb = bx, slice = 0, s0 = 0, s1 = G, m_base = 0;
@@ -336,7 +336,7 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
 #pragma unroll
           for (int j = 0; j < NT; ++j) {
             swf[q][j] = half_bits_to_float(*reinterpret_cast<const uint16_t*>(mine + sw_rd + i * (NT * 32) + j * 32));
-                    }
+          }
           if constexpr (kTokenOuter) {
             I8Pair b[NT];
 #pragma unroll
@@ -396,7 +396,7 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
 #pragma unroll
           for (int j = 0; j < NT; ++j) {
             swf[q][j] = half_bits_to_float(*reinterpret_cast<const uint16_t*>(mine + sw_rd + i * (NT * 32) + j * 32));
-                    }
+          }
           v8h a[TM][4];
 #pragma unroll
           for (int t = 0; t < TM; ++t)
@@ -436,8 +436,8 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
     }
   }
 
-  // ---- combine the eight wavefronts through LDS: a wavefront lays its sums down 16 bytes per lane, as it holds
-  // them (four tokens of one output), and adds up every eighth output tile; a 4 x 4 transposition among the lanes
+  // ---- combine the W wavefronts through LDS: a wavefront lays its sums down 16 bytes per lane, as it holds
+  // them (four tokens of one output), and adds up every W-th output tile; a 4 x 4 transposition among the lanes
   // of a quad then gives every lane four adjacent outputs of one token.  Rows past M take no part.  With
   // K-slices the sums go to the workspace first, and the workgroup that arrives last at the tile
   // block's counter adds the slices in slice order.
@@ -464,7 +464,7 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
       float4 v[W];
 #pragma unroll
       for (int u = 0; u < W; ++u) v[u] = *reinterpret_cast<const float4*>(lds + u * C::kRegion + o * 1024 + lane * 16);
-      __builtin_amdgcn_sched_barrier(0);                     // (all eight on the way)
+      __builtin_amdgcn_sched_barrier(0);                     // (all of them on the way)
       float4 s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int u = 0; u < W; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
@@ -493,7 +493,7 @@ __device__ __forceinline__ void stream_product(QSPEC_STREAM_PARAMS) {
 
 template <bool W4A4, int TM, int NT>
 __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(QSPEC_STREAM_PARAMS) {
-  stream_product<W4A4, TM, NT, kStreamWaves>(codes, scalesT, act_rows, sa, M, N, K, xcds, ms, ms_rcp, rest);
+  stream_product<W4A4, TM, NT, kStreamWaves>(codes, scalesT, act_rows, sa, M, N, K, workgroups, ms, ms_rcp, rest);
 }
 
 // The same on four wavefronts, for plans of between one and two (from two token tiles on: three) rounds of
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void gemm_stream_kernel(QSPEC
 namespace waves4 {
 template <bool W4A4, int TM, int NT>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(QSPEC_STREAM_PARAMS) {
-  stream_product<W4A4, TM, NT, 4>(codes, scalesT, act_rows, sa, M, N, K, xcds, ms, ms_rcp, rest);
+  stream_product<W4A4, TM, NT, 4>(codes, scalesT, act_rows, sa, M, N, K, workgroups, ms, ms_rcp, rest);
 }
 }  // namespace waves4
 

@@ -331,8 +331,8 @@ template <bool W4A4, int TM, int NT>
 int launch_stream_inst(const StreamArgs& a, const StreamPlan& plan, hipStream_t s) {
   const auto launch = [&](auto kernel) {
     const StreamRest rest{a.y, a.ws, a.tickets, a.S, a.per_slice, a.more_slice, a.blocks};
-    launch_kernel(kernel, dim3(a.xcds), dim3(plan.waves * 64), 0, s, a.codes, a.scalesT, a.act, a.sa, a.M, a.N, a.K,
-                  a.xcds, a.S > 1 ? 0 : a.ms, a.ms_rcp, rest);
+    launch_kernel(kernel, dim3(a.workgroups), dim3(plan.waves * 64), 0, s, a.codes, a.scalesT, a.act, a.sa, a.M, a.N, a.K,
+                  a.workgroups, a.S > 1 ? 0 : a.ms, a.ms_rcp, rest);
     return QSPEC_OK;
   };
   if constexpr (NT >= 2 && TM <= 4) {
@@ -361,7 +361,7 @@ int launch_stream(const StreamPlan& plan, StreamArgs a, void* workspace, hipStre
   a.blocks = plan.blocks;
   a.ms = plan.ms;
   a.ms_rcp = (uint32_t)((0x100000000ull + plan.ms - 1) / plan.ms);
-  a.xcds = (uint32_t)(plan.blocks * plan.S * plan.ms);
+  a.workgroups = (uint32_t)(plan.blocks * plan.S * plan.ms);
   a.tickets = static_cast<unsigned*>(workspace);
   a.ws = plan.S > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + kTicketBytes) : nullptr;
   switch (plan.tm) {

@@ -31,10 +31,11 @@ __device__ inline float row16_max(float a) {
 // code word); 16 adjacent lanes (one row) own one group, so the absmax is a
 // 4-step fold inside the row and no LDS is needed.
 //
-// The correctly rounded v / s from y, the correctly rounded 1 / s, for v / s below 2^4 and
-// operands whose quotient and remainder are normal (fp16 values over a seventh of one are):
-// v y is within 1.5 units in the last place, one remainder step brings it below one unit,
-// and from there a second one rounds correctly (Markstein 1990: the remainder is exact).
+// The correctly rounded v / s from y, the correctly rounded 1 / s, for operands whose quotient and
+// remainder are normal (fp16 values over a seventh or a 119th of one are): v y is within 1.5 units in the
+// last place, one remainder step brings it below one unit, and from there a second one rounds
+// correctly (Markstein 1990: the remainder is exact).  Checked for every s = a / 7 and a / 119 of a finite fp16
+// value a > 0 and every fp16 value v from 0 to a, 1.0e9 quotients of up to 119.
 // Five operations where the compiler's division takes a dozen.
 __device__ inline float div_by_reciprocal(float v, float s, float y) {
   float q = v * y;
