@@ -193,10 +193,12 @@ inline int stream_tm_split(int M, int ms) { return stream_tm(16 * (((M + ms - 1)
 //   fixed + round (rounds - 1) + ng (group + again (rounds - 1)) + G / 8 x workgroups per unit x (load + tokens x share of live rows)
 // Fitted to timed plans, on rotating weights inside HIP graphs: in the draft mode 5500 problems of layers 128 to 57344
 // wide and 128 to 28672 long at 1 to 2050 tokens and 1400 layers of Llama-shaped blocks at 1 to 256, in the verify mode
-// 3300 and 1200 at 1 to 128, every instance with the row blocks that cover M.  On 520 problems timed afterwards
-// (profiles/stream_plan_times.txt) the choice among these and the tiled plans is 0.9 % slower than the best one on average and
-// 15 % at most (verify mode past 32 tokens, where a rule bounds it: 1.6 and 32 %), and takes no more than 1.12 times
-// what the kernels and rules before the cost tables took.  (Tables fitted to 17 to 600 tokens and layers from 512 long
+// 3300 and 1200 at 1 to 128, every instance with the row blocks that cover M.  On 520 problems timed afterwards, with
+// the kernels of the fit (profiles/stream_plan_times.txt), the choice among these and the tiled plans is 0.9 % slower than the
+// best one on average and 15 % at most (verify mode past 32 tokens, where a rule bounds it: 1.6 and 32 %), and takes no more
+// than 1.12 times what the kernels and rules before the cost tables took.  The kernels have gained since, the streaming ones
+// more; with the present ones the choice on those problems is 1.9 % slower on average and 53 % at most (11664 outputs from
+// 1536 at 67 tokens on packed codes, tiled 10.0 us, streaming 6.6; profiles/plan_choice_present_kernels.txt).  (Tables fitted to 17 to 600 tokens and layers from 512 long
 // and 1024 wide alone were too low where few workgroups or few groups leave nothing to hide the latency behind: 224
 // outputs from 10240 at 1200 tokens 17.1 us tiled, 23.4 as chosen; 11696 from 1152 at 43 tokens 8.6 us, 6.7 now.  A rule for up
 // to 16 tokens, rounds x groups per wavefront x (NT + activations), was 0.4 % behind the best instance on average on the
@@ -398,7 +400,7 @@ constexpr TileShape kShapes16[] = {     // verify mode (gemm_tile16w_kernel): TN
 // Fitted to 38000 timed plans of 1716 problems: 16 to 128256 outputs from 128 to 28672 inputs at 33 to 2050
 // tokens and some up to 9000, every shape below, one to eight slices, on rotating weights inside HIP
 // graphs.  The choice is 0.6 % slower than the best of them on average and 19 % at most (368 outputs from 3584 at
-// 1002 tokens), and 1.2 % (18 %) on 228 more with long inputs or up to 9000 tokens; profiles/verify_plan_times.txt
+// 1002 tokens; 23 % there with the present kernels, and 0.8 % on average on the 400 problems of the sample), and 1.2 % (18 %) on 228 more with long inputs or up to 9000 tokens; profiles/verify_plan_times.txt
 // lists a sample, the worst ones included.  (A table of five numbers a shape fitted to 14 large layers, without
 // the further rounds' cost and without 128 x 128 and 128 x 64 blocks in a single round, left 2.3 % on average and
 // was up to 39 % slower than the fill rules before both on short inputs: 28672 outputs from 512 at 256 tokens

@@ -1,5 +1,6 @@
 """The choice between the streaming and tiled kernels, and of their plans, against timed plans
-(profiles/stream_plan_times.txt): the draft mode on both activation formats at 1 to 2050 tokens, the verify mode at
+(profiles/stream_plan_times.txt, with the kernels that the cost tables were fitted to: it holds the planner to its tables, not
+to what the present kernels take): the draft mode on both activation formats at 1 to 2050 tokens, the verify mode at
 1 to 128.  Needs no GPU: the choice is a pure function of the sizes.  Bounds: the timings repeat within 3 % (a few
 within 10 %); the cost tables leave 1 % on average, and 20 % at most but for a few per cent of layers with few groups."""
 import math

@@ -1,5 +1,5 @@
-"""The choice of the verify-mode tiled plan against timed plans (profiles/verify_plan_times.txt):
-no problem of the table may run slower than with the kernels and fill rules that the planner's cost
+"""The choice of the verify-mode tiled plan against timed plans (profiles/verify_plan_times.txt, with the kernels that
+the cost table was fitted to): no problem of the table may run slower than with the kernels and fill rules that the planner's cost
 table replaced, and the chosen plans stay near the best ones.  Needs no GPU: the choice is a pure
 function of the sizes.  Bounds: the timings repeat within 3 %; the cost table leaves 1.5 % on
 average on these problems (the worst-predicted 40 are among them) and 19 % at most."""
